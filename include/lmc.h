@@ -128,9 +128,11 @@ typedef struct {
 /* Each layer's allocation must cover every run the strides can reach:
  *   (P-1)*plane_stride + (NB-1)*block_stride + (BS-1)*token_stride + (H-1)*head_stride
  *   + head_dim*elem_bytes bytes.
- * The kernels move min(16, largest power of two dividing head_dim*elem_bytes and every
- * stride) bytes per lane; the layer base pointers and staging_dev must be aligned to
- * that, else LMC_ERR_INVAL.  16-byte multiples everywhere give the fast path. */
+ * The layer base pointers and staging_dev must be aligned to min(16, largest power of two
+ * dividing head_dim*elem_bytes and every stride) bytes, else LMC_ERR_INVAL.  The kernels
+ * move 16 bytes per lane wherever a contiguous run (a token's row, or a head's if the heads
+ * are apart) has that many, aligned or not; shorter runs go in pieces of that alignment.
+ * 16-byte multiples everywhere are fastest. */
 
 typedef struct {
     lmc_kv_geom_t geom;

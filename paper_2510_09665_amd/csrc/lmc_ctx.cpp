@@ -44,8 +44,12 @@ static lmc_status_t derive_geometry(const lmc_kv_geom_t &g, lmc::KernelGeom *k, 
     vec = gcd_pow2(g.block_stride, vec);
     vec = gcd_pow2(g.token_stride, vec);
     if (!row_contiguous) vec = gcd_pow2(g.head_stride, vec);
-    const int64_t pairs = int64_t(g.chunk_tokens) * (row / vec);
-    if (pairs >= (int64_t(1) << 31)) return LMC_ERR_INVAL;
+    if (int64_t(g.chunk_tokens) * (row / vec) >= (int64_t(1) << 31)) return LMC_ERR_INVAL;
+    const int64_t moved_run = row_contiguous ? row : run;   // contiguous on both sides
+    const int64_t runs = row / moved_run;
+    const bool wide = vec < 16 && moved_run >= 16;
+    const int64_t vec_per_run = wide ? (moved_run + 15) / 16 : moved_run / vec;
+    const int64_t pairs = int64_t(g.chunk_tokens) * runs * vec_per_run;   // wide: no more than above
 
     k->block_stride = g.block_stride;
     k->token_stride = g.token_stride;
@@ -55,12 +59,15 @@ static lmc_status_t derive_geometry(const lmc_kv_geom_t &g, lmc::KernelGeom *k, 
     k->n_slots = uint32_t(n_slots);
     k->chunk_tokens = uint32_t(g.chunk_tokens);
     k->vec_per_plane = uint32_t(pairs);
-    k->runs_per_row = row_contiguous ? 1u : uint32_t(g.num_heads);
+    k->runs_per_row = uint32_t(runs);
     k->n_layer_planes = uint32_t(g.num_layers * g.num_planes);
-    k->vec = uint32_t(vec);
+    k->vec = wide ? uint32_t(lmc::kWide) : uint32_t(vec);
+    k->align = uint32_t(vec);
+    k->run_bytes = uint32_t(moved_run);
+    k->row_bytes = uint32_t(row);
     k->by_tiles_per_plane = lmc::make_fastdiv(uint32_t((pairs + 255) / 256));
-    k->by_vec_per_row = lmc::make_fastdiv(uint32_t(row / vec));
-    k->by_vec_per_run = lmc::make_fastdiv(uint32_t((row_contiguous ? row : run) / vec));
+    k->by_vec_per_row = lmc::make_fastdiv(uint32_t(runs * vec_per_run));
+    k->by_vec_per_run = lmc::make_fastdiv(uint32_t(vec_per_run));
     k->by_block_size = lmc::make_fastdiv(uint32_t(g.block_size));
     *chunk_bytes = int64_t(k->chunk_bytes);
     return LMC_OK;
@@ -70,7 +77,7 @@ lmc_status_t build_layer_ptrs(const lmc_ctx *c, void *const *kv_layers, lmc::Lay
     const lmc_kv_geom_t &g = c->cfg.geom;
     for (int l = 0; l < g.num_layers; l++) {
         uint8_t *base = static_cast<uint8_t *>(kv_layers[l]);
-        if (base == nullptr || (reinterpret_cast<uintptr_t>(base) % c->kg.vec) != 0)
+        if (base == nullptr || (reinterpret_cast<uintptr_t>(base) % c->kg.align) != 0)
             return LMC_ERR_INVAL;
         for (int p = 0; p < g.num_planes; p++)
             out->p[l * g.num_planes + p] = base + int64_t(p) * g.plane_stride;
@@ -428,9 +435,10 @@ lmc_status_t lmc_create(const lmc_config_t *cfg, lmc_ctx_t **ctx_out) {
     if (rc == LMC_OK) {
         c->n_pool_slots = int64_t(cfg->host_pool_bytes / uint64_t(c->chunk_bytes));
         if (c->n_pool_slots < 1) rc = LMC_ERR_INVAL;
-        // one launch must be able to cover a whole staging buffer
-        if (int64_t(cfg->staging_chunks) > int64_t(lmc::max_chunks_per_launch(c->kg, lmc::bulk_view(c->kg))))
-            rc = LMC_ERR_INVAL;
+        // one launch must be able to cover a whole staging buffer, also one whose lanes move
+        // only `align` bytes each
+        const uint64_t tiles = (c->kg.plane_bytes / c->kg.align + 255) / 256 * c->kg.n_layer_planes;
+        if (uint64_t(cfg->staging_chunks) > 0x00FFFFFFu / tiles) rc = LMC_ERR_INVAL;
     }
     if (rc != LMC_OK) {
         delete c;

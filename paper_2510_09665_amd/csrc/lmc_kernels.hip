@@ -34,6 +34,9 @@ template <> struct VecOf<8> { typedef unsigned int type __attribute__((ext_vecto
 template <> struct VecOf<4> { typedef unsigned int type; };
 template <> struct VecOf<2> { typedef unsigned short type; };
 template <> struct VecOf<1> { typedef unsigned char type; };
+// kWide: 16 bytes at any address (gfx950 takes unaligned global accesses in one instruction)
+template <> struct VecOf<kWide> { typedef unsigned int type __attribute__((ext_vector_type(4), aligned(1))); };
+template <int VEC> constexpr uint32_t kBytesOf = VEC == kWide ? 16u : uint32_t(VEC);
 
 #define LMC_GLOBAL __attribute__((address_space(1)))
 
@@ -65,7 +68,7 @@ __device__ __forceinline__ FastDiv pin(FastDiv f) {
 // Everything a tile needs besides its own number, held in scalar registers.
 struct TileArgs {
     FastDiv by_tiles, by_lp, by_row, by_run, by_bs;
-    uint32_t lp_base, vec_per_plane, chunk_tokens, n_slots, runs_per_row;
+    uint32_t lp_base, vec_per_plane, chunk_tokens, n_slots, runs_per_row, run_bytes, row_bytes;
     uint64_t chunk_stride, plane_bytes, slots_at, staging_at, bad_flag_at;
     int64_t block_stride, token_stride, run_stride;
 };
@@ -73,6 +76,7 @@ struct TileArgs {
 // Fetches every kernel argument at once, in one batch of scalar loads.  Left alone the
 // compiler loads each field just before its first use, which puts four scalar-load
 // round trips behind the slot load on every wavefront's critical path.
+template <int VEC>
 __device__ __forceinline__ TileArgs fetch_args(const KernelGeom &g, const LaunchView &view,
                                                const int64_t *slot_mapping, uint8_t *staging,
                                                int32_t *bad_flag) {
@@ -88,6 +92,10 @@ __device__ __forceinline__ TileArgs fetch_args(const KernelGeom &g, const Launch
     a.chunk_tokens = pin(g.chunk_tokens);
     a.n_slots = pin(g.n_slots);
     a.runs_per_row = pin(g.runs_per_row);
+    if (VEC == kWide) {
+        a.run_bytes = pin(g.run_bytes);
+        a.row_bytes = pin(g.row_bytes);
+    }
     a.block_stride = pin(g.block_stride);
     a.token_stride = pin(g.token_stride);
     a.run_stride = pin(g.run_stride);
@@ -96,6 +104,24 @@ __device__ __forceinline__ TileArgs fetch_args(const KernelGeom &g, const Launch
     a.staging_at = pin(uint64_t(staging));
     a.bad_flag_at = pin(uint64_t(bad_flag));
     return a;
+}
+
+// Where vector w of a token's row lies: *in_page relative to the token's first byte in its
+// page, *in_row relative to the row's first byte in the chunk.  A wide row (kWide) is cut
+// run by run: every run of run_bytes >= 16 bytes takes ceil(run_bytes / 16) vectors, the
+// last of them moved back so that it ends with the run.  It overlaps its neighbour, and
+// the overlapped bytes are moved twice, with equal values, by lanes of one launch.
+template <int VEC>
+__device__ __forceinline__ void place(const TileArgs &a, uint32_t w, int64_t *in_page, uint64_t *in_row) {
+    uint32_t run = 0, dv = w;
+    if (a.runs_per_row > 1) {
+        run = a.by_run.div(w);
+        dv = w - run * a.by_run.d;
+    }
+    uint32_t off = dv * kBytesOf<VEC>;
+    if (VEC == kWide) off = min(off, a.run_bytes - 16u);
+    *in_page = int64_t(run) * a.run_stride + int64_t(off);
+    *in_row = VEC == kWide ? uint64_t(run) * a.run_bytes + off : uint64_t(w) * kBytesOf<VEC>;
 }
 
 // One tile (256 consecutive vectors of one plane of one chunk) of the path's copy in
@@ -123,15 +149,12 @@ __device__ __forceinline__ void move_tile(const TileArgs &a, const LayerPtrs &la
     const uint32_t su = valid ? uint32_t(s) : 0u;  // slot 0 is always inside the pages
     const uint32_t b = a.by_bs.div(su);
     const uint32_t o = su - b * a.by_bs.d;
-    uint32_t run = 0, dv = w;
-    if (a.runs_per_row > 1) {
-        run = a.by_run.div(w);
-        dv = w - run * a.by_run.d;
-    }
-    const uint64_t page = layer + uint64_t(int64_t(b) * a.block_stride + int64_t(o) * a.token_stride +
-                                           int64_t(run) * a.run_stride + int64_t(dv) * VEC);
+    int64_t in_page;
+    uint64_t in_row;
+    place<VEC>(a, w, &in_page, &in_row);
+    const uint64_t page = layer + uint64_t(int64_t(b) * a.block_stride + int64_t(o) * a.token_stride + in_page);
     const uint64_t st = a.staging_at + uint64_t(c) * a.chunk_stride + uint64_t(lp) * a.plane_bytes +
-                        uint64_t(r) * VEC;
+                        (VEC == kWide ? uint64_t(t) * a.row_bytes + in_row : uint64_t(r) * kBytesOf<VEC>);
     if (GATHER) {
         V v = load_vec<V, NT_LD>(page);
         if (!valid) v = V(0);
@@ -148,7 +171,7 @@ __global__ __launch_bounds__(kThreads) void move_rows(const KernelGeom g, const 
                                                       const int64_t *__restrict__ slot_mapping,
                                                       uint8_t *staging, int32_t *bad_flag,
                                                       uint32_t n_blocks_permuted, uint32_t xcd_shift) {
-    const TileArgs a = fetch_args(g, view, slot_mapping, staging, bad_flag);
+    const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
     uint32_t blk = blockIdx.x;
     if (blk < n_blocks_permuted) {
         // hardware deals consecutive workgroup ids to the 8 XCDs in turn; give each XCD
@@ -174,7 +197,7 @@ __global__ __launch_bounds__(kThreads) void move_rows_paced(const KernelGeom g, 
                                                             const int64_t *__restrict__ slot_mapping,
                                                             uint8_t *staging, int32_t *bad_flag,
                                                             uint32_t n_blocks) {
-    const TileArgs a = fetch_args(g, view, slot_mapping, staging, bad_flag);
+    const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
     const uint32_t step = pin(uint32_t(gridDim.x)), end = pin(n_blocks);
     for (uint32_t blk = blockIdx.x; blk < end; blk += step)
         move_tile<VEC, GATHER, NT_LD, NT_ST>(a, layers, blk);
@@ -294,7 +317,7 @@ __global__ __launch_bounds__(kThreads) void scatter_rows_ordered(const KernelGeo
                                                                  FastDiv by_chunk_tokens, uint32_t group_rows,
                                                                  uint32_t n_blocks_permuted, uint32_t xcd_shift) {
     typedef typename VecOf<VEC>::type V;
-    const TileArgs a = fetch_args(g, view, nullptr, const_cast<uint8_t *>(staging), nullptr);
+    const TileArgs a = fetch_args<VEC>(g, view, nullptr, const_cast<uint8_t *>(staging), nullptr);
     const FastDiv by_tiles = pin(by_tiles_per_group), by_ct = pin(by_chunk_tokens);
     const uint64_t pairs_at = pin(uint64_t(pairs));
     const uint32_t n_rows = pin(*n_rows_at), rows = pin(group_rows);
@@ -320,15 +343,13 @@ __global__ __launch_bounds__(kThreads) void scatter_rows_ordered(const KernelGeo
     const uint32_t t = tok - c * by_ct.d;
     const uint32_t b = a.by_bs.div(su);
     const uint32_t o = su - b * a.by_bs.d;
-    uint32_t run = 0, dv = w;
-    if (a.runs_per_row > 1) {
-        run = a.by_run.div(w);
-        dv = w - run * a.by_run.d;
-    }
-    const uint64_t page = layer + uint64_t(int64_t(b) * a.block_stride + int64_t(o) * a.token_stride +
-                                           int64_t(run) * a.run_stride + int64_t(dv) * VEC);
+    int64_t in_page;
+    uint64_t in_row;
+    place<VEC>(a, w, &in_page, &in_row);
+    const uint64_t page = layer + uint64_t(int64_t(b) * a.block_stride + int64_t(o) * a.token_stride + in_page);
+    const uint64_t row_bytes = VEC == kWide ? a.row_bytes : a.by_row.d * kBytesOf<VEC>;
     const uint64_t st = a.staging_at + uint64_t(c) * a.chunk_stride + uint64_t(lp) * a.plane_bytes +
-                        (uint64_t(t) * a.by_row.d + w) * VEC;
+                        t * row_bytes + in_row;
     store_vec<V, NT_ST>(page, load_vec<V, NT_LD>(st));
 }
 
@@ -468,6 +489,7 @@ hipError_t launch_move(const KernelGeom &g, const LaunchView &v, const LaunchSha
                        uint8_t *staging, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
                        hipEvent_t stop) {
     switch (g.vec) {
+        case kWide: return launch_move_v<kWide, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
         case 16: return launch_move_v<16, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
         case 8: return launch_move_v<8, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
         case 4: return launch_move_v<4, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
@@ -599,6 +621,7 @@ hipError_t launch_scatter_ordered(const KernelGeom &g, const LaunchView &v, cons
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     switch (g.vec) {
+        case kWide: return launch_scatter_ordered_v<kWide>(g, v, s, layers, n_tokens, o, staging, stream, start, stop);
         case 16: return launch_scatter_ordered_v<16>(g, v, s, layers, n_tokens, o, staging, stream, start, stop);
         case 8: return launch_scatter_ordered_v<8>(g, v, s, layers, n_tokens, o, staging, stream, start, stop);
         case 4: return launch_scatter_ordered_v<4>(g, v, s, layers, n_tokens, o, staging, stream, start, stop);

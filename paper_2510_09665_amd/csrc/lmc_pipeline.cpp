@@ -625,7 +625,7 @@ static lmc_status_t device_only(lmc_ctx_t *c, bool gather, void *const *kv_layer
     if (!c || n_chunks < 0 || !kv_layers || (n_chunks > 0 && (!slot_mapping || !staging)))
         return LMC_ERR_INVAL;
     if (!c->has_device) return LMC_ERR_NODEVICE;
-    if (reinterpret_cast<uintptr_t>(staging) % c->kg.vec) return LMC_ERR_INVAL;
+    if (reinterpret_cast<uintptr_t>(staging) % c->kg.align) return LMC_ERR_INVAL;
     std::lock_guard<std::mutex> lock(c->mu);
     c->cur_ticket = 0;
     DeviceScope dev(c);

@@ -226,7 +226,7 @@ lmc_status_t make_ring(lmc_ctx *c, Ring &r);
 // lmc_pipeline.cpp
 lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
-                          uint8_t *staging, hipStream_t stream);
+                          uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list = nullptr);
 // lmc_streams.cpp
 lmc_status_t shares_a_queue(lmc_ctx *c, hipStream_t busy, bool by_kernel, hipStream_t other, uint8_t *devbuf,
                             uint64_t nbytes, hipEvent_t a0, hipEvent_t a1, hipEvent_t k1, bool *shares);

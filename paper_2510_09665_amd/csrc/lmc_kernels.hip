@@ -185,12 +185,52 @@ __global__ __launch_bounds__(kThreads) void move_rows(const KernelGeom g, const 
     move_tile<VEC, GATHER, NT_LD, NT_ST>(a, layers, blk);
 }
 
+// The same tile for a workgroup that takes many, one after the other.  Everything is read
+// without a branch (a lane past the end of the plane reads what the last one reads), only the
+// store is conditional.  With a list, chunk c of the launch lies list->slot[c] chunk strides
+// into the buffer.
+template <int VEC, bool GATHER, bool NT_LD, bool NT_ST>
+__device__ __forceinline__ void move_tile_in_turn(const TileArgs &a, const LayerPtrs &layers, uint32_t blk,
+                                                  const ChunkList *list) {
+    typedef typename VecOf<VEC>::type V;
+    const uint32_t q = a.by_tiles.div(blk);
+    const uint32_t tile = blk - q * a.by_tiles.d;
+    const uint32_t c = a.by_lp.div(q);
+    const uint32_t lp = q - c * a.by_lp.d;
+    const uint32_t r0 = tile * kThreads + threadIdx.x;
+    const uint32_t r = min(r0, a.vec_per_plane - 1);
+    const uint32_t t = a.by_row.div(r);
+    const uint32_t w = r - t * a.by_row.d;
+    const int64_t s = load_vec<int64_t, false>(a.slots_at + (uint64_t(c) * a.chunk_tokens + t) * 8u);
+    const uint64_t layer = uint64_t(layers.p[a.lp_base + lp]);
+    const uint32_t c_buf = list ? uint32_t(list->slot[c]) : c;
+    int64_t in_page;
+    uint64_t in_row;
+    place<VEC>(a, w, &in_page, &in_row);
+    const uint64_t st = a.staging_at + uint64_t(c_buf) * a.chunk_stride + uint64_t(lp) * a.plane_bytes +
+                        (VEC == kWide ? uint64_t(t) * a.row_bytes + in_row : uint64_t(r) * kBytesOf<VEC>);
+    const bool has_page = uint64_t(s) < uint64_t(a.n_slots);  // negative wraps to huge
+    const bool mine = r0 < a.vec_per_plane;
+    if (mine && s >= int64_t(a.n_slots)) store_vec<int32_t, false>(a.bad_flag_at, 1);
+    const uint32_t su = has_page ? uint32_t(s) : 0u;  // slot 0 is always inside the pages
+    const uint32_t b = a.by_bs.div(su);
+    const uint32_t o = su - b * a.by_bs.d;
+    const uint64_t page = layer + uint64_t(int64_t(b) * a.block_stride + int64_t(o) * a.token_stride + in_page);
+    V v = load_vec<V, NT_LD>(GATHER ? page : st);
+    if (GATHER && !has_page) v = V(0);
+    if (mine && (GATHER || has_page)) store_vec<V, NT_ST>(GATHER ? st : page, v);
+}
+
 // Across the host link (pages <-> pinned pool, no staging): the link, not HBM, sets the
 // pace, and it runs best when few workgroups walk the host side in order.  Measured with a
 // plain copy kernel on this part: 64 workgroups taking tiles in turn reach 57.6 GB/s
 // reading host memory and 56.2 GB/s writing it (the runtime's own copies: 57.2 / 57.0),
 // one tile per workgroup over thousands of workgroups 55.7 / 54.4.  The grid is fixed and
 // every workgroup takes tiles blk, blk + gridDim.x, ... until the launch's n_blocks.
+// Two or four tiles at a time in a half or a quarter of the workgroups reach the same rate
+// alone (12 MiB from the host 222-224 us, 32 MiB to it 601-607), but beside another such
+// launch loads are slower: three contexts in turn, 12 MiB each in 256-byte rows, 236 us a
+// pass with 64 x 1 tile, 244 with 32 x 2, 242 with 16 x 4.
 template <int VEC, bool GATHER, bool NT_LD, bool NT_ST>
 __global__ __launch_bounds__(kThreads) void move_rows_paced(const KernelGeom g, const LaunchView view,
                                                             const LayerPtrs layers,
@@ -200,7 +240,23 @@ __global__ __launch_bounds__(kThreads) void move_rows_paced(const KernelGeom g, 
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
     const uint32_t step = pin(uint32_t(gridDim.x)), end = pin(n_blocks);
     for (uint32_t blk = blockIdx.x; blk < end; blk += step)
-        move_tile<VEC, GATHER, NT_LD, NT_ST>(a, layers, blk);
+        move_tile_in_turn<VEC, GATHER, NT_LD, NT_ST>(a, layers, blk, nullptr);
+}
+
+// The same for chunks in any pool slots (a fragmented pool, a batch of requests): one launch
+// instead of one per run of consecutive slots, each of which ends with the link running dry
+// and is followed by a gap of 4-5 us.  A store of 25 chunks of 2 MiB in 12 runs: 12 launches
+// take 975 us on the device, one takes 946 (1123 and 1089 us for the whole call).
+template <int VEC, bool GATHER, bool NT_LD, bool NT_ST>
+__global__ __launch_bounds__(kThreads) void move_rows_listed(const KernelGeom g, const LaunchView view,
+                                                             const LayerPtrs layers,
+                                                             const int64_t *__restrict__ slot_mapping,
+                                                             uint8_t *staging, int32_t *bad_flag,
+                                                             uint32_t n_blocks, const ChunkList list) {
+    const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
+    const uint32_t step = pin(uint32_t(gridDim.x)), end = pin(n_blocks);
+    for (uint32_t blk = blockIdx.x; blk < end; blk += step)
+        move_tile_in_turn<VEC, GATHER, NT_LD, NT_ST>(a, layers, blk, &list);
 }
 
 // ---- scatter in the order of the destination ---------------------------------------------
@@ -450,7 +506,8 @@ template <int VEC, bool GATHER>
 hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                          const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                          uint8_t *staging, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
-                         hipEvent_t stop) {
+                         hipEvent_t stop, const ChunkList *list) {
+    if (list != nullptr && (s.paced_groups == 0 || n_chunks > uint32_t(kMaxListed))) return hipErrorInvalidValue;
     const uint32_t n_blocks = n_chunks * v.by_n_lp.d * g.by_tiles_per_plane.d;
     if (n_blocks == 0) return hipSuccess;
     uint32_t shift = 0, permuted = 0;
@@ -462,13 +519,16 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
     if (s.paced_groups > 0) {
         // blk + step must not wrap: n_blocks < 2^24 (max_chunks_per_launch) and the grid is small
         grid = dim3(std::min(n_blocks, s.paced_groups));
-#define LMC_GO(LD, ST)                                                                                \
-    hipExtLaunchKernelGGL((move_rows_paced<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
+#define LMC_GO(LD, ST)                                                                                  \
+    if (list != nullptr)                                                                                \
+        hipExtLaunchKernelGGL((move_rows_listed<VEC, GATHER, LD, ST>), grid, block, 0, stream, start,    \
+                              stop, 0, g, v, layers, slot_mapping, staging, bad_flag, n_blocks, *list);  \
+    else hipExtLaunchKernelGGL((move_rows_paced<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
                           0, g, v, layers, slot_mapping, staging, bad_flag, n_blocks)
-        if (s.nt_load && s.nt_store) LMC_GO(true, true);
-        else if (s.nt_load) LMC_GO(true, false);
-        else if (s.nt_store) LMC_GO(false, true);
-        else LMC_GO(false, false);
+        if (s.nt_load && s.nt_store) { LMC_GO(true, true); }
+        else if (s.nt_load) { LMC_GO(true, false); }
+        else if (s.nt_store) { LMC_GO(false, true); }
+        else { LMC_GO(false, false); }
 #undef LMC_GO
         return hipGetLastError();
     }
@@ -487,14 +547,14 @@ template <bool GATHER>
 hipError_t launch_move(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                        const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                        uint8_t *staging, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
-                       hipEvent_t stop) {
+                       hipEvent_t stop, const ChunkList *list) {
     switch (g.vec) {
-        case kWide: return launch_move_v<kWide, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
-        case 16: return launch_move_v<16, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
-        case 8: return launch_move_v<8, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
-        case 4: return launch_move_v<4, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
-        case 2: return launch_move_v<2, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
-        case 1: return launch_move_v<1, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
+        case kWide: return launch_move_v<kWide, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
+        case 16: return launch_move_v<16, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
+        case 8: return launch_move_v<8, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
+        case 4: return launch_move_v<4, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
+        case 2: return launch_move_v<2, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
+        case 1: return launch_move_v<1, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
     }
     return hipErrorInvalidValue;
 }
@@ -543,17 +603,17 @@ LaunchView layer_view(const KernelGeom &g, uint32_t planes_per_layer, uint32_t f
 hipError_t launch_gather(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                          const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                          uint8_t *staging, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
-                         hipEvent_t stop) {
+                         hipEvent_t stop, const ChunkList *list) {
     return launch_move<true>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream,
-                             start, stop);
+                             start, stop, list);
 }
 
 hipError_t launch_scatter(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                           const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                           const uint8_t *staging, int32_t *bad_flag, hipStream_t stream,
-                          hipEvent_t start, hipEvent_t stop) {
+                          hipEvent_t start, hipEvent_t stop, const ChunkList *list) {
     return launch_move<false>(g, v, s, layers, slot_mapping, n_chunks,
-                              const_cast<uint8_t *>(staging), bad_flag, stream, start, stop);
+                              const_cast<uint8_t *>(staging), bad_flag, stream, start, stop, list);
 }
 
 uint64_t order_table_words(const KernelGeom &g) { return g.n_slots; }

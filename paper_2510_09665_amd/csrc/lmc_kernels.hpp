@@ -81,18 +81,27 @@ struct LaunchShape {
                               // launches whose other side is host memory
 };
 
+// Where the chunks of one link-paced launch lie when they are not back to back: chunk i of
+// the launch has its bytes at staging + slot[i] * chunk_stride.  By value, like LayerPtrs
+// (a launch's arguments stay below 4 KiB).
+constexpr int kMaxListed = 256;
+struct ChunkList {
+    int32_t slot[kMaxListed];
+};
+
 // pages -> n_chunks chunks of the slot mapping, written back to back from `staging`
 // (gather), or the reverse (scatter).  bad_flag: device-visible int set to 1 on a slot
 // >= n_slots.  start / stop: optional events (timing enabled) that receive the
 // kernel's own begin and end time stamps; no marker is put on the stream for them.
+// list (paced launches of at most kMaxListed chunks only): where each chunk lies.
 hipError_t launch_gather(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                          const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                          uint8_t *staging, int32_t *bad_flag, hipStream_t stream,
-                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
+                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr, const ChunkList *list = nullptr);
 hipError_t launch_scatter(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                           const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                           const uint8_t *staging, int32_t *bad_flag, hipStream_t stream,
-                          hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
+                          hipEvent_t start = nullptr, hipEvent_t stop = nullptr, const ChunkList *list = nullptr);
 // Scatter in the order of the destination: the rows of the launch are visited in ascending
 // slot order, plane by plane (see lmc_kernels.hip).  The order is built on the device in
 // scratch memory the caller provides: token_at (order_table_words() words), counts

@@ -69,7 +69,7 @@ static lmc_status_t prepare_order_scratch(lmc_ctx *c, uint64_t n_tokens, hipStre
 
 lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
-                          uint8_t *staging, hipStream_t stream) {
+                          uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list) {
     // LMC_FLAG_TIMING: the launch itself carries a start and a stop event, which receive
     // the kernel's own begin / end time stamps; the stream gets no extra marker.
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -98,10 +98,10 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
     }
     hipError_t e =
         injected_failure(c) ? hipErrorUnknown
-        : gather  ? lmc::launch_gather(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, e1)
+        : gather  ? lmc::launch_gather(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, e1, list)
         : ordered ? lmc::launch_scatter_ordered(c->kg, view, s, ptrs, slots, uint32_t(n_tokens), c->order, staging,
                                                 c->bad_flag_dev, stream, e0, e1)
-                  : lmc::launch_scatter(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, e1);
+                  : lmc::launch_scatter(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, e1, list);
     if (ordered && e == hipSuccess) e = hipEventRecord(c->order_free, stream);
     if (e != hipSuccess) {
         if (e0 != nullptr) {
@@ -319,6 +319,41 @@ static lmc_status_t after_stores(lmc_ctx *c, const int64_t *pool_slots, int64_t 
     return LMC_OK;
 }
 
+// The part of n chunks that `view` describes, moved between the pages and the chunks' pool
+// slots by kernels that cross the link themselves (no staging, no copy engine).  Chunk i is
+// chunk `chunk[i]` of the slot mapping (null: i); one launch covers chunks that are
+// consecutive there.  Where their pool slots are consecutive too the first one's address is
+// all a launch needs; where they are not they are listed, so that a fragmented pool costs one
+// launch for every kMaxListed chunks and not one for every run of slots.
+static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, uint64_t pool_off,
+                                const lmc::LayerPtrs &ptrs, const int64_t *slot_mapping, const int64_t *chunk,
+                                const int64_t *pool_slot, int64_t n, hipStream_t stream) {
+    const uint64_t cb = uint64_t(c->chunk_bytes);
+    const int64_t CT = c->cfg.geom.chunk_tokens;
+    view.chunk_stride = cb;  // chunks lie one pool slot apart
+    const int64_t max_k = int64_t(lmc::max_chunks_per_launch(c->kg, view));
+    // "link_groups" 0 asks for launches of one tile per workgroup, which take no list
+    const bool may_list = c->link_groups > 0 && c->n_pool_slots <= INT32_MAX;
+    for (int64_t i0 = 0, k = 0; i0 < n; i0 += k) {
+        int64_t in_map = 1;
+        while (in_map < max_k && i0 + in_map < n && (!chunk || chunk[i0 + in_map] == chunk[i0] + in_map)) in_map++;
+        for (k = 1; k < in_map && pool_slot[i0 + k] == pool_slot[i0] + k;) k++;
+        lmc::ChunkList list;
+        const bool listed = may_list && k < in_map && k < lmc::kMaxListed;
+        if (listed) {
+            k = std::min<int64_t>(lmc::kMaxListed, in_map);
+            for (int64_t i = 0; i < k; i++) list.slot[i] = int32_t(pool_slot[i0 + i]);
+        }
+        lmc_status_t rc = timed_launch(c, gather, view, ptrs, slot_mapping + (chunk ? chunk[i0] : i0) * CT, uint32_t(k),
+                                       c->pool_dev + (listed ? 0 : uint64_t(pool_slot[i0]) * cb) + pool_off, stream,
+                                       listed ? &list : nullptr);
+        if (rc != LMC_OK) return rc;
+        (gather ? c->stats.bytes_d2h : c->stats.bytes_h2d) += uint64_t(k) * view.by_n_lp.d * c->kg.plane_bytes;
+        if ((rc = force_sync(c, stream)) != LMC_OK) return rc;
+    }
+    return LMC_OK;
+}
+
 // Retrieve, bulk (layers_per_step == 0) or layer by layer (paper section 5.2).
 static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunks,
                          const int64_t *slot_mapping, void *const *kv_layers, void *user_stream,
@@ -365,25 +400,11 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     if (n_chunks == 0) return finish_op(c, std::move(op), nullptr, false, ticket_out);
 
     Ring &ring = c->load_ring;
-    const uint64_t cb = uint64_t(c->chunk_bytes);
     const int64_t per = c->cfg.staging_chunks;
     // without staging (LMC_FLAG_DIRECT, or a small bulk call): no copy, the scatter kernel
-    // reads the pinned pool over the link; one launch per run of consecutive pool slots
-    // (and per layer step)
-    auto load_direct = [&](lmc::LaunchView view, uint64_t pool_off) -> lmc_status_t {
-        view.chunk_stride = cb;  // chunks lie one pool slot apart
-        const int64_t max_k = int64_t(lmc::max_chunks_per_launch(c->kg, view));
-        for (int64_t i0 = 0; i0 < n_chunks;) {
-            int64_t k = 1;
-            while (k < max_k && i0 + k < n_chunks && pool_slots[size_t(i0 + k)] == pool_slots[size_t(i0)] + k) k++;
-            lmc_status_t r = timed_launch(c, false, view, ptrs, slot_mapping + i0 * CT, uint32_t(k),
-                                          c->pool_dev + uint64_t(pool_slots[size_t(i0)]) * cb + pool_off, c->s_scatter);
-            if (r != LMC_OK) return r;
-            c->stats.bytes_h2d += uint64_t(k) * view.by_n_lp.d * c->kg.plane_bytes;
-            if ((r = force_sync(c, c->s_scatter)) != LMC_OK) return r;
-            i0 += k;
-        }
-        return LMC_OK;
+    // reads the pinned pool over the link
+    auto load_direct = [&](const lmc::LaunchView &view, uint64_t pool_off) {
+        return move_direct(c, false, view, pool_off, ptrs, slot_mapping, nullptr, pool_slots.data(), n_chunks, c->s_scatter);
     };
     // one group: copies into the next ring buffer on the H2D stream, scatter on the
     // scatter stream; the buffer is released when the scatter has read it
@@ -542,27 +563,9 @@ static lmc_status_t store_groups(lmc_ctx *c, const lmc::LaunchView &view, uint64
                                  std::vector<hipEvent_t> *group_events = nullptr) {
     Ring &ring = c->store_ring;
     const int64_t CT = c->cfg.geom.chunk_tokens;
-    if (direct) {
-        // no staging, no copy: the gather kernel writes the pinned pool over the link; one
-        // launch per run of chunks that are consecutive both in the slot mapping and in the pool
-        lmc::LaunchView v = view;
-        v.chunk_stride = uint64_t(c->chunk_bytes);
-        const size_t max_k = size_t(lmc::max_chunks_per_launch(c->kg, v));
-        for (size_t j0 = 0; j0 < new_chunk.size();) {
-            size_t k = 1;
-            while (k < max_k && j0 + k < new_chunk.size() && new_chunk[j0 + k] == new_chunk[j0] + int64_t(k) &&
-                   new_slot[j0 + k] == new_slot[j0] + int64_t(k))
-                k++;
-            lmc_status_t rc = timed_launch(c, true, v, ptrs, slot_mapping + new_chunk[j0] * CT, uint32_t(k),
-                                           c->pool_dev + uint64_t(new_slot[j0]) * v.chunk_stride + pool_off,
-                                           c->s_gather);
-            if (rc != LMC_OK) return rc;
-            c->stats.bytes_d2h += uint64_t(k) * v.by_n_lp.d * c->kg.plane_bytes;
-            if ((rc = force_sync(c, c->s_gather)) != LMC_OK) return rc;
-            j0 += k;
-        }
-        return LMC_OK;
-    }
+    if (direct)   // no staging, no copy: the gather kernel writes the pinned pool over the link
+        return move_direct(c, true, view, pool_off, ptrs, slot_mapping, new_chunk.data(), new_slot.data(),
+                           int64_t(new_chunk.size()), c->s_gather);
     const size_t per = size_t(cap_chunks);
     const bool two_copy_streams = !other_direction_busy(c, true);
     hipStream_t copies = on_second_stream ? c->s_d2h2 : c->s_d2h, other = on_second_stream ? c->s_d2h : c->s_d2h2;

@@ -85,7 +85,8 @@ enum {
                                       pinned pool over the host link (64 workgroups, resident
                                       for the length of the transfer).  Same results.
                                       Without the flag only calls of at most 64 MiB go this
-                                      way (lmc_tune "direct_store_below" / "..._retrieve_below"). */
+                                      way, and steps of at most 2 MiB of a layer-wise store
+                                      (lmc_tune "direct_store_below" / "..._retrieve_below"). */
 #define LMC_FLAG_EVICT_LRU 32u     /* a new chunk that finds the pool full takes the slot of
                                       the least recently used chunk that is not pinned, has
                                       no transfer in flight and is not used by the same
@@ -569,8 +570,10 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * LMC_FLAG_TIMING), "trace" (0/1: switches LMC_FLAG_TRACE; 1 also empties the trace and
  * restarts its clock), "direct_store_below" / "direct_retrieve_below" (bytes, default 64 MiB
  * each: an lmc_store with at most that many new bytes, or an lmc_retrieve /
- * lmc_retrieve_batch of at most that many bytes, goes the LMC_FLAG_DIRECT way: one launch
- * instead of kernel, event, copy, event; 0 = never), "scatter_order" (default 0; 1 or 2:
+ * lmc_retrieve_batch / lmc_retrieve_layerwise of at most that many bytes, goes the
+ * LMC_FLAG_DIRECT way: one launch instead of kernel, event, copy, event; an lmc_store_layers
+ * call does if its store has at most that many new bytes and the call itself moves at most
+ * 2 MiB; 0 = never), "scatter_order" (default 0; 1 or 2:
  * scatter launches visit their rows in ascending slot order, built on the device, so that
  * the writes sweep every plane once; 1 = only launches with at least "ordered_min_pages"
  * pages that cover at least one block in "ordered_min_density_inv" of a plane, 2 = every

@@ -573,9 +573,12 @@ lmc_status_t lmc_wait(lmc_ctx_t *c, uint64_t ticket) {
             continue;
         }
         if (o.done == nullptr) continue;
-        const size_t i = size_t(std::find(streams.begin(), streams.end(), o.final_stream) - streams.begin());
+        // a layer-wise store ends when its last layer is submitted, perhaps behind a newer
+        // ticket on the same stream: it is waited for by itself
+        const size_t i = o.layerwise ? streams.size()
+                                     : size_t(std::find(streams.begin(), streams.end(), o.final_stream) - streams.begin());
         if (i == streams.size()) {
-            streams.push_back(o.final_stream);
+            streams.push_back(o.layerwise ? nullptr : o.final_stream);
             last.push_back(o.done);
         } else {
             last[i] = o.done;   // c->ops is in ticket order, and a stream finishes in order

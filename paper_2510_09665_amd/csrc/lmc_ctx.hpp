@@ -46,7 +46,7 @@ struct Op {
     bool pending = false;                 // a store whose layers have not all been submitted
     int32_t next_layer = 0;               // first layer not yet submitted
     int32_t steps = 0;                    // pending store: lmc_store_layers calls served so far
-    bool both_copy_streams = false;       // pending store: steps went to the two copy streams in turn
+    std::vector<hipStream_t> ends_on;     // pending store: the streams its steps so far end on
     std::vector<int64_t> new_chunk;       // pending store: chunk numbers that are new
     const int64_t *slot_mapping = nullptr;  // pending store: the caller's slot mapping
     std::vector<hipEvent_t> layer_done;   // per layer: event after which the layer is in place
@@ -124,8 +124,18 @@ struct lmc_ctx {
     // one launch instead of kernel, event, copy, event halves; up to 64 MiB the single
     // launch is still 2-5 % faster and is over within a millisecond or so, beyond that
     // the staged pipeline keeps the compute units free.  0 = never.
+    // Layer-wise retrieves have the same line: the steps of a small transfer are shorter than
+    // the chain of calls that staging takes for each.  Llama-3-8B shape, one layer a step, 32 and
+    // 64 MiB: 933 and 1493 us staged, 740 and 1330 direct; with the consumer's products between
+    // the steps 5174 and 5842 against 4681 and 4999; 128 MiB: 5403 against 6449.
+    // A layer-wise store's step goes this way if, besides, it moves at most 2 MiB: its kernels
+    // slow the producer's own down while they last, which the calls saved make up for only
+    // there.  One layer a step, 32 and 64 MiB: 1188 and 1580 us staged, 696 and 1300 direct; beside
+    // the producer's products, 32 MiB in steps of 1, 2, 4, 8 MiB: 5682, 5170, 4914, 4588 against 5059,
+    // 5005, 4945, 4874; 64 MiB in steps of 2, 4, 8 MiB: 6486, 4958, 4741 against 5736, 5700, 5570.
     int64_t direct_store_below = int64_t(64) << 20;
     int64_t direct_retrieve_below = int64_t(64) << 20;
+    static constexpr int64_t kDirectStoreStep = int64_t(2) << 20;
     int64_t chunk_bytes = 0;
     int64_t n_pool_slots = 0;
     uint8_t *pool = nullptr;
@@ -226,7 +236,8 @@ lmc_status_t make_ring(lmc_ctx *c, Ring &r);
 // lmc_pipeline.cpp
 lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
-                          uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list = nullptr);
+                          uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list = nullptr,
+                          hipEvent_t stop = nullptr);
 // lmc_streams.cpp
 lmc_status_t shares_a_queue(lmc_ctx *c, hipStream_t busy, bool by_kernel, hipStream_t other, uint8_t *devbuf,
                             uint64_t nbytes, hipEvent_t a0, hipEvent_t a1, hipEvent_t k1, bool *shares);

@@ -69,7 +69,7 @@ static lmc_status_t prepare_order_scratch(lmc_ctx *c, uint64_t n_tokens, hipStre
 
 lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
-                          uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list) {
+                          uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list, hipEvent_t stop) {
     // LMC_FLAG_TIMING: the launch itself carries a start and a stop event, which receive
     // the kernel's own begin / end time stamps; the stream gets no extra marker.
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -83,6 +83,9 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
     if (c->pool_dev != nullptr && staging >= c->pool_dev &&
         staging < c->pool_dev + uint64_t(c->n_pool_slots) * uint64_t(c->chunk_bytes))
         s.paced_groups = c->link_groups;
+    // `stop` completes with the launch: as the launch's own stop event, which costs the GPU and
+    // the calling thread 3 and 1 us less than an event recorded behind it, unless timing needs that
+    const hipEvent_t end = e1 != nullptr ? e1 : stop;
     const uint64_t moved = uint64_t(n_chunks) * view.by_n_lp.d * c->kg.plane_bytes;
     const uint64_t n_tokens = uint64_t(n_chunks) * c->kg.chunk_tokens;
     const bool ordered = !gather && s.paced_groups == 0 && use_ordered_scatter(c, view, n_tokens);
@@ -98,11 +101,12 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
     }
     hipError_t e =
         injected_failure(c) ? hipErrorUnknown
-        : gather  ? lmc::launch_gather(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, e1, list)
+        : gather  ? lmc::launch_gather(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, end, list)
         : ordered ? lmc::launch_scatter_ordered(c->kg, view, s, ptrs, slots, uint32_t(n_tokens), c->order, staging,
-                                                c->bad_flag_dev, stream, e0, e1)
-                  : lmc::launch_scatter(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, e1, list);
+                                                c->bad_flag_dev, stream, e0, end)
+                  : lmc::launch_scatter(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, end, list);
     if (ordered && e == hipSuccess) e = hipEventRecord(c->order_free, stream);
+    if (stop != nullptr && end != stop && e == hipSuccess) e = hipEventRecord(stop, stream);
     if (e != hipSuccess) {
         if (e0 != nullptr) {
             c->free_time_events.push_back(e0);
@@ -325,9 +329,10 @@ static lmc_status_t after_stores(lmc_ctx *c, const int64_t *pool_slots, int64_t 
 // consecutive there.  Where their pool slots are consecutive too the first one's address is
 // all a launch needs; where they are not they are listed, so that a fragmented pool costs one
 // launch for every kMaxListed chunks and not one for every run of slots.
+// stop (may be null): completes with the last launch.
 static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, uint64_t pool_off,
                                 const lmc::LayerPtrs &ptrs, const int64_t *slot_mapping, const int64_t *chunk,
-                                const int64_t *pool_slot, int64_t n, hipStream_t stream) {
+                                const int64_t *pool_slot, int64_t n, hipStream_t stream, hipEvent_t stop = nullptr) {
     const uint64_t cb = uint64_t(c->chunk_bytes);
     const int64_t CT = c->cfg.geom.chunk_tokens;
     view.chunk_stride = cb;  // chunks lie one pool slot apart
@@ -346,7 +351,7 @@ static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, u
         }
         lmc_status_t rc = timed_launch(c, gather, view, ptrs, slot_mapping + (chunk ? chunk[i0] : i0) * CT, uint32_t(k),
                                        c->pool_dev + (listed ? 0 : uint64_t(pool_slot[i0]) * cb) + pool_off, stream,
-                                       listed ? &list : nullptr);
+                                       listed ? &list : nullptr, i0 + k == n ? stop : nullptr);
         if (rc != LMC_OK) return rc;
         (gather ? c->stats.bytes_d2h : c->stats.bytes_h2d) += uint64_t(k) * view.by_n_lp.d * c->kg.plane_bytes;
         if ((rc = force_sync(c, stream)) != LMC_OK) return rc;
@@ -397,8 +402,7 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     hipStream_t user = static_cast<hipStream_t>(user_stream);
     const lmc_kv_geom_t &geom = c->cfg.geom;
     const int64_t CT = geom.chunk_tokens;
-    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 ||
-                        (layers_per_step == 0 && n_chunks * c->chunk_bytes <= c->direct_retrieve_below);
+    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 || n_chunks * c->chunk_bytes <= c->direct_retrieve_below;
     const bool on_caller = n_chunks > 0 && direct && layers_per_step == 0 && launches_on_caller(c, user);
     hipStream_t scatters = on_caller ? user : c->s_scatter;
     // the pages may still be in use, and the slot mapping still be on its way, by work
@@ -424,10 +428,10 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
 
     Ring &ring = c->load_ring;
     const int64_t per = c->cfg.staging_chunks;
-    // without staging (LMC_FLAG_DIRECT, or a small bulk call): no copy, the scatter kernel
-    // reads the pinned pool over the link
-    auto load_direct = [&](const lmc::LaunchView &view, uint64_t pool_off) {
-        return move_direct(c, false, view, pool_off, ptrs, slot_mapping, nullptr, pool_slots.data(), n_chunks, scatters);
+    // without staging (LMC_FLAG_DIRECT, or a small call): no copy, the scatter kernel reads the
+    // pinned pool over the link
+    auto load_direct = [&](const lmc::LaunchView &view, uint64_t pool_off, hipEvent_t stop) {
+        return move_direct(c, false, view, pool_off, ptrs, slot_mapping, nullptr, pool_slots.data(), n_chunks, scatters, stop);
     };
     // one group: copies into the next ring buffer on the H2D stream, scatter on the
     // scatter stream; the buffer is released when the scatter has read it
@@ -472,7 +476,7 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     const bool two_copy_streams = !other_direction_busy(c, false);
     auto enqueue = [&]() -> lmc_status_t {
         if (direct && !op.layerwise) {
-            if ((rc = load_direct(lmc::bulk_view(c->kg), 0)) != LMC_OK) return rc;
+            if ((rc = load_direct(lmc::bulk_view(c->kg), 0, nullptr)) != LMC_OK) return rc;
             // the operation's last event stays on a stream of the library's own: the caller may
             // destroy its stream before the event is asked for
             if (on_caller && (rc = order_after(c, c->s_scatter, user)) != LMC_OK) return rc;
@@ -496,8 +500,11 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
             for (int32_t l0 = 0; l0 < L; l0 += layers_per_step) {
                 const int32_t kk = std::min(layers_per_step, L - l0);
                 const lmc::LaunchView view = lmc::layer_view(c->kg, uint32_t(P), uint32_t(l0), uint32_t(kk));
+                hipEvent_t e;
+                if ((rc = get_event(c, false, &e)) != LMC_OK) return rc;
+                op.owned_events.push_back(e);
                 if (direct) {
-                    if ((rc = load_direct(view, uint64_t(l0) * layer_bytes)) != LMC_OK) return rc;
+                    if ((rc = load_direct(view, uint64_t(l0) * layer_bytes, e)) != LMC_OK) return rc;
                 } else {
                     const int64_t cap = layer_group_chunks(c, ring, view, n_chunks);
                     if ((rc = ring_reslot(c, ring, (uint64_t(cap) * view.chunk_stride + 255) / 256 * 256, c->s_h2d,
@@ -511,10 +518,7 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
                         if ((rc = load_group(view, uint64_t(l0) * layer_bytes, i0, std::min(cap, n_chunks - i0), cs, nullptr)) != LMC_OK)
                             return rc;
                 }
-                hipEvent_t e;
-                if ((rc = get_event(c, false, &e)) != LMC_OK) return rc;
-                op.owned_events.push_back(e);
-                HIPCHK(c, hipEventRecord(e, c->s_scatter));
+                if (!direct) HIPCHK(c, hipEventRecord(e, c->s_scatter));
                 for (int32_t l = l0; l < l0 + kk; l++) op.layer_done[size_t(l)] = e;
             }
         }
@@ -586,12 +590,12 @@ static lmc_status_t store_groups(lmc_ctx *c, const lmc::LaunchView &view, uint64
                                  const std::vector<int64_t> &new_chunk,
                                  const std::vector<int64_t> &new_slot, int64_t cap_chunks,
                                  bool edge_group, bool direct, bool layer_step = false, bool on_second_stream = false,
-                                 std::vector<hipEvent_t> *group_events = nullptr) {
+                                 std::vector<hipEvent_t> *group_events = nullptr, hipEvent_t stop = nullptr) {
     Ring &ring = c->store_ring;
     const int64_t CT = c->cfg.geom.chunk_tokens;
     if (direct)   // no staging, no copy: the gather kernel writes the pinned pool over the link
         return move_direct(c, true, view, pool_off, ptrs, slot_mapping, new_chunk.data(), new_slot.data(),
-                           int64_t(new_chunk.size()), c->s_gather);
+                           int64_t(new_chunk.size()), c->s_gather, stop);
     const size_t per = size_t(cap_chunks);
     const bool two_copy_streams = !other_direction_busy(c, true);
     hipStream_t copies = on_second_stream ? c->s_d2h2 : c->s_d2h, other = on_second_stream ? c->s_d2h : c->s_d2h2;
@@ -771,7 +775,10 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
                                                  uint32_t(n_layers));
     const uint64_t layer_bytes = uint64_t(geom.num_planes) * c->kg.plane_bytes;
     const int64_t cap = layer_group_chunks(c, c->store_ring, view, int64_t(op->new_chunk.size()));
-    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0;
+    const int64_t n_new = int64_t(op->new_chunk.size());
+    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 ||
+                        (n_new * c->chunk_bytes <= c->direct_store_below &&
+                         n_new * int64_t(layer_bytes) * n_layers <= lmc_ctx::kDirectStoreStep);
     // Steps take the two copy streams in turn (as the steps of a layer-wise retrieve do):
     // between two copies of one stream the runtime leaves the link idle for some 20 us,
     // 7 % of a step of one Llama-3-8B layer, while on the other stream (another hardware
@@ -784,19 +791,21 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     if (rc == LMC_OK && !direct)
         rc = ring_reslot(c, c->store_ring, (uint64_t(cap) * view.chunk_stride + 255) / 256 * 256, c->s_gather, c->s_d2h,
                          nullptr, c->s_d2h2);
-    if (rc == LMC_OK)
-        rc = store_groups(c, view, uint64_t(first_layer) * layer_bytes, ptrs, op->slot_mapping, op->new_chunk,
-                          op->slots, cap, false, direct, true, on_second);
     hipEvent_t e = nullptr;
     if (rc == LMC_OK) rc = get_event(c, false, &e);
     if (rc == LMC_OK) {
         op->owned_events.push_back(e);
+        rc = store_groups(c, view, uint64_t(first_layer) * layer_bytes, ptrs, op->slot_mapping, op->new_chunk,
+                          op->slots, cap, false, direct, true, on_second, nullptr, e);
+    }
+    if (rc == LMC_OK) {
         rc = [&]() -> lmc_status_t {
-            HIPCHK(c, hipEventRecord(e, last));
+            if (!direct) HIPCHK(c, hipEventRecord(e, last));
             if (first_layer + n_layers == geom.num_layers) {
-                // the ticket is complete when the steps of both streams are
-                lmc_status_t r = (op->both_copy_streams || on_second)
-                                     ? order_after(c, last, on_second ? c->s_d2h : c->s_d2h2) : LMC_OK;
+                // the ticket is complete when the steps of every stream are
+                lmc_status_t r = LMC_OK;
+                for (hipStream_t s : op->ends_on)
+                    if (r == LMC_OK && s != last) r = order_after(c, last, s);
                 if (r == LMC_OK) r = get_event(c, false, &op->done);
                 if (r != LMC_OK) return r;
                 op->owned_events.push_back(op->done);   // given back with the others if the record fails
@@ -820,7 +829,7 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     for (int32_t l = first_layer; l < first_layer + n_layers; l++) op->layer_done[size_t(l)] = e;
     op->next_layer = first_layer + n_layers;
     op->steps++;
-    op->both_copy_streams = op->both_copy_streams || on_second;
+    if (std::find(op->ends_on.begin(), op->ends_on.end(), last) == op->ends_on.end()) op->ends_on.push_back(last);
     if (op->next_layer == geom.num_layers) op->pending = false;
     return LMC_OK;
 }

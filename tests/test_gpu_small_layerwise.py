@@ -1,0 +1,130 @@
+"""Layer-wise calls that skip staging by their size: retrieves of at most 64 MiB, and steps of at
+most 2 MiB of a store of at most 64 MiB (one store may mix such steps with staged ones).  Bytes
+against the CPU oracle; every layer is read as soon as its wait returns."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_09665_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _setup(n, seed, name="llama3_8b", **kw):
+    import torch
+    from gpu_util import PagedKV, slots_to_device
+    g = W.geometry(name, **dict(dict(L=8, NB=128), **kw))
+    rng = np.random.default_rng(seed)
+    blocks = rng.permutation(g.NB)
+    per = n * g.CT // g.BS
+    slots = W.slots_from_blocks(g, blocks[:per], n * g.CT)
+    tau = W.slots_from_blocks(g, blocks[per:2 * per], n * g.CT)
+    src = PagedKV(g, np.arange(g.NB), rng)
+    dst = PagedKV(g, np.arange(g.NB), fill="sentinel")
+    want = oracle.gather(g, src.host, slots)
+    oracle.scatter(g, want, tau, dst.host)
+    torch.cuda.synchronize()
+    return g, src, dst, want, slots_to_device(slots), slots_to_device(tau), np.arange(1, 1 + n, dtype=np.uint64)
+
+
+# steps of 2 MiB (two chunks, one layer) go direct, larger ones through staging
+@pytest.mark.parametrize("steps", [(1,) * 8, (1, 2, 1, 3, 1), (3, 1, 4), (2, 2, 2, 1, 1), (8,)])
+@pytest.mark.parametrize("timing", [False, True])
+def test_store_steps_of_any_size(steps, timing):
+    import torch
+    from paper_2510_09665_amd import lmc
+    g, src, dst, want, d_slots, d_tau, ids = _setup(2, sum(i * s for i, s in enumerate(steps)))
+    stream = torch.cuda.Stream()
+    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=2, flags=lmc.LMC_FLAG_TIMING if timing else 0) as c:
+        for again in range(2):
+            live = [torch.zeros_like(d) for d in src.dev]        # filled layer by layer on the caller's stream
+            torch.cuda.synchronize()
+            t = c.store_begin(d_slots, ids, stream)
+            l = 0
+            for k in steps:
+                with torch.cuda.stream(stream):
+                    for i in range(l, l + k):
+                        live[i].copy_(src.dev[i])
+                c.store_layers(t, l, k, live, stream)
+                l += k
+            assert l == g.L
+            c.wait_layer(t, 0, stream)
+            c.wait(t)
+            for i, w in zip(ids, want):
+                assert np.array_equal(c.get_host(i), w)
+            assert c.get_stats()["bytes_d2h"] == (again + 1) * 2 * g.chunk_bytes
+            c.clear(ids)
+
+
+@pytest.mark.parametrize("n,k,staged", [(1, 1, False), (2, 3, False), (2, 8, False), (2, 1, True)])
+def test_retrieve_behind_the_store_and_each_layer_at_once(n, k, staged):
+    """Layer-wise store, layer-wise retrieve and a reader of every layer, no host wait between."""
+    import torch
+    from gpu_util import assert_layers_equal
+    from paper_2510_09665_amd import lmc
+    g, src, dst, want, d_slots, d_tau, ids = _setup(n, 11 * n + k)
+    consumer = torch.cuda.Stream()
+    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=2) as c:
+        if staged:
+            c.tune("direct_store_below", 0)
+            c.tune("direct_retrieve_below", 0)
+        t0 = c.store_begin(d_slots, ids)
+        for l in range(g.L):
+            c.store_layers(t0, l, 1, src.dev)
+        t1 = c.retrieve_layerwise(ids, d_tau, dst.dev, k)
+        seen = []
+        for l in range(g.L):
+            c.wait_layer(t1, l, consumer)
+            with torch.cuda.stream(consumer):
+                seen.append(dst.dev[l].clone())
+        consumer.synchronize()
+        assert_layers_equal([d.cpu().numpy() for d in seen], dst.host, "as each wait returned")
+        c.wait(t1)
+        assert c.get_stats()["scatter_launches"] == -(-g.L // k)
+        c.clear(ids)
+
+
+def test_wait_covers_a_layerwise_store_that_ends_behind_a_newer_ticket():
+    """A layer-wise store is begun, a small store follows and is done, then the layers are
+    submitted: waiting for the newer ticket waits for the older one too."""
+    from paper_2510_09665_amd import lmc
+    g, src, dst, want, d_slots, d_tau, ids = _setup(2, 5, L=32, NB=64)
+    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=2) as c:
+        c.tune("direct_store_below", 3 * g.chunk_bytes)
+        t0 = c.store_begin(d_slots, ids)
+        t1 = c.store(src.dev, d_slots, [77])
+        for l in range(g.L):
+            c.store_layers(t0, l, 1, src.dev)
+        c.wait(t1)
+        assert c.test(t0)
+        for i, w in zip(ids, want):
+            assert np.array_equal(c.get_host(i), w)
+
+
+def test_a_staged_layerwise_store_that_fails_is_taken_back_as_a_whole():
+    from paper_2510_09665_amd import lmc
+    g, src, dst, want, d_slots, d_tau, ids = _setup(3, 23, name="tiny", L=4, NB=128)
+    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=2) as c:
+        c.tune("direct_store_below", 0)
+        failures = 0
+        for nth in range(1, 200):
+            t = c.store_begin(d_slots, ids)
+            try:
+                for l in range(g.L):
+                    if l == 2:
+                        c.tune("fail_hip_after", nth)
+                    c.store_layers(t, l, 1, src.dev)
+            except lmc.LMCError as e:
+                assert e.status == lmc.LMC_ERR_HIP, e
+                failures += 1
+                assert c.lookup(ids) == 0 and c.get_stats()["pool_slots_used"] == 0
+                c.wait()
+                continue
+            c.tune("fail_hip_after", 0)
+            c.wait(t)
+            break
+        else:
+            raise AssertionError("the store never got through")
+        assert failures >= 3
+        for i, w in zip(ids, want):
+            assert np.array_equal(c.get_host(i), w)

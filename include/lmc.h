@@ -554,7 +554,8 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * "nt_store" (0/1: non-temporal hints on the kernels' streaming accesses), "xcd_run"
  * (consecutive tiles handed to one XCD, 0 = hardware round-robin), "link_groups" (default
  * 64: launches that read or write the pinned pool themselves run as that many workgroups
- * taking tiles in turn, which is what the host link likes; 0 = one tile per workgroup as
+ * taking tiles in turn (half as many again for long launches that write it), which is what
+ * the host link likes; 0 = one tile per workgroup as
  * for launches inside HBM), "copy_kernel" (default 0; bit 0: copies from staging to the
  * pool are made by the library's own link-paced copy kernel instead of hipMemcpyAsync;
  * bit 1: copies from the pool to staging too.  2-3 % slower than the runtime's copies,

@@ -53,6 +53,34 @@ template <typename V, bool NT> __device__ __forceinline__ void store_vec(uint64_
     else *p = v;
 }
 
+// How the kernels write: as the compiler does, with the non-temporal hint, or at system scope
+// (sc0 sc1 nt).  A store at system scope goes through the XCD's L2 instead of staying there
+// until it is evicted or the kernel ends, and has reached memory, the host's included, when it
+// completes.  For whole cache lines that nobody on the GPU reads back soon that is the faster
+// way: 64 MiB to the pinned pool by a plain copy 57.1 GB/s, the same in every run, against
+// 55.4-56.0 (the runtime's own copies: 56.9); inside HBM a gather of random 32 KiB pages 6.62
+// against 6.52 TB/s, a linear copy 6.76 against 6.48.  The scatter of such pages does not care
+// (5.83-5.88), and lines written in parts suffer, since nothing puts them together any more: the
+// gather of 216-byte rows took 53.8 us instead of 45.7.  Hence launch_move_v's rule.
+enum StoreKind { kStorePlain = 0, kStoreNonTemporal = 1, kStoreThrough = 2 };
+// s_nop: a store of more than 64 bits needs a wait state before its data registers are written
+// again, and the compiler does not see the store.
+__device__ __forceinline__ void store_through(uint64_t addr, typename VecOf<16>::type v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 0" ::"v"(addr), "v"(v) : "memory");
+}
+// The flag the host reads: it must not stay in an L2 either.
+__device__ __forceinline__ void raise_flag(uint64_t addr) {
+    asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(addr), "v"(1) : "memory");
+}
+template <int VEC, int ST> __device__ __forceinline__ void store_out(uint64_t addr, typename VecOf<VEC>::type v) {
+    if constexpr (ST == kStoreThrough) {
+        static_assert(VEC == 16, "whole lines only");
+        store_through(addr, v);
+    } else {
+        store_vec<typename VecOf<VEC>::type, ST != kStorePlain>(addr, v);
+    }
+}
+
 // Keeps a wave-uniform value in scalar registers from this point on.
 template <typename T> __device__ __forceinline__ T pin(T v) {
     asm volatile("" : "+s"(v));
@@ -129,7 +157,7 @@ __device__ __forceinline__ void place(const TileArgs &a, uint32_t w, int64_t *in
 //   GATHER: chunk[c][lp][r] = valid(slot[c][t]) ? page(lp, slot[c][t])[r % vec_per_row] : 0
 //   else  : if valid(slot[c][t]):  page(lp, slot[c][t])[r % vec_per_row] = chunk[c][lp][r]
 // blk numbers the launch's tiles in chunk-buffer order: tile, then layer-plane, then chunk.
-template <int VEC, bool GATHER, bool NT_LD, bool NT_ST>
+template <int VEC, bool GATHER, bool NT_LD, int ST>
 __device__ __forceinline__ void move_tile(const TileArgs &a, const LayerPtrs &layers, uint32_t blk) {
     typedef typename VecOf<VEC>::type V;
     const uint32_t q = a.by_tiles.div(blk);
@@ -145,7 +173,7 @@ __device__ __forceinline__ void move_tile(const TileArgs &a, const LayerPtrs &la
     // the plane's base pointer is fetched while the slot is on its way
     const uint64_t layer = pin(uint64_t(layers.p[a.lp_base + lp]));
     const bool valid = uint64_t(s) < uint64_t(a.n_slots);  // negative wraps to huge
-    if (s >= int64_t(a.n_slots)) store_vec<int32_t, false>(a.bad_flag_at, 1);
+    if (s >= int64_t(a.n_slots)) raise_flag(a.bad_flag_at);
     const uint32_t su = valid ? uint32_t(s) : 0u;  // slot 0 is always inside the pages
     const uint32_t b = a.by_bs.div(su);
     const uint32_t o = su - b * a.by_bs.d;
@@ -158,14 +186,14 @@ __device__ __forceinline__ void move_tile(const TileArgs &a, const LayerPtrs &la
     if (GATHER) {
         V v = load_vec<V, NT_LD>(page);
         if (!valid) v = V(0);
-        store_vec<V, NT_ST>(st, v);
+        store_out<VEC, ST>(st, v);
     } else if (valid) {
-        store_vec<V, NT_ST>(page, load_vec<V, NT_LD>(st));
+        store_vec<V, ST != kStorePlain>(page, load_vec<V, NT_LD>(st));
     }
 }
 
 // HBM to HBM (pages <-> staging): one tile per workgroup, a very large grid.
-template <int VEC, bool GATHER, bool NT_LD, bool NT_ST>
+template <int VEC, bool GATHER, bool NT_LD, int ST>
 __global__ __launch_bounds__(kThreads) void move_rows(const KernelGeom g, const LaunchView view,
                                                       const LayerPtrs layers,
                                                       const int64_t *__restrict__ slot_mapping,
@@ -182,14 +210,14 @@ __global__ __launch_bounds__(kThreads) void move_rows(const KernelGeom g, const 
         const uint32_t grp = local >> xcd_shift;
         blk = (((grp << 3) + xcd) << xcd_shift) + (local & ((1u << xcd_shift) - 1u));
     }
-    move_tile<VEC, GATHER, NT_LD, NT_ST>(a, layers, blk);
+    move_tile<VEC, GATHER, NT_LD, ST>(a, layers, blk);
 }
 
 // The same tile for a workgroup that takes many, one after the other.  Everything is read
 // without a branch (a lane past the end of the plane reads what the last one reads), only the
 // store is conditional.  With a list, chunk c of the launch lies list->slot[c] chunk strides
 // into the buffer.
-template <int VEC, bool GATHER, bool NT_LD, bool NT_ST>
+template <int VEC, bool GATHER, bool NT_LD, int ST>
 __device__ __forceinline__ void move_tile_in_turn(const TileArgs &a, const LayerPtrs &layers, uint32_t blk,
                                                   const ChunkList *list) {
     typedef typename VecOf<VEC>::type V;
@@ -211,27 +239,32 @@ __device__ __forceinline__ void move_tile_in_turn(const TileArgs &a, const Layer
                         (VEC == kWide ? uint64_t(t) * a.row_bytes + in_row : uint64_t(r) * kBytesOf<VEC>);
     const bool has_page = uint64_t(s) < uint64_t(a.n_slots);  // negative wraps to huge
     const bool mine = r0 < a.vec_per_plane;
-    if (mine && s >= int64_t(a.n_slots)) store_vec<int32_t, false>(a.bad_flag_at, 1);
+    if (mine && s >= int64_t(a.n_slots)) raise_flag(a.bad_flag_at);
     const uint32_t su = has_page ? uint32_t(s) : 0u;  // slot 0 is always inside the pages
     const uint32_t b = a.by_bs.div(su);
     const uint32_t o = su - b * a.by_bs.d;
     const uint64_t page = layer + uint64_t(int64_t(b) * a.block_stride + int64_t(o) * a.token_stride + in_page);
     V v = load_vec<V, NT_LD>(GATHER ? page : st);
     if (GATHER && !has_page) v = V(0);
-    if (mine && (GATHER || has_page)) store_vec<V, NT_ST>(GATHER ? st : page, v);
+    if (GATHER) {
+        if (mine) store_out<VEC, ST>(st, v);
+    } else if (mine && has_page) {
+        store_vec<V, ST != kStorePlain>(page, v);
+    }
 }
 
 // Across the host link (pages <-> pinned pool, no staging): the link, not HBM, sets the
 // pace, and it runs best when few workgroups walk the host side in order.  Measured with a
 // plain copy kernel on this part: 64 workgroups taking tiles in turn reach 57.6 GB/s
 // reading host memory and 56.2 GB/s writing it (the runtime's own copies: 57.2 / 57.0),
-// one tile per workgroup over thousands of workgroups 55.7 / 54.4.  The grid is fixed and
+// one tile per workgroup over thousands of workgroups 55.7 / 54.4; with stores at system scope
+// (StoreKind) writing is at 57.1.  The grid is fixed and
 // every workgroup takes tiles blk, blk + gridDim.x, ... until the launch's n_blocks.
 // Two or four tiles at a time in a half or a quarter of the workgroups reach the same rate
 // alone (12 MiB from the host 222-224 us, 32 MiB to it 601-607), but beside another such
 // launch loads are slower: three contexts in turn, 12 MiB each in 256-byte rows, 236 us a
 // pass with 64 x 1 tile, 244 with 32 x 2, 242 with 16 x 4.
-template <int VEC, bool GATHER, bool NT_LD, bool NT_ST>
+template <int VEC, bool GATHER, bool NT_LD, int ST>
 __global__ __launch_bounds__(kThreads) void move_rows_paced(const KernelGeom g, const LaunchView view,
                                                             const LayerPtrs layers,
                                                             const int64_t *__restrict__ slot_mapping,
@@ -240,14 +273,14 @@ __global__ __launch_bounds__(kThreads) void move_rows_paced(const KernelGeom g, 
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
     const uint32_t step = pin(uint32_t(gridDim.x)), end = pin(n_blocks);
     for (uint32_t blk = blockIdx.x; blk < end; blk += step)
-        move_tile_in_turn<VEC, GATHER, NT_LD, NT_ST>(a, layers, blk, nullptr);
+        move_tile_in_turn<VEC, GATHER, NT_LD, ST>(a, layers, blk, nullptr);
 }
 
 // The same for chunks in any pool slots (a fragmented pool, a batch of requests): one launch
 // instead of one per run of consecutive slots, each of which ends with the link running dry
 // and is followed by a gap of 4-5 us.  A store of 25 chunks of 2 MiB in 12 runs: 12 launches
 // take 975 us on the device, one takes 946 (1123 and 1089 us for the whole call).
-template <int VEC, bool GATHER, bool NT_LD, bool NT_ST>
+template <int VEC, bool GATHER, bool NT_LD, int ST>
 __global__ __launch_bounds__(kThreads) void move_rows_listed(const KernelGeom g, const LaunchView view,
                                                              const LayerPtrs layers,
                                                              const int64_t *__restrict__ slot_mapping,
@@ -256,7 +289,7 @@ __global__ __launch_bounds__(kThreads) void move_rows_listed(const KernelGeom g,
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
     const uint32_t step = pin(uint32_t(gridDim.x)), end = pin(n_blocks);
     for (uint32_t blk = blockIdx.x; blk < end; blk += step)
-        move_tile_in_turn<VEC, GATHER, NT_LD, NT_ST>(a, layers, blk, &list);
+        move_tile_in_turn<VEC, GATHER, NT_LD, ST>(a, layers, blk, &list);
 }
 
 // ---- scatter in the order of the destination ---------------------------------------------
@@ -421,12 +454,12 @@ __global__ __launch_bounds__(kThreads) void check_slots(const int64_t *__restric
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// Streaming copy, one 16-byte vector per lane, non-temporal both ways: the fastest of
-// the plain-copy shapes measured on this part.
+// Streaming copy, one 16-byte vector per lane, non-temporal loads, stores through the L2: the
+// fastest of the plain-copy shapes measured on this part.
 __global__ __launch_bounds__(kThreads) void copy_bytes(u32x4 *__restrict__ dst,
                                                        const u32x4 *__restrict__ src, uint64_t n_vec) {
     const uint64_t i = uint64_t(blockIdx.x) * kThreads + threadIdx.x;
-    if (i < n_vec) __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
+    if (i < n_vec) store_through(uint64_t(dst + i), __builtin_nontemporal_load(src + i));
 }
 
 // Plain copy of 4 KiB tiles in a given order, no slot mapping, no geometry: workgroup w
@@ -442,7 +475,7 @@ __global__ __launch_bounds__(kThreads) void copy_tiles(u32x4 *dst, const uint32_
     const uint64_t s = (src_order ? uint64_t(src_order[w]) : uint64_t(w)) * kThreads + threadIdx.x;
     const uint64_t d = (dst_order ? uint64_t(dst_order[w]) : uint64_t(w)) * kThreads + threadIdx.x;
     if (mode == 0) {
-        __builtin_nontemporal_store(__builtin_nontemporal_load(src + s), dst + d);
+        store_through(uint64_t(dst + d), __builtin_nontemporal_load(src + s));
     } else if (mode == 1) {
         const u32x4 v = __builtin_nontemporal_load(src + s);
         if (v.x == 0x9E3779B9u && v.y == 0x7F4A7C15u && v.z == 0xF39CC060u && v.w == 0x5CEDC834u) *sink = v;
@@ -456,6 +489,7 @@ __global__ __launch_bounds__(kThreads) void copy_tiles(u32x4 *dst, const uint32_
 // move_rows_paced: a fixed, small grid whose workgroups take 4 KiB tiles in turn.  The
 // bytes form `rows` rows of width_vec 16-byte vectors, src_pitch / dst_pitch bytes apart
 // (one row per chunk; pitch == width gives a plain copy).
+template <bool TO_POOL>
 __global__ __launch_bounds__(kThreads) void copy_rect_paced(uint8_t *__restrict__ dst, uint64_t dst_pitch,
                                                             const uint8_t *__restrict__ src,
                                                             uint64_t src_pitch, uint64_t width_vec,
@@ -469,7 +503,8 @@ __global__ __launch_bounds__(kThreads) void copy_rect_paced(uint8_t *__restrict_
         const uint64_t v = uint64_t(t - row * by_tpr.d) * kThreads + threadIdx.x;
         if (v >= wv) continue;
         const u32x4 x = load_vec<u32x4, true>(src_at + uint64_t(row) * sp + v * 16u);
-        store_vec<u32x4, true>(dst_at + uint64_t(row) * dp + v * 16u, x);
+        if (TO_POOL) store_through(dst_at + uint64_t(row) * dp + v * 16u, x);
+        else store_vec<u32x4, true>(dst_at + uint64_t(row) * dp + v * 16u, x);
     }
 }
 
@@ -492,7 +527,8 @@ __global__ __launch_bounds__(kThreads) void copy_pieces_paced(uint8_t *__restric
         const uint64_t in_pool = pool_at + uint64_t(uint32_t(slots.slot[row])) * pp + v * 16u;
         const uint64_t in_stage = stage_at + uint64_t(row) * sp + v * 16u;
         const u32x4 x = load_vec<u32x4, true>(TO_POOL ? in_stage : in_pool);
-        store_vec<u32x4, true>(TO_POOL ? in_pool : in_stage, x);
+        if (TO_POOL) store_through(in_pool, x);
+        else store_vec<u32x4, true>(in_stage, x);
     }
 }
 
@@ -510,6 +546,11 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
     if (list != nullptr && (s.paced_groups == 0 || n_chunks > uint32_t(kMaxListed))) return hipErrorInvalidValue;
     const uint32_t n_blocks = n_chunks * v.by_n_lp.d * g.by_tiles_per_plane.d;
     if (n_blocks == 0) return hipSuccess;
+    // the gather's contiguous side goes through the L2 where every wavefront writes whole lines
+    // of 128 bytes: 16-byte lanes, and planes that begin on a line
+    const bool through = GATHER && VEC == 16 && s.nt_load && s.nt_store &&
+                         ((uint64_t(reinterpret_cast<uintptr_t>(staging)) | v.chunk_stride | g.plane_bytes) % 128) == 0;
+    constexpr int kThrough = GATHER && VEC == 16 ? kStoreThrough : kStoreNonTemporal;   // nothing else is instantiated
     uint32_t shift = 0, permuted = 0;
     if (s.xcd_run > 0) {
         while ((2u << shift) <= s.xcd_run) shift++;                      // floor(log2(xcd_run))
@@ -518,27 +559,34 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
     dim3 grid(n_blocks), block(kThreads);
     if (s.paced_groups > 0) {
         // blk + step must not wrap: n_blocks < 2^24 (max_chunks_per_launch) and the grid is small
-        grid = dim3(std::min(n_blocks, s.paced_groups));
+        // A store at system scope ends at the host's memory, and a wavefront waits for it before
+        // it uses the next slot: long launches need half as many workgroups more.  32 MiB by
+        // 64, 96, 128 workgroups: 607, 590, 590 us (601 with 64 and non-temporal stores); 4 to
+        // 12 MiB: the same by 64 and 96; 1 MiB and less: 96 workgroups 5 % slower.
+        const uint32_t groups = through && n_blocks >= 4096 ? s.paced_groups + s.paced_groups / 2 : s.paced_groups;
+        grid = dim3(std::min(n_blocks, groups));
 #define LMC_GO(LD, ST)                                                                                  \
     if (list != nullptr)                                                                                \
         hipExtLaunchKernelGGL((move_rows_listed<VEC, GATHER, LD, ST>), grid, block, 0, stream, start,    \
                               stop, 0, g, v, layers, slot_mapping, staging, bad_flag, n_blocks, *list);  \
     else hipExtLaunchKernelGGL((move_rows_paced<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
                           0, g, v, layers, slot_mapping, staging, bad_flag, n_blocks)
-        if (s.nt_load && s.nt_store) { LMC_GO(true, true); }
-        else if (s.nt_load) { LMC_GO(true, false); }
-        else if (s.nt_store) { LMC_GO(false, true); }
-        else { LMC_GO(false, false); }
+        if (through) { LMC_GO(true, kThrough); }
+        else if (s.nt_load && s.nt_store) { LMC_GO(true, kStoreNonTemporal); }
+        else if (s.nt_load) { LMC_GO(true, kStorePlain); }
+        else if (s.nt_store) { LMC_GO(false, kStoreNonTemporal); }
+        else { LMC_GO(false, kStorePlain); }
 #undef LMC_GO
         return hipGetLastError();
     }
 #define LMC_GO(LD, ST)                                                                          \
     hipExtLaunchKernelGGL((move_rows<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
                           0, g, v, layers, slot_mapping, staging, bad_flag, permuted, shift)
-    if (s.nt_load && s.nt_store) LMC_GO(true, true);
-    else if (s.nt_load) LMC_GO(true, false);
-    else if (s.nt_store) LMC_GO(false, true);
-    else LMC_GO(false, false);
+    if (through) LMC_GO(true, kThrough);
+    else if (s.nt_load && s.nt_store) LMC_GO(true, kStoreNonTemporal);
+    else if (s.nt_load) LMC_GO(true, kStorePlain);
+    else if (s.nt_store) LMC_GO(false, kStoreNonTemporal);
+    else LMC_GO(false, kStorePlain);
 #undef LMC_GO
     return hipGetLastError();
 }
@@ -724,7 +772,7 @@ hipError_t launch_copy_tiles(uint8_t *dst, const uint32_t *dst_order, const uint
 }
 
 hipError_t launch_copy_rect(uint8_t *dst, uint64_t dst_pitch, const uint8_t *src, uint64_t src_pitch,
-                            uint64_t width, uint64_t rows, uint32_t groups, hipStream_t stream) {
+                            uint64_t width, uint64_t rows, bool to_pool, uint32_t groups, hipStream_t stream) {
     if (width == 0 || rows == 0) return hipSuccess;
     if ((width % 16) != 0 || (dst_pitch % 16) != 0 || (src_pitch % 16) != 0 || groups == 0 ||
         (reinterpret_cast<uintptr_t>(dst) % 16) != 0 || (reinterpret_cast<uintptr_t>(src) % 16) != 0)
@@ -737,9 +785,9 @@ hipError_t launch_copy_rect(uint8_t *dst, uint64_t dst_pitch, const uint8_t *src
     for (uint64_t r0 = 0; r0 < rows; r0 += rows_per_launch) {
         const uint64_t n = std::min(rows - r0, rows_per_launch);
         const uint32_t n_tiles = uint32_t(n * tiles_per_row);
-        hipLaunchKernelGGL(copy_rect_paced, dim3(std::min(n_tiles, groups)), dim3(kThreads), 0, stream,
-                           dst + r0 * dst_pitch, dst_pitch, src + r0 * src_pitch, src_pitch, width_vec,
-                           make_fastdiv(uint32_t(tiles_per_row)), n_tiles);
+        hipLaunchKernelGGL(to_pool ? copy_rect_paced<true> : copy_rect_paced<false>, dim3(std::min(n_tiles, groups)),
+                           dim3(kThreads), 0, stream, dst + r0 * dst_pitch, dst_pitch, src + r0 * src_pitch, src_pitch,
+                           width_vec, make_fastdiv(uint32_t(tiles_per_row)), n_tiles);
     }
     return hipGetLastError();
 }

@@ -136,8 +136,9 @@ hipError_t launch_copy_tiles(uint8_t *dst, const uint32_t *dst_order, const uint
 // rows x width bytes, rows src_pitch / dst_pitch apart, by `groups` workgroups that take
 // tiles in turn (the shape that suits a copy whose one side is pinned host memory).
 // Everything must be a multiple of 16 bytes, else hipErrorInvalidValue.
+// to_pool: dst is the pinned pool.
 hipError_t launch_copy_rect(uint8_t *dst, uint64_t dst_pitch, const uint8_t *src, uint64_t src_pitch,
-                            uint64_t width, uint64_t rows, uint32_t groups, hipStream_t stream);
+                            uint64_t width, uint64_t rows, bool to_pool, uint32_t groups, hipStream_t stream);
 // Pool slots of the pieces of one copy_pieces launch, by value like LayerPtrs.
 constexpr int kMaxPieces = 256;
 struct PieceSlots {

@@ -175,8 +175,8 @@ static lmc_status_t copy_group(lmc_ctx *c, bool to_host, uint8_t *staging, uint6
             uint8_t *pool_at = c->pool_dev + uint64_t(pool_slots[j]) * cb + pool_off;
             uint8_t *stage_at = staging + uint64_t(j) * stride;
             const uint32_t groups = c->link_groups ? c->link_groups : 64u;
-            if (to_host) HIPCHK(c, lmc::launch_copy_rect(pool_at, cb, stage_at, stride, width, uint64_t(m), groups, stream));
-            else HIPCHK(c, lmc::launch_copy_rect(stage_at, stride, pool_at, cb, width, uint64_t(m), groups, stream));
+            if (to_host) HIPCHK(c, lmc::launch_copy_rect(pool_at, cb, stage_at, stride, width, uint64_t(m), true, groups, stream));
+            else HIPCHK(c, lmc::launch_copy_rect(stage_at, stride, pool_at, cb, width, uint64_t(m), false, groups, stream));
             if (to_host) c->stats.bytes_d2h += uint64_t(m) * width;
             else c->stats.bytes_h2d += uint64_t(m) * width;
             j += m;

@@ -36,7 +36,10 @@ template <> struct VecOf<2> { typedef unsigned short type; };
 template <> struct VecOf<1> { typedef unsigned char type; };
 // kWide: 16 bytes at any address (gfx950 takes unaligned global accesses in one instruction)
 template <> struct VecOf<kWide> { typedef unsigned int type __attribute__((ext_vector_type(4), aligned(1))); };
-template <int VEC> constexpr uint32_t kBytesOf = VEC == kWide ? 16u : uint32_t(VEC);
+// kPacked: a gather's 16 bytes on the chunk side, put together from rows of any length
+constexpr int kPacked = 18;
+template <> struct VecOf<kPacked> { typedef VecOf<16>::type type; };
+template <int VEC> constexpr uint32_t kBytesOf = VEC == kWide || VEC == kPacked ? 16u : uint32_t(VEC);
 
 #define LMC_GLOBAL __attribute__((address_space(1)))
 
@@ -56,12 +59,13 @@ template <typename V, bool NT> __device__ __forceinline__ void store_vec(uint64_
 // How the kernels write: as the compiler does, with the non-temporal hint, or at system scope
 // (sc0 sc1 nt).  A store at system scope goes through the XCD's L2 instead of staying there
 // until it is evicted or the kernel ends, and has reached memory, the host's included, when it
-// completes.  For whole cache lines that nobody on the GPU reads back soon that is the faster
-// way: 64 MiB to the pinned pool by a plain copy 57.1 GB/s, the same in every run, against
-// 55.4-56.0 (the runtime's own copies: 56.9); inside HBM a gather of random 32 KiB pages 6.62
-// against 6.52 TB/s, a linear copy 6.76 against 6.48.  The scatter of such pages does not care
-// (5.83-5.88), and lines written in parts suffer, since nothing puts them together any more: the
-// gather of 216-byte rows took 53.8 us instead of 45.7.  Hence launch_move_v's rule.
+// completes.  Across the host link that is the faster way to write whole cache lines: 64 MiB to
+// the pinned pool by a plain copy 57.1 GB/s, the same in every run, against 55.4-56.0 (the
+// runtime's own copies: 56.9).  Lines written in parts suffer, since nothing puts them together
+// any more (a gather of 216-byte rows inside HBM: 53.8 us instead of 45.7).  Inside HBM a linear
+// copy gains 3 % (6.76 against 6.48 TB/s), a gather of 512 MiB in random 32 KiB pages 0.4 %, one
+// of 32 MiB loses 2 % (11.1 against 10.9 us) and the scatter does not care: gathers and scatters
+// keep the hint there.
 enum StoreKind { kStorePlain = 0, kStoreNonTemporal = 1, kStoreThrough = 2 };
 // s_nop: a store of more than 64 bits needs a wait state before its data registers are written
 // again, and the compiler does not see the store.
@@ -74,7 +78,7 @@ __device__ __forceinline__ void raise_flag(uint64_t addr) {
 }
 template <int VEC, int ST> __device__ __forceinline__ void store_out(uint64_t addr, typename VecOf<VEC>::type v) {
     if constexpr (ST == kStoreThrough) {
-        static_assert(VEC == 16, "whole lines only");
+        static_assert(VEC == 16 || VEC == kPacked, "whole lines only");
         store_through(addr, v);
     } else {
         store_vec<typename VecOf<VEC>::type, ST != kStorePlain>(addr, v);
@@ -120,10 +124,8 @@ __device__ __forceinline__ TileArgs fetch_args(const KernelGeom &g, const Launch
     a.chunk_tokens = pin(g.chunk_tokens);
     a.n_slots = pin(g.n_slots);
     a.runs_per_row = pin(g.runs_per_row);
-    if (VEC == kWide) {
-        a.run_bytes = pin(g.run_bytes);
-        a.row_bytes = pin(g.row_bytes);
-    }
+    if (VEC == kWide || VEC == kPacked) a.run_bytes = pin(g.run_bytes);
+    if (VEC == kWide) a.row_bytes = pin(g.row_bytes);
     a.block_stride = pin(g.block_stride);
     a.token_stride = pin(g.token_stride);
     a.run_stride = pin(g.run_stride);
@@ -152,6 +154,51 @@ __device__ __forceinline__ void place(const TileArgs &a, uint32_t w, int64_t *in
     *in_row = VEC == kWide ? uint64_t(run) * a.run_bytes + off : uint64_t(w) * kBytesOf<VEC>;
 }
 
+// One 16-byte piece r of plane (c, layer) of a chunk for kPacked, gathered from the pages.
+// Here by_run divides a byte of the plane by run_bytes, which gives the run that holds it, and
+// by_row divides a run by the runs of a row, which gives the token (packed_geom).  A run has 16
+// bytes or more, so a piece holds bytes of one run or of two that follow each other; of those
+// the first's last 16 bytes and the second's first 16 are loaded, so that nothing outside the
+// runs is read, and shifted together.  Tokens without a page give zeros.
+template <bool NT_LD>
+__device__ __forceinline__ typename VecOf<16>::type packed_piece(const TileArgs &a, uint64_t layer, uint32_t c, uint32_t r,
+                                                                 bool flag_bad) {
+    typedef typename VecOf<kWide>::type W;
+    const uint32_t byte = r * 16u;
+    const uint32_t run = a.by_run.div(byte);
+    const uint32_t off = byte - run * a.run_bytes;
+    const uint32_t rest = a.run_bytes - off;          // bytes of this run from here on
+    const uint32_t run2 = rest < 16u ? run + 1u : run;
+    const uint32_t t = a.by_row.div(run), t2 = a.by_row.div(run2);
+    const uint64_t map = a.slots_at + uint64_t(c) * a.chunk_tokens * 8u;
+    const int64_t s = load_vec<int64_t, false>(map + uint64_t(t) * 8u), s2 = load_vec<int64_t, false>(map + uint64_t(t2) * 8u);
+    auto page = [&](int64_t slot, uint32_t token, uint32_t run_of_plane) {
+        const uint32_t su = uint64_t(slot) < uint64_t(a.n_slots) ? uint32_t(slot) : 0u;
+        const uint32_t b = a.by_bs.div(su);
+        return layer + uint64_t(int64_t(b) * a.block_stride + int64_t(su - b * a.by_bs.d) * a.token_stride +
+                                int64_t(run_of_plane - token * a.by_row.d) * a.run_stride);
+    };
+    if (flag_bad && (s >= int64_t(a.n_slots) || s2 >= int64_t(a.n_slots))) raise_flag(a.bad_flag_at);
+    W x = load_vec<W, NT_LD>(page(s, t, run) + min(off, a.run_bytes - 16u));
+    W y = W(0);
+    if (rest < 16u) y = load_vec<W, NT_LD>(page(s2, t2, run2));
+    if (uint64_t(s) >= uint64_t(a.n_slots)) x = W(0);
+    if (uint64_t(s2) >= uint64_t(a.n_slots)) y = W(0);
+    if (rest < 16u) {
+        // bytes 16 - rest .. 15 of x, then bytes 0 .. 15 - rest of y
+        const uint32_t bits = (16u - rest) * 8u;
+        const uint64_t x0 = x.x | uint64_t(x.y) << 32, x1 = x.z | uint64_t(x.w) << 32;
+        const uint64_t y0 = y.x | uint64_t(y.y) << 32, y1 = y.z | uint64_t(y.w) << 32;
+        const unsigned __int128 both = ((unsigned __int128)x1 << 64 | x0) >> bits | ((unsigned __int128)y1 << 64 | y0) << (128u - bits);
+        const uint64_t z0 = uint64_t(both), z1 = uint64_t(both >> 64);
+        x.x = uint32_t(z0);
+        x.y = uint32_t(z0 >> 32);
+        x.z = uint32_t(z1);
+        x.w = uint32_t(z1 >> 32);
+    }
+    return x;
+}
+
 // One tile (256 consecutive vectors of one plane of one chunk) of the path's copy in
 // either direction; lane = one vector r of plane lp of chunk c, token t = r / vec_per_row:
 //   GATHER: chunk[c][lp][r] = valid(slot[c][t]) ? page(lp, slot[c][t])[r % vec_per_row] : 0
@@ -166,6 +213,11 @@ __device__ __forceinline__ void move_tile(const TileArgs &a, const LayerPtrs &la
     const uint32_t lp = q - c * a.by_lp.d;  // plane inside this launch's part of the chunk
     const uint32_t r = tile * kThreads + threadIdx.x;
     if (r >= a.vec_per_plane) return;
+    if constexpr (VEC == kPacked) {
+        const uint64_t st = a.staging_at + uint64_t(c) * a.chunk_stride + uint64_t(lp) * a.plane_bytes + uint64_t(r) * 16u;
+        store_out<VEC, ST>(st, packed_piece<NT_LD>(a, pin(uint64_t(layers.p[a.lp_base + lp])), c, r, true));
+        return;
+    }
     const uint32_t t = a.by_row.div(r);
     const uint32_t w = r - t * a.by_row.d;
 
@@ -227,6 +279,13 @@ __device__ __forceinline__ void move_tile_in_turn(const TileArgs &a, const Layer
     const uint32_t lp = q - c * a.by_lp.d;
     const uint32_t r0 = tile * kThreads + threadIdx.x;
     const uint32_t r = min(r0, a.vec_per_plane - 1);
+    if constexpr (VEC == kPacked) {
+        const uint64_t st = a.staging_at + uint64_t(list ? uint32_t(list->slot[c]) : c) * a.chunk_stride +
+                            uint64_t(lp) * a.plane_bytes + uint64_t(r) * 16u;
+        const V v = packed_piece<NT_LD>(a, uint64_t(layers.p[a.lp_base + lp]), c, r, r0 < a.vec_per_plane);
+        if (r0 < a.vec_per_plane) store_out<VEC, ST>(st, v);
+        return;
+    }
     const uint32_t t = a.by_row.div(r);
     const uint32_t w = r - t * a.by_row.d;
     const int64_t s = load_vec<int64_t, false>(a.slots_at + (uint64_t(c) * a.chunk_tokens + t) * 8u);
@@ -546,11 +605,12 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
     if (list != nullptr && (s.paced_groups == 0 || n_chunks > uint32_t(kMaxListed))) return hipErrorInvalidValue;
     const uint32_t n_blocks = n_chunks * v.by_n_lp.d * g.by_tiles_per_plane.d;
     if (n_blocks == 0) return hipSuccess;
-    // the gather's contiguous side goes through the L2 where every wavefront writes whole lines
-    // of 128 bytes: 16-byte lanes, and planes that begin on a line
-    const bool through = GATHER && VEC == 16 && s.nt_load && s.nt_store &&
+    // a gather into the pool writes through the L2 where every wavefront writes whole lines of
+    // 128 bytes: 16-byte lanes, and planes that begin on a line
+    constexpr bool kLines = GATHER && (VEC == 16 || VEC == kPacked);
+    const bool through = kLines && s.paced_groups > 0 && s.nt_load && s.nt_store &&
                          ((uint64_t(reinterpret_cast<uintptr_t>(staging)) | v.chunk_stride | g.plane_bytes) % 128) == 0;
-    constexpr int kThrough = GATHER && VEC == 16 ? kStoreThrough : kStoreNonTemporal;   // nothing else is instantiated
+    constexpr int kThrough = kLines ? kStoreThrough : kStoreNonTemporal;   // nothing else is instantiated
     uint32_t shift = 0, permuted = 0;
     if (s.xcd_run > 0) {
         while ((2u << shift) <= s.xcd_run) shift++;                      // floor(log2(xcd_run))
@@ -562,8 +622,11 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
         // A store at system scope ends at the host's memory, and a wavefront waits for it before
         // it uses the next slot: long launches need half as many workgroups more.  32 MiB by
         // 64, 96, 128 workgroups: 607, 590, 590 us (601 with 64 and non-temporal stores); 4 to
-        // 12 MiB: the same by 64 and 96; 1 MiB and less: 96 workgroups 5 % slower.
-        const uint32_t groups = through && n_blocks >= 4096 ? s.paced_groups + s.paced_groups / 2 : s.paced_groups;
+        // 12 MiB: the same by 64 and 96; 1 MiB and less: 96 workgroups 5 % slower.  Pieces put
+        // together from two loads take longer still: 8.7 MiB in 216-byte rows, planes of 16
+        // tokens, by 64 and 128: 175, 168 us.
+        const uint32_t groups = VEC == kPacked ? (n_blocks >= 512 ? 2 * s.paced_groups : s.paced_groups)
+                                : through && n_blocks >= 4096 ? s.paced_groups + s.paced_groups / 2 : s.paced_groups;
         grid = dim3(std::min(n_blocks, groups));
 #define LMC_GO(LD, ST)                                                                                  \
     if (list != nullptr)                                                                                \
@@ -582,8 +645,7 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
 #define LMC_GO(LD, ST)                                                                          \
     hipExtLaunchKernelGGL((move_rows<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
                           0, g, v, layers, slot_mapping, staging, bad_flag, permuted, shift)
-    if (through) LMC_GO(true, kThrough);
-    else if (s.nt_load && s.nt_store) LMC_GO(true, kStoreNonTemporal);
+    if (s.nt_load && s.nt_store) LMC_GO(true, kStoreNonTemporal);
     else if (s.nt_load) LMC_GO(true, kStorePlain);
     else if (s.nt_store) LMC_GO(false, kStoreNonTemporal);
     else LMC_GO(false, kStorePlain);
@@ -591,11 +653,32 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
     return hipGetLastError();
 }
 
+// A gather of wide rows into the pool, whose planes are whole 16-byte pieces, goes piece by
+// piece of the chunk (kPacked) instead of row by row: whole lines are written, which may then
+// go through the L2.  44 MiB in 216-byte rows: 871 us with 8-byte lanes, 816 so; in 360-byte
+// rows, whose planes are no whole lines, 934 and 869.  Inside HBM the second load and the
+// shifts cost more than that is worth (121 MiB in 216-byte rows: 61.7 us against 44 row by row).
+bool packs(const KernelGeom &g, const LaunchView &v, const uint8_t *staging) {
+    return g.vec == uint32_t(kWide) && g.plane_bytes < (uint64_t(1) << 31) &&
+           ((uint64_t(reinterpret_cast<uintptr_t>(staging)) | v.chunk_stride | g.plane_bytes) % 16) == 0;
+}
+KernelGeom packed_geom(const KernelGeom &g) {
+    KernelGeom p = g;
+    p.vec_per_plane = uint32_t(g.plane_bytes / 16);
+    p.by_tiles_per_plane = make_fastdiv((p.vec_per_plane + kThreads - 1) / kThreads);
+    p.by_vec_per_run = make_fastdiv(g.run_bytes);
+    p.by_vec_per_row = make_fastdiv(g.runs_per_row);
+    return p;
+}
+
 template <bool GATHER>
 hipError_t launch_move(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                        const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                        uint8_t *staging, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
                        hipEvent_t stop, const ChunkList *list) {
+    if constexpr (GATHER)
+        if (s.paced_groups > 0 && packs(g, v, staging))
+            return launch_move_v<kPacked, true>(packed_geom(g), v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
     switch (g.vec) {
         case kWide: return launch_move_v<kWide, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
         case 16: return launch_move_v<16, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);

@@ -1,7 +1,7 @@
-"""The gather's contiguous side is written at system scope where every wavefront writes whole
-cache lines (16-byte lanes, planes that begin on a multiple of 128 bytes), with the
-non-temporal hint elsewhere; long launches into the pinned pool use more workgroups.  Byte for
-byte against the CPU oracle on both sides of these lines."""
+"""A gather into the pinned pool writes at system scope where every wavefront writes whole cache
+lines (16-byte lanes, planes that begin on a multiple of 128 bytes), with the non-temporal hint
+elsewhere; long launches use more workgroups.  Byte for byte against the CPU oracle on both
+sides of these lines."""
 import numpy as np
 import pytest
 
@@ -11,10 +11,30 @@ from paper_2510_09665_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
+SHAPES = [dict(L=3, P=2, H=4, D=64, e=2, BS=16, NB=48, CT=256),      # planes of whole lines
+          dict(L=3, P=2, H=1, D=24, e=2, BS=4, NB=96, CT=27),       # 48-byte rows, planes are not
+          dict(L=3, P=2, H=1, D=8, e=2, BS=4, NB=96, CT=8)]         # planes of one line
+
+
+@pytest.mark.parametrize("kw", SHAPES)
+def test_store_of_planes_on_and_off_a_line(kw):
+    from gpu_util import PagedKV, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(**kw)
+    rng = np.random.default_rng(g.CT)
+    src = PagedKV(g, np.arange(g.NB), rng)
+    slots = rng.permutation(g.n_slots)[:2 * g.CT].astype(np.int64)
+    slots[rng.integers(0, slots.size, 2)] = -1
+    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=2) as c:
+        c.put_host([9], np.full(g.chunk_bytes, 0xCD, dtype=np.uint8))      # the chunks lie behind it
+        c.wait(c.store(src.dev, slots_to_device(slots), [1, 2]))
+        for i, w in zip((1, 2), oracle.gather(g, src.host, slots)):
+            assert np.array_equal(c.get_host(i), w)
+        assert (c.get_host(9) == 0xCD).all()
+
+
 @pytest.mark.parametrize("off", [0, 16, 64, 112, 128])
-@pytest.mark.parametrize("kw", [dict(L=3, P=2, H=4, D=64, e=2, BS=16, NB=48, CT=256),      # planes of whole lines
-                                dict(L=3, P=2, H=1, D=24, e=2, BS=4, NB=96, CT=27),       # 48-byte rows, planes are not
-                                dict(L=3, P=2, H=1, D=8, e=2, BS=4, NB=96, CT=8)])        # planes of one line
+@pytest.mark.parametrize("kw", SHAPES)
 def test_gather_into_buffers_on_and_off_a_line(kw, off):
     import torch
     from gpu_util import PagedKV, slots_to_device

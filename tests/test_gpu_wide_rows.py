@@ -23,6 +23,9 @@ SHAPES = {
     "row216_fp8": (dict(L=5, P=2, H=3, D=72, e=1, BS=16, NB=56, CT=256), 8),
     "row360_bs12": (dict(L=3, P=2, H=5, D=36, e=2, BS=12, NB=40, CT=84), 8),
     "whole_pieces_of_8_byte_heads": (dict(L=3, P=2, H=4, D=36, e=2, BS=4, NB=40, CT=32), 8),
+    "run16_only": (dict(L=2, P=1, H=1, D=16, e=1, BS=4, NB=40, CT=17, block_pad=8), 8),
+    "run17_whole_planes": (dict(L=2, P=2, H=1, D=17, e=1, BS=4, NB=40, CT=32), 1),
+    "run30_hnd_tiles": (dict(L=2, P=2, H=3, D=15, e=2, BS=4, NB=80, CT=96, layout="HND"), 2),
     "hnd_run72_blocks_outer": (dict(L=3, P=2, H=3, D=36, e=2, BS=4, NB=64, CT=32, order="NP", layout="HND",
                                     block_pad=8), 24),
 }
@@ -40,8 +43,10 @@ def _shifted(layers, off):
 
 
 @pytest.mark.parametrize("name", list(SHAPES))
-@pytest.mark.parametrize("ordered", [False, True])
-def test_both_kernels_match_oracle(name, ordered):
+@pytest.mark.parametrize("ordered,at", [(False, None), (True, None), (False, 0), (False, 16), (False, 128)])
+def test_both_kernels_match_oracle(name, ordered, at):
+    """at: by how many bytes the buffer is off its allocation (None: as the layers).  From a
+    multiple of 16 on, a gather whose planes are whole pieces of 16 bytes goes piece by piece."""
     import torch
     from gpu_util import PagedKV, assert_layers_equal, slots_to_device
     from paper_2510_09665_amd import lmc
@@ -58,6 +63,7 @@ def test_both_kernels_match_oracle(name, ordered):
     with lmc.Context(g, 4 * g.chunk_bytes) as c:
         if ordered:
             c.tune("scatter_order", 2)
+        off = off if at is None else at
         buf = torch.full((off + n * g.chunk_bytes + 64,), 0xCD, dtype=torch.uint8, device="cuda")
         c.gather(src_dev, slots_to_device(slots), n, buf[off:], torch.cuda.current_stream())
         torch.cuda.synchronize()

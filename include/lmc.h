@@ -82,7 +82,7 @@ enum {
                                       then shows as corrupt data.  For tests. */
 #define LMC_FLAG_DIRECT 16u        /* no staging buffer and no copy engine for any call: the
                                       gather kernel writes, and the scatter kernel reads, the
-                                      pinned pool over the host link (64 workgroups, resident
+                                      pinned pool over the host link (64-128 workgroups, resident
                                       for the length of the transfer).  Same results.
                                       Without the flag only calls of at most 64 MiB go this
                                       way, and steps of at most 2 MiB of a layer-wise store
@@ -554,12 +554,13 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * "nt_store" (0/1: non-temporal hints on the kernels' streaming accesses), "xcd_run"
  * (consecutive tiles handed to one XCD, 0 = hardware round-robin), "link_groups" (default
  * 64: launches that read or write the pinned pool themselves run as that many workgroups
- * taking tiles in turn (half as many again for long launches that write it), which is what
- * the host link likes; 0 = one tile per workgroup as
- * for launches inside HBM), "copy_kernel" (default 0; bit 0: copies from staging to the
+ * taking tiles in turn (up to twice as many for long launches that write it), which is
+ * what the host link likes; 0 = one tile per workgroup as for launches inside HBM),
+ * "copy_kernel" (default 0; bit 0: copies from staging to the
  * pool are made by the library's own link-paced copy kernel instead of hipMemcpyAsync;
- * bit 1: copies from the pool to staging too.  2-3 % slower than the runtime's copies,
- * but independent of which engine the runtime picks and of what else that engine is doing),
+ * bit 1: copies from the pool to staging too.  At the rate of the runtime's copies and
+ * independent of which engine the runtime picks and of what else that engine is doing, but
+ * dense products beside such a kernel take some 40 % longer while it lasts),
  * "d2h_guard" (default 1: the library times the runtime's copies to the host of 32 MiB
  * and more, one per group, and when two of the last four fell below six tenths of the
  * best rate it has seen it makes these copies with its own kernel for 0.25 s, then tries

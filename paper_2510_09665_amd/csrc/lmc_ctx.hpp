@@ -82,12 +82,13 @@ struct lmc_ctx {
     uint32_t link_groups = 64;  // workgroups of a launch whose other side is the pinned pool; 0 = as for HBM
     // Which copies between staging and the pool the library's own link-paced copy kernel
     // makes instead of hipMemcpyAsync: bit 0 = to the host, bit 1 = from the host.  Off
-    // by default: the runtime's copies are 2-3 % faster.  But for some seconds after tens
+    // by default: the runtime's copies leave the compute units to the engine (dense products
+    // beside the kernel take some 40 % longer).  But for some seconds after tens
     // of GiB of device or pinned memory have been freed or allocated in the process, the
     // runtime's device-to-host copies inside a store ran at 31.5 GB/s instead of 57 on
     // the machine this was measured on (not with HSA_ENABLE_SDMA=0, which points at the
     // copy engines being busy with the driver's own work on that memory); the kernel's
-    // 55 GB/s does not depend on that.
+    // 57 GB/s does not depend on that.
     uint32_t copy_kernel = 0;
     // ... and the guard that switches device-to-host copies to the kernel by itself while
     // the runtime's are slow (lmc_guard.hpp).  On unless switched off (lmc_tune "d2h_guard"):

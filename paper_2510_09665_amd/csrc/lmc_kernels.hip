@@ -13,7 +13,8 @@
 //     The contiguous side of the copy is then swept linearly by the launch as a
 //     whole, and the paged side is touched page by page (a page's tokens are
 //     consecutive rows).  Ordering by layer-plane first cost 5-10 %.
-//   - Non-temporal loads and stores: nothing is read twice.
+//   - Non-temporal loads and stores inside HBM: nothing is read twice.  Stores to the host
+//     go through the L2 instead (StoreKind).
 //   - Index arithmetic (which chunk, plane, token, vector; slot -> block and offset)
 //     uses multiply-high division by host-precomputed constants; the workgroup-level
 //     part is wave-uniform and runs on the scalar unit.

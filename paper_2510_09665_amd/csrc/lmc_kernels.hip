@@ -68,10 +68,10 @@ template <typename V, bool NT> __device__ __forceinline__ void store_vec(uint64_
 // of 32 MiB loses 2 % (11.1 against 10.9 us) and the scatter does not care: gathers and scatters
 // keep the hint there.
 enum StoreKind { kStorePlain = 0, kStoreNonTemporal = 1, kStoreThrough = 2 };
-// s_nop: a store of more than 64 bits needs a wait state before its data registers are written
-// again, and the compiler does not see the store.
+// s_nop 1: gfx950 wants two wait states between a store of more than 64 bits and an instruction
+// that writes its data registers again, and the compiler, which does not see the store, adds none.
 __device__ __forceinline__ void store_through(uint64_t addr, typename VecOf<16>::type v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 0" ::"v"(addr), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" ::"v"(addr), "v"(v) : "memory");
 }
 // The flag the host reads: it must not stay in an L2 either.
 __device__ __forceinline__ void raise_flag(uint64_t addr) {

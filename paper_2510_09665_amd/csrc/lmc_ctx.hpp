@@ -40,6 +40,8 @@ struct Op {
     uint64_t ticket = 0;
     hipEvent_t done = nullptr;       // null: nothing enqueued (yet) for this ticket
     hipStream_t final_stream = nullptr;  // the library stream `done` was recorded on
+    bool on_caller = false;              // its kernels run on the caller's own stream ...
+    hipStream_t caller = nullptr;        // ... this one
     std::vector<int64_t> slots;      // pool slots whose in-flight count this op holds
     // layer-wise operations (paper section 5.2)
     bool layerwise = false;

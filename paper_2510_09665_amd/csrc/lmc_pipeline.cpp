@@ -369,10 +369,22 @@ static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, u
 // stream is not to wait ("caller_waits" 0), where the library itself waits before it launches
 // (LMC_FLAG_VALIDATE_SLOTS) or where a launch leaves an event behind on its stream (timing,
 // trace, and the scratch of ordered scatters, which "link_groups" 0 lets through).
+// And not beside any transfer of the context's that is under way, other than retrieves that run
+// on that same stream:
+//   - retrieves into the same pages take effect in the order of the calls, which the scatter
+//     stream sees to, and the caller's stream does not;
+//   - the caller's stream may share a hardware queue with the gather stream or a copy stream of
+//     a store, behind whose work the kernels would then wait: 8 MiB beside a store of 1 GiB that
+//     takes 19 ms came back after 11-24 ms from such a stream, from the scatter stream after
+//     0.2-1.1 ms, and whatever is issued next to the scatter stream would wait as long.
+// A stream that is destroyed has finished its work (hipStreamDestroy blocks on this runtime), so a
+// stream that takes the handle of a destroyed one has nothing to be ordered behind.
 static bool launches_on_caller(const lmc_ctx *c, hipStream_t user) {
     if (!c->caller_waits || c->link_groups == 0 ||
         (c->cfg.flags & (LMC_FLAG_VALIDATE_SLOTS | LMC_FLAG_TIMING | LMC_FLAG_TRACE)) != 0)
         return false;
+    for (const Op &o : c->ops)   // what reap() has left
+        if (!o.on_caller || o.caller != user) return false;
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     hipDevice_t dev = c->cfg.device;
     const bool ok = hipStreamIsCapturing(user, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone &&
@@ -424,6 +436,8 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     op.ticket = c->next_ticket++;
     c->cur_ticket = op.ticket;
     op.layerwise = layers_per_step > 0;
+    op.on_caller = on_caller;
+    op.caller = on_caller ? user : nullptr;
     if (n_chunks == 0) return finish_op(c, std::move(op), nullptr, false, ticket_out);
 
     Ring &ring = c->load_ring;

@@ -117,3 +117,88 @@ def test_threads_with_streams_of_their_own():
         for dst, _, _ in work:
             assert_layers_equal([d.cpu().numpy() for d in dst.dev], dst.host, "thread")
         c.clear(ids)
+
+
+def _products(stream, n=40):
+    """Some milliseconds of work on a stream."""
+    import torch
+    with torch.cuda.stream(stream):
+        a = torch.ones(4096, 4096, device="cuda", dtype=torch.bfloat16)
+        for _ in range(n):
+            a = (a @ a).clamp_(-1, 1)
+    return a
+
+
+@pytest.mark.parametrize("first,second", [("bulk", "other"), ("layers", "other"), ("layers", "same"), ("bulk", "null")])
+def test_retrieves_into_the_same_pages_take_effect_in_the_order_of_the_calls(first, second):
+    """The first retrieve has to wait for what is on its stream; the second, from a stream that is
+    idle, fills the same pages with another chunk, and the pages end up with that one."""
+    import torch
+    from gpu_util import PagedKV, assert_layers_equal, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.geometry("tiny", NB=256)
+    rng = np.random.default_rng(31)
+    src, dst = PagedKV(g, np.arange(g.NB), rng), PagedKV(g, np.arange(g.NB), fill="sentinel")
+    slots = rng.permutation(g.n_slots)[:2 * g.CT].astype(np.int64)
+    tau = rng.permutation(g.n_slots)[:g.CT].astype(np.int64)
+    oracle.scatter(g, oracle.gather(g, src.host, slots)[1:], tau, dst.host)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    with lmc.Context(g, 2 * g.chunk_bytes, staging_chunks=2) as c:
+        c.wait(c.store(src.dev, slots_to_device(slots), [1, 2]))
+        d_tau = slots_to_device(tau)
+        torch.cuda.synchronize()
+        keep = _products(a)
+        assert not a.query()
+        if first == "bulk":
+            c.retrieve([1], d_tau, dst.dev, a)
+        else:
+            c.retrieve_layerwise([1], d_tau, dst.dev, 1, a)
+        c.retrieve([2], d_tau, dst.dev, {"other": b, "same": a, "null": None}[second])
+        c.wait()
+        torch.cuda.synchronize()
+        del keep
+        assert_layers_equal([d.cpu().numpy() for d in dst.dev], dst.host, "pages")
+
+
+def test_beside_a_store_from_a_stream_in_its_hardware_queue():
+    """A small retrieve from a stream that shares a hardware queue with a stream of a large store
+    comes back long before the store does."""
+    import time
+    import torch
+    from gpu_util import slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.geometry("llama3_8b", L=8, NB=4096)
+    n, rng = 128, np.random.default_rng(37)
+    blocks = rng.permutation(g.NB)
+    d_ss = slots_to_device(W.slots_from_blocks(g, blocks[:n * 16], n * g.CT))
+    d_ts = slots_to_device(W.slots_from_blocks(g, blocks[n * 16:(n + 1) * 16], g.CT))
+    layers = [torch.zeros(g.layer_bytes, dtype=torch.uint8, device="cuda") for _ in range(g.L)]
+    ids = np.arange(1, n + 1, dtype=np.uint64)
+    producer, streams = torch.cuda.Stream(), [torch.cuda.Stream() for _ in range(12)]
+    for s in streams + [producer]:
+        with torch.cuda.stream(s):
+            torch.zeros(1, device="cuda").add_(1)          # a stream gets its queue when it is first used
+    torch.cuda.synchronize()
+    with lmc.Context(g, (n + 1) * g.chunk_bytes, staging_chunks=8) as c:
+        c.put_host([9999], np.zeros(g.chunk_bytes, dtype=np.uint8))
+        masks = [c.probe_stream(s) for s in streams]
+        # bits 2 to 4: the streams of a store; bit 5: the scatter stream
+        sharing = [s for s, m in zip(streams, masks) if m & 0b011100 and not m & 0b100000][:4]
+        if not sharing:
+            pytest.skip("no stream shares a queue with the store's: %s" % masks)
+        for s in sharing:
+            c.wait(c.store(layers, d_ss, ids, producer))   # what a first pass costs is behind it
+            c.clear(ids)
+            t0 = time.perf_counter()
+            stored = c.store(layers, d_ss, ids, producer)
+            time.sleep(0.002)
+            t1 = time.perf_counter()
+            loaded = c.retrieve([9999], d_ts, layers, s)
+            while not c.test(loaded):
+                pass
+            t2 = time.perf_counter()
+            c.wait(stored)
+            t3 = time.perf_counter()
+            c.clear(ids)
+            torch.cuda.synchronize()
+            assert t2 - t1 < (t3 - t0) / 3, ("retrieve %.1f of %.1f ms" % ((t2 - t1) * 1e3, (t3 - t0) * 1e3), masks)

@@ -85,7 +85,11 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
         s.paced_groups = c->link_groups;
     // `stop` completes with the launch: as the launch's own stop event, which costs the GPU and
     // the calling thread 3 and 1 us less than an event recorded behind it, unless timing needs that
-    const hipEvent_t end = e1 != nullptr ? e1 : stop;
+    // or the stream is being captured, where waits go by the events recorded on it
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    const bool own_stop = stop != nullptr && e1 == nullptr && hipStreamIsCapturing(stream, &capturing) == hipSuccess &&
+                          capturing == hipStreamCaptureStatusNone;
+    const hipEvent_t end = own_stop ? stop : e1;
     const uint64_t moved = uint64_t(n_chunks) * view.by_n_lp.d * c->kg.plane_bytes;
     const uint64_t n_tokens = uint64_t(n_chunks) * c->kg.chunk_tokens;
     const bool ordered = !gather && s.paced_groups == 0 && use_ordered_scatter(c, view, n_tokens);
@@ -106,7 +110,7 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                                                 c->bad_flag_dev, stream, e0, end)
                   : lmc::launch_scatter(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, end, list);
     if (ordered && e == hipSuccess) e = hipEventRecord(c->order_free, stream);
-    if (stop != nullptr && end != stop && e == hipSuccess) e = hipEventRecord(stop, stream);
+    if (stop != nullptr && !own_stop && e == hipSuccess) e = hipEventRecord(stop, stream);
     if (e != hipSuccess) {
         if (e0 != nullptr) {
             c->free_time_events.push_back(e0);

@@ -128,3 +128,46 @@ def test_a_staged_layerwise_store_that_fails_is_taken_back_as_a_whole():
         assert failures >= 3
         for i, w in zip(ids, want):
             assert np.array_equal(c.get_host(i), w)
+
+
+@pytest.mark.parametrize("flag", [False, True])
+@pytest.mark.parametrize("what", ["retrieve", "store"])
+def test_captured_into_a_graph(what, flag):
+    """Layer-wise calls from a stream that is being captured, with a wait for every layer: the
+    graph holds the launches and moves the bytes of the moment each time it is replayed."""
+    import torch
+    from gpu_util import assert_layers_equal
+    from paper_2510_09665_amd import lmc
+    g, src, dst, want, d_slots, d_tau, ids = _setup(2, 41, name="tiny", L=4, NB=128)
+    untouched = [d.clone() for d in dst.dev]
+    stream = torch.cuda.Stream()
+    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=2, flags=lmc.LMC_FLAG_DIRECT if flag else 0) as c:
+        if what == "retrieve":
+            c.wait(c.store(src.dev, d_slots, ids))
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream, capture_error_mode="relaxed"):
+            if what == "retrieve":
+                t = c.retrieve_layerwise(ids, d_tau, dst.dev, 1, stream)
+            else:
+                t = c.store_begin(d_slots, ids, stream)
+                for l in range(g.L):
+                    c.store_layers(t, l, 1, src.dev, stream)
+            for l in range(g.L):
+                c.wait_layer(t, l, stream)
+        for replay in range(3):
+            if what == "retrieve":
+                for d, u in zip(dst.dev, untouched):
+                    d.copy_(u)
+            else:
+                for d in src.dev:
+                    d.bitwise_xor_(255)               # other bytes each time
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            if what == "retrieve":
+                assert_layers_equal([d.cpu().numpy() for d in dst.dev], dst.host, "replay %d" % replay)
+            else:
+                for i, w in zip(ids, want):
+                    assert np.array_equal(c.get_host(i), w ^ (255 if replay % 2 == 0 else 0)), replay
+        del graph

@@ -343,9 +343,11 @@ static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, u
     const int64_t max_k = int64_t(lmc::max_chunks_per_launch(c->kg, view));
     // "link_groups" 0 asks for launches of one tile per workgroup, which take no list
     const bool may_list = c->link_groups > 0 && c->n_pool_slots <= INT32_MAX;
+    int64_t map_end = 0;   // chunks i0 .. map_end - 1 are consecutive in the mapping; found once for all of them
     for (int64_t i0 = 0, k = 0; i0 < n; i0 += k) {
-        int64_t in_map = 1;
-        while (in_map < max_k && i0 + in_map < n && (!chunk || chunk[i0 + in_map] == chunk[i0] + in_map)) in_map++;
+        if (map_end <= i0)
+            for (map_end = i0 + 1; map_end < n && (!chunk || chunk[map_end] == chunk[map_end - 1] + 1);) map_end++;
+        const int64_t in_map = std::min(max_k, map_end - i0);
         for (k = 1; k < in_map && pool_slot[i0 + k] == pool_slot[i0] + k;) k++;
         lmc::ChunkList list;
         const bool listed = may_list && k < in_map && k < lmc::kMaxListed;

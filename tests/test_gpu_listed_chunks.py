@@ -78,3 +78,33 @@ def test_scattered_slots_match_oracle(rows, n, run, how):
         assert c.get_stats()["bytes_h2d"] == n * g.chunk_bytes
     oracle.scatter(g, want, tau, dst.host)
     assert_layers_equal([d.cpu().numpy() for d in dst.dev], dst.host, rows)
+
+
+def test_cost_of_a_call_grows_with_its_chunks_and_no_faster():
+    """"link_groups" 0 and every other pool slot taken: a launch for each chunk.  Four times the
+    chunks take about four times as long to enqueue; a search that begins anew for each launch took
+    ten times."""
+    import time
+    import torch
+    from gpu_util import slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(L=1, P=1, H=1, D=16, e=1, BS=4, NB=4, CT=4)
+    most = 131072
+    layers = [torch.zeros(g.layer_bytes, dtype=torch.uint8, device="cuda")]
+    slots = slots_to_device(np.tile(np.arange(g.CT, dtype=np.int64), most))
+    with lmc.Context(g, 2 * most * g.chunk_bytes, staging_chunks=2) as c:
+        c.tune("link_groups", 0)
+        other = (1 << 32) + np.arange(2 * most, dtype=np.uint64)
+        c.put_host(other, np.zeros(2 * most * g.chunk_bytes, dtype=np.uint8))
+        c.clear(other[::2])
+        took = {}
+        for n in (most // 4, most) * 3:
+            ids = np.arange(1, n + 1, dtype=np.uint64)
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            ticket = c.store(layers, slots, ids)
+            took[n] = min(took.get(n, 1e9), time.perf_counter() - t)
+            c.wait(ticket)
+            c.clear(ids)
+        assert c.get_stats()["gather_launches"] == 3 * (most + most // 4)
+        assert took[most] < 6.5 * took[most // 4], took

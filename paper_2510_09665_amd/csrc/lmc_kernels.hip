@@ -214,11 +214,6 @@ __device__ __forceinline__ void move_tile(const TileArgs &a, const LayerPtrs &la
     const uint32_t lp = q - c * a.by_lp.d;  // plane inside this launch's part of the chunk
     const uint32_t r = tile * kThreads + threadIdx.x;
     if (r >= a.vec_per_plane) return;
-    if constexpr (VEC == kPacked) {
-        const uint64_t st = a.staging_at + uint64_t(c) * a.chunk_stride + uint64_t(lp) * a.plane_bytes + uint64_t(r) * 16u;
-        store_out<VEC, ST>(st, packed_piece<NT_LD>(a, pin(uint64_t(layers.p[a.lp_base + lp])), c, r, true));
-        return;
-    }
     const uint32_t t = a.by_row.div(r);
     const uint32_t w = r - t * a.by_row.d;
 
@@ -678,21 +673,24 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
 #undef LMC_GO
         return hipGetLastError();
     }
-    if constexpr (GATHER && VEC == 16)
-        if (g.by_vec_per_run.d % 64 == 0 && s.nt_load && s.nt_store && reinterpret_cast<uintptr_t>(slot_mapping) % 8 == 0) {
-            hipExtLaunchKernelGGL(gather_rows_by_wave, grid, block, 0, stream, start, stop, 0, g, v, layers, slot_mapping,
-                                  staging, bad_flag, permuted, shift);
-            return hipGetLastError();
-        }
+    if constexpr (VEC != kPacked) {
+        if constexpr (GATHER && VEC == 16)
+            if (g.by_vec_per_run.d % 64 == 0 && s.nt_load && s.nt_store && reinterpret_cast<uintptr_t>(slot_mapping) % 8 == 0) {
+                hipExtLaunchKernelGGL(gather_rows_by_wave, grid, block, 0, stream, start, stop, 0, g, v, layers, slot_mapping,
+                                      staging, bad_flag, permuted, shift);
+                return hipGetLastError();
+            }
 #define LMC_GO(LD, ST)                                                                          \
-    hipExtLaunchKernelGGL((move_rows<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
-                          0, g, v, layers, slot_mapping, staging, bad_flag, permuted, shift)
-    if (s.nt_load && s.nt_store) LMC_GO(true, kStoreNonTemporal);
-    else if (s.nt_load) LMC_GO(true, kStorePlain);
-    else if (s.nt_store) LMC_GO(false, kStoreNonTemporal);
-    else LMC_GO(false, kStorePlain);
+        hipExtLaunchKernelGGL((move_rows<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
+                              0, g, v, layers, slot_mapping, staging, bad_flag, permuted, shift)
+        if (s.nt_load && s.nt_store) LMC_GO(true, kStoreNonTemporal);
+        else if (s.nt_load) LMC_GO(true, kStorePlain);
+        else if (s.nt_store) LMC_GO(false, kStoreNonTemporal);
+        else LMC_GO(false, kStorePlain);
 #undef LMC_GO
-    return hipGetLastError();
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;   // packed pieces go across the link only (packs)
 }
 
 // A gather of wide rows into the pool, whose planes are whole 16-byte pieces, goes piece by

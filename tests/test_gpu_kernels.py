@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 # shapes chosen to cross every kernel path: 16-byte vectors with contiguous rows,
 # per-head runs (HND), padded blocks, rows that are not a multiple of a wavefront
-# (MLA: 72 and 36 vectors), narrow vectors (8/4/2/1 bytes), a block size that is not a
+# (MLA: 72 and 36 vectors), narrow vectors (4 and 1 bytes; the rest in test_gpu_pool_rows.py),
+# runs of 16 bytes and more on strides that are multiples of 8 or 2, a block size that is not a
 # power of two, planes whose size is not a multiple of a 256-vector tile, P=1 and P=2,
 # pages ordered blocks-outermost (the K and V page of a block adjacent in memory).
 SHAPES = {

@@ -1,7 +1,7 @@
 """A gather into the pinned pool writes at system scope where every wavefront writes whole cache
 lines (16-byte lanes, planes that begin on a multiple of 128 bytes), with the non-temporal hint
 elsewhere; long launches use more workgroups.  Byte for byte against the CPU oracle on both
-sides of these lines."""
+sides of these lines.  Gathers into buffers in HBM keep the hint wherever the buffer lies."""
 import numpy as np
 import pytest
 

@@ -45,8 +45,9 @@ def _shifted(layers, off):
 @pytest.mark.parametrize("name", list(SHAPES))
 @pytest.mark.parametrize("ordered,at", [(False, None), (True, None), (False, 0), (False, 16), (False, 128)])
 def test_both_kernels_match_oracle(name, ordered, at):
-    """at: by how many bytes the buffer is off its allocation (None: as the layers).  From a
-    multiple of 16 on, a gather whose planes are whole pieces of 16 bytes goes piece by piece."""
+    """at: by how many bytes the buffer is off its allocation (None: as the layers).  Inside HBM both
+    kernels go row by row wherever the buffer lies; gathers into the pool, which put whole pieces
+    of 16 bytes together, are in test_gpu_pool_rows.py."""
     import torch
     from gpu_util import PagedKV, assert_layers_equal, slots_to_device
     from paper_2510_09665_amd import lmc

@@ -241,9 +241,10 @@ lmc_status_t lmc_store(lmc_ctx_t *ctx, void *const *kv_layers, const int64_t *sl
  * then the caller orders its work after lmc_wait itself).  Enqueue only.  The kernels of a
  * call that goes without staging run on that stream itself where nothing else of the context's
  * is under way but such calls from the same stream; elsewhere, and always while the stream is
- * being captured, for a stream of another GPU, with "caller_waits" 0, "link_groups" 0 or one of
- * LMC_FLAG_VALIDATE_SLOTS, _TIMING and _TRACE, on a stream of the library's.  Either way the
- * retrieves of a context fill the pages in the order in which they were called.
+ * being captured, for hipStreamPerThread or a stream of another GPU, with "caller_waits" 0,
+ * "link_groups" 0 or one of LMC_FLAG_VALIDATE_SLOTS, _TIMING and _TRACE, they run on a stream
+ * of the library's.  Either way the retrieves of a context fill the pages in the order in which
+ * they were called.
  * LMC_ERR_HIP in the middle of the call: what had been enqueued is waited for, no count
  * stays on the chunks, no ticket is issued; the pages named by slot_mapping are then
  * partly written. */

@@ -383,10 +383,11 @@ static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, u
 //     a store, behind whose work the kernels would then wait: 8 MiB beside a store of 1 GiB that
 //     takes 19 ms came back after 11-24 ms from such a stream, from the scatter stream after
 //     0.2-1.1 ms, and whatever is issued next to the scatter stream would wait as long.
+// hipStreamPerThread is one name for many streams, one a thread: the library's stream it is.
 // A stream that is destroyed has finished its work (hipStreamDestroy blocks on this runtime), so a
 // stream that takes the handle of a destroyed one has nothing to be ordered behind.
 static bool launches_on_caller(const lmc_ctx *c, hipStream_t user) {
-    if (!c->caller_waits || c->link_groups == 0 ||
+    if (!c->caller_waits || c->link_groups == 0 || user == hipStreamPerThread ||
         (c->cfg.flags & (LMC_FLAG_VALIDATE_SLOTS | LMC_FLAG_TIMING | LMC_FLAG_TRACE)) != 0)
         return false;
     for (const Op &o : c->ops)   // what reap() has left

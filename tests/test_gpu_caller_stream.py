@@ -202,3 +202,40 @@ def test_beside_a_store_from_a_stream_in_its_hardware_queue():
             c.clear(ids)
             torch.cuda.synchronize()
             assert t2 - t1 < (t3 - t0) / 3, ("retrieve %.1f of %.1f ms" % ((t2 - t1) * 1e3, (t3 - t0) * 1e3), masks)
+
+
+def test_the_per_thread_stream_is_another_one_in_each_thread():
+    """Two threads name hipStreamPerThread: one name, two streams.  The first thread's is busy, the
+    second's is not; the pages they both fill end up as the second call left them."""
+    import torch
+    from gpu_util import PagedKV, assert_layers_equal, slots_to_device
+    from paper_2510_09665_amd import lmc
+    per_thread = 2                                          # hipStreamPerThread
+    g = W.geometry("tiny", NB=256)
+    rng = np.random.default_rng(43)
+    src, dst = PagedKV(g, np.arange(g.NB), rng), PagedKV(g, np.arange(g.NB), fill="sentinel")
+    slots = rng.permutation(g.n_slots)[:2 * g.CT].astype(np.int64)
+    tau = rng.permutation(g.n_slots)[:g.CT].astype(np.int64)
+    oracle.scatter(g, oracle.gather(g, src.host, slots)[1:], tau, dst.host)
+    with lmc.Context(g, 2 * g.chunk_bytes, staging_chunks=2) as c:
+        c.wait(c.store(src.dev, slots_to_device(slots), [1, 2]))
+        d_tau = slots_to_device(tau)
+        torch.cuda.synchronize()
+        errors, keep = [], []
+
+        def load(chunk, products):
+            try:
+                if products:
+                    keep.append(_products(torch.cuda.ExternalStream(per_thread), products))
+                c.retrieve([chunk], d_tau, dst.dev, per_thread)
+            except Exception as e:
+                errors.append(e)
+
+        for args in ((1, 40), (2, 0)):
+            t = threading.Thread(target=load, args=args)
+            t.start()
+            t.join()
+        assert not errors, errors
+        c.wait()
+        torch.cuda.synchronize()
+        assert_layers_equal([d.cpu().numpy() for d in dst.dev], dst.host, "pages")

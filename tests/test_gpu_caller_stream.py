@@ -239,3 +239,34 @@ def test_the_per_thread_stream_is_another_one_in_each_thread():
         c.wait()
         torch.cuda.synchronize()
         assert_layers_equal([d.cpu().numpy() for d in dst.dev], dst.host, "pages")
+
+
+def test_a_retrieve_that_fails_on_the_callers_stream_can_be_repeated():
+    """Every checked HIP call of a retrieve on the caller's stream fails once (on the host): no count
+    stays on the chunks, and the call made again fills the pages."""
+    import torch
+    from gpu_util import assert_layers_equal
+    from paper_2510_09665_amd import lmc
+    g, src, dst, d_slots, d_tau, ids = _case(5, 61)
+    stream = torch.cuda.Stream()
+    with lmc.Context(g, 5 * g.chunk_bytes, staging_chunks=2) as c:
+        c.wait(c.store(src.dev, d_slots, ids))
+        torch.cuda.synchronize()
+        failures = 0
+        for nth in range(1, 50):
+            c.tune("fail_hip_after", nth)
+            try:
+                t = c.retrieve(ids, d_tau, dst.dev, stream)
+            except lmc.LMCError as e:
+                assert e.status == lmc.LMC_ERR_HIP, e
+                failures += 1
+                assert c.lookup(ids) == ids.size
+                continue
+            c.tune("fail_hip_after", 0)
+            c.wait(t)
+            break
+        else:
+            raise AssertionError("the retrieve never got through")
+        assert failures >= 4, failures        # launch, event and wait behind it, the ticket's event
+        c.clear(ids)                          # BUSY if a count had stayed
+        assert_layers_equal([d.cpu().numpy() for d in dst.dev], dst.host, "pages")

@@ -244,7 +244,8 @@ lmc_status_t lmc_store(lmc_ctx_t *ctx, void *const *kv_layers, const int64_t *sl
  * being captured, for hipStreamPerThread or a stream of another GPU, with "caller_waits" 0,
  * "link_groups" 0 or one of LMC_FLAG_VALIDATE_SLOTS, _TIMING and _TRACE, they run on a stream
  * of the library's.  Either way the retrieves of a context fill the pages in the order in which
- * they were called.
+ * they were called.  On the caller's stream the first such call also pays for the runtime's
+ * set-up of a stream that has run nothing yet (up to 30 us once, as any first launch would).
  * LMC_ERR_HIP in the middle of the call: what had been enqueued is waited for, no count
  * stays on the chunks, no ticket is issued; the pages named by slot_mapping are then
  * partly written. */

@@ -128,12 +128,13 @@ struct lmc_ctx {
     // launch is still 2-5 % faster and is over within a millisecond or so, beyond that
     // the staged pipeline keeps the compute units free.  0 = never.
     // Layer-wise retrieves have the same line: the steps of a small transfer are shorter than
-    // the chain of calls that staging takes for each.  Llama-3-8B shape, one layer a step, 32 and
-    // 64 MiB: 933 and 1493 us staged, 740 and 1330 direct; with the consumer's products between
-    // the steps 5174 and 5842 against 4681 and 4999; 128 MiB: 5403 against 6449.
+    // the chain of calls that staging takes for each.  Llama-3-8B shape, one layer a step, from the
+    // first call to an idle device, 32 and 64 MiB: 970 and 1709 us staged, 811 and 1531 direct; with
+    // the consumer's products between the steps 5174 and 5842 against 4681 and 4999; 128 MiB: 5403
+    // against 6449.
     // A layer-wise store's step goes this way if, besides, it moves at most 2 MiB: its kernels
     // slow the producer's own down while they last, which the calls saved make up for only
-    // there.  One layer a step, 32 and 64 MiB: 1188 and 1580 us staged, 696 and 1300 direct; beside
+    // there.  One layer a step, 32 and 64 MiB: 1213 and 1612 us staged, 729 and 1346 direct; beside
     // the producer's products, 32 MiB in steps of 1, 2, 4, 8 MiB: 5682, 5170, 4914, 4588 against 5059,
     // 5005, 4945, 4874; 64 MiB in steps of 2, 4, 8 MiB: 6486, 4958, 4741 against 5736, 5700, 5570.
     int64_t direct_store_below = int64_t(64) << 20;

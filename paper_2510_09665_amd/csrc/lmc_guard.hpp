@@ -6,8 +6,8 @@
 // this or by the previous process) they ran at 31.5 GB/s instead of 57, on and off; and in a
 // mix of stores and retrieves of many requests (32 MiB copies into a fragmented pool beside
 // copies the other way) whole stores ran at 12.7 GB/s, one in five, while a copy kernel's
-// rate (55 GB/s) did not change.  When healthy, the runtime's copy is the faster one and
-// occupies no compute unit, so it stays the first choice.
+// rate (57 GB/s) did not change.  When healthy, the runtime's copy is as fast and occupies no
+// compute unit, so it stays the first choice.
 //
 // Policy: remember the best rate a runtime copy has reached.  When two of the last four
 // watched copies were below six tenths of it (in the slow state the small copy at the

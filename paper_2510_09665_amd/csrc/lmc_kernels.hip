@@ -301,10 +301,11 @@ __global__ __launch_bounds__(kThreads) void gather_rows_by_wave(const KernelGeom
     __builtin_nontemporal_store(v, (LMC_GLOBAL V *)st + lane);
 }
 
-// The same tile for a workgroup that takes many, one after the other.  Everything is read
-// without a branch (a lane past the end of the plane reads what the last one reads), only the
-// store is conditional.  With a list, chunk c of the launch lies list->slot[c] chunk strides
-// into the buffer.
+// The same tile for a workgroup that takes many, one after the other: no early return, a lane
+// past the end of the plane reads the slot that the last one reads and moves nothing.  The
+// compiler puts the load of the data under the store's condition, so a token without a page
+// costs no traffic on the link.  With a list, chunk c of the launch lies list->slot[c] chunk
+// strides into the buffer.
 template <int VEC, bool GATHER, bool NT_LD, int ST>
 __device__ __forceinline__ void move_tile_in_turn(const TileArgs &a, const LayerPtrs &layers, uint32_t blk,
                                                   const ChunkList *list) {

@@ -369,9 +369,10 @@ static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, u
 // They start after what is on it and it continues after them, which is the contract, and no
 // event has to cross from that stream to the library's and back: those two hand-overs cost the
 // calling thread 26 us (a query and a wait between streams are 12-14 us each on this runtime)
-// and leave the link idle in between when one such retrieve follows another.  Measured from
-// one stream, call after call: 0.5 MiB 57 -> 36 us, 12 MiB in 256-byte rows 250 -> 228 us.  Not while
-// the stream is being captured, not for a stream of another GPU, and not where the caller's
+// and leave the link idle in between when one such retrieve follows another.  Call after call, three
+// contexts in turn: 0.5 MiB 53 -> 36 us, 12 MiB in 256-byte rows 234 -> 223 us.  What the runtime does
+// for the first launch on a stream that has run nothing is now done inside the call: a program's
+// first 0.5 MiB takes 155-190 us instead of 150-160.  Not while the stream is being captured, not for a stream of another GPU, and not where the caller's
 // stream is not to wait ("caller_waits" 0), where the library itself waits before it launches
 // (LMC_FLAG_VALIDATE_SLOTS) or where a launch leaves an event behind on its stream (timing,
 // trace, and the scratch of ordered scatters, which "link_groups" 0 lets through).

@@ -160,7 +160,7 @@ typedef struct {
     uint64_t d2h_guard_active;    /* 1 while they are with the copy kernel, else 0 */
     uint64_t bytes_gathered, bytes_scattered; /* chunk payload through the kernels */
     uint64_t bytes_d2h, bytes_h2d;            /* chunk payload over the host link */
-    uint64_t gather_launches, scatter_launches;
+    uint64_t gather_launches, scatter_launches; /* each step of a layer-wise retrieve counts */
     uint64_t timed_gather_launches, timed_scatter_launches; /* LMC_FLAG_TIMING, completed */
     double gather_ms, scatter_ms;             /* sum of their HIP-event durations */
     double d2h_copy_best_gbps;    /* best rate seen of a runtime copy to the host of 32 MiB or
@@ -269,6 +269,10 @@ lmc_status_t lmc_retrieve_batch(lmc_ctx_t *ctx, int64_t n_req, const int64_t *re
  * slots) and scattered, then the next layers follow, so that layer l's pages are
  * complete long before the last layer's.  The consumer orders itself per layer with
  * lmc_wait_layer; unlike lmc_retrieve, no stream is made to wait for the whole call.
+ * Without staging (a small call, or LMC_FLAG_DIRECT) one launch moves all the layers, step by
+ * step, unless the stream is being captured, "link_groups" is 0, more than 256 chunks lie in
+ * scattered slots or one of LMC_FLAG_TIMING, _TRACE and _FORCE_SYNC is set: then each step is
+ * a launch.
  * stream_to_wait_on: the call is ordered after work already on it (old users of the
  * pages, producer of the slot mapping).  layers_per_step >= 1 (values above num_layers
  * mean "all").  Errors as lmc_retrieve, and LMC_ERR_BUSY if one of the chunks belongs
@@ -299,7 +303,8 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *ctx, uint64_t ticket, int32_t first_lay
 /* Make `stream` (hipStream_t, NULL = null stream) wait, on the device, until layer
  * `layer` of a layer-wise ticket is in place: loaded into its pages (retrieve) or
  * arrived in the pool (store).  The host does not block.  A finished ticket needs no
- * wait and returns LMC_OK.  LMC_ERR_INVAL for a ticket that is not layer-wise or a
+ * wait and returns LMC_OK.  (A stream of another GPU waits for all the layers where one launch
+ * moves them.)  LMC_ERR_INVAL for a ticket that is not layer-wise or a
  * layer out of range; LMC_ERR_BUSY for a store layer that has not been submitted. */
 lmc_status_t lmc_wait_layer(lmc_ctx_t *ctx, uint64_t ticket, int32_t layer, void *stream);
 
@@ -558,11 +563,13 @@ lmc_status_t lmc_measure_link_duplex_kernel(lmc_ctx_t *ctx, uint64_t nbytes, int
 lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
 
 /* Run-time knobs for experiments; the defaults are the measured best.  Keys: "nt_load",
- * "nt_store" (0/1: non-temporal hints on the kernels' streaming accesses), "xcd_run"
+ * "nt_store" (0/1: non-temporal hints on the kernels' streaming accesses, except those of
+ * scatters that read the pool itself), "xcd_run"
  * (consecutive tiles handed to one XCD, 0 = hardware round-robin), "link_groups" (default
- * 64: launches that read or write the pinned pool themselves run as that many workgroups
- * taking tiles in turn (up to twice as many for long launches that write it), which is
- * what the host link likes; 0 = one tile per workgroup as for launches inside HBM),
+ * 64: launches that read or write the pinned pool themselves run as that many groups of 256
+ * lanes taking tiles in turn (up to twice as many for long launches that write it), which is
+ * what the host link likes; those that read it put two groups to a workgroup and keep its compute
+ * unit to themselves; 0 = one tile per workgroup as for launches inside HBM),
  * "copy_kernel" (default 0; bit 0: copies from staging to the
  * pool are made by the library's own link-paced copy kernel instead of hipMemcpyAsync;
  * bit 1: copies from the pool to staging too.  At the rate of the runtime's copies and

@@ -388,6 +388,7 @@ static void destroy_ctx(lmc_ctx *c) {
         for (hipStream_t s : {c->s_gather, c->s_d2h, c->s_h2d, c->s_scatter, c->s_h2d2, c->s_d2h2})
             if (s) (void)hipStreamDestroy(s);
         if (c->bad_flag_host) (void)hipHostFree(c->bad_flag_host);
+        if (c->words) (void)hipFree(c->words);
         if (c->pool) (void)hipHostFree(c->pool);
     } else {
         std::free(c->pool);
@@ -488,6 +489,15 @@ lmc_status_t lmc_create(const lmc_config_t *cfg, lmc_ctx_t **ctx_out) {
         std::memset(c->bad_flag_host, 0, 64);
         if (hipHostGetDevicePointer(reinterpret_cast<void **>(&c->bad_flag_dev), c->bad_flag_host, 0) != hipSuccess)
             return fail(LMC_ERR_HIP);
+        int can_wait = 0;
+        if (hipDeviceGetAttribute(&can_wait, hipDeviceAttributeCanUseStreamWaitValue, cfg->device) == hipSuccess && can_wait) {
+            constexpr size_t kBytes = size_t(lmc_ctx::kWords) * lmc::kWordStride;
+            if (hipMalloc(reinterpret_cast<void **>(&c->words), kBytes) != hipSuccess) {
+                c->words = nullptr;
+                return fail(LMC_ERR_NOMEM);
+            }
+            if (hipMemset(c->words, 0, kBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) return fail(LMC_ERR_HIP);
+        }
         for (hipStream_t *s : {&c->s_gather, &c->s_d2h, &c->s_h2d, &c->s_scatter, &c->s_h2d2, &c->s_d2h2})
             if (hipStreamCreateWithFlags(s, hipStreamNonBlocking) != hipSuccess) return fail(LMC_ERR_HIP);
         if ((e = resolve_static_scratch(cfg->device)) != hipSuccess) {

@@ -53,6 +53,10 @@ struct Op {
     const int64_t *slot_mapping = nullptr;  // pending store: the caller's slot mapping
     std::vector<hipEvent_t> layer_done;   // per layer: event after which the layer is in place
     std::vector<hipEvent_t> owned_events; // the distinct events behind layer_done
+    // A layer-wise retrieve that runs as one launch (scatter_steps) has words instead: the layers of
+    // step i are in place when word i of the context has reached step_target[i].
+    int32_t step_layers = 0;
+    std::vector<uint64_t> step_target;
 };
 
 // One timed step of a pipeline: a kernel launch (LMC_FLAG_TIMING, LMC_FLAG_TRACE) or the
@@ -155,6 +159,15 @@ struct lmc_ctx {
     std::vector<hipStream_t> retired_streams;   // see arrange_streams; destroyed with the context, after the events
     Ring store_ring, load_ring;
     int32_t *bad_flag_host = nullptr, *bad_flag_dev = nullptr;
+    // Words in device memory at which scatters from the pool count themselves off (lmc::Arrivals),
+    // kWordStride bytes apart: kBulkWord for bulk retrieves, the others one for each step of a
+    // layer-wise one.  The launches that use a word run one after the other, so a word only grows and
+    // word_target[i], what it will have reached when everything launched so far is done, says
+    // when the newest of them is.  Null where a stream cannot wait for a value.
+    static constexpr int kBulkWord = LMC_MAX_LAYERS, kWords = LMC_MAX_LAYERS + 1;
+    uint64_t *words = nullptr;
+    uint64_t word_target[kWords] = {};
+    uint64_t *word(int i) const { return words + size_t(i) * (lmc::kWordStride / sizeof(uint64_t)); }
     std::deque<Op> ops;
     std::deque<Timing> timings;
     // LMC_FLAG_TRACE: finished steps, oldest first, at most kTraceCap; device time counts from trace_epoch
@@ -241,7 +254,7 @@ lmc_status_t make_ring(lmc_ctx *c, Ring &r);
 lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
                           uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list = nullptr,
-                          hipEvent_t stop = nullptr);
+                          hipEvent_t stop = nullptr, lmc::Arrivals *arrivals = nullptr, uint32_t planes_per_step = 0);
 // lmc_streams.cpp
 lmc_status_t shares_a_queue(lmc_ctx *c, hipStream_t busy, bool by_kernel, hipStream_t other, uint8_t *devbuf,
                             uint64_t nbytes, hipEvent_t a0, hipEvent_t a1, hipEvent_t k1, bool *shares);

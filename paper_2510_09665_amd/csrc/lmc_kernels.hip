@@ -23,6 +23,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace lmc {
 namespace {
@@ -43,6 +44,7 @@ template <> struct VecOf<kPacked> { typedef VecOf<16>::type type; };
 template <int VEC> constexpr uint32_t kBytesOf = VEC == kWide || VEC == kPacked ? 16u : uint32_t(VEC);
 
 #define LMC_GLOBAL __attribute__((address_space(1)))
+#define LMC_LDS __attribute__((address_space(3)))
 
 // Addresses are carried as integers (so they can be pinned in scalar registers) and
 // dereferenced as global-memory pointers, never as flat ones.
@@ -78,12 +80,27 @@ __device__ __forceinline__ void raise_flag(uint64_t addr) {
     asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(addr), "v"(1) : "memory");
 }
 template <int VEC, int ST> __device__ __forceinline__ void store_out(uint64_t addr, typename VecOf<VEC>::type v) {
-    if constexpr (ST == kStoreThrough) {
-        static_assert(VEC == 16 || VEC == kPacked, "whole lines only");
+    typedef typename VecOf<VEC>::type V;
+    if constexpr (ST != kStoreThrough) {
+        store_vec<V, ST != kStorePlain>(addr, v);
+    } else if constexpr (sizeof(V) == 16) {
         store_through(addr, v);
+    } else if constexpr (sizeof(V) == 8) {
+        __hip_atomic_store((LMC_GLOBAL uint64_t *)addr, __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     } else {
-        store_vec<typename VecOf<VEC>::type, ST != kStorePlain>(addr, v);
+        __hip_atomic_store((LMC_GLOBAL V *)addr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
+}
+
+// Tells the device's queues, while the kernel still runs, that this wavefront's stores so far have
+// reached memory: adds one to a word, which hipStreamWaitValue64 compares with the number of
+// wavefronts that owe it one.  The stores are at system scope (kStoreThrough), so when they have
+// completed nothing of them is left in an L2 that would have to be written back: no release
+// fence, which takes 4 us of a kernel that moves 0.5 MiB across the link in 13.
+__device__ __forceinline__ void arrive(uint64_t word_at) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if ((threadIdx.x & 63u) == 0)
+        (void)__hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)word_at, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Keeps a wave-uniform value in scalar registers from this point on.
@@ -301,14 +318,12 @@ __global__ __launch_bounds__(kThreads) void gather_rows_by_wave(const KernelGeom
     __builtin_nontemporal_store(v, (LMC_GLOBAL V *)st + lane);
 }
 
-// The same tile for a workgroup that takes many, one after the other: no early return, a lane
-// past the end of the plane reads the slot that the last one reads and moves nothing.  The
-// compiler puts the load of the data under the store's condition, so a token without a page
-// costs no traffic on the link.  With a list, chunk c of the launch lies list->slot[c] chunk
-// strides into the buffer.
-template <int VEC, bool GATHER, bool NT_LD, int ST>
-__device__ __forceinline__ void move_tile_in_turn(const TileArgs &a, const LayerPtrs &layers, uint32_t blk,
-                                                  const ChunkList *list) {
+// The gather's tile for a workgroup that takes many, one after the other: no early return, a lane
+// past the end of the plane reads the slot that the last one reads and moves nothing.  With a list,
+// chunk c of the launch lies list->slot[c] chunk strides into the buffer.
+template <int VEC, bool NT_LD, int ST>
+__device__ __forceinline__ void gather_tile_in_turn(const TileArgs &a, const LayerPtrs &layers, uint32_t blk,
+                                                    const ChunkList *list) {
     typedef typename VecOf<VEC>::type V;
     const uint32_t q = a.by_tiles.div(blk);
     const uint32_t tile = blk - q * a.by_tiles.d;
@@ -339,14 +354,9 @@ __device__ __forceinline__ void move_tile_in_turn(const TileArgs &a, const Layer
     const uint32_t su = has_page ? uint32_t(s) : 0u;  // slot 0 is always inside the pages
     const uint32_t b = a.by_bs.div(su);
     const uint32_t o = su - b * a.by_bs.d;
-    const uint64_t page = layer + uint64_t(int64_t(b) * a.block_stride + int64_t(o) * a.token_stride + in_page);
-    V v = load_vec<V, NT_LD>(GATHER ? page : st);
-    if (GATHER && !has_page) v = V(0);
-    if (GATHER) {
-        if (mine) store_out<VEC, ST>(st, v);
-    } else if (mine && has_page) {
-        store_vec<V, ST != kStorePlain>(page, v);
-    }
+    V v = load_vec<V, NT_LD>(layer + uint64_t(int64_t(b) * a.block_stride + int64_t(o) * a.token_stride + in_page));
+    if (!has_page) v = V(0);
+    if (mine) store_out<VEC, ST>(st, v);
 }
 
 // Across the host link (pages <-> pinned pool, no staging): the link, not HBM, sets the
@@ -360,32 +370,150 @@ __device__ __forceinline__ void move_tile_in_turn(const TileArgs &a, const Layer
 // alone (12 MiB from the host 222-224 us, 32 MiB to it 601-607), but beside another such
 // launch loads are slower: three contexts in turn, 12 MiB each in 256-byte rows, 236 us a
 // pass with 64 x 1 tile, 244 with 32 x 2, 242 with 16 x 4.
-template <int VEC, bool GATHER, bool NT_LD, int ST>
-__global__ __launch_bounds__(kThreads) void move_rows_paced(const KernelGeom g, const LaunchView view,
-                                                            const LayerPtrs layers,
-                                                            const int64_t *__restrict__ slot_mapping,
-                                                            uint8_t *staging, int32_t *bad_flag,
-                                                            uint32_t n_blocks) {
+template <int VEC, bool NT_LD, int ST>
+__global__ __launch_bounds__(kThreads) void gather_paced(const KernelGeom g, const LaunchView view,
+                                                         const LayerPtrs layers,
+                                                         const int64_t *__restrict__ slot_mapping,
+                                                         uint8_t *staging, int32_t *bad_flag,
+                                                         uint32_t n_blocks) {
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
     const uint32_t step = pin(uint32_t(gridDim.x)), end = pin(n_blocks);
     for (uint32_t blk = blockIdx.x; blk < end; blk += step)
-        move_tile_in_turn<VEC, GATHER, NT_LD, ST>(a, layers, blk, nullptr);
+        gather_tile_in_turn<VEC, NT_LD, ST>(a, layers, blk, nullptr);
 }
 
 // The same for chunks in any pool slots (a fragmented pool, a batch of requests): one launch
 // instead of one per run of consecutive slots, each of which ends with the link running dry
 // and is followed by a gap of 4-5 us.  A store of 25 chunks of 2 MiB in 12 runs: 12 launches
 // take 975 us on the device, one takes 946 (1123 and 1089 us for the whole call).
-template <int VEC, bool GATHER, bool NT_LD, int ST>
-__global__ __launch_bounds__(kThreads) void move_rows_listed(const KernelGeom g, const LaunchView view,
-                                                             const LayerPtrs layers,
-                                                             const int64_t *__restrict__ slot_mapping,
-                                                             uint8_t *staging, int32_t *bad_flag,
-                                                             uint32_t n_blocks, const ChunkList list) {
+template <int VEC, bool NT_LD, int ST>
+__global__ __launch_bounds__(kThreads) void gather_listed(const KernelGeom g, const LaunchView view,
+                                                          const LayerPtrs layers,
+                                                          const int64_t *__restrict__ slot_mapping,
+                                                          uint8_t *staging, int32_t *bad_flag,
+                                                          uint32_t n_blocks, const ChunkList list) {
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
     const uint32_t step = pin(uint32_t(gridDim.x)), end = pin(n_blocks);
     for (uint32_t blk = blockIdx.x; blk < end; blk += step)
-        move_tile_in_turn<VEC, GATHER, NT_LD, ST>(a, layers, blk, &list);
+        gather_tile_in_turn<VEC, NT_LD, ST>(a, layers, blk, &list);
+}
+
+// What reads host memory keeps the compute unit to itself: a workgroup asks for all of its LDS, of
+// which it uses nothing.  A load of host memory takes 4 us and more with the link busy, and the
+// loads of whatever else runs on that compute unit queue up behind it.  A dense bf16 product of 128,
+// 512, 1024 or 4096 rows by 4096 x 4096 (31, 34, 44, 111 us alone) beside 64 groups took 158, 159, 191,
+// 189 us without the claim and takes 38, 55, 78, 189 with it.  Nothing is lost while the GPU is full:
+// 0.5 MiB issued into a queue of products, attention or softmax ends within the spread of the
+// unclaimed (15-110 us), as soon as one compute unit runs out of work of the kernel before.
+// Hence also two groups of 256 lanes to a workgroup: as many tiles in flight on half the compute
+// units, at the same rate (64 MiB in 1182 us).
+constexpr int kPacedThreads = 2 * kThreads;
+constexpr int kLdsBytes = 160 * 1024;
+__device__ __forceinline__ void claim_compute_unit() {
+    __shared__ char all[kLdsBytes];
+    asm volatile("" ::"v"((LMC_LDS char *)all));
+}
+
+// One lane's piece of a tile of a scatter from the pool: where it comes from, and what its
+// destination is worked out from once the slot is known.
+struct Piece {
+    uint64_t from, layer;
+    int64_t in_page, slot;
+    bool mine;            // not past the end of the plane
+};
+struct BackToBack {};     // in a list's place: chunk c lies c chunk strides into the pool
+template <int VEC, typename List>
+__device__ __forceinline__ Piece find_piece(const TileArgs &a, const LayerPtrs &layers, uint32_t blk, uint32_t lane, const List &list) {
+    const uint32_t q = a.by_tiles.div(blk);
+    const uint32_t tile = blk - q * a.by_tiles.d;
+    const uint32_t c = a.by_lp.div(q);
+    const uint32_t lp = q - c * a.by_lp.d;
+    const uint32_t r0 = tile * kThreads + lane;
+    const uint32_t r = min(r0, a.vec_per_plane - 1);
+    const uint32_t t = a.by_row.div(r);
+    const uint32_t w = r - t * a.by_row.d;
+    Piece p;
+    p.slot = load_vec<int64_t, false>(a.slots_at + (uint64_t(c) * a.chunk_tokens + t) * 8u);
+    p.mine = r0 < a.vec_per_plane;
+    p.layer = uint64_t(layers.p[a.lp_base + lp]);
+    uint32_t c_buf = c;
+    if constexpr (!std::is_same_v<List, BackToBack>) c_buf = uint32_t(list.slot[c]);
+    uint64_t in_row;
+    place<VEC>(a, w, &p.in_page, &in_row);
+    p.from = a.staging_at + uint64_t(c_buf) * a.chunk_stride + uint64_t(lp) * a.plane_bytes +
+             (VEC == kWide ? uint64_t(t) * a.row_bytes + in_row : uint64_t(r) * kBytesOf<VEC>);
+    return p;
+}
+
+// The scatter across the link, for chunks back to back or in listed pool slots, in one or more
+// steps: a step is the next planes of every chunk, and a workgroup goes on with its next tile
+// whichever step that is in.  With words, the wavefronts count themselves off at the step's word
+// when their last tile of it is in the pages, between the load and the store of the next tile,
+// where they wait anyway; so the layers of a layer-wise retrieve need neither a launch each,
+// with the link idle for 5 us of 41 in between (2 MiB a step), nor an event each, which takes the
+// thread that waits for it on another queue 13 us where a word takes 2.
+// While a tile's data crosses the link the slots of the next tile are fetched, so a workgroup
+// spends nothing but the link's round trip on a tile; stores are waited for only with the data
+// behind them.  They are at system scope, for the words and because a wavefront has nothing
+// else to do at this pace.
+template <int VEC, typename List>
+__global__ __launch_bounds__(kPacedThreads) void scatter_paced(const KernelGeom g, const LaunchView view,
+                                                          const StepView steps, const LayerPtrs layers,
+                                                          const int64_t *__restrict__ slot_mapping, const uint8_t *pool,
+                                                          int32_t *bad_flag, uint64_t *words, const List list) {
+    typedef typename VecOf<VEC>::type V;
+    claim_compute_unit();
+    const uint32_t half = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), lane = threadIdx.x % kThreads;
+    TileArgs a = fetch_args<VEC>(g, view, slot_mapping, const_cast<uint8_t *>(pool), bad_flag);
+    const uint32_t groups = pin(steps.groups), n_steps = pin(steps.n_steps);
+    const uint32_t planes = a.by_lp.d, last_blocks = pin(steps.last_blocks);
+    const FastDiv by_last = pin(steps.by_last_lp);
+    const uint64_t words_at = pin(uint64_t(words));
+    uint32_t blk = half * gridDim.x + blockIdx.x, step = 0, told = 0;   // told: steps this wavefront has counted itself off at
+    uint32_t blocks = n_steps > 1 ? pin(steps.n_blocks) : last_blocks;
+    if (n_steps == 1) a.by_lp = by_last;
+    if (blk >= groups) return;                       // an odd number of groups leaves a half without work
+    // goes on to the step that tile blk lies in; false behind the last
+    auto in_step = [&]() {
+        while (blk >= blocks) {
+            blk -= blocks;
+            if (++step >= n_steps) return false;
+            a.lp_base += planes;
+            a.staging_at += uint64_t(planes) * a.plane_bytes;
+            if (step + 1 == n_steps) {
+                blocks = last_blocks;
+                a.by_lp = by_last;
+            }
+        }
+        return true;
+    };
+    if (in_step()) {
+        Piece p = find_piece<VEC>(a, layers, blk, lane, list);
+        asm volatile("" : "+v"(p.slot));   // arrived: the loop then has no load of its own to wait for at its head
+        for (bool more = true; more;) {
+            const bool moves = p.mine && uint64_t(p.slot) < uint64_t(a.n_slots);   // negative wraps to huge
+            V v = V(0);
+            if (moves) v = load_vec<V, true>(p.from);      // a token without a page costs the link nothing
+            if (p.mine && p.slot >= int64_t(a.n_slots)) raise_flag(a.bad_flag_at);
+            const uint32_t before = step;
+            blk += groups;
+            more = in_step();
+            Piece next = p;
+            if (more) next = find_piece<VEC>(a, layers, blk, lane, list);
+            const uint32_t su = moves ? uint32_t(p.slot) : 0u;
+            const uint32_t b = a.by_bs.div(su);
+            const uint32_t o = su - b * a.by_bs.d;
+            const uint64_t page = p.layer + uint64_t(int64_t(b) * a.block_stride + int64_t(o) * a.token_stride + p.in_page);
+            if (words_at != 0)
+                for (; told < before; told++) arrive(words_at + told * kWordStride);
+            // the next slot is waited for here, with the data, and not behind the store
+            asm volatile("" : "+v"(next.slot));
+            if (moves) store_out<VEC, kStoreThrough>(page, v);
+            p = next;
+        }
+    }
+    if (words_at != 0)
+        for (; told < n_steps; told++) arrive(words_at + told * kWordStride);
 }
 
 // ---- scatter in the order of the destination ---------------------------------------------
@@ -629,69 +757,106 @@ __global__ __launch_bounds__(kThreads) void fill_bytes(uint8_t *dst, uint8_t val
         dst[i] = value;
 }
 
+// Inside HBM.
 template <int VEC, bool GATHER>
 hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                          const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                          uint8_t *staging, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
-                         hipEvent_t stop, const ChunkList *list) {
-    if (list != nullptr && (s.paced_groups == 0 || n_chunks > uint32_t(kMaxListed))) return hipErrorInvalidValue;
+                         hipEvent_t stop) {
     const uint32_t n_blocks = n_chunks * v.by_n_lp.d * g.by_tiles_per_plane.d;
     if (n_blocks == 0) return hipSuccess;
-    // a gather into the pool writes through the L2 where every wavefront writes whole lines of
-    // 128 bytes: 16-byte lanes, and planes that begin on a line
-    constexpr bool kLines = GATHER && (VEC == 16 || VEC == kPacked);
-    const bool through = kLines && s.paced_groups > 0 && s.nt_load && s.nt_store &&
-                         ((uint64_t(reinterpret_cast<uintptr_t>(staging)) | v.chunk_stride | g.plane_bytes) % 128) == 0;
-    constexpr int kThrough = kLines ? kStoreThrough : kStoreNonTemporal;   // nothing else is instantiated
     uint32_t shift = 0, permuted = 0;
     if (s.xcd_run > 0) {
         while ((2u << shift) <= s.xcd_run) shift++;                      // floor(log2(xcd_run))
         permuted = n_blocks & ~((8u << shift) - 1u);                     // the tail keeps its order
     }
-    dim3 grid(n_blocks), block(kThreads);
-    if (s.paced_groups > 0) {
-        // blk + step must not wrap: n_blocks < 2^24 (max_chunks_per_launch) and the grid is small
-        // A store at system scope ends at the host's memory, and a wavefront waits for it before
-        // it uses the next slot: long launches need half as many workgroups more.  32 MiB by
-        // 64, 96, 128 workgroups: 607, 590, 590 us (601 with 64 and non-temporal stores); 4 to
-        // 12 MiB: the same by 64 and 96; 1 MiB and less: 96 workgroups 5 % slower.  Pieces put
-        // together from two loads take longer still: 8.7 MiB in 216-byte rows, planes of 16
-        // tokens, by 64 and 128: 175, 168 us.
-        const uint32_t groups = VEC == kPacked ? (n_blocks >= 512 ? 2 * s.paced_groups : s.paced_groups)
-                                : through && n_blocks >= 4096 ? s.paced_groups + s.paced_groups / 2 : s.paced_groups;
-        grid = dim3(std::min(n_blocks, groups));
+    const dim3 grid(n_blocks), block(kThreads);
+    if constexpr (GATHER && VEC == 16)
+        if (g.by_vec_per_run.d % 64 == 0 && s.nt_load && s.nt_store && reinterpret_cast<uintptr_t>(slot_mapping) % 8 == 0) {
+            hipExtLaunchKernelGGL(gather_rows_by_wave, grid, block, 0, stream, start, stop, 0, g, v, layers, slot_mapping,
+                                  staging, bad_flag, permuted, shift);
+            return hipGetLastError();
+        }
+#define LMC_GO(LD, ST)                                                                          \
+    hipExtLaunchKernelGGL((move_rows<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
+                          0, g, v, layers, slot_mapping, staging, bad_flag, permuted, shift)
+    if (s.nt_load && s.nt_store) LMC_GO(true, kStoreNonTemporal);
+    else if (s.nt_load) LMC_GO(true, kStorePlain);
+    else if (s.nt_store) LMC_GO(false, kStoreNonTemporal);
+    else LMC_GO(false, kStorePlain);
+#undef LMC_GO
+    return hipGetLastError();
+}
+
+// Pages into the pool.
+template <int VEC>
+hipError_t launch_gather_paced(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
+                               const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
+                               uint8_t *pool, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
+                               hipEvent_t stop, const ChunkList *list) {
+    const uint32_t n_blocks = n_chunks * v.by_n_lp.d * g.by_tiles_per_plane.d;
+    if (n_blocks == 0) return hipSuccess;
+    // through the L2 where every wavefront writes whole lines of 128 bytes: 16-byte lanes, and
+    // planes that begin on a line
+    constexpr bool kLines = VEC == 16 || VEC == kPacked;
+    const bool through = kLines && s.nt_load && s.nt_store &&
+                         ((uint64_t(reinterpret_cast<uintptr_t>(pool)) | v.chunk_stride | g.plane_bytes) % 128) == 0;
+    constexpr int kThrough = kLines ? kStoreThrough : kStoreNonTemporal;   // nothing else is instantiated
+    // blk + step must not wrap: n_blocks < 2^24 (max_chunks_per_launch) and the grid is small
+    // A store at system scope ends at the host's memory, and a wavefront waits for it before
+    // it uses the next slot: long launches need half as many workgroups more.  32 MiB by
+    // 64, 96, 128 workgroups: 607, 590, 590 us (601 with 64 and non-temporal stores); 4 to
+    // 12 MiB: the same by 64 and 96; 1 MiB and less: 96 workgroups 5 % slower.  Pieces put
+    // together from two loads take longer still: 8.7 MiB in 216-byte rows, planes of 16
+    // tokens, by 64 and 128: 175, 168 us.
+    const uint32_t groups = VEC == kPacked ? (n_blocks >= 512 ? 2 * s.paced_groups : s.paced_groups)
+                            : through && n_blocks >= 4096 ? s.paced_groups + s.paced_groups / 2 : s.paced_groups;
+    const dim3 grid(std::min(n_blocks, groups)), block(kThreads);
 #define LMC_GO(LD, ST)                                                                                  \
     if (list != nullptr)                                                                                \
-        hipExtLaunchKernelGGL((move_rows_listed<VEC, GATHER, LD, ST>), grid, block, 0, stream, start,    \
-                              stop, 0, g, v, layers, slot_mapping, staging, bad_flag, n_blocks, *list);  \
-    else hipExtLaunchKernelGGL((move_rows_paced<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
-                          0, g, v, layers, slot_mapping, staging, bad_flag, n_blocks)
-        if (through) { LMC_GO(true, kThrough); }
-        else if (s.nt_load && s.nt_store) { LMC_GO(true, kStoreNonTemporal); }
-        else if (s.nt_load) { LMC_GO(true, kStorePlain); }
-        else if (s.nt_store) { LMC_GO(false, kStoreNonTemporal); }
-        else { LMC_GO(false, kStorePlain); }
+        hipExtLaunchKernelGGL((gather_listed<VEC, LD, ST>), grid, block, 0, stream, start, stop, 0, g, v, \
+                              layers, slot_mapping, pool, bad_flag, n_blocks, *list);                   \
+    else hipExtLaunchKernelGGL((gather_paced<VEC, LD, ST>), grid, block, 0, stream, start, stop, 0, g, v, \
+                          layers, slot_mapping, pool, bad_flag, n_blocks)
+    if (through) { LMC_GO(true, kThrough); }
+    else if (s.nt_load && s.nt_store) { LMC_GO(true, kStoreNonTemporal); }
+    else if (s.nt_load) { LMC_GO(true, kStorePlain); }
+    else if (s.nt_store) { LMC_GO(false, kStoreNonTemporal); }
+    else { LMC_GO(false, kStorePlain); }
 #undef LMC_GO
-        return hipGetLastError();
-    }
-    if constexpr (VEC != kPacked) {
-        if constexpr (GATHER && VEC == 16)
-            if (g.by_vec_per_run.d % 64 == 0 && s.nt_load && s.nt_store && reinterpret_cast<uintptr_t>(slot_mapping) % 8 == 0) {
-                hipExtLaunchKernelGGL(gather_rows_by_wave, grid, block, 0, stream, start, stop, 0, g, v, layers, slot_mapping,
-                                      staging, bad_flag, permuted, shift);
-                return hipGetLastError();
-            }
-#define LMC_GO(LD, ST)                                                                          \
-        hipExtLaunchKernelGGL((move_rows<VEC, GATHER, LD, ST>), grid, block, 0, stream, start, stop, \
-                              0, g, v, layers, slot_mapping, staging, bad_flag, permuted, shift)
-        if (s.nt_load && s.nt_store) LMC_GO(true, kStoreNonTemporal);
-        else if (s.nt_load) LMC_GO(true, kStorePlain);
-        else if (s.nt_store) LMC_GO(false, kStoreNonTemporal);
-        else LMC_GO(false, kStorePlain);
-#undef LMC_GO
-        return hipGetLastError();
-    }
-    return hipErrorInvalidValue;   // packed pieces go across the link only (packs)
+    return hipGetLastError();
+}
+
+// The pool into pages, `planes` planes of every chunk in each step.  The non-temporal hints of the
+// launch shape are for HBM and change nothing here.
+template <int VEC>
+hipError_t launch_scatter_paced(const KernelGeom &g, const LaunchView &v, uint32_t planes, uint32_t groups,
+                                const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
+                                const uint8_t *pool, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
+                                hipEvent_t stop, const ChunkList *list, Arrivals *arrivals) {
+    const uint64_t tiles = uint64_t(n_chunks) * v.by_n_lp.d * g.by_tiles_per_plane.d;   // < 2^24 (max_chunks_per_launch)
+    if (arrivals != nullptr) arrivals->count = 0;
+    if (tiles == 0) return hipSuccess;
+    LaunchView step = v;
+    step.by_n_lp = make_fastdiv(planes);
+    StepView steps;
+    steps.n_steps = (v.by_n_lp.d + planes - 1) / planes;
+    const uint32_t last = v.by_n_lp.d - (steps.n_steps - 1) * planes;
+    steps.n_blocks = n_chunks * planes * g.by_tiles_per_plane.d;
+    steps.last_blocks = n_chunks * last * g.by_tiles_per_plane.d;
+    steps.by_last_lp = make_fastdiv(last);
+    steps.groups = uint32_t(std::min<uint64_t>(tiles, groups));
+    const dim3 grid((steps.groups + 1) / 2), block(kPacedThreads);
+    uint64_t *words = arrivals != nullptr ? arrivals->words : nullptr;
+    if (list != nullptr)
+        hipExtLaunchKernelGGL((scatter_paced<VEC, ChunkList>), grid, block, 0, stream, start, stop, 0, g, step, steps, layers,
+                              slot_mapping, pool, bad_flag, words, *list);
+    else
+        hipExtLaunchKernelGGL((scatter_paced<VEC, BackToBack>), grid, block, 0, stream, start, stop, 0, g, step, steps, layers,
+                              slot_mapping, pool, bad_flag, words, BackToBack{});
+    const hipError_t e = hipGetLastError();
+    if (arrivals != nullptr && e == hipSuccess) arrivals->count = steps.groups * (kThreads / 64);
+    return e;
 }
 
 // A gather of wide rows into the pool, whose planes are whole 16-byte pieces, goes piece by
@@ -712,21 +877,15 @@ KernelGeom packed_geom(const KernelGeom &g) {
     return p;
 }
 
-template <bool GATHER>
-hipError_t launch_move(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
-                       const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
-                       uint8_t *staging, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
-                       hipEvent_t stop, const ChunkList *list) {
-    if constexpr (GATHER)
-        if (s.paced_groups > 0 && packs(g, v, staging))
-            return launch_move_v<kPacked, true>(packed_geom(g), v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
+// Calls f with the lane width of the geometry as a compile-time constant.
+template <typename F> hipError_t by_vec(const KernelGeom &g, F f) {
     switch (g.vec) {
-        case kWide: return launch_move_v<kWide, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
-        case 16: return launch_move_v<16, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
-        case 8: return launch_move_v<8, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
-        case 4: return launch_move_v<4, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
-        case 2: return launch_move_v<2, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
-        case 1: return launch_move_v<1, GATHER>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list);
+        case kWide: return f(std::integral_constant<int, kWide>());
+        case 16: return f(std::integral_constant<int, 16>());
+        case 8: return f(std::integral_constant<int, 8>());
+        case 4: return f(std::integral_constant<int, 4>());
+        case 2: return f(std::integral_constant<int, 2>());
+        case 1: return f(std::integral_constant<int, 1>());
     }
     return hipErrorInvalidValue;
 }
@@ -776,16 +935,32 @@ hipError_t launch_gather(const KernelGeom &g, const LaunchView &v, const LaunchS
                          const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                          uint8_t *staging, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
                          hipEvent_t stop, const ChunkList *list) {
-    return launch_move<true>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream,
-                             start, stop, list);
+    if (list != nullptr && (s.paced_groups == 0 || n_chunks > uint32_t(kMaxListed))) return hipErrorInvalidValue;
+    if (s.paced_groups > 0 && packs(g, v, staging))
+        return launch_gather_paced<kPacked>(packed_geom(g), v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream,
+                                            start, stop, list);
+    return by_vec(g, [&](auto vec) {
+        return s.paced_groups > 0
+                   ? launch_gather_paced<vec.value>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list)
+                   : launch_move_v<vec.value, true>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
+    });
 }
 
 hipError_t launch_scatter(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                           const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                           const uint8_t *staging, int32_t *bad_flag, hipStream_t stream,
-                          hipEvent_t start, hipEvent_t stop, const ChunkList *list) {
-    return launch_move<false>(g, v, s, layers, slot_mapping, n_chunks,
-                              const_cast<uint8_t *>(staging), bad_flag, stream, start, stop, list);
+                          hipEvent_t start, hipEvent_t stop, const ChunkList *list, Arrivals *arrivals,
+                          uint32_t planes_per_step) {
+    if (list != nullptr && n_chunks > uint32_t(kMaxListed)) return hipErrorInvalidValue;
+    if (s.paced_groups == 0 && (list != nullptr || arrivals != nullptr || planes_per_step != 0)) return hipErrorInvalidValue;
+    const uint32_t planes = planes_per_step == 0 ? v.by_n_lp.d : std::min(planes_per_step, v.by_n_lp.d);
+    return by_vec(g, [&](auto vec) {
+        return s.paced_groups > 0
+                   ? launch_scatter_paced<vec.value>(g, v, planes, s.paced_groups, layers, slot_mapping, n_chunks, staging,
+                                                     bad_flag, stream, start, stop, list, arrivals)
+                   : launch_move_v<vec.value, false>(g, v, s, layers, slot_mapping, n_chunks, const_cast<uint8_t *>(staging),
+                                                     bad_flag, stream, start, stop);
+    });
 }
 
 uint64_t order_table_words(const KernelGeom &g) { return g.n_slots; }

@@ -89,11 +89,28 @@ struct ChunkList {
     int32_t slot[kMaxListed];
 };
 
+// Words in device memory, kWordStride bytes apart, one for each step of a scatter from the pool:
+// each wavefront of the launch adds one to a step's word when its stores of that step have reached
+// memory, so that a queue can wait for the word's value instead of for an event of the kernel.
+// count: receives how many wavefronts will.
+struct Arrivals {
+    uint64_t *words;
+    uint32_t count;
+};
+constexpr uint32_t kWordStride = 64;
+// The steps of such a launch: tiles in a step, and in the last one, whose planes may be fewer.
+struct StepView {
+    uint32_t groups, n_steps, n_blocks, last_blocks;   // groups of 256 lanes that take tiles in turn
+    FastDiv by_last_lp;
+};
+
 // pages -> n_chunks chunks of the slot mapping, written back to back from `staging`
 // (gather), or the reverse (scatter).  bad_flag: device-visible int set to 1 on a slot
 // >= n_slots.  start / stop: optional events (timing enabled) that receive the
 // kernel's own begin and end time stamps; no marker is put on the stream for them.
 // list (paced launches of at most kMaxListed chunks only): where each chunk lies.
+// planes_per_step (paced scatters only): the view's planes go so many at a time, each step's planes
+// of every chunk before the next step's; 0 = all at once.  arrivals (paced scatters only): one word a step.
 hipError_t launch_gather(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                          const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                          uint8_t *staging, int32_t *bad_flag, hipStream_t stream,
@@ -101,7 +118,8 @@ hipError_t launch_gather(const KernelGeom &g, const LaunchView &v, const LaunchS
 hipError_t launch_scatter(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                           const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                           const uint8_t *staging, int32_t *bad_flag, hipStream_t stream,
-                          hipEvent_t start = nullptr, hipEvent_t stop = nullptr, const ChunkList *list = nullptr);
+                          hipEvent_t start = nullptr, hipEvent_t stop = nullptr, const ChunkList *list = nullptr,
+                          Arrivals *arrivals = nullptr, uint32_t planes_per_step = 0);
 // Scatter in the order of the destination: the rows of the launch are visited in ascending
 // slot order, plane by plane (see lmc_kernels.hip).  The order is built on the device in
 // scratch memory the caller provides: token_at (order_table_words() words), counts

@@ -69,7 +69,8 @@ static lmc_status_t prepare_order_scratch(lmc_ctx *c, uint64_t n_tokens, hipStre
 
 lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
-                          uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list, hipEvent_t stop) {
+                          uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list, hipEvent_t stop,
+                          lmc::Arrivals *arrivals, uint32_t planes_per_step) {
     // LMC_FLAG_TIMING: the launch itself carries a start and a stop event, which receive
     // the kernel's own begin / end time stamps; the stream gets no extra marker.
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -108,7 +109,8 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
         : gather  ? lmc::launch_gather(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, end, list)
         : ordered ? lmc::launch_scatter_ordered(c->kg, view, s, ptrs, slots, uint32_t(n_tokens), c->order, staging,
                                                 c->bad_flag_dev, stream, e0, end)
-                  : lmc::launch_scatter(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, end, list);
+                  : lmc::launch_scatter(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, end, list,
+                                        arrivals, planes_per_step);
     if (ordered && e == hipSuccess) e = hipEventRecord(c->order_free, stream);
     if (stop != nullptr && !own_stop && e == hipSuccess) e = hipEventRecord(stop, stream);
     if (e != hipSuccess) {
@@ -333,10 +335,12 @@ static lmc_status_t after_stores(lmc_ctx *c, const int64_t *pool_slots, int64_t 
 // consecutive there.  Where their pool slots are consecutive too the first one's address is
 // all a launch needs; where they are not they are listed, so that a fragmented pool costs one
 // launch for every kMaxListed chunks and not one for every run of slots.
-// stop (may be null): completes with the last launch.
+// stop (may be null): completes with the last launch.  arrivals (may be null): the word at which the
+// last launch of a scatter counts itself off; the others are over when it begins.
 static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, uint64_t pool_off,
                                 const lmc::LayerPtrs &ptrs, const int64_t *slot_mapping, const int64_t *chunk,
-                                const int64_t *pool_slot, int64_t n, hipStream_t stream, hipEvent_t stop = nullptr) {
+                                const int64_t *pool_slot, int64_t n, hipStream_t stream, hipEvent_t stop = nullptr,
+                                lmc::Arrivals *arrivals = nullptr) {
     const uint64_t cb = uint64_t(c->chunk_bytes);
     const int64_t CT = c->cfg.geom.chunk_tokens;
     view.chunk_stride = cb;  // chunks lie one pool slot apart
@@ -357,11 +361,66 @@ static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, u
         }
         lmc_status_t rc = timed_launch(c, gather, view, ptrs, slot_mapping + (chunk ? chunk[i0] : i0) * CT, uint32_t(k),
                                        c->pool_dev + (listed ? 0 : uint64_t(pool_slot[i0]) * cb) + pool_off, stream,
-                                       listed ? &list : nullptr, i0 + k == n ? stop : nullptr);
+                                       listed ? &list : nullptr, i0 + k == n ? stop : nullptr,
+                                       i0 + k == n ? arrivals : nullptr);
         if (rc != LMC_OK) return rc;
         (gather ? c->stats.bytes_d2h : c->stats.bytes_h2d) += uint64_t(k) * view.by_n_lp.d * c->kg.plane_bytes;
         if ((rc = force_sync(c, stream)) != LMC_OK) return rc;
     }
+    return LMC_OK;
+}
+
+static bool is_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    const bool no = hipStreamIsCapturing(stream, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return !no;
+}
+
+// Can `stream` wait for a word of the context's (lmc_ctx::words)?  Not while it is being captured
+// (the wait is no part of a graph), nor from another GPU.
+static bool may_wait_for_word(const lmc_ctx *c, hipStream_t stream) {
+    hipDevice_t dev = c->cfg.device;
+    const bool ok = c->words != nullptr && !is_capturing(stream) &&
+                    (stream == nullptr || stream == hipStreamPerThread || hipStreamGetDevice(stream, &dev) == hipSuccess) &&
+                    dev == c->cfg.device;
+    (void)hipGetLastError();
+    return ok;
+}
+
+static lmc_status_t wait_for_word(lmc_ctx *c, hipStream_t stream, int word, uint64_t target) {
+    HIPCHK(c, hipStreamWaitValue64(stream, c->word(word), target, hipStreamWaitValueGte, ~uint64_t(0)));
+    return LMC_OK;
+}
+
+// All layers of n chunks into their pages, layers_per_step at a time, by one launch on the scatter
+// stream (lmc::launch_scatter_steps); each step's layers are in place when its word says so.  *done:
+// whether the transfer can go this way at all.  It cannot where the launch would have to be
+// several (more chunks in scattered slots than a launch can list, "link_groups" 0), where each step
+// is to have time stamps of its own or is to be waited for, or while the stream is being captured.
+static lmc_status_t retrieve_in_steps(lmc_ctx *c, const lmc::LayerPtrs &ptrs, const int64_t *slot_mapping,
+                                      const std::vector<int64_t> &pool_slots, int32_t layers_per_step, Op *op, bool *done) {
+    const int64_t n = int64_t(pool_slots.size());
+    const uint32_t planes = uint32_t(layers_per_step) * uint32_t(c->cfg.geom.num_planes);
+    const lmc::LaunchView view = lmc::bulk_view(c->kg);
+    const bool listed = several_runs(pool_slots.data(), n);
+    *done = c->link_groups > 0 && n <= int64_t(lmc::max_chunks_per_launch(c->kg, view)) &&
+            (!listed || (n <= lmc::kMaxListed && c->n_pool_slots <= INT32_MAX)) &&
+            (c->cfg.flags & (LMC_FLAG_TIMING | LMC_FLAG_TRACE | LMC_FLAG_FORCE_SYNC)) == 0 && may_wait_for_word(c, c->s_scatter);
+    if (!*done) return LMC_OK;
+    lmc::ChunkList list;
+    if (listed)
+        for (int64_t i = 0; i < n; i++) list.slot[i] = int32_t(pool_slots[size_t(i)]);
+    lmc::Arrivals arrivals{c->words, 0};
+    const lmc_status_t rc = timed_launch(c, false, view, ptrs, slot_mapping, uint32_t(n),
+                                         c->pool_dev + (listed ? 0 : pool_slots[0] * c->chunk_bytes), c->s_scatter,
+                                         listed ? &list : nullptr, nullptr, &arrivals, planes);
+    if (rc != LMC_OK) return rc;
+    const int32_t steps = (c->cfg.geom.num_layers + layers_per_step - 1) / layers_per_step;
+    op->step_layers = layers_per_step;
+    for (int32_t i = 0; i < steps; i++) op->step_target.push_back(c->word_target[i] += arrivals.count);
+    c->stats.scatter_launches += uint64_t(steps - 1);   // each step counts as a launch
+    c->stats.bytes_h2d += uint64_t(n) * uint64_t(c->chunk_bytes);
     return LMC_OK;
 }
 
@@ -393,10 +452,9 @@ static bool launches_on_caller(const lmc_ctx *c, hipStream_t user) {
         return false;
     for (const Op &o : c->ops)   // what reap() has left
         if (!o.on_caller || o.caller != user) return false;
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     hipDevice_t dev = c->cfg.device;
-    const bool ok = hipStreamIsCapturing(user, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone &&
-                    (user == nullptr || hipStreamGetDevice(user, &dev) == hipSuccess) && dev == c->cfg.device;
+    const bool ok = !is_capturing(user) && (user == nullptr || hipStreamGetDevice(user, &dev) == hipSuccess) &&
+                    dev == c->cfg.device;
     (void)hipGetLastError();
     return ok;
 }
@@ -514,6 +572,11 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
                 if ((rc = load_group(view, 0, i0, k, c->s_h2d, two_copy_streams ? c->s_h2d2 : nullptr)) != LMC_OK) return rc;
             }
         } else {
+            if (direct) {
+                bool done = false;
+                if ((rc = retrieve_in_steps(c, ptrs, slot_mapping, pool_slots, layers_per_step, &op, &done)) != LMC_OK || done)
+                    return rc;
+            }
             // All chunks' share of a few layers at a time: one rectangle copy per run of pool
             // slots, one scatter launch, one event that says "these layers are in place".
             const int32_t L = geom.num_layers, P = geom.num_planes;
@@ -877,6 +940,13 @@ lmc_status_t lmc_wait_layer(lmc_ctx_t *c, uint64_t ticket, int32_t layer, void *
     const Op *op = find_op(c, ticket);
     if (op == nullptr) return LMC_OK;                       // finished long ago
     if (!op->layerwise) return LMC_ERR_INVAL;
+    if (!op->step_target.empty()) {
+        const int32_t i = layer / op->step_layers;
+        if (may_wait_for_word(c, static_cast<hipStream_t>(stream)))
+            return wait_for_word(c, static_cast<hipStream_t>(stream), i, op->step_target[size_t(i)]);
+        HIPCHK(c, hipStreamWaitEvent(static_cast<hipStream_t>(stream), op->done, 0));   // all layers
+        return LMC_OK;
+    }
     if (op->layer_done.empty() || (op->layer_done[size_t(layer)] == nullptr && !op->pending))
         return LMC_OK;                                      // nothing was enqueued for it
     if (op->layer_done[size_t(layer)] == nullptr) return LMC_ERR_BUSY;  // layer not submitted yet

@@ -1,0 +1,174 @@
+"""Layer-wise retrieves without staging run as one launch whose steps count themselves off at words
+in device memory; consumers wait for the words' values.  Byte for byte against the CPU oracle,
+every layer read as soon as its wait returns, by a stream whose caches hold the pages as they were
+before: rows of every kind, steps that do not divide the layers, steps with fewer tiles than
+workgroups, chunks back to back and in scattered slots, tokens without a page."""
+import zlib
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_09665_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "rows_of_256": dict(L=7, P=2, H=1, D=128, e=2, BS=16, NB=96, CT=64),
+    "rows_of_2048": dict(L=5, P=2, H=8, D=128, e=2, BS=16, NB=96, CT=128),
+    "mla": dict(L=6, P=1, H=1, D=576, e=1, BS=64, NB=40, CT=256),
+    "hnd": dict(L=4, P=2, H=4, D=64, e=2, BS=16, NB=64, CT=64, layout="HND"),
+    "wide_row216": dict(L=5, P=2, H=3, D=72, e=1, BS=16, NB=56, CT=64),
+    "wide_hnd_run33": dict(L=3, P=2, H=3, D=33, e=1, BS=4, NB=90, CT=32, layout="HND"),
+    "narrow_8": dict(L=3, P=1, H=1, D=4, e=2, BS=4, NB=90, CT=32),
+    "narrow_4": dict(L=3, P=2, H=1, D=6, e=2, BS=4, NB=90, CT=32),
+    "narrow_2": dict(L=3, P=2, H=1, D=5, e=2, BS=4, NB=90, CT=32),
+    "narrow_1": dict(L=3, P=1, H=1, D=5, e=1, BS=4, NB=90, CT=32),
+}
+
+
+def _request(g, n, rng):
+    tau = rng.permutation(g.n_slots)[:n * g.CT].astype(np.int64)
+    tau[rng.integers(0, n * g.CT, 2)] = -1
+    return tau
+
+
+def _pool(c, g, n, scattered, rng):
+    """n chunks of random bytes in the pool, at every other slot in random order if scattered."""
+    want = rng.integers(0, 256, (n, g.chunk_bytes), dtype=np.uint8)
+    ids = np.arange(1, n + 1, dtype=np.uint64)
+    if scattered:
+        other = (1 << 40) + np.arange(2 * n, dtype=np.uint64)
+        c.put_host(other, np.zeros((2 * n, g.chunk_bytes), dtype=np.uint8))
+        c.clear(other[::2])
+    for i in rng.permutation(n) if scattered else range(n):
+        c.put_host(ids[i:i + 1], want[i])
+    return want, ids
+
+
+@pytest.mark.parametrize("shape", list(SHAPES))
+@pytest.mark.parametrize("n,step,scattered,groups", [(1, 1, False, 64), (1, 2, False, 1), (2, 3, False, 64), (3, 1, True, 5),
+                                                     (2, 99, True, 64)])
+def test_each_layer_is_there_when_its_wait_returns(shape, n, step, scattered, groups):
+    import torch
+    from gpu_util import assert_layers_equal, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(**SHAPES[shape])
+    rng = np.random.default_rng(zlib.crc32(("%s %d %d" % (shape, n, step)).encode()))
+    consumer = torch.cuda.Stream()
+    with lmc.Context(g, 2 * n * g.chunk_bytes, staging_chunks=2) as c:
+        want, ids = _pool(c, g, n, scattered, rng)
+        c.tune("link_groups", groups)         # two to a workgroup: an odd number leaves a half without work
+        c.reset_stats()
+        for again in range(3):
+            tau = _request(g, n, rng)
+            host = [W.sentinel_layer(g, l) for l in range(g.L)]
+            dev = [torch.from_numpy(h).cuda() for h in host]
+            d_tau = slots_to_device(tau)
+            oracle.scatter(g, want, tau, host)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(consumer):
+                before = [d.clone() for d in dev]         # the pages as they are now, in the caches
+            t = c.retrieve_layerwise(ids, d_tau, dev, step, consumer)
+            seen = []
+            for l in range(g.L):
+                c.wait_layer(t, l, consumer)
+                with torch.cuda.stream(consumer):
+                    seen.append(dev[l].clone())
+            consumer.synchronize()
+            assert_layers_equal([d.cpu().numpy() for d in seen], host, "as each wait returned, pass %d" % again)
+            c.wait(t)
+            c.wait_layer(t, 0, consumer)                    # finished: nothing to wait for
+            del before
+        assert c.get_stats()["scatter_launches"] == 3 * -(-g.L // min(step, g.L))
+        assert c.get_stats()["bytes_h2d"] == 3 * n * g.chunk_bytes
+
+
+def test_slot_outside_the_pages_is_reported_and_the_rest_is_carried_out():
+    import torch
+    from gpu_util import assert_layers_equal, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(**SHAPES["rows_of_256"])
+    rng = np.random.default_rng(3)
+    with lmc.Context(g, 4 * g.chunk_bytes, staging_chunks=2) as c:
+        want, ids = _pool(c, g, 2, False, rng)
+        tau = _request(g, 2, rng)
+        host = [W.sentinel_layer(g, l) for l in range(g.L)]
+        dev = [torch.from_numpy(h).cuda() for h in host]
+        bad = tau.copy()
+        bad[5] = g.n_slots
+        tau[5] = -1
+        oracle.scatter(g, want, tau, host)
+        d_bad = slots_to_device(bad)
+        t = c.retrieve_layerwise(ids, d_bad, dev, 2, torch.cuda.current_stream())
+        with pytest.raises(lmc.LMCError) as e:
+            c.wait(t)
+        assert e.value.status == lmc.LMC_ERR_BADSLOT
+        assert_layers_equal([d.cpu().numpy() for d in dev], host)
+
+
+@pytest.mark.parametrize("kind", ["null", "per_thread", "blocking", "copy_engine"])
+def test_every_kind_of_consumer(kind):
+    """The null stream, a blocking stream, one name for many streams, and copies to the host behind the
+    waits; two retrieves into the same pages under way at once, the later one's bytes stay."""
+    import torch
+    from gpu_util import assert_layers_equal, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(**SHAPES["rows_of_2048"])
+    rng = np.random.default_rng(17)
+    stream = torch.cuda.Stream() if kind == "copy_engine" else None
+    handle = {"null": None, "per_thread": 2, "blocking": torch.cuda.ExternalStream(0), "copy_engine": stream}[kind]
+    with lmc.Context(g, 5 * g.chunk_bytes, staging_chunks=2) as c:
+        want, ids = _pool(c, g, 4, False, rng)
+        tau = _request(g, 2, rng)
+        host = [W.sentinel_layer(g, l) for l in range(g.L)]
+        dev = [torch.from_numpy(h).cuda() for h in host]
+        d_tau = slots_to_device(tau)
+        oracle.scatter(g, want[2:], tau, host)
+        out = [torch.empty(g.layer_bytes, dtype=torch.uint8, pin_memory=True) for _ in range(g.L)]
+        torch.cuda.synchronize()
+        c.retrieve_layerwise(ids[:2], d_tau, dev, 1, handle)
+        t = c.retrieve_layerwise(ids[2:], d_tau, dev, 2, handle)
+        for l in range(g.L):
+            c.wait_layer(t, l, handle)
+            if kind == "copy_engine":
+                with torch.cuda.stream(stream):
+                    out[l].copy_(dev[l], non_blocking=True)
+        if kind == "copy_engine":
+            stream.synchronize()
+            assert_layers_equal([o.numpy() for o in out], host)
+        c.wait(t)
+        torch.cuda.synchronize()
+        assert_layers_equal([d.cpu().numpy() for d in dev], host)
+
+
+def test_while_another_stream_is_captured():
+    """The call and its waits go on, and nothing of them gets into the graph."""
+    import torch
+    from gpu_util import assert_layers_equal, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(**SHAPES["rows_of_256"])
+    rng = np.random.default_rng(29)
+    consumer, captured = torch.cuda.Stream(), torch.cuda.Stream()
+    with lmc.Context(g, 4 * g.chunk_bytes, staging_chunks=2) as c:
+        want, ids = _pool(c, g, 2, False, rng)
+        tau = _request(g, 2, rng)
+        host = [W.sentinel_layer(g, l) for l in range(g.L)]
+        dev = [torch.from_numpy(h).cuda() for h in host]
+        d_tau = slots_to_device(tau)
+        x = torch.zeros(64, device="cuda")
+        oracle.scatter(g, want, tau, host)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=captured, capture_error_mode="relaxed"):
+            t = c.retrieve_layerwise(ids, d_tau, dev, 1, consumer)
+            for l in range(g.L):
+                c.wait_layer(t, l, consumer)
+            x.add_(1)
+        c.wait(t)
+        consumer.synchronize()
+        for _ in range(3):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert_layers_equal([d.cpu().numpy() for d in dev], host)
+        assert x.cpu().tolist() == [3.0] * 64

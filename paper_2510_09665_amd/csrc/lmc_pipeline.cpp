@@ -411,7 +411,7 @@ static lmc_status_t retrieve_in_steps(lmc_ctx *c, const lmc::LayerPtrs &ptrs, co
     lmc::ChunkList list;
     if (listed)
         for (int64_t i = 0; i < n; i++) list.slot[i] = int32_t(pool_slots[size_t(i)]);
-    lmc::Arrivals arrivals{c->words, 0};
+    lmc::Arrivals arrivals{c->word(0), 0};
     const lmc_status_t rc = timed_launch(c, false, view, ptrs, slot_mapping, uint32_t(n),
                                          c->pool_dev + (listed ? 0 : pool_slots[0] * c->chunk_bytes), c->s_scatter,
                                          listed ? &list : nullptr, nullptr, &arrivals, planes);
@@ -429,9 +429,12 @@ static lmc_status_t retrieve_in_steps(lmc_ctx *c, const lmc::LayerPtrs &ptrs, co
 // event has to cross from that stream to the library's and back: those two hand-overs cost the
 // calling thread 26 us (a query and a wait between streams are 12-14 us each on this runtime)
 // and leave the link idle in between when one such retrieve follows another.  Call after call, three
-// contexts in turn: 0.5 MiB 53 -> 36 us, 12 MiB in 256-byte rows 234 -> 223 us.  What the runtime does
+// contexts in turn: 0.5 MiB 53 -> 36 us, 12 MiB in 256-byte rows 234 -> 223 us.  The scatter stream,
+// which keeps the operation's last event, waits for the kernel's word, which takes 2 us where an
+// event from the caller's stream takes 13 (0.5 MiB 34 -> 21 us).  What the runtime does
 // for the first launch on a stream that has run nothing is now done inside the call: a program's
-// first 0.5 MiB takes 155-190 us instead of 150-160.  Not while the stream is being captured, not for a stream of another GPU, and not where the caller's
+// first 0.5 MiB takes 155-190 us instead of 150-160.
+// Not while the stream is being captured, not for a stream of another GPU, and not where the caller's
 // stream is not to wait ("caller_waits" 0), where the library itself waits before it launches
 // (LMC_FLAG_VALIDATE_SLOTS) or where a launch leaves an event behind on its stream (timing,
 // trace, and the scratch of ordered scatters, which "link_groups" 0 lets through).
@@ -510,9 +513,11 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     const int64_t per = c->cfg.staging_chunks;
     // without staging (LMC_FLAG_DIRECT, or a small call): no copy, the scatter kernel reads the
     // pinned pool over the link
-    auto load_direct = [&](const lmc::LaunchView &view, uint64_t pool_off, hipEvent_t stop) {
-        return move_direct(c, false, view, pool_off, ptrs, slot_mapping, nullptr, pool_slots.data(), n_chunks, scatters, stop);
+    auto load_direct = [&](const lmc::LaunchView &view, uint64_t pool_off, hipEvent_t stop, lmc::Arrivals *arrivals) {
+        return move_direct(c, false, view, pool_off, ptrs, slot_mapping, nullptr, pool_slots.data(), n_chunks, scatters, stop,
+                           arrivals);
     };
+    bool by_word = false;   // the whole transfer is in place when the bulk word has reached its target
     // one group: copies into the next ring buffer on the H2D stream, scatter on the
     // scatter stream; the buffer is released when the scatter has read it
     auto load_group = [&](const lmc::LaunchView &view, uint64_t pool_off, int64_t i0, int64_t k,
@@ -556,10 +561,22 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     const bool two_copy_streams = !other_direction_busy(c, false);
     auto enqueue = [&]() -> lmc_status_t {
         if (direct && !op.layerwise) {
-            if ((rc = load_direct(lmc::bulk_view(c->kg), 0, nullptr)) != LMC_OK) return rc;
+            lmc::Arrivals arrivals{nullptr, 0};
+            hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+            HIPCHK(c, hipStreamIsCapturing(c->s_scatter, &capturing));
+            const bool tells = c->words != nullptr && c->link_groups > 0 && capturing == hipStreamCaptureStatusNone;
+            if (tells) arrivals.words = c->word(lmc_ctx::kBulkWord);
+            rc = load_direct(lmc::bulk_view(c->kg), 0, nullptr, tells ? &arrivals : nullptr);
+            c->word_target[lmc_ctx::kBulkWord] += arrivals.count;
+            if (rc != LMC_OK) return rc;
+            by_word = arrivals.count > 0;
             // the operation's last event stays on a stream of the library's own: the caller may
             // destroy its stream before the event is asked for
-            if (on_caller && (rc = order_after(c, c->s_scatter, user)) != LMC_OK) return rc;
+            if (on_caller) {
+                rc = by_word ? wait_for_word(c, c->s_scatter, lmc_ctx::kBulkWord, c->word_target[lmc_ctx::kBulkWord])
+                             : order_after(c, c->s_scatter, user);
+                if (rc != LMC_OK) return rc;
+            }
         } else if (!op.layerwise) {
             const lmc::LaunchView view = lmc::bulk_view(c->kg);
             if ((rc = ring_reslot(c, ring, ring.buf_bytes, c->s_h2d, c->s_scatter, c->s_h2d2)) != LMC_OK) return rc;
@@ -589,7 +606,7 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
                 if ((rc = get_event(c, false, &e)) != LMC_OK) return rc;
                 op.owned_events.push_back(e);
                 if (direct) {
-                    if ((rc = load_direct(view, uint64_t(l0) * layer_bytes, e)) != LMC_OK) return rc;
+                    if ((rc = load_direct(view, uint64_t(l0) * layer_bytes, e, nullptr)) != LMC_OK) return rc;
                 } else {
                     const int64_t cap = layer_group_chunks(c, ring, view, n_chunks);
                     if ((rc = ring_reslot(c, ring, (uint64_t(cap) * view.chunk_stride + 255) / 256 * 256, c->s_h2d,
@@ -625,7 +642,11 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     c->stats.chunks_retrieved += uint64_t(n_chunks);
     // bulk: the caller's stream continues when everything is in place; layer-wise: the
     // caller orders its streams per layer with lmc_wait_layer
-    if (!layerwise && !on_caller && c->caller_waits) HIPCHK(c, hipStreamWaitEvent(user, c->ops.back().done, 0));
+    if (!layerwise && !on_caller && c->caller_waits) {
+        if (by_word && may_wait_for_word(c, user))
+            return wait_for_word(c, user, lmc_ctx::kBulkWord, c->word_target[lmc_ctx::kBulkWord]);
+        HIPCHK(c, hipStreamWaitEvent(user, c->ops.back().done, 0));
+    }
     return LMC_OK;
 }
 
@@ -941,6 +962,8 @@ lmc_status_t lmc_wait_layer(lmc_ctx_t *c, uint64_t ticket, int32_t layer, void *
     if (op == nullptr) return LMC_OK;                       // finished long ago
     if (!op->layerwise) return LMC_ERR_INVAL;
     if (!op->step_target.empty()) {
+        if (hipEventQuery(op->done) == hipSuccess) return LMC_OK;
+        (void)hipGetLastError();   // "not ready" is an answer, not a failure
         const int32_t i = layer / op->step_layers;
         if (may_wait_for_word(c, static_cast<hipStream_t>(stream)))
             return wait_for_word(c, static_cast<hipStream_t>(stream), i, op->step_target[size_t(i)]);

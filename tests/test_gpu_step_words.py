@@ -142,6 +142,44 @@ def test_every_kind_of_consumer(kind):
         assert_layers_equal([d.cpu().numpy() for d in dev], host)
 
 
+@pytest.mark.parametrize("shape", ["rows_of_256", "wide_row216", "narrow_4"])
+@pytest.mark.parametrize("library_stream", [False, True])
+def test_bulk_retrieves_hand_over_by_word(shape, library_stream):
+    """Small retrieves one behind another into the same pages, from two streams in turn or from one (on
+    whose own stream the kernels then run); a reader on the stream of each, whose caches hold the pages
+    as they were, sees that retrieve's bytes, and the last one's stay."""
+    import torch
+    from gpu_util import assert_layers_equal, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(**SHAPES[shape])
+    rng = np.random.default_rng(zlib.crc32(shape.encode()) + 5)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    with lmc.Context(g, 8 * g.chunk_bytes, staging_chunks=2) as c:
+        want, ids = _pool(c, g, 4, True, rng)
+        tau = _request(g, 2, rng)
+        d_tau = slots_to_device(tau)
+        dev = [torch.from_numpy(W.sentinel_layer(g, l)).cuda() for l in range(g.L)]
+        hosts = []
+        for first in (0, 2):
+            hosts.append([W.sentinel_layer(g, l) for l in range(g.L)])
+            oracle.scatter(g, want[first:first + 2], tau, hosts[-1])
+        torch.cuda.synchronize()
+        seen = []
+        for k in range(12):
+            s = b if library_stream and k % 3 == 1 else a
+            with torch.cuda.stream(s):
+                c.retrieve(ids[2 * (k % 2):2 * (k % 2) + 2], d_tau, dev, s)
+                seen.append([d.clone() for d in dev])
+            (a if s is b else b).wait_stream(s)            # the next retrieve finds the pages read
+        t = c.retrieve(ids[:2], d_tau, dev, a)
+        c.wait(t)
+        assert c.test(t)
+        torch.cuda.synchronize()
+        for k, one in enumerate(seen):
+            assert_layers_equal([d.cpu().numpy() for d in one], hosts[k % 2], "retrieve %d" % k)
+        assert_layers_equal([d.cpu().numpy() for d in dev], hosts[0])
+
+
 def test_while_another_stream_is_captured():
     """The call and its waits go on, and nothing of them gets into the graph."""
     import torch

@@ -566,10 +566,10 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * "nt_store" (0/1: non-temporal hints on the kernels' streaming accesses, except those of
  * scatters that read the pool itself), "xcd_run"
  * (consecutive tiles handed to one XCD, 0 = hardware round-robin), "link_groups" (default
- * 64: launches that read or write the pinned pool themselves run as that many groups of 256
- * lanes taking tiles in turn (up to twice as many for long launches that write it), which is
- * what the host link likes; those that read it put two groups to a workgroup and keep its compute
- * unit to themselves; 0 = one tile per workgroup as for launches inside HBM),
+ * 64: launches that read or write the pinned pool themselves run as three quarters of that many
+ * groups of 256 lanes taking tiles in turn (as many, or twice as many, where rows are no
+ * multiples of 16 bytes), which is what the host link likes, two groups to a workgroup, which keeps
+ * its compute unit to itself; 0 = one tile per workgroup as for launches inside HBM),
  * "copy_kernel" (default 0; bit 0: copies from staging to the
  * pool are made by the library's own link-paced copy kernel instead of hipMemcpyAsync;
  * bit 1: copies from the pool to staging too.  At the rate of the runtime's copies and

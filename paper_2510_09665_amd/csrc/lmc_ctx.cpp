@@ -123,7 +123,8 @@ void reap(lmc_ctx *c) {
     c->stats.d2h_copy_last_gbps = c->d2h_guard.last_rate() * 1e-9;
     for (size_t i = 0; i < c->ops.size();) {
         Op &op = c->ops[i];
-        const bool finished = op.done != nullptr ? hipEventQuery(op.done) == hipSuccess : !op.pending;
+        const bool finished = c->is_stored(op.stored_target) ||
+                              (op.done != nullptr ? hipEventQuery(op.done) == hipSuccess : !op.pending);
         if (!finished) {
             i++;
             continue;
@@ -317,17 +318,39 @@ void end_use(lmc_ctx *c, const uint64_t *ids, int64_t n) {
     }
 }
 
-// Sleeps until every event of `evs` has completed, with the context's mutex released so
+// What a thread waits for: an event, and for a store that tells the host itself (Op::stored_target)
+// the value of the context's stored_host.
+struct Awaited {
+    hipEvent_t event;
+    uint64_t stored_target;
+};
+
+// Waits for `a`: looks at the word for as long as a store of the size that tells takes, or a little longer,
+// and then leaves the rest to the event.
+static hipError_t await(const lmc_ctx *c, const Awaited &a) {
+    if (a.stored_target != 0) {
+        const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(1500);
+        do {
+            for (int i = 0; i < 64; i++) {
+                if (c->is_stored(a.stored_target)) return hipSuccess;
+                __builtin_ia32_pause();
+            }
+        } while (std::chrono::steady_clock::now() < until);
+    }
+    return hipEventSynchronize(a.event);
+}
+
+// Sleeps until everything in `all` has completed, with the context's mutex released so
 // that other threads go on storing, loading and looking up meanwhile.  The events stay
 // valid: whatever reap() frees while somebody sleeps is parked (lmc_ctx::waiters).
 static lmc_status_t sync_unlocked(lmc_ctx *c, std::unique_lock<std::mutex> &lock,
-                           const std::vector<hipEvent_t> &evs) {
-    if (evs.empty()) return LMC_OK;
+                           const std::vector<Awaited> &all) {
+    if (all.empty()) return LMC_OK;
     c->waiters++;
     lock.unlock();
     hipError_t err = hipSuccess;
-    for (hipEvent_t e : evs) {
-        const hipError_t x = hipEventSynchronize(e);
+    for (const Awaited &a : all) {
+        const hipError_t x = await(c, a);
         if (x != hipSuccess && err == hipSuccess) err = x;
     }
     lock.lock();
@@ -344,10 +367,10 @@ static lmc_status_t sync_unlocked(lmc_ctx *c, std::unique_lock<std::mutex> &lock
 }
 
 // The store that fills the slot of chunk `id`, if it is still under way: the event behind
-// the copies of the chunk's group, or else the store's last event, goes to *ev (null =
+// the copies of the chunk's group, or else the store's last event, goes to *ev (no event:
 // nothing to wait for).  LMC_ERR_MISS / LMC_ERR_BUSY as lmc_get_host.
-static lmc_status_t pending_fill(lmc_ctx *c, uint64_t id, int64_t *slot_out, hipEvent_t *ev) {
-    *ev = nullptr;
+static lmc_status_t pending_fill(lmc_ctx *c, uint64_t id, int64_t *slot_out, Awaited *ev) {
+    *ev = Awaited{nullptr, 0};
     const int64_t s = c->index.find(id);
     if (s < 0) return LMC_ERR_MISS;
     *slot_out = s;
@@ -355,7 +378,8 @@ static lmc_status_t pending_fill(lmc_ctx *c, uint64_t id, int64_t *slot_out, hip
     if (m.ready_ticket != 0) {
         const Op *o = find_op(c, m.ready_ticket);
         if (o != nullptr && o->pending) return LMC_ERR_BUSY;
-        if (o != nullptr) *ev = m.ready_event != nullptr ? static_cast<hipEvent_t>(m.ready_event) : o->done;
+        if (o != nullptr)
+            *ev = m.ready_event != nullptr ? Awaited{static_cast<hipEvent_t>(m.ready_event), 0} : Awaited{o->done, o->stored_target};
     }
     return LMC_OK;
 }
@@ -389,6 +413,7 @@ static void destroy_ctx(lmc_ctx *c) {
             if (s) (void)hipStreamDestroy(s);
         if (c->bad_flag_host) (void)hipHostFree(c->bad_flag_host);
         if (c->words) (void)hipFree(c->words);
+        if (c->stored_host) (void)hipHostFree(c->stored_host);
         if (c->pool) (void)hipHostFree(c->pool);
     } else {
         std::free(c->pool);
@@ -496,6 +521,13 @@ lmc_status_t lmc_create(const lmc_config_t *cfg, lmc_ctx_t **ctx_out) {
                 c->words = nullptr;
                 return fail(LMC_ERR_NOMEM);
             }
+            if (hipHostMalloc(reinterpret_cast<void **>(&c->stored_host), 64, hipHostMallocMapped) != hipSuccess) {
+                c->stored_host = nullptr;
+                return fail(LMC_ERR_NOMEM);
+            }
+            std::memset(c->stored_host, 0, 64);
+            if (hipHostGetDevicePointer(reinterpret_cast<void **>(&c->stored_dev), c->stored_host, 0) != hipSuccess)
+                return fail(LMC_ERR_HIP);
             if (hipMemset(c->words, 0, kBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) return fail(LMC_ERR_HIP);
         }
         for (hipStream_t *s : {&c->s_gather, &c->s_d2h, &c->s_h2d, &c->s_scatter, &c->s_h2d2, &c->s_d2h2})
@@ -573,7 +605,7 @@ lmc_status_t lmc_wait(lmc_ctx_t *c, uint64_t ticket) {
     // retrieve on the scatter stream), so the newest operation alone says nothing about
     // the older ones: the newest event of every such stream is waited for.
     std::vector<hipStream_t> streams;
-    std::vector<hipEvent_t> last;
+    std::vector<Awaited> last;
     for (const Op &o : c->ops) {
         if (o.ticket > ticket) continue;
         if (o.pending) {
@@ -589,9 +621,9 @@ lmc_status_t lmc_wait(lmc_ctx_t *c, uint64_t ticket) {
                                      : size_t(std::find(streams.begin(), streams.end(), o.final_stream) - streams.begin());
         if (i == streams.size()) {
             streams.push_back(o.layerwise ? nullptr : o.final_stream);
-            last.push_back(o.done);
+            last.push_back(Awaited{o.done, o.stored_target});
         } else {
-            last[i] = o.done;   // c->ops is in ticket order, and a stream finishes in order
+            last[i] = Awaited{o.done, o.stored_target};   // c->ops is in ticket order, and a stream finishes in order
         }
     }
     const lmc_status_t rc = sync_unlocked(c, lock, last);
@@ -658,10 +690,10 @@ lmc_status_t lmc_get_host(lmc_ctx_t *c, uint64_t id, void *host_dst) {
     // that fills the slot; the chunk may be gone when this thread is back
     for (;;) {
         int64_t s = -1;
-        hipEvent_t ev = nullptr;
+        Awaited ev{};
         lmc_status_t rc = pending_fill(c, id, &s, &ev);
         if (rc != LMC_OK) return rc;
-        if (ev == nullptr || hipEventQuery(ev) == hipSuccess) {
+        if (ev.event == nullptr || hipEventQuery(ev.event) == hipSuccess) {
             std::memcpy(host_dst, c->pool + s * c->chunk_bytes, size_t(c->chunk_bytes));
             return LMC_OK;
         }
@@ -677,10 +709,10 @@ lmc_status_t lmc_chunk_acquire(lmc_ctx_t *c, uint64_t id, const void **host_ptr_
     if (c->has_device) reap(c);
     for (;;) {
         int64_t s = -1;
-        hipEvent_t ev = nullptr;
+        Awaited ev{};
         lmc_status_t rc = pending_fill(c, id, &s, &ev);
         if (rc != LMC_OK) return rc;
-        if (ev == nullptr || hipEventQuery(ev) == hipSuccess) {
+        if (ev.event == nullptr || hipEventQuery(ev.event) == hipSuccess) {
             c->index.meta(s).refs++;
             *host_ptr_out = c->pool + s * c->chunk_bytes;
             return LMC_OK;

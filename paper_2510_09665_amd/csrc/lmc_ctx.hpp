@@ -40,6 +40,7 @@ struct Op {
     uint64_t ticket = 0;
     hipEvent_t done = nullptr;       // null: nothing enqueued (yet) for this ticket
     hipStream_t final_stream = nullptr;  // the library stream `done` was recorded on
+    uint64_t stored_target = 0;          // not 0: finished when the context's stored_host has reached this
     bool on_caller = false;              // its kernels run on the caller's own stream ...
     hipStream_t caller = nullptr;        // ... this one
     std::vector<int64_t> slots;      // pool slots whose in-flight count this op holds
@@ -85,7 +86,7 @@ struct lmc_ctx {
     lmc_config_t cfg{};
     lmc::KernelGeom kg{};
     lmc::LaunchShape shape{};
-    uint32_t link_groups = 64;  // workgroups of a launch whose other side is the pinned pool; 0 = as for HBM
+    uint32_t link_groups = 64;  // groups of 256 lanes of a launch whose other side is the pinned pool; 0 = as for HBM
     // Which copies between staging and the pool the library's own link-paced copy kernel
     // makes instead of hipMemcpyAsync: bit 0 = to the host, bit 1 = from the host.  Off
     // by default: the runtime's copies leave the compute units to the engine (dense products
@@ -164,7 +165,12 @@ struct lmc_ctx {
     // layer-wise one.  The launches that use a word run one after the other, so a word only grows and
     // word_target[i], what it will have reached when everything launched so far is done, says
     // when the newest of them is.  Null where a stream cannot wait for a value.
-    static constexpr int kBulkWord = LMC_MAX_LAYERS, kWords = LMC_MAX_LAYERS + 1;
+    // kStoreWord is for bulk stores without staging, whose kernels pass its value on to
+    // *stored_host: a thread that waits for such a store sees it there 5 us before the event
+    // behind the kernel completes.
+    static constexpr int kBulkWord = LMC_MAX_LAYERS, kStoreWord = LMC_MAX_LAYERS + 1, kWords = LMC_MAX_LAYERS + 2;
+    uint64_t *stored_host = nullptr, *stored_dev = nullptr;   // one word of host memory and its address on the GPU
+    bool is_stored(uint64_t target) const { return target != 0 && __atomic_load_n(stored_host, __ATOMIC_ACQUIRE) >= target; }
     uint64_t *words = nullptr;
     uint64_t word_target[kWords] = {};
     uint64_t *word(int i) const { return words + size_t(i) * (lmc::kWordStride / sizeof(uint64_t)); }
@@ -254,7 +260,8 @@ lmc_status_t make_ring(lmc_ctx *c, Ring &r);
 lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
                           uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list = nullptr,
-                          hipEvent_t stop = nullptr, lmc::Arrivals *arrivals = nullptr, uint32_t planes_per_step = 0);
+                          hipEvent_t stop = nullptr, lmc::Arrivals *arrivals = nullptr, uint32_t planes_per_step = 0,
+                          lmc::HostWord *told = nullptr);
 // lmc_streams.cpp
 lmc_status_t shares_a_queue(lmc_ctx *c, hipStream_t busy, bool by_kernel, hipStream_t other, uint8_t *devbuf,
                             uint64_t nbytes, hipEvent_t a0, hipEvent_t a1, hipEvent_t k1, bool *shares);

@@ -102,6 +102,14 @@ __device__ __forceinline__ void arrive(uint64_t word_at) {
     if ((threadIdx.x & 63u) == 0)
         (void)__hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)word_at, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+// The same for the host: the last wavefront to arrive, which brings the word to `target`, writes that
+// to a word in host memory.
+__device__ __forceinline__ void arrive_and_tell(uint64_t word_at, uint64_t target, uint64_t host_at) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if ((threadIdx.x & 63u) == 0 &&
+        __hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)word_at, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1 == target)
+        __hip_atomic_store((LMC_GLOBAL uint64_t *)host_at, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 // Keeps a wave-uniform value in scalar registers from this point on.
 template <typename T> __device__ __forceinline__ T pin(T v) {
@@ -318,18 +326,35 @@ __global__ __launch_bounds__(kThreads) void gather_rows_by_wave(const KernelGeom
     __builtin_nontemporal_store(v, (LMC_GLOBAL V *)st + lane);
 }
 
+// What crosses the link keeps the compute unit to itself: a workgroup asks for all of its LDS, of
+// which it uses nothing.  A load of host memory takes 4 us and more with the link busy, stores to it
+// queue up likewise, and the loads of whatever else runs on that compute unit wait behind them.  A
+// dense bf16 product of 128, 512, 1024 or 4096 rows by 4096 x 4096 (31, 34, 44, 111 us alone) beside
+// 64 groups that load took 158, 159, 191, 189 us without the claim and takes 38, 55, 78, 189 with it;
+// beside as many that store 157, 159, 193, 257 and 40, 55, 84, 194.  Nothing is lost while the GPU is
+// full: 0.5 MiB issued into a queue of products, attention or softmax ends within the spread of the
+// unclaimed (15-110 us), as soon as one compute unit runs out of work of the kernel before.
+// Hence also two groups of 256 lanes to a workgroup: as many tiles in flight on half the compute
+// units, at the same rate.
+constexpr int kPacedThreads = 2 * kThreads;
+constexpr int kLdsBytes = 160 * 1024;
+__device__ __forceinline__ void claim_compute_unit() {
+    __shared__ char all[kLdsBytes];
+    asm volatile("" ::"v"((LMC_LDS char *)all));
+}
+
 // The gather's tile for a workgroup that takes many, one after the other: no early return, a lane
 // past the end of the plane reads the slot that the last one reads and moves nothing.  With a list,
 // chunk c of the launch lies list->slot[c] chunk strides into the buffer.
 template <int VEC, bool NT_LD, int ST>
 __device__ __forceinline__ void gather_tile_in_turn(const TileArgs &a, const LayerPtrs &layers, uint32_t blk,
-                                                    const ChunkList *list) {
+                                                    uint32_t lane, const ChunkList *list) {
     typedef typename VecOf<VEC>::type V;
     const uint32_t q = a.by_tiles.div(blk);
     const uint32_t tile = blk - q * a.by_tiles.d;
     const uint32_t c = a.by_lp.div(q);
     const uint32_t lp = q - c * a.by_lp.d;
-    const uint32_t r0 = tile * kThreads + threadIdx.x;
+    const uint32_t r0 = tile * kThreads + lane;
     const uint32_t r = min(r0, a.vec_per_plane - 1);
     if constexpr (VEC == kPacked) {
         const uint64_t st = a.staging_at + uint64_t(list ? uint32_t(list->slot[c]) : c) * a.chunk_stride +
@@ -360,26 +385,26 @@ __device__ __forceinline__ void gather_tile_in_turn(const TileArgs &a, const Lay
 }
 
 // Across the host link (pages <-> pinned pool, no staging): the link, not HBM, sets the
-// pace, and it runs best when few workgroups walk the host side in order.  Measured with a
-// plain copy kernel on this part: 64 workgroups taking tiles in turn reach 57.6 GB/s
+// pace, and it runs best when few groups of 256 lanes walk the host side in order.  Measured with a
+// plain copy kernel on this part: 64 groups taking tiles in turn reach 57.6 GB/s
 // reading host memory and 56.2 GB/s writing it (the runtime's own copies: 57.2 / 57.0),
 // one tile per workgroup over thousands of workgroups 55.7 / 54.4; with stores at system scope
 // (StoreKind) writing is at 57.1.  The grid is fixed and
-// every workgroup takes tiles blk, blk + gridDim.x, ... until the launch's n_blocks.
-// Two or four tiles at a time in a half or a quarter of the workgroups reach the same rate
-// alone (12 MiB from the host 222-224 us, 32 MiB to it 601-607), but beside another such
-// launch loads are slower: three contexts in turn, 12 MiB each in 256-byte rows, 236 us a
-// pass with 64 x 1 tile, 244 with 32 x 2, 242 with 16 x 4.
+// every group takes tiles blk, blk + groups, ... until the launch's n_blocks.
 template <int VEC, bool NT_LD, int ST>
-__global__ __launch_bounds__(kThreads) void gather_paced(const KernelGeom g, const LaunchView view,
+__global__ __launch_bounds__(kPacedThreads) void gather_paced(const KernelGeom g, const LaunchView view,
                                                          const LayerPtrs layers,
                                                          const int64_t *__restrict__ slot_mapping,
                                                          uint8_t *staging, int32_t *bad_flag,
-                                                         uint32_t n_blocks) {
+                                                         uint32_t n_blocks, uint32_t groups, const HostWord told) {
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
-    const uint32_t step = pin(uint32_t(gridDim.x)), end = pin(n_blocks);
-    for (uint32_t blk = blockIdx.x; blk < end; blk += step)
-        gather_tile_in_turn<VEC, NT_LD, ST>(a, layers, blk, nullptr);
+    claim_compute_unit();
+    const uint32_t step = pin(groups), end = pin(n_blocks), lane = threadIdx.x % kThreads;
+    const uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) * gridDim.x + blockIdx.x;
+    if (first >= step) return;                       // an odd number of groups leaves a half without work
+    for (uint32_t blk = first; blk < end; blk += step)
+        gather_tile_in_turn<VEC, NT_LD, ST>(a, layers, blk, lane, nullptr);
+    if (ST == kStoreThrough && told.word != nullptr) arrive_and_tell(uint64_t(told.word), told.target, uint64_t(told.host));
 }
 
 // The same for chunks in any pool slots (a fragmented pool, a batch of requests): one launch
@@ -387,31 +412,19 @@ __global__ __launch_bounds__(kThreads) void gather_paced(const KernelGeom g, con
 // and is followed by a gap of 4-5 us.  A store of 25 chunks of 2 MiB in 12 runs: 12 launches
 // take 975 us on the device, one takes 946 (1123 and 1089 us for the whole call).
 template <int VEC, bool NT_LD, int ST>
-__global__ __launch_bounds__(kThreads) void gather_listed(const KernelGeom g, const LaunchView view,
+__global__ __launch_bounds__(kPacedThreads) void gather_listed(const KernelGeom g, const LaunchView view,
                                                           const LayerPtrs layers,
                                                           const int64_t *__restrict__ slot_mapping,
                                                           uint8_t *staging, int32_t *bad_flag,
-                                                          uint32_t n_blocks, const ChunkList list) {
+                                                          uint32_t n_blocks, uint32_t groups, const HostWord told, const ChunkList list) {
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
-    const uint32_t step = pin(uint32_t(gridDim.x)), end = pin(n_blocks);
-    for (uint32_t blk = blockIdx.x; blk < end; blk += step)
-        gather_tile_in_turn<VEC, NT_LD, ST>(a, layers, blk, &list);
-}
-
-// What reads host memory keeps the compute unit to itself: a workgroup asks for all of its LDS, of
-// which it uses nothing.  A load of host memory takes 4 us and more with the link busy, and the
-// loads of whatever else runs on that compute unit queue up behind it.  A dense bf16 product of 128,
-// 512, 1024 or 4096 rows by 4096 x 4096 (31, 34, 44, 111 us alone) beside 64 groups took 158, 159, 191,
-// 189 us without the claim and takes 38, 55, 78, 189 with it.  Nothing is lost while the GPU is full:
-// 0.5 MiB issued into a queue of products, attention or softmax ends within the spread of the
-// unclaimed (15-110 us), as soon as one compute unit runs out of work of the kernel before.
-// Hence also two groups of 256 lanes to a workgroup: as many tiles in flight on half the compute
-// units, at the same rate (64 MiB in 1182 us).
-constexpr int kPacedThreads = 2 * kThreads;
-constexpr int kLdsBytes = 160 * 1024;
-__device__ __forceinline__ void claim_compute_unit() {
-    __shared__ char all[kLdsBytes];
-    asm volatile("" ::"v"((LMC_LDS char *)all));
+    claim_compute_unit();
+    const uint32_t step = pin(groups), end = pin(n_blocks), lane = threadIdx.x % kThreads;
+    const uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) * gridDim.x + blockIdx.x;
+    if (first >= step) return;                       // an odd number of groups leaves a half without work
+    for (uint32_t blk = first; blk < end; blk += step)
+        gather_tile_in_turn<VEC, NT_LD, ST>(a, layers, blk, lane, &list);
+    if (ST == kStoreThrough && told.word != nullptr) arrive_and_tell(uint64_t(told.word), told.target, uint64_t(told.host));
 }
 
 // One lane's piece of a tile of a scatter from the pool: where it comes from, and what its
@@ -705,7 +718,7 @@ __global__ __launch_bounds__(kThreads) void copy_tiles(u32x4 *dst, const uint32_
 }
 
 // Copy between device memory and the pinned pool, paced for the host link like
-// move_rows_paced: a fixed, small grid whose workgroups take 4 KiB tiles in turn.  The
+// gather_paced: a fixed, small grid whose workgroups take 4 KiB tiles in turn.  The
 // bytes form `rows` rows of width_vec 16-byte vectors, src_pitch / dst_pitch bytes apart
 // (one row per chunk; pitch == width gives a plain copy).
 template <bool TO_POOL>
@@ -788,12 +801,15 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
     return hipGetLastError();
 }
 
+// How many of the groups asked for a launch gets where three quarters do.
+uint32_t paced_part(uint32_t groups) { return std::max(1u, groups - groups / 4); }
+
 // Pages into the pool.
 template <int VEC>
 hipError_t launch_gather_paced(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                                const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                                uint8_t *pool, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
-                               hipEvent_t stop, const ChunkList *list) {
+                               hipEvent_t stop, const ChunkList *list, HostWord *told) {
     const uint32_t n_blocks = n_chunks * v.by_n_lp.d * g.by_tiles_per_plane.d;
     if (n_blocks == 0) return hipSuccess;
     // through the L2 where every wavefront writes whole lines of 128 bytes: 16-byte lanes, and
@@ -803,28 +819,36 @@ hipError_t launch_gather_paced(const KernelGeom &g, const LaunchView &v, const L
                          ((uint64_t(reinterpret_cast<uintptr_t>(pool)) | v.chunk_stride | g.plane_bytes) % 128) == 0;
     constexpr int kThrough = kLines ? kStoreThrough : kStoreNonTemporal;   // nothing else is instantiated
     // blk + step must not wrap: n_blocks < 2^24 (max_chunks_per_launch) and the grid is small
-    // A store at system scope ends at the host's memory, and a wavefront waits for it before
-    // it uses the next slot: long launches need half as many workgroups more.  32 MiB by
-    // 64, 96, 128 workgroups: 607, 590, 590 us (601 with 64 and non-temporal stores); 4 to
-    // 12 MiB: the same by 64 and 96; 1 MiB and less: 96 workgroups 5 % slower.  Pieces put
-    // together from two loads take longer still: 8.7 MiB in 216-byte rows, planes of 16
-    // tokens, by 64 and 128: 175, 168 us.
-    const uint32_t groups = VEC == kPacked ? (n_blocks >= 512 ? 2 * s.paced_groups : s.paced_groups)
-                            : through && n_blocks >= 4096 ? s.paced_groups + s.paced_groups / 2 : s.paced_groups;
-    const dim3 grid(std::min(n_blocks, groups)), block(kThreads);
+    // The rate does not grow steadily with the groups: 8, 32 and 64 MiB by 32, 48, 64, 96, 128 of them
+    // 166, 165, 167, 164, 163; 609, 605, 623, 606, 606; 1202, 1195, 1233, 1198, 1195 us (0.5 to 4 MiB
+    // within 2 %), so three quarters of the 64 that the knob stands at, on as few compute units as
+    // that takes: a product of 128 rows by 4096 x 4096 (31 us alone) takes 33 us beside 48 groups, 40
+    // beside 96.  Pieces put together from two loads take longer: 8.7 MiB in 216-byte rows, planes of
+    // 16 tokens, by 64 and 128: 189, 184 us.
+    uint32_t groups = VEC == kPacked ? (n_blocks >= 512 ? 2 * s.paced_groups : s.paced_groups)
+                      : through ? paced_part(s.paced_groups) : s.paced_groups;
+    groups = std::min(n_blocks, groups);
+    const dim3 grid((groups + 1) / 2), block(kPacedThreads);
+    HostWord done{nullptr, nullptr, 0};
+    if (told != nullptr && through) {
+        done = *told;
+        done.target += groups * (kThreads / 64);
+    }
 #define LMC_GO(LD, ST)                                                                                  \
     if (list != nullptr)                                                                                \
         hipExtLaunchKernelGGL((gather_listed<VEC, LD, ST>), grid, block, 0, stream, start, stop, 0, g, v, \
-                              layers, slot_mapping, pool, bad_flag, n_blocks, *list);                   \
+                              layers, slot_mapping, pool, bad_flag, n_blocks, groups, done, *list);     \
     else hipExtLaunchKernelGGL((gather_paced<VEC, LD, ST>), grid, block, 0, stream, start, stop, 0, g, v, \
-                          layers, slot_mapping, pool, bad_flag, n_blocks)
+                          layers, slot_mapping, pool, bad_flag, n_blocks, groups, done)
     if (through) { LMC_GO(true, kThrough); }
     else if (s.nt_load && s.nt_store) { LMC_GO(true, kStoreNonTemporal); }
     else if (s.nt_load) { LMC_GO(true, kStorePlain); }
     else if (s.nt_store) { LMC_GO(false, kStoreNonTemporal); }
     else { LMC_GO(false, kStorePlain); }
 #undef LMC_GO
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (told != nullptr && e == hipSuccess && done.word != nullptr) told->target = done.target;
+    return e;
 }
 
 // The pool into pages, `planes` planes of every chunk in each step.  The non-temporal hints of the
@@ -845,7 +869,8 @@ hipError_t launch_scatter_paced(const KernelGeom &g, const LaunchView &v, uint32
     steps.n_blocks = n_chunks * planes * g.by_tiles_per_plane.d;
     steps.last_blocks = n_chunks * last * g.by_tiles_per_plane.d;
     steps.by_last_lp = make_fastdiv(last);
-    steps.groups = uint32_t(std::min<uint64_t>(tiles, groups));
+    // 64 MiB by 32, 48, 64, 96 groups: 1189, 1182, 1183, 1227 us; 12 MiB by 48, 64: 225, 225; 0.5 MiB alike
+    steps.groups = uint32_t(std::min<uint64_t>(tiles, paced_part(groups)));
     const dim3 grid((steps.groups + 1) / 2), block(kPacedThreads);
     uint64_t *words = arrivals != nullptr ? arrivals->words : nullptr;
     if (list != nullptr)
@@ -934,14 +959,15 @@ LaunchView layer_view(const KernelGeom &g, uint32_t planes_per_layer, uint32_t f
 hipError_t launch_gather(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                          const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                          uint8_t *staging, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
-                         hipEvent_t stop, const ChunkList *list) {
+                         hipEvent_t stop, const ChunkList *list, HostWord *told) {
     if (list != nullptr && (s.paced_groups == 0 || n_chunks > uint32_t(kMaxListed))) return hipErrorInvalidValue;
     if (s.paced_groups > 0 && packs(g, v, staging))
         return launch_gather_paced<kPacked>(packed_geom(g), v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream,
-                                            start, stop, list);
+                                            start, stop, list, told);
     return by_vec(g, [&](auto vec) {
         return s.paced_groups > 0
-                   ? launch_gather_paced<vec.value>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop, list)
+                   ? launch_gather_paced<vec.value>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start,
+                                                    stop, list, told)
                    : launch_move_v<vec.value, true>(g, v, s, layers, slot_mapping, n_chunks, staging, bad_flag, stream, start, stop);
     });
 }

@@ -77,8 +77,8 @@ struct LaunchShape {
     uint32_t ordered_group_rows;  // scatter in destination order: rows (tokens) per group, see
                                   // launch_scatter_ordered; 0 = one group, the launch goes plane by plane
     uint32_t paced_groups;    // 0: one tile per workgroup (HBM-bound launches); n > 0: a
-                              // fixed grid of n workgroups that take tiles in turn, for
-                              // launches whose other side is host memory
+                              // fixed grid of about n groups of 256 lanes that take tiles in
+                              // turn, for launches whose other side is host memory
 };
 
 // Where the chunks of one link-paced launch lie when they are not back to back: chunk i of
@@ -98,6 +98,15 @@ struct Arrivals {
     uint32_t count;
 };
 constexpr uint32_t kWordStride = 64;
+// Where a gather into the pool tells the host that its last store has reached the pool: the wavefronts
+// count themselves off at `word`, and the one that brings it to `target` writes that to `host`.
+// Handed to a launch, target is what the word will have reached before it; it receives what it will
+// have reached behind it, or stays as it is where the launch cannot tell (its stores do not go
+// through the L2).
+struct HostWord {
+    uint64_t *word, *host;
+    uint64_t target;
+};
 // The steps of such a launch: tiles in a step, and in the last one, whose planes may be fewer.
 struct StepView {
     uint32_t groups, n_steps, n_blocks, last_blocks;   // groups of 256 lanes that take tiles in turn
@@ -114,7 +123,8 @@ struct StepView {
 hipError_t launch_gather(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                          const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                          uint8_t *staging, int32_t *bad_flag, hipStream_t stream,
-                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr, const ChunkList *list = nullptr);
+                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr, const ChunkList *list = nullptr,
+                         HostWord *told = nullptr);
 hipError_t launch_scatter(const KernelGeom &g, const LaunchView &v, const LaunchShape &s,
                           const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                           const uint8_t *staging, int32_t *bad_flag, hipStream_t stream,

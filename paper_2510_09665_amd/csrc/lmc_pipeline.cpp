@@ -70,7 +70,7 @@ static lmc_status_t prepare_order_scratch(lmc_ctx *c, uint64_t n_tokens, hipStre
 lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
                           uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list, hipEvent_t stop,
-                          lmc::Arrivals *arrivals, uint32_t planes_per_step) {
+                          lmc::Arrivals *arrivals, uint32_t planes_per_step, lmc::HostWord *told) {
     // LMC_FLAG_TIMING: the launch itself carries a start and a stop event, which receive
     // the kernel's own begin / end time stamps; the stream gets no extra marker.
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -106,7 +106,7 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
     }
     hipError_t e =
         injected_failure(c) ? hipErrorUnknown
-        : gather  ? lmc::launch_gather(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, end, list)
+        : gather  ? lmc::launch_gather(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, end, list, told)
         : ordered ? lmc::launch_scatter_ordered(c->kg, view, s, ptrs, slots, uint32_t(n_tokens), c->order, staging,
                                                 c->bad_flag_dev, stream, e0, end)
                   : lmc::launch_scatter(c->kg, view, s, ptrs, slots, n_chunks, staging, c->bad_flag_dev, stream, e0, end, list,
@@ -336,11 +336,12 @@ static lmc_status_t after_stores(lmc_ctx *c, const int64_t *pool_slots, int64_t 
 // all a launch needs; where they are not they are listed, so that a fragmented pool costs one
 // launch for every kMaxListed chunks and not one for every run of slots.
 // stop (may be null): completes with the last launch.  arrivals (may be null): the word at which the
-// last launch of a scatter counts itself off; the others are over when it begins.
+// last launch of a scatter counts itself off, told (likewise) that of a gather; the others are over
+// when it begins.
 static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, uint64_t pool_off,
                                 const lmc::LayerPtrs &ptrs, const int64_t *slot_mapping, const int64_t *chunk,
                                 const int64_t *pool_slot, int64_t n, hipStream_t stream, hipEvent_t stop = nullptr,
-                                lmc::Arrivals *arrivals = nullptr) {
+                                lmc::Arrivals *arrivals = nullptr, lmc::HostWord *told = nullptr) {
     const uint64_t cb = uint64_t(c->chunk_bytes);
     const int64_t CT = c->cfg.geom.chunk_tokens;
     view.chunk_stride = cb;  // chunks lie one pool slot apart
@@ -362,7 +363,7 @@ static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, u
         lmc_status_t rc = timed_launch(c, gather, view, ptrs, slot_mapping + (chunk ? chunk[i0] : i0) * CT, uint32_t(k),
                                        c->pool_dev + (listed ? 0 : uint64_t(pool_slot[i0]) * cb) + pool_off, stream,
                                        listed ? &list : nullptr, i0 + k == n ? stop : nullptr,
-                                       i0 + k == n ? arrivals : nullptr);
+                                       i0 + k == n ? arrivals : nullptr, 0, i0 + k == n ? told : nullptr);
         if (rc != LMC_OK) return rc;
         (gather ? c->stats.bytes_d2h : c->stats.bytes_h2d) += uint64_t(k) * view.by_n_lp.d * c->kg.plane_bytes;
         if ((rc = force_sync(c, stream)) != LMC_OK) return rc;
@@ -696,12 +697,13 @@ static lmc_status_t store_groups(lmc_ctx *c, const lmc::LaunchView &view, uint64
                                  const std::vector<int64_t> &new_chunk,
                                  const std::vector<int64_t> &new_slot, int64_t cap_chunks,
                                  bool edge_group, bool direct, bool layer_step = false, bool on_second_stream = false,
-                                 std::vector<hipEvent_t> *group_events = nullptr, hipEvent_t stop = nullptr) {
+                                 std::vector<hipEvent_t> *group_events = nullptr, hipEvent_t stop = nullptr,
+                                 lmc::HostWord *told = nullptr) {
     Ring &ring = c->store_ring;
     const int64_t CT = c->cfg.geom.chunk_tokens;
     if (direct)   // no staging, no copy: the gather kernel writes the pinned pool over the link
         return move_direct(c, true, view, pool_off, ptrs, slot_mapping, new_chunk.data(), new_slot.data(),
-                           int64_t(new_chunk.size()), c->s_gather, stop);
+                           int64_t(new_chunk.size()), c->s_gather, stop, nullptr, told);
     const size_t per = size_t(cap_chunks);
     const bool two_copy_streams = !other_direction_busy(c, true);
     hipStream_t copies = on_second_stream ? c->s_d2h2 : c->s_d2h, other = on_second_stream ? c->s_d2h : c->s_d2h2;
@@ -818,9 +820,14 @@ lmc_status_t lmc_store(lmc_ctx_t *c, void *const *kv_layers, const int64_t *slot
     const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 ||
                         int64_t(new_chunk.size()) * c->chunk_bytes <= c->direct_store_below;
     rc = direct ? LMC_OK : ring_reslot(c, c->store_ring, c->store_ring.buf_bytes, c->s_gather, c->s_d2h, nullptr, c->s_d2h2);
-    if (rc == LMC_OK)
+    if (rc == LMC_OK) {
+        uint64_t &reached = c->word_target[lmc_ctx::kStoreWord];
+        lmc::HostWord told{c->words ? c->word(lmc_ctx::kStoreWord) : nullptr, c->stored_dev, reached};
+        const bool tells = direct && c->words != nullptr && !is_capturing(c->s_gather);
         rc = store_groups(c, lmc::bulk_view(c->kg), 0, ptrs, slot_mapping, new_chunk, op.slots,
-                          c->cfg.staging_chunks, true, direct, false, false, &op.owned_events);
+                          c->cfg.staging_chunks, true, direct, false, false, &op.owned_events, nullptr, tells ? &told : nullptr);
+        if (told.target != reached) op.stored_target = reached = told.target;
+    }
     if (rc == LMC_OK)
         rc = finish_op(c, std::move(op), direct ? c->s_gather : c->s_d2h, !new_chunk.empty(), ticket_out);
     if (rc != LMC_OK) {
@@ -901,8 +908,14 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     if (rc == LMC_OK) rc = get_event(c, false, &e);
     if (rc == LMC_OK) {
         op->owned_events.push_back(e);
+        // the last step of a store whose steps all ran on the gather stream ends the store
+        const bool tells = direct && first_layer + n_layers == geom.num_layers && c->words != nullptr && !is_capturing(c->s_gather) &&
+                           std::all_of(op->ends_on.begin(), op->ends_on.end(), [&](hipStream_t s) { return s == c->s_gather; });
+        uint64_t &reached = c->word_target[lmc_ctx::kStoreWord];
+        lmc::HostWord told{tells ? c->word(lmc_ctx::kStoreWord) : nullptr, c->stored_dev, reached};
         rc = store_groups(c, view, uint64_t(first_layer) * layer_bytes, ptrs, op->slot_mapping, op->new_chunk,
-                          op->slots, cap, false, direct, true, on_second, nullptr, e);
+                          op->slots, cap, false, direct, true, on_second, nullptr, e, tells ? &told : nullptr);
+        if (told.target != reached) op->stored_target = reached = told.target;
     }
     if (rc == LMC_OK) {
         rc = [&]() -> lmc_status_t {

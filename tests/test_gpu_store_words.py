@@ -1,0 +1,95 @@
+"""Stores without staging tell the host through a word of its memory that their last byte is in the
+pool.  The bytes are read where they lie as soon as the wait returns, from one thread and from
+several, for rows whose stores go through the L2 (which tell) and others (which do not), for chunks
+back to back and listed, layer by layer, and mixed with staged stores."""
+import threading
+import zlib
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_09665_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "tells_256": dict(L=3, P=2, H=1, D=128, e=2, BS=16, NB=96, CT=64),
+    "tells_packed_216": dict(L=4, P=2, H=3, D=72, e=1, BS=16, NB=96, CT=64),
+    "silent_360": dict(L=3, P=2, H=5, D=36, e=2, BS=12, NB=96, CT=84),
+    "silent_narrow": dict(L=2, P=1, H=1, D=5, e=1, BS=4, NB=90, CT=32),
+}
+
+
+@pytest.mark.parametrize("shape", list(SHAPES))
+@pytest.mark.parametrize("how", ["bulk", "listed", "layers", "mixed", "odd_groups"])
+def test_bytes_are_in_the_pool_when_the_wait_returns(shape, how):
+    import torch
+    from gpu_util import PagedKV, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(**SHAPES[shape])
+    rng = np.random.default_rng(zlib.crc32((shape + how).encode()))
+    n = 3
+    slots = rng.permutation(g.n_slots)[:n * g.CT].astype(np.int64)
+    slots[rng.integers(0, n * g.CT, 2)] = -1
+    src = PagedKV(g, np.arange(g.NB), rng)
+    want = {flip: oracle.gather(g, [h ^ flip for h in src.host], slots) for flip in (0, 255)}
+    d_slots = slots_to_device(slots)
+    ids = np.arange(1, n + 1, dtype=np.uint64)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with lmc.Context(g, 3 * n * g.chunk_bytes, staging_chunks=2) as c:
+        if how == "listed":
+            other = (1 << 40) + np.arange(2 * n, dtype=np.uint64)
+            c.put_host(other, np.zeros((2 * n, g.chunk_bytes), dtype=np.uint8))
+            c.clear(other[::2])
+        if how == "odd_groups":
+            c.tune("link_groups", 7)
+        for k in range(8):
+            for d in src.dev:
+                d.bitwise_xor_(255)
+            torch.cuda.synchronize()
+            if how == "layers":
+                t = c.store_begin(d_slots, ids, stream)
+                for l in range(g.L):
+                    c.store_layers(t, l, 1, src.dev, stream)
+            else:
+                c.tune("direct_store_below", 0 if how == "mixed" and k % 2 else 1 << 26)
+                t = c.store(src.dev, d_slots, ids, stream)
+            c.wait(t)
+            assert c.test(t)
+            flip = 255 if k % 2 == 0 else 0
+            for i in range(n):
+                chunk = c.chunk_acquire(ids[i])
+                assert np.array_equal(chunk, want[flip][i]), (k, i)
+                c.chunk_release(ids[i])
+            c.clear(ids)
+
+
+def test_threads_wait_each_for_their_own_store():
+    import torch
+    from gpu_util import PagedKV, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(**SHAPES["tells_256"])
+    rng = np.random.default_rng(5)
+    src = PagedKV(g, np.arange(g.NB), rng)
+    slots = [rng.permutation(g.n_slots)[:g.CT].astype(np.int64) for _ in range(4)]
+    want = [oracle.gather(g, src.host, s)[0] for s in slots]
+    d_slots = [slots_to_device(s) for s in slots]
+    torch.cuda.synchronize()
+    wrong = []
+    with lmc.Context(g, 8 * g.chunk_bytes, staging_chunks=2) as c:
+        def work(i):
+            ids = np.array([100 + i], dtype=np.uint64)
+            for k in range(60):
+                c.wait(c.store(src.dev, d_slots[i], ids))
+                if not np.array_equal(c.chunk_acquire(ids[0]), want[i]):
+                    wrong.append((i, k))
+                c.chunk_release(ids[0])
+                c.clear(ids)
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    assert not wrong, wrong

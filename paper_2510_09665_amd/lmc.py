@@ -1,5 +1,6 @@
-"""ctypes binding of liblmc (include/lmc.h).  Argument marshalling only: every step of
-the store / retrieve path runs inside the library.
+"""Binding of liblmc (include/lmc.h).  Argument marshalling only: every step of
+the store / retrieve path runs inside the library.  The calls an engine makes for every request
+or layer go through a small extension module (csrc/lmc_py.cpp), the others through ctypes.
 
 Device buffers are passed as objects with a ``data_ptr()`` method (torch tensors) or as
 integer addresses; streams as objects with a ``cuda_stream`` attribute (torch streams;
@@ -85,10 +86,15 @@ class LMCError(RuntimeError):
 
 
 _LIB = None
+_native = None      # the extension module, once _lib() has bound it to the library
+
+
+def _failed(status, what, ticket, ctx):
+    raise LMCError(status, what, ticket, _lib().lmc_last_hip_error(ctx))
 
 
 def _lib():
-    global _LIB
+    global _LIB, _native
     if _LIB is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError("liblmc.so is not built: run `python -m paper_2510_09665_amd.build` "
@@ -172,7 +178,14 @@ def _lib():
         for name, (res, args) in sig.items():
             f = getattr(lib, name)
             f.restype, f.argtypes = res, args
+        try:
+            from . import _lmc_native
+        except ImportError as e:
+            raise ImportError("_lmc_native.so is not built: run `python -m paper_2510_09665_amd.build`; "
+                              "there is no fallback path") from e
         _LIB = lib
+        _lmc_native.bind(LIB_PATH, _failed)
+        _native = _lmc_native
     return _LIB
 
 
@@ -207,7 +220,7 @@ class Context:
                  hash_seed=0):
         """staging_chunks=16 is the measured sweet spot on MI355X (one launch then covers a
         4096-token request); it costs 2 * num_staging * staging_chunks chunks of HBM."""
-        self._h = None
+        self._h, self._p = None, 0
         g = geom if isinstance(geom, lmc_kv_geom_t) else make_geom(geom)
         cfg = lmc_config_t(g, host_pool_bytes, num_staging, staging_chunks, device, flags,
                            hash_seed)
@@ -215,15 +228,16 @@ class Context:
         rc = _lib().lmc_create(ctypes.byref(cfg), ctypes.byref(h))
         if rc != LMC_OK:
             raise LMCError(rc, "lmc_create")
-        self._h = h
+        self._h, self._p = h, h.value
         self.chunk_tokens = g.chunk_tokens
         self.num_layers = g.num_layers
+        self._chunk_bytes = self.chunk_bytes()
 
     # -- lifetime ---------------------------------------------------------------
     def destroy(self):
         if self._h is not None:
             _lib().lmc_destroy(self._h)
-            self._h = None
+            self._h, self._p = None, 0
 
     def __del__(self):
         try:
@@ -256,12 +270,7 @@ class Context:
 
     # -- token processor / index --------------------------------------------------
     def hash_chunks(self, tokens):
-        tok, tp = _host(tokens, np.int32)
-        out = np.empty(tok.size // self.chunk_tokens, dtype=np.uint64)
-        n = ctypes.c_int64()
-        self._check(_lib().lmc_hash_chunks(self._h, tp, tok.size, ctypes.c_void_p(out.ctypes.data),
-                                           ctypes.byref(n)), "lmc_hash_chunks")
-        return out[:n.value]
+        return _native.hash_chunks(self._p, tokens, self.chunk_tokens)
 
     def hash_chunks_from(self, prev_id, tokens):
         tok, tp = _host(tokens, np.int32)
@@ -276,85 +285,46 @@ class Context:
         return Sequence(self, prompt_tokens, prompt_slots)
 
     def lookup(self, chunk_ids):
-        ids, ip = _host(chunk_ids, np.uint64)
-        n = ctypes.c_int64()
-        self._check(_lib().lmc_lookup(self._h, ip, ids.size, ctypes.byref(n)), "lmc_lookup")
-        return n.value
+        return _native.lookup(self._p, chunk_ids)
 
     # -- the path -----------------------------------------------------------------
     def store(self, kv_layers, slot_mapping, chunk_ids, stream_to_wait_on=None):
         """Enqueue; returns the ticket.  On LMC_ERR_NOMEM the error carries the ticket."""
-        ids, ip = _host(chunk_ids, np.uint64)
-        t = ctypes.c_uint64()
-        rc = _lib().lmc_store(self._h, self._layers(kv_layers), _dev(slot_mapping), ip, ids.size,
-                              _stream(stream_to_wait_on), ctypes.byref(t))
-        self._check(rc, "lmc_store", t.value)
-        return t.value
+        return _native.store(self._p, self.num_layers, kv_layers, slot_mapping, chunk_ids, stream_to_wait_on)
 
     def retrieve(self, chunk_ids, slot_mapping, kv_layers, stream_to_signal=None):
-        ids, ip = _host(chunk_ids, np.uint64)
-        t = ctypes.c_uint64()
-        rc = _lib().lmc_retrieve(self._h, ip, ids.size, _dev(slot_mapping), self._layers(kv_layers),
-                                 _stream(stream_to_signal), ctypes.byref(t))
-        self._check(rc, "lmc_retrieve", t.value)
-        return t.value
+        return _native.retrieve(self._p, self.num_layers, chunk_ids, slot_mapping, kv_layers, stream_to_signal)
 
     def retrieve_batch(self, req_chunk_offsets, chunk_ids, slot_mapping, kv_layers,
                        stream_to_signal=None):
-        off, op = _host(req_chunk_offsets, np.int64)
-        ids, ip = _host(chunk_ids, np.uint64)
-        t = ctypes.c_uint64()
-        rc = _lib().lmc_retrieve_batch(self._h, off.size - 1, op, ip, _dev(slot_mapping),
-                                       self._layers(kv_layers), _stream(stream_to_signal),
-                                       ctypes.byref(t))
-        self._check(rc, "lmc_retrieve_batch", t.value)
-        return t.value
+        return _native.retrieve_batch(self._p, self.num_layers, req_chunk_offsets, chunk_ids, slot_mapping, kv_layers,
+                                      stream_to_signal)
 
     def retrieve_layerwise(self, chunk_ids, slot_mapping, kv_layers, layers_per_step=1,
                            stream_to_wait_on=None):
-        ids, ip = _host(chunk_ids, np.uint64)
-        t = ctypes.c_uint64()
-        rc = _lib().lmc_retrieve_layerwise(self._h, ip, ids.size, _dev(slot_mapping),
-                                           self._layers(kv_layers), layers_per_step,
-                                           _stream(stream_to_wait_on), ctypes.byref(t))
-        self._check(rc, "lmc_retrieve_layerwise", t.value)
-        return t.value
+        return _native.retrieve_layerwise(self._p, self.num_layers, chunk_ids, slot_mapping, kv_layers, layers_per_step,
+                                          stream_to_wait_on)
 
     def store_begin(self, slot_mapping, chunk_ids, stream_to_wait_on=None):
-        ids, ip = _host(chunk_ids, np.uint64)
-        t = ctypes.c_uint64()
-        rc = _lib().lmc_store_begin(self._h, _dev(slot_mapping), ip, ids.size,
-                                    _stream(stream_to_wait_on), ctypes.byref(t))
-        self._check(rc, "lmc_store_begin", t.value)
-        return t.value
+        return _native.store_begin(self._p, slot_mapping, chunk_ids, stream_to_wait_on)
 
     def store_layers(self, ticket, first_layer, n_layers, kv_layers, stream_to_wait_on=None):
-        self._check(_lib().lmc_store_layers(self._h, ticket, first_layer, n_layers,
-                                            self._layers(kv_layers), _stream(stream_to_wait_on)),
-                    "lmc_store_layers")
+        _native.store_layers(self._p, self.num_layers, ticket, first_layer, n_layers, kv_layers, stream_to_wait_on)
 
     def wait_layer(self, ticket, layer, stream=None):
-        self._check(_lib().lmc_wait_layer(self._h, ticket, layer, _stream(stream)), "lmc_wait_layer")
+        _native.wait_layer(self._p, ticket, layer, stream)
 
     def test(self, ticket):
         """True if the ticket's work has finished (never blocks)."""
-        rc = _lib().lmc_test(self._h, ticket)
-        if rc == LMC_ERR_BUSY:
-            return False
-        self._check(rc, "lmc_test")
-        return True
+        return _native.test(self._p, ticket)
 
     def chunk_acquire(self, chunk_id):
         """Raises the chunk's reference counter; returns a read-only numpy view of its
         bytes in the pinned pool, valid until chunk_release."""
-        p = ctypes.c_void_p()
-        self._check(_lib().lmc_chunk_acquire(self._h, int(chunk_id), ctypes.byref(p)), "lmc_chunk_acquire")
-        a = np.ctypeslib.as_array(ctypes.cast(p, ctypes.POINTER(ctypes.c_uint8)), shape=(self.chunk_bytes(),))
-        a.flags.writeable = False
-        return a
+        return _native.chunk_acquire(self._p, chunk_id, self._chunk_bytes)
 
     def chunk_release(self, chunk_id):
-        self._check(_lib().lmc_chunk_release(self._h, int(chunk_id)), "lmc_chunk_release")
+        _native.chunk_release(self._p, chunk_id)
 
     def tier_open(self, dirs, n_threads=2):
         return Tier(self, dirs, n_threads)
@@ -363,15 +333,13 @@ class Context:
         return Window(self, window_pages, max_batch_pages)
 
     def wait(self, ticket=0):
-        self._check(_lib().lmc_wait(self._h, ticket), "lmc_wait")
+        _native.wait(self._p, ticket)
 
     def gather(self, kv_layers, slot_mapping, n_chunks, staging_dev, stream=None):
-        self._check(_lib().lmc_gather(self._h, self._layers(kv_layers), _dev(slot_mapping), n_chunks,
-                                      _dev(staging_dev), _stream(stream)), "lmc_gather")
+        _native.gather(self._p, self.num_layers, kv_layers, slot_mapping, n_chunks, staging_dev, stream)
 
     def scatter(self, staging_dev, slot_mapping, n_chunks, kv_layers, stream=None):
-        self._check(_lib().lmc_scatter(self._h, _dev(staging_dev), _dev(slot_mapping), n_chunks,
-                                       self._layers(kv_layers), _stream(stream)), "lmc_scatter")
+        _native.scatter(self._p, self.num_layers, staging_dev, slot_mapping, n_chunks, kv_layers, stream)
 
     def store_static(self, kv_layers, slot_mapping, n_chunks, host_dst, stream=None):
         """host_dst: a pinned uint8 tensor (or address) of n_chunks * chunk_bytes."""
@@ -418,8 +386,7 @@ class Context:
                 return np.concatenate(parts)
 
     def clear(self, chunk_ids):
-        ids, ip = _host(chunk_ids, np.uint64)
-        self._check(_lib().lmc_clear(self._h, ip, ids.size), "lmc_clear")
+        _native.clear(self._p, chunk_ids)
 
     # -- stats, measurement, tuning ---------------------------------------------------
     def get_stats(self):

@@ -812,11 +812,13 @@ hipError_t launch_gather_paced(const KernelGeom &g, const LaunchView &v, const L
                                hipEvent_t stop, const ChunkList *list, HostWord *told) {
     const uint32_t n_blocks = n_chunks * v.by_n_lp.d * g.by_tiles_per_plane.d;
     if (n_blocks == 0) return hipSuccess;
-    // through the L2 where every wavefront writes whole lines of 128 bytes: 16-byte lanes, and
-    // planes that begin on a line
+    // through the L2 where lanes write 16 bytes at multiples of 16.  Planes that begin inside a line of
+    // 128 bytes leave a wavefront's first and last line to two wavefronts, which costs the link less
+    // than non-temporal stores do: 5.9 and 29 MiB in 360-byte rows (planes of 90720 bytes) 136 and
+    // 597 us so, 124 and 582 through; 8 MiB in 208-byte rows, planes of 7488 bytes, 179 and 167.
     constexpr bool kLines = VEC == 16 || VEC == kPacked;
     const bool through = kLines && s.nt_load && s.nt_store &&
-                         ((uint64_t(reinterpret_cast<uintptr_t>(pool)) | v.chunk_stride | g.plane_bytes) % 128) == 0;
+                         ((uint64_t(reinterpret_cast<uintptr_t>(pool)) | v.chunk_stride | g.plane_bytes) % 16) == 0;
     constexpr int kThrough = kLines ? kStoreThrough : kStoreNonTemporal;   // nothing else is instantiated
     // blk + step must not wrap: n_blocks < 2^24 (max_chunks_per_launch) and the grid is small
     // The rate does not grow steadily with the groups: 8, 32 and 64 MiB by 32, 48, 64, 96, 128 of them

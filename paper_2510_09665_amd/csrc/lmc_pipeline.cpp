@@ -573,9 +573,11 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
         if ((r = trace_end(c, copy_stream, traced, LMC_STAGE_H2D, k, uint64_t(k) * view.by_n_lp.d * c->kg.plane_bytes)) != LMC_OK)
             return r;
         HIPCHK(c, hipEventRecord(ring.filled[b], copy_stream));
-        // the steps of a layer-wise retrieve are short, and take two copy streams in turn
+        // the steps of a layer-wise retrieve are short, and take two copy streams in turn; the copies of
+        // scattered chunks, two at a time, lose more to the write at the end of a group than to the poll
+        // (20 x 8.6 MiB 3306 us without it, 3314 with it)
         uint64_t filled_at = 0;
-        if (!op.layerwise && (r = hand_over(c, copy_stream, lmc_ctx::kFilledWord, &filled_at)) != LMC_OK) return r;
+        if (!op.layerwise && !used_second && (r = hand_over(c, copy_stream, lmc_ctx::kFilledWord, &filled_at)) != LMC_OK) return r;
         if ((r = force_sync(c, copy_stream)) != LMC_OK) return r;
         if ((r = wait_quietly(c, c->s_scatter, lmc_ctx::kFilledWord, filled_at, ring.filled[b])) != LMC_OK) return r;
         r = timed_launch(c, false, view, ptrs, slot_mapping + i0 * CT, uint32_t(k), buf, c->s_scatter);

@@ -93,3 +93,48 @@ def test_threads_wait_each_for_their_own_store():
         for t in threads:
             t.join()
     assert not wrong, wrong
+
+
+@pytest.mark.parametrize("groups", [1, 7, 64])
+@pytest.mark.parametrize("scattered", [False, True])
+def test_copy_kernels_two_groups_to_a_workgroup(groups, scattered):
+    """Staged transfers whose copies the library's kernels make, rectangles and scattered pieces, bulk
+    and layer by layer, with every number of groups: an odd one leaves half a workgroup without work."""
+    from gpu_util import PagedKV, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(L=3, P=2, H=2, D=72, e=2, BS=16, NB=64, CT=80)
+    rng = np.random.default_rng(groups)
+    n = 5
+    slots, tau = (rng.permutation(g.n_slots)[:n * g.CT].astype(np.int64) for _ in range(2))
+    src, dst = PagedKV(g, np.arange(g.NB), rng), PagedKV(g, np.arange(g.NB), fill="sentinel")
+    want = oracle.gather(g, src.host, slots)
+    moved = [np.zeros(g.layer_bytes, dtype=np.uint8) for _ in range(g.L)]
+    oracle.scatter(g, want, tau, moved)
+    d_slots, d_tau = slots_to_device(slots), slots_to_device(tau)
+    ids = np.arange(1, n + 1, dtype=np.uint64)
+    with lmc.Context(g, 3 * n * g.chunk_bytes, staging_chunks=2) as c:
+        for key, value in (("direct_store_below", 0), ("direct_retrieve_below", 0), ("copy_kernel", 3), ("link_groups", groups)):
+            c.tune(key, value)
+        if scattered:
+            other = (1 << 40) + np.arange(2 * n, dtype=np.uint64)
+            c.put_host(other, np.zeros((2 * n, g.chunk_bytes), dtype=np.uint8))
+            c.clear(other[::2])
+        for layers in (False, True):
+            if layers:
+                t = c.store_begin(d_slots, ids)
+                for l in range(g.L):
+                    c.store_layers(t, l, 1, src.dev)
+            else:
+                t = c.store(src.dev, d_slots, ids)
+            c.wait(t)
+            for i in range(n):
+                assert np.array_equal(c.get_host(ids[i]), want[i]), (layers, i)
+            for d in dst.dev:
+                d.zero_()
+            if layers:
+                c.wait(c.retrieve_layerwise(ids, d_tau, dst.dev, 2))
+            else:
+                c.wait(c.retrieve(ids, d_tau, dst.dev))
+            for l, d in enumerate(dst.dev):
+                assert np.array_equal(d.cpu().numpy(), moved[l]), (layers, l)
+            c.clear(ids)

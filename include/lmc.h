@@ -569,12 +569,12 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * 64: launches that read or write the pinned pool themselves run as three quarters of that many
  * groups of 256 lanes taking tiles in turn (as many, or twice as many, where rows are no
  * multiples of 16 bytes), which is what the host link likes, two groups to a workgroup, which keeps
- * its compute unit to itself; 0 = one tile per workgroup as for launches inside HBM),
+ * its compute unit to itself and starts on one whose LDS no other kernel holds; 0 = one tile per workgroup as for launches inside HBM),
  * "copy_kernel" (default 0; bit 0: copies from staging to the
  * pool are made by the library's own link-paced copy kernel instead of hipMemcpyAsync;
  * bit 1: copies from the pool to staging too.  At the rate of the runtime's copies and
  * independent of which engine the runtime picks and of what else that engine is doing, but
- * dense products beside such a kernel take some 40 % longer while it lasts),
+ * a product that fills every compute unit once takes 1.4 to 1.7 times as long beside it),
  * "d2h_guard" (default 1: the library times the runtime's copies to the host of 32 MiB
  * and more, one per group, and when two of the last four fell below six tenths of the
  * best rate it has seen it makes these copies with its own kernel for 0.25 s, then tries

@@ -90,8 +90,8 @@ struct lmc_ctx {
     uint32_t link_groups = 64;  // groups of 256 lanes of a launch whose other side is the pinned pool; 0 = as for HBM
     // Which copies between staging and the pool the library's own link-paced copy kernel
     // makes instead of hipMemcpyAsync: bit 0 = to the host, bit 1 = from the host.  Off
-    // by default: the runtime's copies leave the compute units to the engine (dense products
-    // beside the kernel take some 40 % longer).  But for some seconds after tens
+    // by default: the runtime's copies leave the compute units to the engine (a product that
+    // fills every compute unit once takes 1.4 to 1.7 times as long beside the kernel).  But for some seconds after tens
     // of GiB of device or pinned memory have been freed or allocated in the process, the
     // runtime's device-to-host copies inside a store ran at 31.5 GB/s instead of 57 on
     // the machine this was measured on (not with HSA_ENABLE_SDMA=0, which points at the

@@ -67,8 +67,8 @@ template <typename V, bool NT> __device__ __forceinline__ void store_vec(uint64_
 // runtime's own copies: 56.9).  Lines written in parts suffer, since nothing puts them together
 // any more (a gather of 216-byte rows inside HBM: 53.8 us instead of 45.7).  Inside HBM a linear
 // copy gains 3 % (6.76 against 6.48 TB/s), a gather of 512 MiB in random 32 KiB pages 0.4 %, one
-// of 32 MiB loses 2 % (11.1 against 10.9 us) and the scatter does not care: gathers and scatters
-// keep the hint there.
+// of 32 MiB loses 2 % (11.1 against 10.9 us) and the scatter does not care while it is alone: gathers
+// and all but the largest scatters keep the hint there.
 enum StoreKind { kStorePlain = 0, kStoreNonTemporal = 1, kStoreThrough = 2 };
 // s_nop 1: gfx950 wants two wait states between a store of more than 64 bits and an instruction
 // that writes its data registers again, and the compiler, which does not see the store, adds none.
@@ -261,7 +261,7 @@ __device__ __forceinline__ void move_tile(const TileArgs &a, const LayerPtrs &la
         if (!valid) v = V(0);
         store_out<VEC, ST>(st, v);
     } else if (valid) {
-        store_vec<V, ST != kStorePlain>(page, load_vec<V, NT_LD>(st));
+        store_out<VEC, ST>(page, load_vec<V, NT_LD>(st));
     }
 }
 
@@ -802,6 +802,23 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
         if (g.by_vec_per_run.d % 64 == 0 && s.nt_load && s.nt_store && reinterpret_cast<uintptr_t>(slot_mapping) % 8 == 0) {
             hipExtLaunchKernelGGL(gather_rows_by_wave, grid, block, 0, stream, start, stop, 0, g, v, layers, slot_mapping,
                                   staging, bad_flag, permuted, shift);
+            return hipGetLastError();
+        }
+    // Large scatters write at system scope and in the plain order of the tiles: launches of several
+    // streams that run into each other, each sweeping its own buffer and its own random pages, lose less
+    // to one another then.  On three streams in turn, non-temporal with runs of 32 and so: Llama-3-8B shape
+    // 512 and 192 MiB 194.4, 188.4 and 72.8, 71.8 us, 70B 480 MiB 183.6, 178.0, 256 MiB in 256-byte
+    // rows 105.0, 100.3, MLA bf16 90.2, 87.0, one-token pages 102.2, 99.7; on one stream 182.5, 182.9;
+    // 70.1, 70.3; 175.0, 175.5; 99.2, 99.9; 86.7, 85.9; 98.4, 99.2.  160 MiB are 1 % slower so, less is
+    // the same either way, and where a wavefront writes lines in parts (pages by head: 92.6, 99.6 on one
+    // stream) it loses.
+    constexpr uint32_t kLargeScatter = 49152;       // tiles of 4 KiB: 192 MiB
+    const bool whole_lines = g.runs_per_row == 1 && (g.row_bytes % 128 == 0 ||
+                                                     (g.token_stride == int64_t(g.row_bytes) && g.by_block_size.d > 1));
+    if constexpr (!GATHER && VEC == 16)
+        if (n_blocks >= kLargeScatter && whole_lines && s.nt_load && s.nt_store) {
+            hipExtLaunchKernelGGL((move_rows<VEC, GATHER, true, kStoreThrough>), grid, block, 0, stream, start, stop, 0, g, v,
+                                  layers, slot_mapping, staging, bad_flag, 0u, 0u);
             return hipGetLastError();
         }
 #define LMC_GO(LD, ST)                                                                          \

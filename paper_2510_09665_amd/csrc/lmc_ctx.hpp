@@ -33,7 +33,6 @@ struct Ring {
     uint32_t slots_per_buf = 1;
     std::vector<hipEvent_t> filled, drained;
     std::vector<char> used;
-    std::vector<uint64_t> drained_at;   // per slot: value of kDrainedWord that follows its `drained`, 0 = none does
     uint64_t pos = 0;
 };
 
@@ -169,10 +168,10 @@ struct lmc_ctx {
     // kStoreWord is for bulk stores without staging, whose kernels pass its value on to
     // *stored_host: a thread that waits for such a store sees it there 5 us before the event
     // behind the kernel completes.
-    // kFilledWord, kDrainedWord and kDoneWord are written by the streams themselves (hand_over) as groups
-    // of bulk transfers through staging reach the staging buffer or leave it, and as retrieves end.
+    // kFilledWord and kDoneWord are written by the streams themselves (hand_over) as groups of a bulk
+    // retrieve reach the staging buffer, and as it ends.
     static constexpr int kBulkWord = LMC_MAX_LAYERS, kStoreWord = LMC_MAX_LAYERS + 1, kFilledWord = LMC_MAX_LAYERS + 2,
-                         kDrainedWord = LMC_MAX_LAYERS + 3, kDoneWord = LMC_MAX_LAYERS + 4, kWords = LMC_MAX_LAYERS + 5;
+                         kDoneWord = LMC_MAX_LAYERS + 3, kWords = LMC_MAX_LAYERS + 4;
     uint64_t *stored_host = nullptr, *stored_dev = nullptr;   // one word of host memory and its address on the GPU
     bool is_stored(uint64_t target) const { return target != 0 && __atomic_load_n(stored_host, __ATOMIC_ACQUIRE) >= target; }
     uint64_t *words = nullptr;

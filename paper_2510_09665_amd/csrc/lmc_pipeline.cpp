@@ -288,7 +288,6 @@ static lmc_status_t ring_reslot(lmc_ctx *c, Ring &r, uint64_t slot_bytes, hipStr
     r.slot_bytes = slot_bytes;
     r.slots_per_buf = per_buf;
     r.used.assign(total, 0);
-    r.drained_at.assign(total, 0);
     r.pos = 0;
     return LMC_OK;
 }
@@ -401,7 +400,8 @@ static lmc_status_t wait_for_word(lmc_ctx *c, hipStream_t stream, int word, uint
 // 56.9, 56.55, 56.25 with one, two, three streams).  So the stream that is waited for writes a word in
 // device memory behind its event, and the other waits for the word first, polling that, and then for
 // the event, which has completed by then: the event is what orders the two, the word only keeps the
-// queue quiet.  A word belongs to one stream, whose writes are in order.
+// queue quiet.  A word belongs to one stream, whose writes are in order.  Only retrieves use this: a
+// store's gathers that wait for their buffers gain 0.1 % by it.
 // hand_over: `stream` writes the word's next value, *at, or 0 where it cannot (capture).
 static lmc_status_t hand_over(lmc_ctx *c, hipStream_t stream, int word, uint64_t *at) {
     *at = 0;
@@ -543,6 +543,11 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
         return move_direct(c, false, view, pool_off, ptrs, slot_mapping, nullptr, pool_slots.data(), n_chunks, scatters, stop,
                            arrivals);
     };
+    // Long waits are quiet (hand_over) in bulk retrieves that have the link to themselves: the steps of a
+    // layer-wise one are short, and take two copy streams in turn, and beside a store the write between
+    // two copies costs more than the poll (5 GiB each way 96 GB/s in all with it, 99.9 without).
+    const bool two_copy_streams = !other_direction_busy(c, false);
+    const bool quiet = !op.layerwise && two_copy_streams;
     bool by_word = false;   // the whole transfer is in place when the bulk word has reached its target
     // one group: copies into the next ring buffer on the H2D stream, scatter on the
     // scatter stream; the buffer is released when the scatter has read it
@@ -573,11 +578,10 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
         if ((r = trace_end(c, copy_stream, traced, LMC_STAGE_H2D, k, uint64_t(k) * view.by_n_lp.d * c->kg.plane_bytes)) != LMC_OK)
             return r;
         HIPCHK(c, hipEventRecord(ring.filled[b], copy_stream));
-        // the steps of a layer-wise retrieve are short, and take two copy streams in turn; the copies of
-        // scattered chunks, two at a time, lose more to the write at the end of a group than to the poll
-        // (20 x 8.6 MiB 3306 us without it, 3314 with it)
+        // the copies of scattered chunks, two at a time, lose more to the write at the end of a group
+        // than to the poll (20 x 8.6 MiB 3306 us without it, 3314 with it)
         uint64_t filled_at = 0;
-        if (!op.layerwise && !used_second && (r = hand_over(c, copy_stream, lmc_ctx::kFilledWord, &filled_at)) != LMC_OK) return r;
+        if (quiet && !used_second && (r = hand_over(c, copy_stream, lmc_ctx::kFilledWord, &filled_at)) != LMC_OK) return r;
         if ((r = force_sync(c, copy_stream)) != LMC_OK) return r;
         if ((r = wait_quietly(c, c->s_scatter, lmc_ctx::kFilledWord, filled_at, ring.filled[b])) != LMC_OK) return r;
         r = timed_launch(c, false, view, ptrs, slot_mapping + i0 * CT, uint32_t(k), buf, c->s_scatter);
@@ -589,7 +593,6 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
         return force_sync(c, c->s_scatter);
     };
 
-    const bool two_copy_streams = !other_direction_busy(c, false);
     auto enqueue = [&]() -> lmc_status_t {
         if (direct && !op.layerwise) {
             lmc::Arrivals arrivals{nullptr, 0};
@@ -677,7 +680,7 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
         if (by_word && may_wait_for_word(c, user))
             return wait_for_word(c, user, lmc_ctx::kBulkWord, c->word_target[lmc_ctx::kBulkWord]);
         uint64_t done_at = 0;
-        if ((rc = hand_over(c, c->s_scatter, lmc_ctx::kDoneWord, &done_at)) != LMC_OK) return rc;
+        if (quiet && (rc = hand_over(c, c->s_scatter, lmc_ctx::kDoneWord, &done_at)) != LMC_OK) return rc;
         return wait_quietly(c, user, lmc_ctx::kDoneWord, done_at, c->ops.back().done);
     }
     return LMC_OK;
@@ -749,10 +752,8 @@ static lmc_status_t store_groups(lmc_ctx *c, const lmc::LaunchView &view, uint64
         while (k < cap && j0 + k < new_chunk.size() && new_chunk[j0 + k] == new_chunk[j0] + int64_t(k)) k++;
         uint8_t *buf;
         const size_t b = ring_next(ring, &buf);
-        lmc_status_t rc = LMC_OK;
-        if (ring.used[b] && (rc = wait_quietly(c, c->s_gather, lmc_ctx::kDrainedWord, ring.drained_at[b], ring.drained[b])) != LMC_OK)
-            return rc;
-        rc = timed_launch(c, true, view, ptrs, slot_mapping + new_chunk[j0] * CT, uint32_t(k),
+        if (ring.used[b]) HIPCHK(c, hipStreamWaitEvent(c->s_gather, ring.drained[b], 0));
+        lmc_status_t rc = timed_launch(c, true, view, ptrs, slot_mapping + new_chunk[j0] * CT, uint32_t(k),
                                        buf, c->s_gather);
         if (rc != LMC_OK) return rc;
         HIPCHK(c, hipEventRecord(ring.filled[b], c->s_gather));
@@ -779,8 +780,6 @@ static lmc_status_t store_groups(lmc_ctx *c, const lmc::LaunchView &view, uint64
             HIPCHK(c, lmc::launch_fill(buf, 0xA5, uint64_t(k) * view.chunk_stride, copies));
         HIPCHK(c, hipEventRecord(ring.drained[b], copies));
         ring.used[b] = 1;
-        ring.drained_at[b] = 0;
-        if (!layer_step && (rc = hand_over(c, copies, lmc_ctx::kDrainedWord, &ring.drained_at[b])) != LMC_OK) return rc;
         if (group_events != nullptr) {
             // "these chunks are in the pool": an event of the group's own (drained[b] is recorded
             // again whenever the buffer comes round), kept by the store until it is reaped

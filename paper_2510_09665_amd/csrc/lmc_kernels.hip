@@ -721,8 +721,8 @@ __global__ __launch_bounds__(kThreads) void copy_tiles(u32x4 *dst, const uint32_
 // gather_paced: a fixed, small grid whose workgroups take 4 KiB tiles in turn.  The
 // bytes form `rows` rows of width_vec 16-byte vectors, src_pitch / dst_pitch bytes apart
 // (one row per chunk; pitch == width gives a plain copy).
-// By 48 groups that keep their compute units to themselves 57.5 GB/s from the host and 57.0 to it
-// (64 that do not: 57.5, 57.1); a product of 128 rows by 4096 x 4096 beside scattered pieces coming up
+// By 48 groups that keep their compute units to themselves 57.5 GB/s from the host and 57.0 to it, by
+// 64 57.1 to it (64 that do not: 57.5, 57.1): rectangles to the host go by all the groups; a product of 128 rows by 4096 x 4096 beside scattered pieces coming up
 // takes 58 us instead of 87 (32 alone).
 template <bool TO_POOL>
 __global__ __launch_bounds__(kPacedThreads) void copy_rect_paced(uint8_t *__restrict__ dst, uint64_t dst_pitch,
@@ -1142,7 +1142,7 @@ hipError_t launch_copy_rect(uint8_t *dst, uint64_t dst_pitch, const uint8_t *src
     const uint64_t rows_per_launch = std::max<uint64_t>(1, uint64_t(0x00FFFFFFu) / tiles_per_row);
     for (uint64_t r0 = 0; r0 < rows; r0 += rows_per_launch) {
         const uint64_t n = std::min(rows - r0, rows_per_launch);
-        const uint32_t n_tiles = uint32_t(n * tiles_per_row), used = std::min(n_tiles, paced_part(groups));
+        const uint32_t n_tiles = uint32_t(n * tiles_per_row), used = std::min(n_tiles, to_pool ? groups : paced_part(groups));
         hipLaunchKernelGGL(to_pool ? copy_rect_paced<true> : copy_rect_paced<false>, dim3((used + 1) / 2),
                            dim3(kPacedThreads), 0, stream, dst + r0 * dst_pitch, dst_pitch, src + r0 * src_pitch, src_pitch,
                            width_vec, make_fastdiv(uint32_t(tiles_per_row)), n_tiles, used);

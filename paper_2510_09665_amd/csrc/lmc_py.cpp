@@ -159,11 +159,12 @@ struct Layers {
             PyErr_Format(PyExc_ValueError, "expected %zd layer pointers", want);
             return false;
         }
-        PyObject *seq = PySequence_Fast(x, "kv_layers must be a sequence");
+        // a tuple of its own: data_ptr() may run Python code that changes the caller's list meanwhile
+        PyObject *seq = PySequence_Tuple(x);
         if (seq == nullptr) return false;
-        bool ok = PySequence_Fast_GET_SIZE(seq) == n;
+        bool ok = PyTuple_GET_SIZE(seq) == n;
         if (!ok) PyErr_Format(PyExc_ValueError, "expected %zd layer pointers", want);
-        for (Py_ssize_t i = 0; ok && i < n; i++) ok = device(PySequence_Fast_GET_ITEM(seq, i), &p[i], false);
+        for (Py_ssize_t i = 0; ok && i < n; i++) ok = device(PyTuple_GET_ITEM(seq, i), &p[i], false);
         Py_DECREF(seq);
         return ok;
     }

@@ -136,6 +136,23 @@ def test_layer_tables_that_are_wrong():
         assert e.value.status == lmc.LMC_ERR_INVAL
 
 
+def test_a_list_that_changes_while_it_is_read():
+    """data_ptr() is Python code and may empty the very list that is being read: the layers are those of
+    the moment of the call."""
+    class Emptying(Tensor):
+        def data_ptr(self):
+            layers.clear()
+            self.filler = [bytearray(64) for _ in range(1000)]     # memory of what was freed is in use again
+            return self.address
+    with _ctx() as c:
+        for call in (lambda: c.store(layers, 64, [1]), lambda: c.retrieve([1], 64, layers),
+                     lambda: c.store_layers(1, 0, 1, layers), lambda: c.gather(layers, 64, 1, 64)):
+            layers = [Emptying(4096), Tensor(8192), Tensor(12288)]
+            with pytest.raises(lmc.LMCError) as e:
+                call()
+            assert e.value.status == lmc.LMC_ERR_NODEVICE and layers == []
+
+
 def test_a_destroyed_context_is_refused():
     c = _ctx()
     c.destroy()

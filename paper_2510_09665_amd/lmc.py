@@ -180,12 +180,11 @@ def _lib():
             f.restype, f.argtypes = res, args
         try:
             from . import _lmc_native
+            _lmc_native.bind(LIB_PATH, _failed)
         except ImportError as e:
-            raise ImportError("_lmc_native.so is not built: run `python -m paper_2510_09665_amd.build`; "
-                              "there is no fallback path") from e
-        _LIB = lib
-        _lmc_native.bind(LIB_PATH, _failed)
-        _native = _lmc_native
+            raise ImportError("_lmc_native.so is not built, or not for this liblmc.so: run "
+                              "`python -m paper_2510_09665_amd.build`; there is no fallback path") from e
+        _native, _LIB = _lmc_native, lib      # only now: a failure is met again by the next call
     return _LIB
 
 

@@ -153,6 +153,25 @@ def test_a_list_that_changes_while_it_is_read():
             assert e.value.status == lmc.LMC_ERR_NODEVICE and layers == []
 
 
+def test_an_extension_that_does_not_bind_is_refused_every_time(monkeypatch):
+    import paper_2510_09665_amd
+    lmc._lib()
+
+    class Other:
+        @staticmethod
+        def bind(path, failed):
+            raise ImportError("liblmc.so has no lmc_store")
+    with monkeypatch.context() as m:
+        m.setattr(lmc, "_LIB", None)
+        m.setattr(lmc, "_native", None)
+        m.setattr(paper_2510_09665_amd, "_lmc_native", Other)
+        for _ in range(2):
+            with pytest.raises(ImportError, match="paper_2510_09665_amd.build"):
+                _ctx()
+    with _ctx() as c:
+        assert c.lookup([1]) == 0
+
+
 def test_a_destroyed_context_is_refused():
     c = _ctx()
     c.destroy()

@@ -389,6 +389,13 @@ static bool may_wait_for_word(const lmc_ctx *c, hipStream_t stream) {
     return ok;
 }
 
+// Does a store without staging tell the host through a word that it has ended?  Not where its launches
+// are timed or traced: the word is there 5 us before a launch's stop event, and what a thread has waited
+// for is to be in the statistics and the trace.
+static bool tells_host(const lmc_ctx *c) {
+    return c->words != nullptr && (c->cfg.flags & (LMC_FLAG_TIMING | LMC_FLAG_TRACE)) == 0 && !is_capturing(c->s_gather);
+}
+
 static lmc_status_t wait_for_word(lmc_ctx *c, hipStream_t stream, int word, uint64_t target) {
     HIPCHK(c, hipStreamWaitValue64(stream, c->word(word), target, hipStreamWaitValueGte, ~uint64_t(0)));
     return LMC_OK;
@@ -858,7 +865,7 @@ lmc_status_t lmc_store(lmc_ctx_t *c, void *const *kv_layers, const int64_t *slot
     if (rc == LMC_OK) {
         uint64_t &reached = c->word_target[lmc_ctx::kStoreWord];
         lmc::HostWord told{c->words ? c->word(lmc_ctx::kStoreWord) : nullptr, c->stored_dev, reached};
-        const bool tells = direct && c->words != nullptr && !is_capturing(c->s_gather);
+        const bool tells = direct && tells_host(c);
         rc = store_groups(c, lmc::bulk_view(c->kg), 0, ptrs, slot_mapping, new_chunk, op.slots,
                           c->cfg.staging_chunks, true, direct, false, false, &op.owned_events, nullptr, tells ? &told : nullptr);
         if (told.target != reached) op.stored_target = reached = told.target;
@@ -944,7 +951,7 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     if (rc == LMC_OK) {
         op->owned_events.push_back(e);
         // the last step of a store whose steps all ran on the gather stream ends the store
-        const bool tells = direct && first_layer + n_layers == geom.num_layers && c->words != nullptr && !is_capturing(c->s_gather) &&
+        const bool tells = direct && first_layer + n_layers == geom.num_layers && tells_host(c) &&
                            std::all_of(op->ends_on.begin(), op->ends_on.end(), [&](hipStream_t s) { return s == c->s_gather; });
         uint64_t &reached = c->word_target[lmc_ctx::kStoreWord];
         lmc::HostWord told{tells ? c->word(lmc_ctx::kStoreWord) : nullptr, c->stored_dev, reached};

@@ -66,6 +66,40 @@ def test_bytes_are_in_the_pool_when_the_wait_returns(shape, how):
             c.clear(ids)
 
 
+@pytest.mark.parametrize("flag", ["timing", "trace"])
+@pytest.mark.parametrize("layers", [False, True])
+def test_a_store_that_was_waited_for_is_in_the_statistics_and_the_trace(flag, layers):
+    """With nothing else between the wait and the reading, every time."""
+    import torch
+    from gpu_util import PagedKV, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(**SHAPES["tells_256"])
+    rng = np.random.default_rng(41)
+    src = PagedKV(g, np.arange(g.NB), rng)
+    d_slots = slots_to_device(rng.permutation(g.n_slots)[:2 * g.CT].astype(np.int64))
+    ids = np.array([1, 2], dtype=np.uint64)
+    launches = g.L if layers else 1
+    torch.cuda.synchronize()
+    with lmc.Context(g, 4 * g.chunk_bytes, staging_chunks=2) as c:
+        c.tune(flag, 1)
+        for k in range(40):
+            if layers:
+                t = c.store_begin(d_slots, ids)
+                for l in range(g.L):
+                    c.store_layers(t, l, 1, src.dev)
+            else:
+                t = c.store(src.dev, d_slots, ids)
+            c.wait(t)
+            if flag == "timing":
+                st = c.get_stats()
+                assert (st["gather_launches"], st["timed_gather_launches"]) == (launches, launches), k
+                c.reset_stats()
+            else:
+                records, dropped = c.trace_read()
+                assert [r["ticket"] for r in records] == [t] * launches and dropped == 0, k
+            c.clear(ids)
+
+
 def test_threads_wait_each_for_their_own_store():
     import torch
     from gpu_util import PagedKV, slots_to_device

@@ -270,7 +270,7 @@ lmc_status_t lmc_retrieve_batch(lmc_ctx_t *ctx, int64_t n_req, const int64_t *re
  * complete long before the last layer's.  The consumer orders itself per layer with
  * lmc_wait_layer; unlike lmc_retrieve, no stream is made to wait for the whole call.
  * Without staging (a small call, or LMC_FLAG_DIRECT) one launch moves all the layers, step by
- * step, unless the stream is being captured, "link_groups" is 0, more than 256 chunks lie in
+ * step, unless the stream is being captured, "link_groups" or "value_waits" is 0, more than 256 chunks lie in
  * scattered slots or one of LMC_FLAG_TIMING, _TRACE and _FORCE_SYNC is set: then each step is
  * a launch.
  * stream_to_wait_on: the call is ordered after work already on it (old users of the
@@ -303,8 +303,10 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *ctx, uint64_t ticket, int32_t first_lay
 /* Make `stream` (hipStream_t, NULL = null stream) wait, on the device, until layer
  * `layer` of a layer-wise ticket is in place: loaded into its pages (retrieve) or
  * arrived in the pool (store).  The host does not block.  A finished ticket needs no
- * wait and returns LMC_OK.  (A stream of another GPU waits for all the layers where one launch
- * moves them.)  LMC_ERR_INVAL for a ticket that is not layer-wise or a
+ * wait and returns LMC_OK.  Where one launch moves all the layers (lmc_retrieve_layerwise) the
+ * stream waits for a value in device memory, which the runtime does by a kernel of one wavefront
+ * that runs on the stream until the layer is there (lmc_tune "value_waits"); a stream of another GPU, or any
+ * stream with "value_waits" 0, then waits for all the layers.  LMC_ERR_INVAL for a ticket that is not layer-wise or a
  * layer out of range; LMC_ERR_BUSY for a store layer that has not been submitted. */
 lmc_status_t lmc_wait_layer(lmc_ctx_t *ctx, uint64_t ticket, int32_t layer, void *stream);
 
@@ -606,7 +608,15 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * ends by making the caller's stream wait for it; 0: it does not, and the caller orders its
  * work after the ticket itself with lmc_wait.  A wait that stands at the head of an
  * otherwise idle hardware queue for the length of a large retrieve cost that retrieve
- * 0.5 % on MI355X), "arrange_streams" (1: place the library's streams on hardware queues
+ * 0.5 % on MI355X), "value_waits" (default 1: the streams of a retrieve that wait for each other, or for
+ * a layer, do so by the value of a word in device memory (hipStreamWaitValue64) where that is
+ * cheaper than an event: 2 us of the calling thread instead of 13, and no polling over the link that
+ * the transfer uses.  On this runtime such a wait is a kernel of one wavefront that runs until
+ * the value is there.  Under a tool that lets the GPU run only one kernel at a time, as profilers
+ * do while they collect counters, it may start before the kernel that brings the value about and
+ * never end: set 0 there, before the first transfer; all waits are events then, and layer-wise
+ * retrieves a launch per step.  The default is 0 under rocprofv3 --pmc, which is recognised by
+ * ROCPROF_COUNTER_COLLECTION in the environment), "arrange_streams" (1: place the library's streams on hardware queues
  * again, as lmc_create does without LMC_FLAG_KEEP_STREAMS, e.g. after the process has made
  * its own streams; LMC_ERR_BUSY unless every ticket has been waited for),
  * "fail_hip_after" (for tests of the

@@ -854,6 +854,8 @@ lmc_status_t lmc_tune(lmc_ctx_t *c, const char *key, int64_t value) {
         c->pieces_by_kernel_below = uint64_t(value);
     } else if (k == "caller_waits" && value <= 1) {
         c->caller_waits = value != 0;
+    } else if (k == "value_waits" && value <= 1) {
+        c->value_waits = value != 0;
     } else if (k == "copy_kernel" && value <= 3) {
         c->copy_kernel = uint32_t(value);
     } else if (k == "link_groups") {

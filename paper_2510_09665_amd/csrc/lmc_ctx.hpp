@@ -176,6 +176,17 @@ struct lmc_ctx {
     bool is_stored(uint64_t target) const { return target != 0 && __atomic_load_n(stored_host, __ATOMIC_ACQUIRE) >= target; }
     uint64_t *words = nullptr;
     uint64_t word_target[kWords] = {};
+    // May a stream be made to wait for a word (lmc_tune "value_waits")?  The runtime waits for a value,
+    // and writes one, by a kernel: one wavefront that stays until the word is there.  Where two kernels
+    // may run at once that is harmless, since whatever brings the word about has been enqueued before the
+    // wait.  A tool that lets the GPU run one kernel at a time may start the waiting one first, for
+    // good: rocprofv3 does while it collects counters, which it tells the program by this variable.
+    static bool kernels_run_one_by_one() {
+        const char *v = std::getenv("ROCPROF_COUNTER_COLLECTION");
+        return v != nullptr && *v != 0 && std::strcmp(v, "0") != 0;
+    }
+    bool value_waits = !kernels_run_one_by_one();
+    bool can_wait_for_words() const { return words != nullptr && value_waits; }
     uint64_t *word(int i) const { return words + size_t(i) * (lmc::kWordStride / sizeof(uint64_t)); }
     std::deque<Op> ops;
     std::deque<Timing> timings;

@@ -378,11 +378,11 @@ static bool is_capturing(hipStream_t stream) {
     return !no;
 }
 
-// Can `stream` wait for a word of the context's (lmc_ctx::words)?  Not while it is being captured
-// (the wait is no part of a graph), nor from another GPU.
+// Can `stream` wait for a word of the context's (lmc_ctx::words)?  Not with "value_waits" 0, while it is
+// being captured (the wait is no part of a graph), nor from another GPU.
 static bool may_wait_for_word(const lmc_ctx *c, hipStream_t stream) {
     hipDevice_t dev = c->cfg.device;
-    const bool ok = c->words != nullptr && !is_capturing(stream) &&
+    const bool ok = c->can_wait_for_words() && !is_capturing(stream) &&
                     (stream == nullptr || stream == hipStreamPerThread || hipStreamGetDevice(stream, &dev) == hipSuccess) &&
                     dev == c->cfg.device;
     (void)hipGetLastError();
@@ -405,14 +405,15 @@ static lmc_status_t wait_for_word(lmc_ctx *c, hipStream_t stream, int word, uint
 // host memory, over the link that the transfer it waits for is using: each such queue takes 0.6 % of
 // the rate of a copy from the host and 0.25 % of one to it (1.25 GiB up: 57.2 GB/s with nobody waiting,
 // 56.9, 56.55, 56.25 with one, two, three streams).  So the stream that is waited for writes a word in
-// device memory behind its event, and the other waits for the word first, polling that, and then for
+// device memory behind its event, and the other waits for the word first and then for
 // the event, which has completed by then: the event is what orders the two, the word only keeps the
-// queue quiet.  A word belongs to one stream, whose writes are in order.  Only retrieves use this: a
+// queue quiet.  What polls the word is a wavefront on a compute unit (lmc_ctx::value_waits), two of
+// them for the length of a staged retrieve: on the scatter stream and on the caller's.  A word belongs to one stream, whose writes are in order.  Only retrieves use this: a
 // store's gathers that wait for their buffers gain 0.1 % by it.
 // hand_over: `stream` writes the word's next value, *at, or 0 where it cannot (capture).
 static lmc_status_t hand_over(lmc_ctx *c, hipStream_t stream, int word, uint64_t *at) {
     *at = 0;
-    if (c->words == nullptr || is_capturing(stream)) return LMC_OK;
+    if (!c->can_wait_for_words() || is_capturing(stream)) return LMC_OK;
     HIPCHK(c, hipStreamWriteValue64(stream, c->word(word), c->word_target[word] + 1, 0));
     *at = ++c->word_target[word];
     return LMC_OK;
@@ -605,7 +606,7 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
             lmc::Arrivals arrivals{nullptr, 0};
             hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
             HIPCHK(c, hipStreamIsCapturing(c->s_scatter, &capturing));
-            const bool tells = c->words != nullptr && c->link_groups > 0 && capturing == hipStreamCaptureStatusNone;
+            const bool tells = c->can_wait_for_words() && c->link_groups > 0 && capturing == hipStreamCaptureStatusNone;
             if (tells) arrivals.words = c->word(lmc_ctx::kBulkWord);
             rc = load_direct(lmc::bulk_view(c->kg), 0, nullptr, tells ? &arrivals : nullptr);
             c->word_target[lmc_ctx::kBulkWord] += arrivals.count;

@@ -41,6 +41,11 @@
  *   - A chunk id is a 64-bit value, normally from lmc_hash_chunks.  Equal ids mean
  *     the same chunk.
  *   - One context may be used from several threads; calls are serialised inside.
+ *   - Kernels that read or write the pinned pool themselves (small calls, LMC_FLAG_DIRECT, pieces
+ *     of scattered chunks) start on compute units of which other kernels hold at most 32 KiB of LDS.
+ *     A kernel that stays on the GPU and holds more on every compute unit keeps them waiting until
+ *     it ends: if it is itself to wait for a store, a retrieve or a layer of one, call
+ *     lmc_tune("link_lds_kib", 0) first, and they ask for none.
  */
 #ifndef LMC_H
 #define LMC_H
@@ -571,8 +576,11 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * many, scatters of 192 MiB and more none), "link_groups" (default
  * 64: launches that read or write the pinned pool themselves run as three quarters of that many
  * groups of 256 lanes taking tiles in turn (as many, or twice as many, where rows are no
- * multiples of 16 bytes), which is what the host link likes, two groups to a workgroup, which keeps
- * its compute unit to itself and starts on one whose LDS no other kernel holds; 0 = one tile per workgroup as for launches inside HBM),
+ * multiples of 16 bytes), which is what the host link likes, two groups to a workgroup; 0 = one tile per workgroup as for launches inside HBM),
+ * "link_lds_kib" (0 .. 160, default 128: KiB of LDS that each of those workgroups claims without
+ * using it, so that kernels with much LDS keep off its compute unit, where their loads would
+ * queue behind those of host memory: a product of 128 rows by 4096 x 4096 beside a load takes 37 us
+ * instead of 76, 33 alone.  0: none, the workgroups share any compute unit; see the conventions above),
  * "copy_kernel" (default 0; bit 0: copies from staging to the
  * pool are made by the library's own link-paced copy kernel instead of hipMemcpyAsync;
  * bit 1: copies from the pool to staging too.  At the rate of the runtime's copies and

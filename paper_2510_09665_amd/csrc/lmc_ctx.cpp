@@ -474,6 +474,7 @@ lmc_status_t lmc_create(const lmc_config_t *cfg, lmc_ctx_t **ctx_out) {
     c->shape.nt_store = true;
     c->shape.xcd_run = 32;
     c->shape.paced_groups = 0;
+    c->shape.paced_lds = lmc::kPacedLds;
     c->shape.ordered_group_rows = 256;
     c->has_device = cfg->device != LMC_DEVICE_NONE;
     const size_t pool_bytes = size_t(c->n_pool_slots) * size_t(c->chunk_bytes);
@@ -861,6 +862,8 @@ lmc_status_t lmc_tune(lmc_ctx_t *c, const char *key, int64_t value) {
     } else if (k == "link_groups") {
         if (value > 65536) return LMC_ERR_INVAL;
         c->link_groups = uint32_t(value);
+    } else if (k == "link_lds_kib" && value <= int64_t(lmc::kLdsBytes >> 10)) {
+        c->shape.paced_lds = uint32_t(value) << 10;
     } else if (k == "scatter_order" && value <= 2) {
         c->scatter_order = int32_t(value);
     } else if (k == "ordered_group_rows" && value < (int64_t(1) << 31)) {

@@ -44,7 +44,6 @@ template <> struct VecOf<kPacked> { typedef VecOf<16>::type type; };
 template <int VEC> constexpr uint32_t kBytesOf = VEC == kWide || VEC == kPacked ? 16u : uint32_t(VEC);
 
 #define LMC_GLOBAL __attribute__((address_space(1)))
-#define LMC_LDS __attribute__((address_space(3)))
 
 // Addresses are carried as integers (so they can be pinned in scalar registers) and
 // dereferenced as global-memory pointers, never as flat ones.
@@ -326,22 +325,23 @@ __global__ __launch_bounds__(kThreads) void gather_rows_by_wave(const KernelGeom
     __builtin_nontemporal_store(v, (LMC_GLOBAL V *)st + lane);
 }
 
-// What crosses the link keeps the compute unit to itself: a workgroup asks for all of its LDS, of
-// which it uses nothing.  A load of host memory takes 4 us and more with the link busy, stores to it
-// queue up likewise, and the loads of whatever else runs on that compute unit wait behind them.  A
-// dense bf16 product of 128, 512, 1024 or 4096 rows by 4096 x 4096 (31, 34, 44, 111 us alone) beside
-// 64 groups that load took 158, 159, 191, 189 us without the claim and takes 38, 55, 78, 189 with it;
-// beside as many that store 157, 159, 193, 257 and 40, 55, 84, 194.  Nothing is lost while the GPU is
-// full: 0.5 MiB issued into a queue of products, attention or softmax ends within the spread of the
+// What crosses the link keeps the compute unit to itself: a workgroup asks for most of its LDS, of
+// which it uses nothing (LaunchShape::paced_lds).  A load of host memory takes 4 us and
+// more with the link busy, stores to it queue up likewise, and the loads of whatever else runs on that
+// compute unit wait behind them.  Beside a load of 64 MiB and beside a store of as much, with 0, 96, 128
+// and 160 KiB claimed: a dense bf16 product of 128 rows by 4096 x 4096 (33 us alone) 76, 77, 37, 36 and
+// 66, 65, 34, 34 us, one of 512 rows (36) 80, 82, 54, 54 and 65, 66, 50, 51, attention (138) 274, 274,
+// 260, 259 and 224, 223, 184, 184, softmax (46) 61, 61, 62, 48 and 55, 54, 54, 46; the transfers
+// themselves 1194 us with any.  64 MiB layer by layer with such products between the layers: 4.92, -,
+// 4.24, 4.24 ms.  Hence 128: what it keeps out is what has much LDS and reads much, and it starts
+// beside a kernel that stays and holds no more than 32 KiB on every compute unit.  Beside one that
+// holds more everywhere it starts when that one ends; for a process that has such a kernel wait for a
+// transfer there is the knob "link_lds_kib".  Nothing is lost while the GPU is full of kernels that
+// end: 0.5 MiB issued into a queue of products, attention or softmax ends within the spread of the
 // unclaimed (15-110 us), as soon as one compute unit runs out of work of the kernel before.
 // Hence also two groups of 256 lanes to a workgroup: as many tiles in flight on half the compute
 // units, at the same rate.
 constexpr int kPacedThreads = 2 * kThreads;
-constexpr int kLdsBytes = 160 * 1024;
-__device__ __forceinline__ void claim_compute_unit() {
-    __shared__ char all[kLdsBytes];
-    asm volatile("" ::"v"((LMC_LDS char *)all));
-}
 
 // The gather's tile for a workgroup that takes many, one after the other: no early return, a lane
 // past the end of the plane reads the slot that the last one reads and moves nothing.  With a list,
@@ -398,7 +398,6 @@ __global__ __launch_bounds__(kPacedThreads) void gather_paced(const KernelGeom g
                                                          uint8_t *staging, int32_t *bad_flag,
                                                          uint32_t n_blocks, uint32_t groups, const HostWord told) {
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
-    claim_compute_unit();
     const uint32_t step = pin(groups), end = pin(n_blocks), lane = threadIdx.x % kThreads;
     const uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) * gridDim.x + blockIdx.x;
     if (first >= step) return;                       // an odd number of groups leaves a half without work
@@ -418,7 +417,6 @@ __global__ __launch_bounds__(kPacedThreads) void gather_listed(const KernelGeom 
                                                           uint8_t *staging, int32_t *bad_flag,
                                                           uint32_t n_blocks, uint32_t groups, const HostWord told, const ChunkList list) {
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
-    claim_compute_unit();
     const uint32_t step = pin(groups), end = pin(n_blocks), lane = threadIdx.x % kThreads;
     const uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) * gridDim.x + blockIdx.x;
     if (first >= step) return;                       // an odd number of groups leaves a half without work
@@ -475,7 +473,6 @@ __global__ __launch_bounds__(kPacedThreads) void scatter_paced(const KernelGeom 
                                                           const int64_t *__restrict__ slot_mapping, const uint8_t *pool,
                                                           int32_t *bad_flag, uint64_t *words, const List list) {
     typedef typename VecOf<VEC>::type V;
-    claim_compute_unit();
     const uint32_t half = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), lane = threadIdx.x % kThreads;
     TileArgs a = fetch_args<VEC>(g, view, slot_mapping, const_cast<uint8_t *>(pool), bad_flag);
     const uint32_t groups = pin(steps.groups), n_steps = pin(steps.n_steps);
@@ -732,7 +729,6 @@ __global__ __launch_bounds__(kPacedThreads) void copy_rect_paced(uint8_t *__rest
     const uint64_t dst_at = pin(uint64_t(dst)), src_at = pin(uint64_t(src));
     const uint64_t dp = pin(dst_pitch), sp = pin(src_pitch), wv = pin(width_vec);
     const FastDiv by_tpr = pin(by_tiles_per_row);
-    claim_compute_unit();
     const uint32_t step = pin(groups), end = pin(n_tiles), lane = threadIdx.x % kThreads;
     const uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) * gridDim.x + blockIdx.x;
     if (first >= step) return;                       // an odd number of groups leaves a half without work
@@ -757,7 +753,6 @@ __global__ __launch_bounds__(kPacedThreads) void copy_pieces_paced(uint8_t *__re
     const uint64_t pool_at = pin(uint64_t(pool)), stage_at = pin(uint64_t(staging));
     const uint64_t pp = pin(pool_pitch), sp = pin(stage_pitch), wv = pin(width_vec);
     const FastDiv by_tpr = pin(by_tiles_per_row);
-    claim_compute_unit();
     const uint32_t step = pin(groups), end = pin(n_tiles), lane = threadIdx.x % kThreads;
     const uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) * gridDim.x + blockIdx.x;
     if (first >= step) return;                       // an odd number of groups leaves a half without work
@@ -869,9 +864,9 @@ hipError_t launch_gather_paced(const KernelGeom &g, const LaunchView &v, const L
     }
 #define LMC_GO(LD, ST)                                                                                  \
     if (list != nullptr)                                                                                \
-        hipExtLaunchKernelGGL((gather_listed<VEC, LD, ST>), grid, block, 0, stream, start, stop, 0, g, v, \
+        hipExtLaunchKernelGGL((gather_listed<VEC, LD, ST>), grid, block, s.paced_lds, stream, start, stop, 0, g, v, \
                               layers, slot_mapping, pool, bad_flag, n_blocks, groups, done, *list);     \
-    else hipExtLaunchKernelGGL((gather_paced<VEC, LD, ST>), grid, block, 0, stream, start, stop, 0, g, v, \
+    else hipExtLaunchKernelGGL((gather_paced<VEC, LD, ST>), grid, block, s.paced_lds, stream, start, stop, 0, g, v, \
                           layers, slot_mapping, pool, bad_flag, n_blocks, groups, done)
     if (through) { LMC_GO(true, kThrough); }
     else if (s.nt_load && s.nt_store) { LMC_GO(true, kStoreNonTemporal); }
@@ -887,7 +882,7 @@ hipError_t launch_gather_paced(const KernelGeom &g, const LaunchView &v, const L
 // The pool into pages, `planes` planes of every chunk in each step.  The non-temporal hints of the
 // launch shape are for HBM and change nothing here.
 template <int VEC>
-hipError_t launch_scatter_paced(const KernelGeom &g, const LaunchView &v, uint32_t planes, uint32_t groups,
+hipError_t launch_scatter_paced(const KernelGeom &g, const LaunchView &v, const LaunchShape &s, uint32_t planes,
                                 const LayerPtrs &layers, const int64_t *slot_mapping, uint32_t n_chunks,
                                 const uint8_t *pool, int32_t *bad_flag, hipStream_t stream, hipEvent_t start,
                                 hipEvent_t stop, const ChunkList *list, Arrivals *arrivals) {
@@ -903,14 +898,14 @@ hipError_t launch_scatter_paced(const KernelGeom &g, const LaunchView &v, uint32
     steps.last_blocks = n_chunks * last * g.by_tiles_per_plane.d;
     steps.by_last_lp = make_fastdiv(last);
     // 64 MiB by 32, 48, 64, 96 groups: 1189, 1182, 1183, 1227 us; 12 MiB by 48, 64: 225, 225; 0.5 MiB alike
-    steps.groups = uint32_t(std::min<uint64_t>(tiles, paced_part(groups)));
+    steps.groups = uint32_t(std::min<uint64_t>(tiles, paced_part(s.paced_groups)));
     const dim3 grid((steps.groups + 1) / 2), block(kPacedThreads);
     uint64_t *words = arrivals != nullptr ? arrivals->words : nullptr;
     if (list != nullptr)
-        hipExtLaunchKernelGGL((scatter_paced<VEC, ChunkList>), grid, block, 0, stream, start, stop, 0, g, step, steps, layers,
+        hipExtLaunchKernelGGL((scatter_paced<VEC, ChunkList>), grid, block, s.paced_lds, stream, start, stop, 0, g, step, steps, layers,
                               slot_mapping, pool, bad_flag, words, *list);
     else
-        hipExtLaunchKernelGGL((scatter_paced<VEC, BackToBack>), grid, block, 0, stream, start, stop, 0, g, step, steps, layers,
+        hipExtLaunchKernelGGL((scatter_paced<VEC, BackToBack>), grid, block, s.paced_lds, stream, start, stop, 0, g, step, steps, layers,
                               slot_mapping, pool, bad_flag, words, BackToBack{});
     const hipError_t e = hipGetLastError();
     if (arrivals != nullptr && e == hipSuccess) arrivals->count = steps.groups * (kThreads / 64);
@@ -1015,7 +1010,7 @@ hipError_t launch_scatter(const KernelGeom &g, const LaunchView &v, const Launch
     const uint32_t planes = planes_per_step == 0 ? v.by_n_lp.d : std::min(planes_per_step, v.by_n_lp.d);
     return by_vec(g, [&](auto vec) {
         return s.paced_groups > 0
-                   ? launch_scatter_paced<vec.value>(g, v, planes, s.paced_groups, layers, slot_mapping, n_chunks, staging,
+                   ? launch_scatter_paced<vec.value>(g, v, s, planes, layers, slot_mapping, n_chunks, staging,
                                                      bad_flag, stream, start, stop, list, arrivals)
                    : launch_move_v<vec.value, false>(g, v, s, layers, slot_mapping, n_chunks, const_cast<uint8_t *>(staging),
                                                      bad_flag, stream, start, stop);
@@ -1130,7 +1125,7 @@ hipError_t launch_copy_tiles(uint8_t *dst, const uint32_t *dst_order, const uint
 }
 
 hipError_t launch_copy_rect(uint8_t *dst, uint64_t dst_pitch, const uint8_t *src, uint64_t src_pitch,
-                            uint64_t width, uint64_t rows, bool to_pool, uint32_t groups, hipStream_t stream) {
+                            uint64_t width, uint64_t rows, bool to_pool, uint32_t groups, uint32_t lds, hipStream_t stream) {
     if (width == 0 || rows == 0) return hipSuccess;
     if ((width % 16) != 0 || (dst_pitch % 16) != 0 || (src_pitch % 16) != 0 || groups == 0 ||
         (reinterpret_cast<uintptr_t>(dst) % 16) != 0 || (reinterpret_cast<uintptr_t>(src) % 16) != 0)
@@ -1144,7 +1139,7 @@ hipError_t launch_copy_rect(uint8_t *dst, uint64_t dst_pitch, const uint8_t *src
         const uint64_t n = std::min(rows - r0, rows_per_launch);
         const uint32_t n_tiles = uint32_t(n * tiles_per_row), used = std::min(n_tiles, to_pool ? groups : paced_part(groups));
         hipLaunchKernelGGL(to_pool ? copy_rect_paced<true> : copy_rect_paced<false>, dim3((used + 1) / 2),
-                           dim3(kPacedThreads), 0, stream, dst + r0 * dst_pitch, dst_pitch, src + r0 * src_pitch, src_pitch,
+                           dim3(kPacedThreads), lds, stream, dst + r0 * dst_pitch, dst_pitch, src + r0 * src_pitch, src_pitch,
                            width_vec, make_fastdiv(uint32_t(tiles_per_row)), n_tiles, used);
     }
     return hipGetLastError();
@@ -1152,7 +1147,7 @@ hipError_t launch_copy_rect(uint8_t *dst, uint64_t dst_pitch, const uint8_t *src
 
 hipError_t launch_copy_pieces(uint8_t *pool, uint64_t pool_pitch, uint8_t *staging, uint64_t stage_pitch,
                               uint64_t width, const PieceSlots &slots, uint32_t n_pieces, bool to_pool,
-                              uint32_t groups, hipStream_t stream) {
+                              uint32_t groups, uint32_t lds, hipStream_t stream) {
     if (width == 0 || n_pieces == 0) return hipSuccess;
     if ((width % 16) != 0 || (pool_pitch % 16) != 0 || (stage_pitch % 16) != 0 || groups == 0 ||
         n_pieces > uint32_t(kMaxPieces) || (reinterpret_cast<uintptr_t>(pool) % 16) != 0 ||
@@ -1168,10 +1163,10 @@ hipError_t launch_copy_pieces(uint8_t *pool, uint64_t pool_pitch, uint8_t *stagi
     const uint32_t used = std::min(n_tiles, paced_part(groups));
     const dim3 grid((used + 1) / 2), block(kPacedThreads);
     if (to_pool)
-        hipLaunchKernelGGL(copy_pieces_paced<true>, grid, block, 0, stream, pool, pool_pitch, staging, stage_pitch,
+        hipLaunchKernelGGL(copy_pieces_paced<true>, grid, block, lds, stream, pool, pool_pitch, staging, stage_pitch,
                            width_vec, make_fastdiv(uint32_t(tiles_per_row)), n_tiles, used, slots);
     else
-        hipLaunchKernelGGL(copy_pieces_paced<false>, grid, block, 0, stream, pool, pool_pitch, staging, stage_pitch,
+        hipLaunchKernelGGL(copy_pieces_paced<false>, grid, block, lds, stream, pool, pool_pitch, staging, stage_pitch,
                            width_vec, make_fastdiv(uint32_t(tiles_per_row)), n_tiles, used, slots);
     return hipGetLastError();
 }

@@ -79,7 +79,10 @@ struct LaunchShape {
     uint32_t paced_groups;    // 0: one tile per workgroup (HBM-bound launches); n > 0: a
                               // fixed grid of about n groups of 256 lanes that take tiles in
                               // turn, for launches whose other side is host memory
+    uint32_t paced_lds;       // bytes of LDS that each workgroup of such a launch claims (and does not
+                              // use) to keep others off its compute unit, at most kLdsBytes
 };
+constexpr uint32_t kLdsBytes = 160u << 10, kPacedLds = 128u << 10;   // of a compute unit; claimed by default
 
 // Where the chunks of one link-paced launch lie when they are not back to back: chunk i of
 // the launch has its bytes at staging + slot[i] * chunk_stride.  By value, like LayerPtrs
@@ -161,12 +164,13 @@ hipError_t launch_copy(uint8_t *dst, const uint8_t *src, uint64_t nbytes, hipStr
 hipError_t launch_copy_tiles(uint8_t *dst, const uint32_t *dst_order, const uint8_t *src,
                              const uint32_t *src_order, uint32_t n_tiles, uint32_t mode, uint8_t *sink,
                              hipStream_t stream);
-// rows x width bytes, rows src_pitch / dst_pitch apart, by `groups` workgroups that take
-// tiles in turn (the shape that suits a copy whose one side is pinned host memory).
+// rows x width bytes, rows src_pitch / dst_pitch apart, by about `groups` groups of 256 lanes that take
+// tiles in turn (the shape that suits a copy whose one side is pinned host memory), two to a workgroup
+// that claims `lds` bytes of LDS.
 // Everything must be a multiple of 16 bytes, else hipErrorInvalidValue.
 // to_pool: dst is the pinned pool.
 hipError_t launch_copy_rect(uint8_t *dst, uint64_t dst_pitch, const uint8_t *src, uint64_t src_pitch,
-                            uint64_t width, uint64_t rows, bool to_pool, uint32_t groups, hipStream_t stream);
+                            uint64_t width, uint64_t rows, bool to_pool, uint32_t groups, uint32_t lds, hipStream_t stream);
 // Pool slots of the pieces of one copy_pieces launch, by value like LayerPtrs.
 constexpr int kMaxPieces = 256;
 struct PieceSlots {
@@ -178,7 +182,7 @@ struct PieceSlots {
 // pool, else pool -> staging.  Everything a multiple of 16 bytes.
 hipError_t launch_copy_pieces(uint8_t *pool, uint64_t pool_pitch, uint8_t *staging, uint64_t stage_pitch,
                               uint64_t width, const PieceSlots &slots, uint32_t n_pieces, bool to_pool,
-                              uint32_t groups, hipStream_t stream);
+                              uint32_t groups, uint32_t lds, hipStream_t stream);
 hipError_t launch_fill(uint8_t *dst, uint8_t value, uint64_t nbytes, hipStream_t stream);
 
 // largest number of chunks one launch may cover (32-bit workgroup index)

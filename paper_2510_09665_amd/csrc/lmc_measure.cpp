@@ -31,8 +31,8 @@ static lmc_status_t measure_link(lmc_ctx_t *c, uint64_t nbytes, int32_t reps, bo
             hipError_t a = hipEventRecord(e0, s);
             const uint32_t groups = c->link_groups ? c->link_groups : 64u;
             hipError_t b = by_kernel
-                ? (dir == 0 ? lmc::launch_copy_rect(devbuf, nbytes, c->pool_dev, nbytes, nbytes, 1, false, groups, s)
-                            : lmc::launch_copy_rect(c->pool_dev, nbytes, devbuf, nbytes, nbytes, 1, true, groups, s))
+                ? (dir == 0 ? lmc::launch_copy_rect(devbuf, nbytes, c->pool_dev, nbytes, nbytes, 1, false, groups, c->shape.paced_lds, s)
+                            : lmc::launch_copy_rect(c->pool_dev, nbytes, devbuf, nbytes, nbytes, 1, true, groups, c->shape.paced_lds, s))
                 : (dir == 0 ? hipMemcpyAsync(devbuf, c->pool, nbytes, hipMemcpyHostToDevice, s)
                             : hipMemcpyAsync(c->pool, devbuf, nbytes, hipMemcpyDeviceToHost, s));
             hipError_t d = hipEventRecord(e1, s);
@@ -98,9 +98,9 @@ static lmc_status_t measure_duplex(lmc_ctx_t *c, uint64_t nbytes, int32_t reps, 
         const uint32_t groups = c->link_groups ? c->link_groups : 64u;
         const uint64_t piece = nbytes / pieces;
         for (uint64_t o = 0; o < nbytes; o += piece) {
-            ok((by_kernel & 1u) ? lmc::launch_copy_rect(up + o, piece, c->pool_dev + o, piece, piece, 1, false, groups, c->s_h2d)
+            ok((by_kernel & 1u) ? lmc::launch_copy_rect(up + o, piece, c->pool_dev + o, piece, piece, 1, false, groups, c->shape.paced_lds, c->s_h2d)
                                 : hipMemcpyAsync(up + o, c->pool + o, piece, hipMemcpyHostToDevice, c->s_h2d));
-            ok((by_kernel & 2u) ? lmc::launch_copy_rect(c->pool_dev + nbytes + o, piece, down + o, piece, piece, 1, true, groups, c->s_d2h)
+            ok((by_kernel & 2u) ? lmc::launch_copy_rect(c->pool_dev + nbytes + o, piece, down + o, piece, piece, 1, true, groups, c->shape.paced_lds, c->s_d2h)
                                 : hipMemcpyAsync(c->pool + nbytes + o, down + o, piece, hipMemcpyDeviceToHost, c->s_d2h));
         }
         ok(hipEventRecord(e1, c->s_d2h));

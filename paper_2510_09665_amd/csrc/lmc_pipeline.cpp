@@ -159,7 +159,7 @@ static lmc_status_t copy_group(lmc_ctx *c, bool to_host, uint8_t *staging, uint6
                 lmc::PieceSlots table;
                 for (int64_t i = 0; i < m; i++) table.slot[i] = int32_t(pool_slots[j + i]);
                 HIPCHK(c, lmc::launch_copy_pieces(c->pool_dev + pool_off, cb, staging + uint64_t(j) * stride, stride,
-                                                  width, table, uint32_t(m), to_host, groups, first));
+                                                  width, table, uint32_t(m), to_host, groups, c->shape.paced_lds, first));
             }
             if (to_host) c->stats.bytes_d2h += uint64_t(k) * width;
             else c->stats.bytes_h2d += uint64_t(k) * width;
@@ -181,8 +181,8 @@ static lmc_status_t copy_group(lmc_ctx *c, bool to_host, uint8_t *staging, uint6
             uint8_t *pool_at = c->pool_dev + uint64_t(pool_slots[j]) * cb + pool_off;
             uint8_t *stage_at = staging + uint64_t(j) * stride;
             const uint32_t groups = c->link_groups ? c->link_groups : 64u;
-            if (to_host) HIPCHK(c, lmc::launch_copy_rect(pool_at, cb, stage_at, stride, width, uint64_t(m), true, groups, stream));
-            else HIPCHK(c, lmc::launch_copy_rect(stage_at, stride, pool_at, cb, width, uint64_t(m), false, groups, stream));
+            if (to_host) HIPCHK(c, lmc::launch_copy_rect(pool_at, cb, stage_at, stride, width, uint64_t(m), true, groups, c->shape.paced_lds, stream));
+            else HIPCHK(c, lmc::launch_copy_rect(stage_at, stride, pool_at, cb, width, uint64_t(m), false, groups, c->shape.paced_lds, stream));
             if (to_host) c->stats.bytes_d2h += uint64_t(m) * width;
             else c->stats.bytes_h2d += uint64_t(m) * width;
             j += m;

@@ -16,7 +16,7 @@ lmc_status_t shares_a_queue(lmc_ctx *c, hipStream_t busy, bool by_kernel, hipStr
         const hipError_t steps[] = {
             hipEventRecord(a0, busy),
             by_kernel ? lmc::launch_copy_rect(devbuf, nbytes, c->pool_dev, nbytes, nbytes, 1, false,
-                                              c->link_groups ? c->link_groups : 64u, busy)
+                                              c->link_groups ? c->link_groups : 64u, c->shape.paced_lds, busy)
                       : hipMemcpyAsync(devbuf, c->pool, nbytes, hipMemcpyHostToDevice, busy),
             hipEventRecord(a1, busy),
             lmc::launch_fill(devbuf + nbytes, 0, 256, other),

@@ -719,8 +719,7 @@ __global__ __launch_bounds__(kThreads) void copy_tiles(u32x4 *dst, const uint32_
 // bytes form `rows` rows of width_vec 16-byte vectors, src_pitch / dst_pitch bytes apart
 // (one row per chunk; pitch == width gives a plain copy).
 // By 48 groups that keep their compute units to themselves 57.5 GB/s from the host and 57.0 to it, by
-// 64 57.1 to it (64 that do not: 57.5, 57.1): rectangles to the host go by all the groups; a product of 128 rows by 4096 x 4096 beside scattered pieces coming up
-// takes 58 us instead of 87 (32 alone).
+// 64 57.1 to it (64 that do not: 57.5, 57.1): rectangles to the host go by all the groups.
 template <bool TO_POOL>
 __global__ __launch_bounds__(kPacedThreads) void copy_rect_paced(uint8_t *__restrict__ dst, uint64_t dst_pitch,
                                                             const uint8_t *__restrict__ src,
@@ -1160,7 +1159,12 @@ hipError_t launch_copy_pieces(uint8_t *pool, uint64_t pool_pitch, uint8_t *stagi
     // the tile index is 32-bit and stays below 2^24, so t + grid never wraps and FastDiv is exact
     if (tiles_per_row * n_pieces >= (uint64_t(1) << 24)) return hipErrorInvalidValue;
     const uint32_t n_tiles = uint32_t(tiles_per_row * n_pieces);
-    const uint32_t used = std::min(n_tiles, paced_part(groups));
+    // Pieces to the host move as fast by three quarters of the groups (16 and 32 chunks layer by
+    // layer: 55.4 and 56.2 GB/s by 48 and by 64), pieces from it by all of them: loads layer by layer of 8,
+    // 16, 32 chunks, two layers a step, 55.2, 55.3, 55.5 GB/s by 48, 56.0, 56.4, 56.7 by 64.  A product of
+    // 128 rows by 4096 x 4096 (33 us alone) beside such a load takes 48-62 us with 48, 73-81 with 64
+    // and took 145-360 with 64 that share their compute units.
+    const uint32_t used = std::min(n_tiles, to_pool ? paced_part(groups) : groups);
     const dim3 grid((used + 1) / 2), block(kPacedThreads);
     if (to_pool)
         hipLaunchKernelGGL(copy_pieces_paced<true>, grid, block, lds, stream, pool, pool_pitch, staging, stage_pitch,

@@ -318,7 +318,9 @@ lmc_status_t lmc_wait_layer(lmc_ctx_t *ctx, uint64_t ticket, int32_t layer, void
 /* wait_store_kv / wait_load_kv of section 6, Table 2 (bulk form; lmc_wait_layer is the
  * per-layer form): block until the work of `ticket` and of every earlier ticket has
  * finished on the device, whichever of the library's streams each of them ended on;
- * ticket 0 means everything enqueued so far.  Returns LMC_ERR_BADSLOT if a
+ * ticket 0 means everything enqueued so far.  The calling thread waits as the runtime's own
+ * waits do: on its core, or asleep if the process has set hipDeviceScheduleBlockingSync.
+ * Returns LMC_ERR_BADSLOT if a
  * kernel since the last lmc_wait met a slot >= num_blocks*block_size (that token was
  * skipped, the rest of the call was carried out), LMC_ERR_HIP on a device error.
  * A layer-wise store that still lacks layers cannot be waited for: LMC_ERR_BUSY if it

@@ -325,10 +325,21 @@ struct Awaited {
     uint64_t stored_target;
 };
 
-// Waits for `a`: looks at the word for as long as a store of the size that tells takes, or a little longer,
-// and then leaves the rest to the event.
+// Does the process want its threads to sleep while they wait for the GPU?
+static bool waits_block() {
+    unsigned flags = 0;
+    const bool known = hipGetDeviceFlags(&flags) == hipSuccess;
+    (void)hipGetLastError();
+    return known && (flags & hipDeviceScheduleMask) == hipDeviceScheduleBlockingSync;
+}
+
+// Waits for `a`: looks at the word for as long as a store of the size that tells takes when it starts at
+// once, or a little longer, and leaves the rest to the event.  The thread stays on its core meanwhile, as
+// it does in hipEventSynchronize to the end of any wait (a store behind 50 ms of other work: 50 ms of
+// the core either way), unless the process has asked for waits that block: then the event alone is
+// waited for, asleep.
 static hipError_t await(const lmc_ctx *c, const Awaited &a) {
-    if (a.stored_target != 0) {
+    if (a.stored_target != 0 && !waits_block()) {
         const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(1500);
         do {
             for (int i = 0; i < 64; i++) {

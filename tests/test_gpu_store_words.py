@@ -100,6 +100,52 @@ def test_a_store_that_was_waited_for_is_in_the_statistics_and_the_trace(flag, la
             c.clear(ids)
 
 
+BLOCKING = """
+import ctypes, sys, time
+sys.path[:0] = [%r, %r]
+import numpy as np, torch
+from conftest import _hip_runtime
+from gpu_util import slots_to_device
+from paper_2510_09665_amd import lmc, workloads as W
+from test_gpu_store_words import SHAPES
+torch.zeros(1, device="cuda")
+hip = _hip_runtime()
+assert hip.hipSetDeviceFlags(ctypes.c_uint(4)) == 0          # hipDeviceScheduleBlockingSync
+g = W.KVGeometry(**SHAPES["tells_256"])
+pages = [torch.zeros(g.layer_bytes, dtype=torch.uint8, device="cuda") for _ in range(g.L)]
+slots, ids, s = slots_to_device(np.arange(g.CT)), np.array([1], dtype=np.uint64), torch.cuda.Stream()
+with lmc.Context(g, g.chunk_bytes, staging_chunks=1) as c:
+    spent = []
+    for k in range(6):
+        c.clear(ids)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            torch.cuda._sleep(1 << 25)
+        begin = time.perf_counter()
+        t = c.store(pages, slots, ids, s)
+        cpu = time.thread_time()
+        c.wait(t)
+        spent.append(time.thread_time() - cpu)
+        took = time.perf_counter() - begin
+print(sorted(spent)[2], took)
+"""
+
+
+def test_a_process_that_asked_for_blocking_waits_does_not_spin():
+    """A store behind some ten milliseconds of other work: the thread that waits for it sleeps."""
+    import os
+    import subprocess
+    import sys
+    here = os.path.dirname(os.path.abspath(__file__))
+    res = subprocess.run([sys.executable, "-c", BLOCKING % (os.path.dirname(here), here)], capture_output=True, text=True,
+                         timeout=110)
+    assert res.returncode == 0, res.stderr[-2000:]
+    cpu, took = map(float, res.stdout.split()[-2:])
+    assert took > 5e-3, res.stdout
+    # looking at the word alone took 1.5 ms; going to sleep and waking up are some tens of microseconds
+    assert cpu < 0.75e-3, res.stdout
+
+
 def test_threads_wait_each_for_their_own_store():
     import torch
     from gpu_util import PagedKV, slots_to_device

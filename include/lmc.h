@@ -575,7 +575,7 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * "nt_store" (0/1: non-temporal hints on the kernels' streaming accesses, except those of
  * scatters that read the pool itself), "xcd_run"
  * (consecutive tiles handed to one XCD, 0 = hardware round-robin; gathers take up to eight times as
- * many, scatters of 192 MiB and more none), "link_groups" (default
+ * many, scatters of 192 MiB and more, where the pages hold 8 KiB or rows of 1 KiB in one piece, none), "link_groups" (default
  * 64: launches that read or write the pinned pool themselves run as three quarters of that many
  * groups of 256 lanes taking tiles in turn (as many, or twice as many, where rows are no
  * multiples of 16 bytes), which is what the host link likes, two groups to a workgroup; 0 = one tile per workgroup as for launches inside HBM),

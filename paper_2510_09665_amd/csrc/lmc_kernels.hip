@@ -798,19 +798,22 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
                                   staging, bad_flag, permuted, shift);
             return hipGetLastError();
         }
-    // Large scatters write at system scope and in the plain order of the tiles: launches of several
-    // streams that run into each other, each sweeping its own buffer and its own random pages, lose less
-    // to one another then.  On three streams in turn, non-temporal with runs of 32 and so: Llama-3-8B shape
-    // 512 and 192 MiB 194.4, 188.4 and 72.8, 71.8 us, 70B 480 MiB 183.6, 178.0, 256 MiB in 256-byte
-    // rows 105.0, 100.3, MLA bf16 90.2, 87.0, one-token pages 102.2, 99.7; on one stream 182.5, 182.9;
-    // 70.1, 70.3; 175.0, 175.5; 99.2, 99.9; 86.7, 85.9; 98.4, 99.2.  160 MiB are 1 % slower so, less is
-    // the same either way, and where a wavefront writes lines in parts (pages by head: 92.6, 99.6 on one
-    // stream) it loses.
-    constexpr uint32_t kLargeScatter = 49152;       // tiles of 4 KiB: 192 MiB
-    const bool whole_lines = g.runs_per_row == 1 && (g.row_bytes % 128 == 0 ||
-                                                     (g.token_stride == int64_t(g.row_bytes) && g.by_block_size.d > 1));
+    // Large scatters write at system scope and in the plain order of the tiles: each stream of writes
+    // sweeps its own buffer, and launches of several streams that run into each other lose less
+    // to one another.  Non-temporal with runs of 32 and so, 256 MiB on one stream and on three in turn: 32 KiB
+    // pages 93.7, 92.3 and 96.7, 94.3 us, 16 KiB 93.8, 93.5 and 97.8, 96.0, 8 KiB 94.8, 95.0 and 98.9, 96.8,
+    // MLA bf16 89.0, 87.3 and 90.5, 88.5, one-token pages of 1 and 4 KiB 95.5, 95.9 and 99.5, 98.1;
+    // 92.5, 91.8 and 97.3, 95.1; 512 MiB of the first 189.3, 188.8 and 196.9, 192.6, 192 MiB 70.3, 69.0 and
+    // 70.7, 70.0.  160 MiB are the same or 1 % slower, less is the same either way.  Smaller pieces (256-byte
+    // rows in 4 KiB pages: 96.9, 98.4 on one stream) and rows whose wavefronts write lines in parts
+    // (pages by head: 92.6, 99.6) lose.
+    constexpr uint64_t kLargeScatter = uint64_t(192) << 20;
+    const uint64_t moved = uint64_t(n_chunks) * v.by_n_lp.d * g.plane_bytes;
+    const bool large_pieces =
+        g.runs_per_row == 1 && ((g.row_bytes % 128 == 0 && g.row_bytes >= 1024) ||
+                                (g.token_stride == int64_t(g.row_bytes) && uint64_t(g.by_block_size.d) * g.row_bytes >= 8192));
     if constexpr (!GATHER && VEC == 16)
-        if (n_blocks >= kLargeScatter && whole_lines && s.nt_load && s.nt_store) {
+        if (moved >= kLargeScatter && large_pieces && s.nt_load && s.nt_store) {
             hipExtLaunchKernelGGL((move_rows<VEC, GATHER, true, kStoreThrough>), grid, block, 0, stream, start, stop, 0, g, v,
                                   layers, slot_mapping, staging, bad_flag, 0u, 0u);
             return hipGetLastError();

@@ -54,3 +54,34 @@ def test_around_the_line(shape, beside):
             else:
                 want.view(g.NB * g.BS, g.H, -1)[sl] = rows
             assert torch.equal(o[l], want), l
+
+
+@pytest.mark.parametrize("beside", [-1, 0, 1])
+@pytest.mark.parametrize("kw", [dict(H=1, D=576, e=1, BS=16, CT=16), dict(H=1, D=128, e=2, BS=16, CT=16),
+                                dict(H=1, D=512, e=2, BS=1, CT=3)], ids=str)
+def test_planes_shorter_than_their_tiles(kw, beside):
+    """The line is in bytes, whatever the number of tiles that they take."""
+    import torch
+    from gpu_util import slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(L=3, P=2, NB=2500, **kw)
+    n = -(-(192 << 20) // g.chunk_bytes) + beside
+    r = np.random.default_rng(n)
+    # more tokens than the pages hold: a slot is taken once, the other tokens have none
+    slots = np.full(n * g.CT, -1, dtype=np.int64)
+    taken = r.permutation(n * g.CT)[:min(n * g.CT, g.n_slots - 5)]
+    slots[taken] = r.permutation(g.n_slots)[:taken.size]
+    d_slots = slots_to_device(slots)
+    buf = torch.randint(0, 256, (n * g.chunk_bytes,), dtype=torch.uint8, device="cuda")
+    out = [torch.full((g.layer_bytes,), 0x5A, dtype=torch.uint8, device="cuda") for _ in range(g.L)]
+    torch.cuda.synchronize()
+    with lmc.Context(g, g.chunk_bytes) as c:
+        c.scatter(buf, d_slots, n, out, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+    keep = d_slots >= 0
+    chunks = buf.view(n, g.L, g.P, g.CT, -1)
+    for l in range(g.L):
+        want = torch.full((g.layer_bytes,), 0x5A, dtype=torch.uint8, device="cuda")
+        for p in range(g.P):
+            want.view(g.P, g.n_slots, -1)[p, d_slots[keep]] = chunks[:, l, p].reshape(n * g.CT, -1)[keep]
+        assert torch.equal(out[l], want), l

@@ -840,14 +840,12 @@ hipError_t launch_gather_paced(const KernelGeom &g, const LaunchView &v, const L
                                hipEvent_t stop, const ChunkList *list, HostWord *told) {
     const uint32_t n_blocks = n_chunks * v.by_n_lp.d * g.by_tiles_per_plane.d;
     if (n_blocks == 0) return hipSuccess;
-    // through the L2 where lanes write 16 bytes at multiples of 16.  Planes that begin inside a line of
-    // 128 bytes leave a wavefront's first and last line to two wavefronts, which costs the link less
+    // through the L2 where lanes write 16 bytes, which the pool's slots, chunks and planes are then multiples
+    // of (16-byte runs make them so, packs() has looked).  Planes that begin inside a line of 128 bytes leave a wavefront's first and last line to two wavefronts, which costs the link less
     // than non-temporal stores do: 5.9 and 29 MiB in 360-byte rows (planes of 90720 bytes) 136 and
     // 597 us so, 124 and 582 through; 8 MiB in 208-byte rows, planes of 7488 bytes, 179 and 167.
     constexpr bool kLines = VEC == 16 || VEC == kPacked;
-    const bool through = kLines && s.nt_load && s.nt_store &&
-                         ((uint64_t(reinterpret_cast<uintptr_t>(pool)) | v.chunk_stride | g.plane_bytes) % 16) == 0;
-    constexpr int kThrough = kLines ? kStoreThrough : kStoreNonTemporal;   // nothing else is instantiated
+    const bool through = kLines && s.nt_load && s.nt_store;
     // blk + step must not wrap: n_blocks < 2^24 (max_chunks_per_launch) and the grid is small
     // The rate does not grow steadily with the groups: 8, 32 and 64 MiB by 32, 48, 64, 96, 128 of them
     // 166, 165, 167, 164, 163; 609, 605, 623, 606, 606; 1202, 1195, 1233, 1198, 1195 us (0.5 to 4 MiB
@@ -870,8 +868,7 @@ hipError_t launch_gather_paced(const KernelGeom &g, const LaunchView &v, const L
                               layers, slot_mapping, pool, bad_flag, n_blocks, groups, done, *list);     \
     else hipExtLaunchKernelGGL((gather_paced<VEC, LD, ST>), grid, block, s.paced_lds, stream, start, stop, 0, g, v, \
                           layers, slot_mapping, pool, bad_flag, n_blocks, groups, done)
-    if (through) { LMC_GO(true, kThrough); }
-    else if (s.nt_load && s.nt_store) { LMC_GO(true, kStoreNonTemporal); }
+    if (s.nt_load && s.nt_store) { LMC_GO(true, (kLines ? kStoreThrough : kStoreNonTemporal)); }
     else if (s.nt_load) { LMC_GO(true, kStorePlain); }
     else if (s.nt_store) { LMC_GO(false, kStoreNonTemporal); }
     else { LMC_GO(false, kStorePlain); }

@@ -87,8 +87,8 @@ enum {
                                       then shows as corrupt data.  For tests. */
 #define LMC_FLAG_DIRECT 16u        /* no staging buffer and no copy engine for any call: the
                                       gather kernel writes, and the scatter kernel reads, the
-                                      pinned pool over the host link (64-128 workgroups, resident
-                                      for the length of the transfer).  Same results.
+                                      pinned pool over the host link (some tens of workgroups,
+                                      resident for the length of the transfer).  Same results.
                                       Without the flag only calls of at most 64 MiB go this
                                       way, and steps of at most 2 MiB of a layer-wise store
                                       (lmc_tune "direct_store_below" / "..._retrieve_below"). */
@@ -631,7 +631,9 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * its own streams; LMC_ERR_BUSY unless every ticket has been waited for),
  * "fail_hip_after" (for tests of the
  * error paths: the n-th HIP call the library checks from now on is not made and counts as
- * failed, once; 0 = off.  Nothing on the device goes wrong).
+ * failed, once; 0 = off.  Nothing on the device goes wrong), "expect_stores_told" (likewise for
+ * tests: LMC_OK if that many stores without staging have told the host of their end by a word in its
+ * memory, and not by an event, since the context was made, else LMC_ERR_INVAL; sets nothing).
  * Unknown key or out-of-range value: LMC_ERR_INVAL. */
 lmc_status_t lmc_tune(lmc_ctx_t *ctx, const char *key, int64_t value);
 

@@ -123,12 +123,14 @@ void reap(lmc_ctx *c) {
     c->stats.d2h_copy_last_gbps = c->d2h_guard.last_rate() * 1e-9;
     for (size_t i = 0; i < c->ops.size();) {
         Op &op = c->ops[i];
-        const bool finished = c->is_stored(op.stored_target) ||
+        const bool told = c->is_stored(op.stored_target);
+        const bool finished = told ||
                               (op.done != nullptr ? hipEventQuery(op.done) == hipSuccess : !op.pending);
         if (!finished) {
             i++;
             continue;
         }
+        c->stores_told += told;
         if (op.done != nullptr) recycle(c, op.done);
         for (hipEvent_t e : op.owned_events) recycle(c, e);
         for (int64_t s : op.slots) {
@@ -891,6 +893,8 @@ lmc_status_t lmc_tune(lmc_ctx_t *c, const char *key, int64_t value) {
     } else if (k == "fail_hip_after") {
         if (value > 0xFFFFFFFFll) return LMC_ERR_INVAL;
         c->fail_hip_after = uint32_t(value);
+    } else if (k == "expect_stores_told") {
+        return uint64_t(value) == c->stores_told ? LMC_OK : LMC_ERR_INVAL;
     } else if (k == "nt_load" && value <= 1) {
         c->shape.nt_load = value != 0;
     } else if (k == "nt_store" && value <= 1) {

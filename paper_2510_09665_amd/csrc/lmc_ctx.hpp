@@ -54,7 +54,7 @@ struct Op {
     const int64_t *slot_mapping = nullptr;  // pending store: the caller's slot mapping
     std::vector<hipEvent_t> layer_done;   // per layer: event after which the layer is in place
     std::vector<hipEvent_t> owned_events; // the distinct events behind layer_done
-    // A layer-wise retrieve that runs as one launch (scatter_steps) has words instead: the layers of
+    // A layer-wise retrieve that runs as one launch (retrieve_in_steps) has words instead: the layers of
     // step i are in place when word i of the context has reached step_target[i].
     int32_t step_layers = 0;
     std::vector<uint64_t> step_target;
@@ -205,6 +205,8 @@ struct lmc_ctx {
     // Test hook (lmc_tune "fail_hip_after"): the n-th checked HIP call from now is not made
     // and counts as failed.  Forces the error paths without any fault on the device.
     uint32_t fail_hip_after = 0;
+    // and another ("expect_stores_told"): stores that the host was told the end of by the word
+    uint64_t stores_told = 0;
     lmc_stats_t stats{};
     int32_t last_hip_error = 0;
 };

@@ -428,7 +428,7 @@ static lmc_status_t wait_quietly(lmc_ctx *c, hipStream_t stream, int word, uint6
 }
 
 // All layers of n chunks into their pages, layers_per_step at a time, by one launch on the scatter
-// stream (lmc::launch_scatter_steps); each step's layers are in place when its word says so.  *done:
+// stream (lmc::launch_scatter with planes_per_step); each step's layers are in place when its word says so.  *done:
 // whether the transfer can go this way at all.  It cannot where the launch would have to be
 // several (more chunks in scattered slots than a launch can list, "link_groups" 0), where each step
 // is to have time stamps of its own or is to be waited for, or while the stream is being captured.

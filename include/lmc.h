@@ -116,7 +116,12 @@ enum {
                                       event markers per group on the copy streams. */
 #define LMC_FLAG_TIMING 8u         /* give every gather / scatter launch a start and a stop
                                       HIP event (kernel begin / end on its own stream);
-                                      durations appear in lmc_stats_t. */
+                                      durations appear in lmc_stats_t.  With this flag or
+                                      LMC_FLAG_TRACE small retrieves run on the library's
+                                      stream, layer-wise ones without staging as a launch per
+                                      step, and lmc_wait waits for stores by event: a call
+                                      that was waited for has been counted, at some us more
+                                      than without. */
 
 /* Geometry of the engine's paged KV memory (section 5: a page is block_size tokens of
  * one layer) and the chunk length (section 5.1).  All strides are in bytes. */
@@ -577,8 +582,8 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * (consecutive tiles handed to one XCD, 0 = hardware round-robin; gathers take up to eight times as
  * many, scatters of 192 MiB and more, where the pages hold 8 KiB or rows of 1 KiB in one piece, none), "link_groups" (default
  * 64: launches that read or write the pinned pool themselves run as three quarters of that many
- * groups of 256 lanes taking tiles in turn (as many, or twice as many, where rows are no
- * multiples of 16 bytes), which is what the host link likes, two groups to a workgroup; 0 = one tile per workgroup as for launches inside HBM),
+ * groups of 256 lanes taking tiles in turn (as many, or twice as many, for stores whose rows are no
+ * multiples of 16 bytes; as many for rectangles to the host and scattered pieces from it), which is what the host link likes, two groups to a workgroup; 0 = one tile per workgroup as for launches inside HBM),
  * "link_lds_kib" (0 .. 160, default 128: KiB of LDS that each of those workgroups claims without
  * using it, so that kernels with much LDS keep off its compute unit, where their loads would
  * queue behind those of host memory: a product of 128 rows by 4096 x 4096 beside a load takes 37 us

@@ -829,7 +829,8 @@ hipError_t launch_move_v(const KernelGeom &g, const LaunchView &v, const LaunchS
     return hipGetLastError();
 }
 
-// How many of the groups asked for a launch gets where three quarters do.
+// How many of the groups asked for a launch gets where three quarters do.  A measured point, no law: the
+// rate does not grow steadily with the groups (figures at each use), and why is not known.
 uint32_t paced_part(uint32_t groups) { return std::max(1u, groups - groups / 4); }
 
 // Pages into the pool.

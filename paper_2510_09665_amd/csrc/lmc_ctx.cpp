@@ -338,17 +338,22 @@ static bool waits_block() {
 // Waits for `a`: looks at the word for as long as a store of the size that tells takes when it starts at
 // once, or a little longer, and leaves the rest to the event.  The thread stays on its core meanwhile, as
 // it does in hipEventSynchronize to the end of any wait (a store behind 50 ms of other work: 50 ms of
-// the core either way), unless the process has asked for waits that block: then the event alone is
-// waited for, asleep.
+// the core either way), unless the process has asked for waits that block: then it looks for 50 us (the
+// runtime itself for 0.7 ms) and sleeps.
 static hipError_t await(const lmc_ctx *c, const Awaited &a) {
-    if (a.stored_target != 0 && !waits_block()) {
-        const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(1500);
-        do {
+    if (a.stored_target != 0) {
+        using std::chrono::microseconds;
+        const auto begin = std::chrono::steady_clock::now();
+        bool asked = false;
+        for (auto now = begin; now < begin + microseconds(1500); now = std::chrono::steady_clock::now()) {
             for (int i = 0; i < 64; i++) {
                 if (c->is_stored(a.stored_target)) return hipSuccess;
                 __builtin_ia32_pause();
             }
-        } while (std::chrono::steady_clock::now() < until);
+            if (asked || now < begin + microseconds(50)) continue;   // the shortest stores end before they ask
+            asked = true;
+            if (waits_block()) break;
+        }
     }
     return hipEventSynchronize(a.event);
 }

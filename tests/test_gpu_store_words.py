@@ -145,8 +145,8 @@ def test_a_process_that_asked_for_blocking_waits_does_not_spin():
     assert res.returncode == 0, res.stderr[-2000:]
     cpu, took = map(float, res.stdout.split()[-2:])
     assert took > 5e-3, res.stdout
-    # looking at the word alone took 1.5 ms; going to sleep and waking up are some tens of microseconds
-    assert cpu < 0.75e-3, res.stdout
+    # the runtime's wait looks for 0.72 ms before it sleeps; 1.5 ms of looking at the word came on top, 2.2 in all
+    assert cpu < 1.45e-3, res.stdout
 
 
 def test_threads_wait_each_for_their_own_store():

@@ -1,5 +1,5 @@
-"""Scatters inside HBM of 192 MiB and more whose rows are whole lines in the pages write at system scope
-and in the plain order of the tiles: the sizes around that line, rows that qualify and rows that do
+"""Scatters inside HBM of 192 MiB and more whose pages hold 8 KiB, or rows of 1 KiB and whole lines, in one
+piece write at system scope and in the plain order of the tiles: the sizes around that line, rows that qualify and rows that do
 not, on two streams at once, against the pages built by indexing."""
 import numpy as np
 import pytest

@@ -861,7 +861,7 @@ lmc_status_t lmc_tune(lmc_ctx_t *c, const char *key, int64_t value) {
     } else if (k == "direct_store_below") {
         c->direct_store_below = value;
     } else if (k == "direct_retrieve_below") {
-        c->direct_retrieve_below = value;
+        c->direct_retrieve_below = c->direct_steps_below = c->direct_beside_store_below = value;
     } else if (k == "xcd_run") {
         if (value > (1 << 20)) return LMC_ERR_INVAL;
         c->shape.xcd_run = uint32_t(value);

@@ -129,22 +129,39 @@ struct lmc_ctx {
     std::vector<uint64_t> evicted;  // LMC_FLAG_EVICT_LRU: ids evicted and not yet drained
     // Bulk calls that move at most this many bytes skip staging and the copy engine (the
     // kernel itself crosses the link).  Small transfers are bound by launch latencies, which
-    // one launch instead of kernel, event, copy, event halves; up to 64 MiB the single
-    // launch is still 2-5 % faster and is over within a millisecond or so, beyond that
-    // the staged pipeline keeps the compute units free.  0 = never.
-    // Layer-wise retrieves have the same line: the steps of a small transfer are shorter than
-    // the chain of calls that staging takes for each.  Llama-3-8B shape, one layer a step, from the
-    // first call to an idle device, 32 and 64 MiB: 970 and 1709 us staged, 811 and 1531 direct; with
-    // the consumer's products between the steps 5174 and 5842 against 4681 and 4999; 128 MiB: 5403
-    // against 6449.
+    // one launch instead of kernel, event, copy, event halves; beyond the line the staged pipeline
+    // keeps the compute units free.  0 = never.
+    // Stores: up to 64 MiB the single launch is 2-7 % faster and over within a millisecond or so.  At 96
+    // and 128 MiB it is 3-4 % faster, and products of 512 to 4096 rows beside it, averaged over the four
+    // hardware queues they can be in, take 9-15 % longer than beside a staged one.
     // A layer-wise store's step goes this way if, besides, it moves at most 2 MiB: its kernels
     // slow the producer's own down while they last, which the calls saved make up for only
     // there.  One layer a step, 32 and 64 MiB: 1213 and 1612 us staged, 729 and 1346 direct; beside
     // the producer's products, 32 MiB in steps of 1, 2, 4, 8 MiB: 5682, 5170, 4914, 4588 against 5059,
     // 5005, 4945, 4874; 64 MiB in steps of 2, 4, 8 MiB: 6486, 4958, 4741 against 5736, 5700, 5570.
     int64_t direct_store_below = int64_t(64) << 20;
-    int64_t direct_retrieve_below = int64_t(64) << 20;
     static constexpr int64_t kDirectStoreStep = int64_t(2) << 20;
+    // Retrieves: up to 256 MiB.  Bulk, 96, 128, 192, 256 MiB: 1857, 2444, 3616, 4793 us staged, 1757, 2340,
+    // 3502, 4684 direct.  What else runs on the GPU loses a part of the compute units to the kernel, but a
+    // staged retrieve makes two hardware queues besides the caller's stand still for as long as it takes,
+    // the copy stream's and the scatter stream's, a direct one only the latter.  128 MiB beside products of 128, 512,
+    // 1536, 4096 rows by 4096 x 4096 of another stream, all of which take 3313, 3238, 3447, 3457 us alone: the
+    // stream in a queue that nothing holds up 3588, 3267, 3259, 4253 (staged) against 3601, 3825, 3924, 4119;
+    // in the copy stream's 5727, 5486, 5676, 5806 against 3581, 3861, 3957, 4170; in the scatter stream's about
+    // 5700 either way; over the four queues 4663, 4381, 4475, 5046 against 4113, 4265, 4368, 4555.
+    // Layer by layer a stage costs 10 us between two copies and 5-7 more for a rectangle besides, so
+    // steps of at most 8 MiB go this way up to twice as much.  The consumer's products between the
+    // layers, 128 MiB in steps of 4 MiB: 9274, 9100, 11231, 14595 staged, 8343, 8996, 10856, 14459 direct with
+    // its stream in the free queue, about 10700, 10900, 13300, 16800 against 8400, 9000, 11000, 14700 in the two copy
+    // streams' queues; 256 MiB in steps of 16: 8997, 8939, 10719, 14104 against 9039, 10054, 11962, 16048 and about
+    // 12800, 13200, 15800, 19300 against 8900, 10100, 12100, 15900; 480 MiB in steps of 6: 15542, 15638, 20038, 28485
+    // against 13938, 16004, 20283, 29657 and 22000, 23600, 28000, 36900 against 13900, 16000, 20400, 29600.
+    // Beside a store that is under way the line is at 64 MiB: a kernel that reads the link while copies write
+    // it gets half of its rate (128 MiB behind a store of 768 MiB 5.3 ms, staged 3.4; 64 MiB 4.2 and 2.0).
+    // lmc_tune "direct_retrieve_below" sets all three.
+    int64_t direct_retrieve_below = int64_t(256) << 20, direct_steps_below = int64_t(512) << 20,
+            direct_beside_store_below = int64_t(64) << 20;
+    static constexpr int64_t kDirectRetrieveStep = int64_t(8) << 20;
     int64_t chunk_bytes = 0;
     int64_t n_pool_slots = 0;
     uint8_t *pool = nullptr;

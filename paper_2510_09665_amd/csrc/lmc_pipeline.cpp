@@ -496,6 +496,15 @@ static bool launches_on_caller(const lmc_ctx *c, hipStream_t user) {
     return ok;
 }
 
+// Does a retrieve of this size skip staging (lmc_ctx::direct_retrieve_below)?
+static bool retrieves_directly(lmc_ctx *c, int64_t n_chunks, int32_t layers_per_step) {
+    const int64_t bytes = n_chunks * c->chunk_bytes;
+    const int64_t step = bytes / c->cfg.geom.num_layers * layers_per_step;
+    const bool small_steps = layers_per_step > 0 && step <= lmc_ctx::kDirectRetrieveStep;
+    if (bytes > (small_steps ? std::max(c->direct_steps_below, c->direct_retrieve_below) : c->direct_retrieve_below)) return false;
+    return bytes <= c->direct_beside_store_below || !other_direction_busy(c, false);
+}
+
 // Retrieve, bulk (layers_per_step == 0) or layer by layer (paper section 5.2).
 static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunks,
                          const int64_t *slot_mapping, void *const *kv_layers, void *user_stream,
@@ -517,7 +526,7 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     hipStream_t user = static_cast<hipStream_t>(user_stream);
     const lmc_kv_geom_t &geom = c->cfg.geom;
     const int64_t CT = geom.chunk_tokens;
-    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 || n_chunks * c->chunk_bytes <= c->direct_retrieve_below;
+    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 || retrieves_directly(c, n_chunks, layers_per_step);
     const bool on_caller = n_chunks > 0 && direct && layers_per_step == 0 && launches_on_caller(c, user);
     hipStream_t scatters = on_caller ? user : c->s_scatter;
     // the pages may still be in use, and the slot mapping still be on its way, by work

@@ -1,0 +1,71 @@
+"""Which retrieves skip staging by their size: up to 256 MiB, up to 512 MiB layer by layer in steps of
+at most 8 MiB, up to 64 MiB beside a store that is under way, and up to the line that is set where
+one is.  At each line, the last size on this side and the first on the other: the trace says
+whether copies into staging were made, and the pages hold the same bytes either way."""
+import numpy as np
+import pytest
+
+from paper_2510_09665_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+CHUNKS = 65
+# chunks of 8 MiB, 128 KiB a layer
+G = W.KVGeometry(L=64, P=2, H=1, D=32, e=2, BS=32, NB=2 * CHUNKS * 32, CT=1024)
+
+
+@pytest.fixture(scope="module")
+def kv():
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    pages = torch.empty((G.L, G.layer_bytes // 8), dtype=torch.int64, device="cuda").random_(generator=gen)
+    blocks = np.split(np.random.default_rng(7).permutation(G.NB), 2)
+    t = np.arange(CHUNKS * G.CT)
+    slots = [torch.from_numpy(b[t // G.BS].astype(np.int64) * G.BS + t % G.BS).cuda() for b in blocks]
+    return pages, [torch.from_numpy(b).cuda() for b in blocks], slots
+
+
+@pytest.mark.parametrize("chunks,step,store,line,direct", [
+    (32, 0, False, None, True), (33, 0, False, None, False),
+    (32, 64, False, None, True), (33, 64, False, None, False),              # one step: as bulk
+    (64, 1, False, None, True), (65, 1, False, None, False),                # 512 MiB, steps of 8 MiB
+    (33, 1, False, None, True), (33, 2, False, None, False),                # steps of 8.25 MiB
+    (8, 0, True, None, True), (9, 0, True, None, False),
+    (8, 1, True, None, True), (9, 1, True, None, False),
+    (2, 0, False, 16, True), (3, 0, False, 16, False), (3, 1, False, 16, False), (1, 1, False, 0, False),
+    (33, 0, False, 264, True), (9, 0, True, 264, True),
+])
+def test_lines(kv, chunks, step, store, line, direct):
+    import torch
+    from paper_2510_09665_amd import lmc
+    pages, blocks, slots = kv
+    per, n = G.CT // G.BS, chunks * G.CT
+    layers = [p.view(torch.uint8) for p in pages.unbind(0)]
+    for l in layers:
+        W.page_view(G, l)[:, blocks[1]] = 0x5A
+    torch.cuda.synchronize()
+    with lmc.Context(G, (chunks + 1) * G.chunk_bytes, staging_chunks=8) as c:
+        ids = np.arange(1, chunks + 1, dtype=np.uint64)
+        c.store(layers, slots[0][:n], ids)
+        c.wait()
+        if line is not None:
+            c.tune("direct_retrieve_below", line * MIB)
+        c.tune("trace", 1)
+        if store:      # under way until its last layers are handed in
+            other = c.store_begin(slots[0][:G.CT], np.array([1 << 40], dtype=np.uint64))
+        if step:
+            t = c.retrieve_layerwise(ids, slots[1][:n], layers, step)
+        else:
+            t = c.retrieve(ids, slots[1][:n], layers)
+        while not c.test(t):
+            pass
+        if store:
+            c.store_layers(other, 0, G.L, layers)
+        c.wait()
+        copies = [r for r in c.trace_read()[0] if r["stage"] == lmc.LMC_STAGE_H2D]
+        assert (not copies) == direct
+    for l in layers:
+        v = W.page_view(G, l)
+        assert torch.equal(v[:, blocks[1][:chunks * per]], v[:, blocks[0][:chunks * per]])
+        assert (v[:, blocks[1][chunks * per:]] == 0x5A).all()

@@ -90,8 +90,7 @@ enum {
                                       pinned pool over the host link (some tens of workgroups,
                                       resident for the length of the transfer).  Same results.
                                       Without the flag only stores of at most 64 MiB and
-                                      retrieves of at most 256 MiB go this way, and steps of at
-                                      most 2 MiB of a layer-wise store (lmc_tune
+                                      retrieves of at most 256 MiB go this way (lmc_tune
                                       "direct_store_below" / "..._retrieve_below"). */
 #define LMC_FLAG_EVICT_LRU 32u     /* a new chunk that finds the pool full takes the slot of
                                       the least recently used chunk that is not pinned, has
@@ -606,10 +605,11 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * restarts its clock), "direct_store_below" / "direct_retrieve_below" (bytes, default 64 and
  * 256 MiB: an lmc_store with at most that many new bytes, or an lmc_retrieve /
  * lmc_retrieve_batch / lmc_retrieve_layerwise of at most that many bytes, goes the
- * LMC_FLAG_DIRECT way: one launch instead of kernel, event, copy, event; an lmc_store_layers
- * call does if its store has at most that many new bytes and the call itself moves at most
- * 2 MiB; 0 = never.  As long as the second is not set, layer-wise retrieves in steps of at most 8 MiB
- * go that way up to 512 MiB, and any retrieve up to 64 MiB only while a store is under way), "scatter_order" (default 0; 1 or 2:
+ * LMC_FLAG_DIRECT way: one launch instead of kernel, event, copy, event; the
+ * lmc_store_layers calls of a store with at most that many new bytes do; 0 = never.  As long as
+ * the first is not set, lmc_store_layers calls that move at most 2 MiB go that way in stores of up to
+ * 256 MiB; as long as the second is not, layer-wise retrieves in steps of at most 8 MiB up to
+ * 512 MiB, and any retrieve up to 64 MiB only while a store is under way), "scatter_order" (default 0; 1 or 2:
  * scatter launches visit their rows in ascending slot order, built on the device, so that
  * the writes sweep every plane once; 1 = only launches with at least "ordered_min_pages"
  * pages that cover at least one block in "ordered_min_density_inv" of a plane, 2 = every

@@ -859,7 +859,7 @@ lmc_status_t lmc_tune(lmc_ctx_t *c, const char *key, int64_t value) {
     } else if (k == "edge_chunks") {
         c->edge_chunks = value;
     } else if (k == "direct_store_below") {
-        c->direct_store_below = value;
+        c->direct_store_below = c->direct_store_steps_below = value;
     } else if (k == "direct_retrieve_below") {
         c->direct_retrieve_below = c->direct_steps_below = c->direct_beside_store_below = value;
     } else if (k == "xcd_run") {

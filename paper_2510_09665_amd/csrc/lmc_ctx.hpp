@@ -134,12 +134,19 @@ struct lmc_ctx {
     // Stores: up to 64 MiB the single launch is 2-7 % faster and over within a millisecond or so.  At 96
     // and 128 MiB it is 3-4 % faster, and products of 512 to 4096 rows beside it, averaged over the four
     // hardware queues they can be in, take 9-15 % longer than beside a staged one.
-    // A layer-wise store's step goes this way if, besides, it moves at most 2 MiB: its kernels
-    // slow the producer's own down while they last, which the calls saved make up for only
-    // there.  One layer a step, 32 and 64 MiB: 1213 and 1612 us staged, 729 and 1346 direct; beside
-    // the producer's products, 32 MiB in steps of 1, 2, 4, 8 MiB: 5682, 5170, 4914, 4588 against 5059,
-    // 5005, 4945, 4874; 64 MiB in steps of 2, 4, 8 MiB: 6486, 4958, 4741 against 5736, 5700, 5570.
-    int64_t direct_store_below = int64_t(64) << 20;
+    // A layer-wise store's steps go this way up to the same line, and steps of at most 2 MiB up to 256 MiB:
+    // a stage costs a step 10 us of the one copy engine that serves copies to the host, besides the calls.
+    // Alone, 32 MiB in steps of 4, 8, 16 MiB: 690, 766, 825 us staged, 660, 618, 612 direct; 64 MiB in steps of
+    // 4, 16, 32: 1434, 1320, 1253 and 1275, 1209, 1204; 80, 160 MiB in steps of 1, 2: 2300-3100, 3800 and 1744,
+    // 3222 (and while the runtime's copies to the host are slow, see copy_kernel, 5977 us for the 64 MiB in steps
+    // of 4 and 16132 for the 160 MiB).  With the producer's products of 128, 512, 1536, 4096 rows before
+    // every step, averaged over the four hardware queues its stream can be in: 64 MiB in steps of 4 MiB 9039, 9036,
+    // 10858, 14797 staged, 8678, 9060, 10866, 15002 direct; in steps of 16 8882, 8970, 10923, 14869 and 8690, 8984,
+    // 10910, 14948; 160 MiB in steps of 2 15583, 15594, 19374, 28685 and 14302, 15279, 19751, 28909.  Larger
+    // stores in larger steps would lose: 192 MiB in steps of 6 10085, 10105, 11891, 15773 and 9469, 10510, 12522,
+    // 16840, 320 MiB in steps of 4 16444, 16448, 20142, 29586 and 15092, 16886, 20496, 31202.
+    // lmc_tune "direct_store_below" sets both lines.
+    int64_t direct_store_below = int64_t(64) << 20, direct_store_steps_below = int64_t(256) << 20;
     static constexpr int64_t kDirectStoreStep = int64_t(2) << 20;
     // Retrieves: up to 256 MiB.  Bulk, 96, 128, 192, 256 MiB: 1857, 2444, 3616, 4793 us staged, 1757, 2340,
     // 3502, 4684 direct.  What else runs on the GPU loses a part of the compute units to the kernel, but a

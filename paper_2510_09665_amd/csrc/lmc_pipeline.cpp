@@ -942,8 +942,8 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     const uint64_t layer_bytes = uint64_t(geom.num_planes) * c->kg.plane_bytes;
     const int64_t cap = layer_group_chunks(c, c->store_ring, view, int64_t(op->new_chunk.size()));
     const int64_t n_new = int64_t(op->new_chunk.size());
-    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 ||
-                        (n_new * c->chunk_bytes <= c->direct_store_below &&
+    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 || n_new * c->chunk_bytes <= c->direct_store_below ||
+                        (n_new * c->chunk_bytes <= c->direct_store_steps_below &&
                          n_new * int64_t(layer_bytes) * n_layers <= lmc_ctx::kDirectStoreStep);
     // Steps take the two copy streams in turn (as the steps of a layer-wise retrieve do):
     // between two copies of one stream the runtime leaves the link idle for some 20 us,

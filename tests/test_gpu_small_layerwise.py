@@ -1,5 +1,4 @@
-"""Layer-wise calls that skip staging by their size: retrieves of at most 64 MiB, and steps of at
-most 2 MiB of a store of at most 64 MiB (one store may mix such steps with staged ones).  Bytes
+"""Layer-wise calls that skip staging by their size.  Bytes
 against the CPU oracle; every layer is read as soon as its wait returns."""
 import numpy as np
 import pytest
@@ -27,7 +26,6 @@ def _setup(n, seed, name="llama3_8b", **kw):
     return g, src, dst, want, slots_to_device(slots), slots_to_device(tau), np.arange(1, 1 + n, dtype=np.uint64)
 
 
-# steps of 2 MiB (two chunks, one layer) go direct, larger ones through staging
 @pytest.mark.parametrize("steps", [(1,) * 8, (1, 2, 1, 3, 1), (3, 1, 4), (2, 2, 2, 1, 1), (8,)])
 @pytest.mark.parametrize("timing", [False, True])
 def test_store_steps_of_any_size(steps, timing):

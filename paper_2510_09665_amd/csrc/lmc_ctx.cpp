@@ -124,8 +124,8 @@ void reap(lmc_ctx *c) {
     for (size_t i = 0; i < c->ops.size();) {
         Op &op = c->ops[i];
         const bool told = c->is_stored(op.stored_target);
-        const bool finished = told ||
-                              (op.done != nullptr ? hipEventQuery(op.done) == hipSuccess : !op.pending);
+        const bool finished = told || c->is_loaded(op.loaded_target) ||
+                              (op.done != nullptr ? hipEventQuery(op.done) == hipSuccess : !op.pending && op.loaded_target == 0);
         if (!finished) {
             i++;
             continue;
@@ -250,6 +250,10 @@ bool other_direction_busy(lmc_ctx *c, bool for_store) {
         const bool is_store = o.pending || o.final_stream == c->s_d2h || o.final_stream == c->s_d2h2 || o.final_stream == c->s_gather;
         if (is_store == for_store) continue;
         if (o.pending) return true;
+        if (o.loaded_target != 0) {
+            if (!c->is_loaded(o.loaded_target)) return true;
+            continue;
+        }
         if (o.done != nullptr && hipEventQuery(o.done) != hipSuccess) {
             (void)hipGetLastError();
             return true;
@@ -320,12 +324,12 @@ void end_use(lmc_ctx *c, const uint64_t *ids, int64_t n) {
     }
 }
 
-// What a thread waits for: an event, and for a store that tells the host itself (Op::stored_target)
-// the value of the context's stored_host.
+// What a thread waits for: an event, and for a transfer that tells the host itself the value of its word.
 struct Awaited {
     hipEvent_t event;
-    uint64_t stored_target;
+    uint64_t stored_target, loaded_target;
 };
+static Awaited end_of(const Op &o) { return Awaited{o.done, o.stored_target, o.loaded_target}; }
 
 // Does the process want its threads to sleep while they wait for the GPU?
 static bool waits_block() {
@@ -341,13 +345,13 @@ static bool waits_block() {
 // the core either way), unless the process has asked for waits that block: then it looks for 50 us (the
 // runtime itself for 0.7 ms) and sleeps.
 static hipError_t await(const lmc_ctx *c, const Awaited &a) {
-    if (a.stored_target != 0) {
+    if (a.stored_target != 0 || a.loaded_target != 0) {
         using std::chrono::microseconds;
         const auto begin = std::chrono::steady_clock::now();
         bool asked = false;
         for (auto now = begin; now < begin + microseconds(1500); now = std::chrono::steady_clock::now()) {
             for (int i = 0; i < 64; i++) {
-                if (c->is_stored(a.stored_target)) return hipSuccess;
+                if (c->is_stored(a.stored_target) || c->is_loaded(a.loaded_target)) return hipSuccess;
                 __builtin_ia32_pause();
             }
             if (asked || now < begin + microseconds(50)) continue;   // the shortest stores end before they ask
@@ -388,7 +392,7 @@ static lmc_status_t sync_unlocked(lmc_ctx *c, std::unique_lock<std::mutex> &lock
 // the copies of the chunk's group, or else the store's last event, goes to *ev (no event:
 // nothing to wait for).  LMC_ERR_MISS / LMC_ERR_BUSY as lmc_get_host.
 static lmc_status_t pending_fill(lmc_ctx *c, uint64_t id, int64_t *slot_out, Awaited *ev) {
-    *ev = Awaited{nullptr, 0};
+    *ev = Awaited{nullptr, 0, 0};
     const int64_t s = c->index.find(id);
     if (s < 0) return LMC_ERR_MISS;
     *slot_out = s;
@@ -397,7 +401,7 @@ static lmc_status_t pending_fill(lmc_ctx *c, uint64_t id, int64_t *slot_out, Awa
         const Op *o = find_op(c, m.ready_ticket);
         if (o != nullptr && o->pending) return LMC_ERR_BUSY;
         if (o != nullptr)
-            *ev = m.ready_event != nullptr ? Awaited{static_cast<hipEvent_t>(m.ready_event), 0} : Awaited{o->done, o->stored_target};
+            *ev = m.ready_event != nullptr ? Awaited{static_cast<hipEvent_t>(m.ready_event), 0, 0} : end_of(*o);
     }
     return LMC_OK;
 }
@@ -540,11 +544,12 @@ lmc_status_t lmc_create(const lmc_config_t *cfg, lmc_ctx_t **ctx_out) {
                 c->words = nullptr;
                 return fail(LMC_ERR_NOMEM);
             }
-            if (hipHostMalloc(reinterpret_cast<void **>(&c->stored_host), 64, hipHostMallocMapped) != hipSuccess) {
+            constexpr size_t kHostBytes = 2 * lmc_ctx::kLoadedAt * sizeof(uint64_t);
+            if (hipHostMalloc(reinterpret_cast<void **>(&c->stored_host), kHostBytes, hipHostMallocMapped) != hipSuccess) {
                 c->stored_host = nullptr;
                 return fail(LMC_ERR_NOMEM);
             }
-            std::memset(c->stored_host, 0, 64);
+            std::memset(c->stored_host, 0, kHostBytes);
             if (hipHostGetDevicePointer(reinterpret_cast<void **>(&c->stored_dev), c->stored_host, 0) != hipSuccess)
                 return fail(LMC_ERR_HIP);
             if (hipMemset(c->words, 0, kBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) return fail(LMC_ERR_HIP);
@@ -625,13 +630,18 @@ lmc_status_t lmc_wait(lmc_ctx_t *c, uint64_t ticket) {
     // the older ones: the newest event of every such stream is waited for.
     std::vector<hipStream_t> streams;
     std::vector<Awaited> last;
-    for (const Op &o : c->ops) {
+    for (Op &o : c->ops) {
         if (o.ticket > ticket) continue;
         if (o.pending) {
             // a layer-wise store still short of layers cannot be waited for; when it is
             // merely older than the ticket asked for, it is left out
             if (everything || o.ticket == ticket) return LMC_ERR_BUSY;
             continue;
+        }
+        if (c->is_loaded(o.loaded_target)) continue;
+        if (o.loaded_target != 0 && o.done == nullptr) {
+            const lmc_status_t rc = scatters_after_loads(c);
+            if (rc != LMC_OK) return rc;
         }
         if (o.done == nullptr) continue;
         // a layer-wise store ends when its last layer is submitted, perhaps behind a newer
@@ -640,9 +650,9 @@ lmc_status_t lmc_wait(lmc_ctx_t *c, uint64_t ticket) {
                                      : size_t(std::find(streams.begin(), streams.end(), o.final_stream) - streams.begin());
         if (i == streams.size()) {
             streams.push_back(o.layerwise ? nullptr : o.final_stream);
-            last.push_back(Awaited{o.done, o.stored_target});
+            last.push_back(end_of(o));
         } else {
-            last[i] = Awaited{o.done, o.stored_target};   // c->ops is in ticket order, and a stream finishes in order
+            last[i] = end_of(o);   // c->ops is in ticket order, and a stream finishes in order
         }
     }
     const lmc_status_t rc = sync_unlocked(c, lock, last);

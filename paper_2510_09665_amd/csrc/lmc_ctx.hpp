@@ -40,7 +40,9 @@ struct Op {
     uint64_t ticket = 0;
     hipEvent_t done = nullptr;       // null: nothing enqueued (yet) for this ticket
     hipStream_t final_stream = nullptr;  // the library stream `done` was recorded on
-    uint64_t stored_target = 0;          // not 0: finished when the context's stored_host has reached this
+    // Not 0: finished when the word of host memory has reached this.  A load that tells (its kernels run on the
+    // caller's own stream) has no event until somebody has to wait for it (scatters_after_loads).
+    uint64_t stored_target = 0, loaded_target = 0;
     bool on_caller = false;              // its kernels run on the caller's own stream ...
     hipStream_t caller = nullptr;        // ... this one
     std::vector<int64_t> slots;      // pool slots whose in-flight count this op holds
@@ -196,8 +198,14 @@ struct lmc_ctx {
     // retrieve reach the staging buffer, and as it ends.
     static constexpr int kBulkWord = LMC_MAX_LAYERS, kStoreWord = LMC_MAX_LAYERS + 1, kFilledWord = LMC_MAX_LAYERS + 2,
                          kDoneWord = LMC_MAX_LAYERS + 3, kWords = LMC_MAX_LAYERS + 4;
-    uint64_t *stored_host = nullptr, *stored_dev = nullptr;   // one word of host memory and its address on the GPU
+    // two words of host memory, kLoadedAt words apart, and their address on the GPU
+    static constexpr int kLoadedAt = 8;
+    uint64_t *stored_host = nullptr, *stored_dev = nullptr;
     bool is_stored(uint64_t target) const { return target != 0 && __atomic_load_n(stored_host, __ATOMIC_ACQUIRE) >= target; }
+    // A bulk load that runs on the caller's stream tells the host likewise, at kBulkWord and the second word: nothing
+    // of the library's then waits for it, on no stream, unless something else is to use the scatter stream meanwhile
+    // or a thread waits for the load.
+    bool is_loaded(uint64_t target) const { return target != 0 && __atomic_load_n(stored_host + kLoadedAt, __ATOMIC_ACQUIRE) >= target; }
     uint64_t *words = nullptr;
     uint64_t word_target[kWords] = {};
     // May a stream be made to wait for a word (lmc_tune "value_waits")?  The runtime waits for a value,
@@ -302,6 +310,7 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list = nullptr,
                           hipEvent_t stop = nullptr, lmc::Arrivals *arrivals = nullptr, uint32_t planes_per_step = 0,
                           lmc::HostWord *told = nullptr);
+lmc_status_t scatters_after_loads(lmc_ctx *c);
 // lmc_streams.cpp
 lmc_status_t shares_a_queue(lmc_ctx *c, hipStream_t busy, bool by_kernel, hipStream_t other, uint8_t *devbuf,
                             uint64_t nbytes, hipEvent_t a0, hipEvent_t a1, hipEvent_t k1, bool *shares);

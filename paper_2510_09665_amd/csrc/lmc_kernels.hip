@@ -101,13 +101,15 @@ __device__ __forceinline__ void arrive(uint64_t word_at) {
     if ((threadIdx.x & 63u) == 0)
         (void)__hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)word_at, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-// The same for the host: the last wavefront to arrive, which brings the word to `target`, writes that
-// to a word in host memory.
-__device__ __forceinline__ void arrive_and_tell(uint64_t word_at, uint64_t target, uint64_t host_at) {
+// The same for a whole workgroup, at the end of a kernel, and for the host too: the last one to arrive, which brings
+// the word to `target`, writes that to a word in host memory.  One count for each workgroup: by 192
+// wavefronts one address in memory is a microsecond longer at work.
+__device__ __forceinline__ void arrive_and_tell(const HostWord &told) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if ((threadIdx.x & 63u) == 0 &&
-        __hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)word_at, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1 == target)
-        __hip_atomic_store((LMC_GLOBAL uint64_t *)host_at, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __syncthreads();
+    if (threadIdx.x == 0 &&
+        __hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)told.word, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1 == told.target)
+        __hip_atomic_store((LMC_GLOBAL uint64_t *)told.host, told.target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Keeps a wave-uniform value in scalar registers from this point on.
@@ -400,10 +402,9 @@ __global__ __launch_bounds__(kPacedThreads) void gather_paced(const KernelGeom g
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
     const uint32_t step = pin(groups), end = pin(n_blocks), lane = threadIdx.x % kThreads;
     const uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) * gridDim.x + blockIdx.x;
-    if (first >= step) return;                       // an odd number of groups leaves a half without work
-    for (uint32_t blk = first; blk < end; blk += step)
+    for (uint32_t blk = first < step ? first : end; blk < end; blk += step)   // an odd number of groups leaves a half without work
         gather_tile_in_turn<VEC, NT_LD, ST>(a, layers, blk, lane, nullptr);
-    if (ST == kStoreThrough && told.word != nullptr) arrive_and_tell(uint64_t(told.word), told.target, uint64_t(told.host));
+    if (ST == kStoreThrough && told.word != nullptr) arrive_and_tell(told);
 }
 
 // The same for chunks in any pool slots (a fragmented pool, a batch of requests): one launch
@@ -419,10 +420,9 @@ __global__ __launch_bounds__(kPacedThreads) void gather_listed(const KernelGeom 
     const TileArgs a = fetch_args<VEC>(g, view, slot_mapping, staging, bad_flag);
     const uint32_t step = pin(groups), end = pin(n_blocks), lane = threadIdx.x % kThreads;
     const uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads) * gridDim.x + blockIdx.x;
-    if (first >= step) return;                       // an odd number of groups leaves a half without work
-    for (uint32_t blk = first; blk < end; blk += step)
+    for (uint32_t blk = first < step ? first : end; blk < end; blk += step)   // an odd number of groups leaves a half without work
         gather_tile_in_turn<VEC, NT_LD, ST>(a, layers, blk, lane, &list);
-    if (ST == kStoreThrough && told.word != nullptr) arrive_and_tell(uint64_t(told.word), told.target, uint64_t(told.host));
+    if (ST == kStoreThrough && told.word != nullptr) arrive_and_tell(told);
 }
 
 // One lane's piece of a tile of a scatter from the pool: where it comes from, and what its
@@ -471,7 +471,8 @@ template <int VEC, typename List>
 __global__ __launch_bounds__(kPacedThreads) void scatter_paced(const KernelGeom g, const LaunchView view,
                                                           const StepView steps, const LayerPtrs layers,
                                                           const int64_t *__restrict__ slot_mapping, const uint8_t *pool,
-                                                          int32_t *bad_flag, uint64_t *words, const List list) {
+                                                          int32_t *bad_flag, uint64_t *words, const HostWord told_host,
+                                                          const List list) {
     typedef typename VecOf<VEC>::type V;
     const uint32_t half = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads), lane = threadIdx.x % kThreads;
     TileArgs a = fetch_args<VEC>(g, view, slot_mapping, const_cast<uint8_t *>(pool), bad_flag);
@@ -482,7 +483,7 @@ __global__ __launch_bounds__(kPacedThreads) void scatter_paced(const KernelGeom 
     uint32_t blk = half * gridDim.x + blockIdx.x, step = 0, told = 0;   // told: steps this wavefront has counted itself off at
     uint32_t blocks = n_steps > 1 ? pin(steps.n_blocks) : last_blocks;
     if (n_steps == 1) a.by_lp = by_last;
-    if (blk >= groups) return;                       // an odd number of groups leaves a half without work
+    const bool works = blk < groups;                 // an odd number of groups leaves a half without work
     // goes on to the step that tile blk lies in; false behind the last
     auto in_step = [&]() {
         while (blk >= blocks) {
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(kPacedThreads) void scatter_paced(const KernelGeom 
         }
         return true;
     };
-    if (in_step()) {
+    if (works && in_step()) {
         Piece p = find_piece<VEC>(a, layers, blk, lane, list);
         asm volatile("" : "+v"(p.slot));   // arrived: the loop then has no load of its own to wait for at its head
         for (bool more = true; more;) {
@@ -522,8 +523,9 @@ __global__ __launch_bounds__(kPacedThreads) void scatter_paced(const KernelGeom 
             p = next;
         }
     }
-    if (words_at != 0)
+    if (words_at != 0 && works)
         for (; told < n_steps; told++) arrive(words_at + told * kWordStride);
+    if (told_host.word != nullptr) arrive_and_tell(told_host);
 }
 
 // ---- scatter in the order of the destination ---------------------------------------------
@@ -861,7 +863,7 @@ hipError_t launch_gather_paced(const KernelGeom &g, const LaunchView &v, const L
     HostWord done{nullptr, nullptr, 0};
     if (told != nullptr && through) {
         done = *told;
-        done.target += groups * (kThreads / 64);
+        done.target += grid.x;
     }
 #define LMC_GO(LD, ST)                                                                                  \
     if (list != nullptr)                                                                                \
@@ -900,15 +902,17 @@ hipError_t launch_scatter_paced(const KernelGeom &g, const LaunchView &v, const 
     // 64 MiB by 32, 48, 64, 96 groups: 1189, 1182, 1183, 1227 us; 12 MiB by 48, 64: 225, 225; 0.5 MiB alike
     steps.groups = uint32_t(std::min<uint64_t>(tiles, paced_part(s.paced_groups)));
     const dim3 grid((steps.groups + 1) / 2), block(kPacedThreads);
-    uint64_t *words = arrivals != nullptr ? arrivals->words : nullptr;
+    uint64_t *words = arrivals != nullptr && arrivals->host == nullptr ? arrivals->words : nullptr;
+    HostWord told{nullptr, nullptr, 0};
+    if (arrivals != nullptr && arrivals->host != nullptr) told = HostWord{arrivals->words, arrivals->host, arrivals->reached + grid.x};
     if (list != nullptr)
         hipExtLaunchKernelGGL((scatter_paced<VEC, ChunkList>), grid, block, s.paced_lds, stream, start, stop, 0, g, step, steps, layers,
-                              slot_mapping, pool, bad_flag, words, *list);
+                              slot_mapping, pool, bad_flag, words, told, *list);
     else
         hipExtLaunchKernelGGL((scatter_paced<VEC, BackToBack>), grid, block, s.paced_lds, stream, start, stop, 0, g, step, steps, layers,
-                              slot_mapping, pool, bad_flag, words, BackToBack{});
+                              slot_mapping, pool, bad_flag, words, told, BackToBack{});
     const hipError_t e = hipGetLastError();
-    if (arrivals != nullptr && e == hipSuccess) arrivals->count = steps.groups * (kThreads / 64);
+    if (arrivals != nullptr && e == hipSuccess) arrivals->count = arrivals->host != nullptr ? grid.x : steps.groups * (kThreads / 64);
     return e;
 }
 
@@ -1008,6 +1012,7 @@ hipError_t launch_scatter(const KernelGeom &g, const LaunchView &v, const Launch
     if (list != nullptr && n_chunks > uint32_t(kMaxListed)) return hipErrorInvalidValue;
     if (s.paced_groups == 0 && (list != nullptr || arrivals != nullptr || planes_per_step != 0)) return hipErrorInvalidValue;
     const uint32_t planes = planes_per_step == 0 ? v.by_n_lp.d : std::min(planes_per_step, v.by_n_lp.d);
+    if (arrivals != nullptr && arrivals->host != nullptr && planes != v.by_n_lp.d) return hipErrorInvalidValue;
     return by_vec(g, [&](auto vec) {
         return s.paced_groups > 0
                    ? launch_scatter_paced<vec.value>(g, v, s, planes, layers, slot_mapping, n_chunks, staging,

@@ -95,13 +95,17 @@ struct ChunkList {
 // Words in device memory, kWordStride bytes apart, one for each step of a scatter from the pool:
 // each wavefront of the launch adds one to a step's word when its stores of that step have reached
 // memory, so that a queue can wait for the word's value instead of for an event of the kernel.
-// count: receives how many wavefronts will.
+// count: receives how many will.  With host (launches of one step only) each workgroup adds one instead, and
+// the one that brings the word, which will have reached `reached` before the launch, to its last value
+// writes that to a word of host memory.
 struct Arrivals {
     uint64_t *words;
     uint32_t count;
+    uint64_t *host;
+    uint64_t reached;
 };
 constexpr uint32_t kWordStride = 64;
-// Where a gather into the pool tells the host that its last store has reached the pool: the wavefronts
+// Where a gather into the pool tells the host that its last store has reached the pool: the workgroups
 // count themselves off at `word`, and the one that brings it to `target` writes that to `host`.
 // Handed to a launch, target is what the word will have reached before it; it receives what it will
 // have reached behind it, or stays as it is where the launch cannot tell (its stores do not go

@@ -255,8 +255,8 @@ static lmc_status_t finish_op(lmc_ctx *c, Op &&op, hipStream_t last_stream, bool
             op.done = nullptr;
             HIPCHK(c, e);
         }
-        op.final_stream = last_stream;
     }
+    op.final_stream = last_stream;
     if (ticket_out) *ticket_out = op.ticket;
     c->ops.push_back(std::move(op));
     return LMC_OK;
@@ -401,6 +401,36 @@ static lmc_status_t wait_for_word(lmc_ctx *c, hipStream_t stream, int word, uint
     return LMC_OK;
 }
 
+// Orders the scatter stream behind the bulk loads that run on a caller's stream and have told nobody yet, and
+// gives them their events, which lie in front of whatever the scatter stream is given next.
+lmc_status_t scatters_after_loads(lmc_ctx *c) {
+    auto lacks_event = [c](const Op &o) { return o.loaded_target != 0 && o.done == nullptr && !c->is_loaded(o.loaded_target); };
+    const Op *last = nullptr;
+    for (const Op &o : c->ops)
+        if (lacks_event(o)) last = &o;      // tickets are in order, and so are the targets; all are on one stream
+    if (last == nullptr) return LMC_OK;
+    if (is_capturing(c->s_scatter)) {       // what is outside a capture cannot be waited for inside
+        while (!c->is_loaded(last->loaded_target)) __builtin_ia32_pause();
+        return LMC_OK;
+    }
+    // "value_waits" may have been switched off since; a stream with work is not destroyed (launches_on_caller)
+    lmc_status_t rc = may_wait_for_word(c, c->s_scatter) ? wait_for_word(c, c->s_scatter, lmc_ctx::kBulkWord, last->loaded_target)
+                                                         : order_after(c, c->s_scatter, last->caller);
+    for (Op &o : c->ops) {
+        if (rc != LMC_OK) return rc;
+        if (!lacks_event(o)) continue;
+        hipEvent_t e = nullptr;
+        if ((rc = get_event(c, false, &e)) != LMC_OK) return rc;
+        const hipError_t x = injected_failure(c) ? hipErrorUnknown : hipEventRecord(e, c->s_scatter);
+        if (x != hipSuccess) {
+            c->free_sync_events.push_back(e);
+            HIPCHK(c, x);
+        }
+        o.done = e;
+    }
+    return rc;
+}
+
 // Long waits of one stream for another.  A queue that stands waiting for an event polls a signal in
 // host memory, over the link that the transfer it waits for is using: each such queue takes 0.6 % of
 // the rate of a copy from the host and 0.25 % of one to it (1.25 GiB up: 57.2 GB/s with nobody waiting,
@@ -445,7 +475,7 @@ static lmc_status_t retrieve_in_steps(lmc_ctx *c, const lmc::LayerPtrs &ptrs, co
     lmc::ChunkList list;
     if (listed)
         for (int64_t i = 0; i < n; i++) list.slot[i] = int32_t(pool_slots[size_t(i)]);
-    lmc::Arrivals arrivals{c->word(0), 0};
+    lmc::Arrivals arrivals{c->word(0), 0, nullptr, 0};
     const lmc_status_t rc = timed_launch(c, false, view, ptrs, slot_mapping, uint32_t(n),
                                          c->pool_dev + (listed ? 0 : pool_slots[0] * c->chunk_bytes), c->s_scatter,
                                          listed ? &list : nullptr, nullptr, &arrivals, planes);
@@ -463,9 +493,10 @@ static lmc_status_t retrieve_in_steps(lmc_ctx *c, const lmc::LayerPtrs &ptrs, co
 // event has to cross from that stream to the library's and back: those two hand-overs cost the
 // calling thread 26 us (a query and a wait between streams are 12-14 us each on this runtime)
 // and leave the link idle in between when one such retrieve follows another.  Call after call, three
-// contexts in turn: 0.5 MiB 53 -> 36 us, 12 MiB in 256-byte rows 234 -> 223 us.  The scatter stream,
-// which keeps the operation's last event, waits for the kernel's word, which takes 2 us where an
-// event from the caller's stream takes 13 (0.5 MiB 34 -> 21 us).  What the runtime does
+// contexts in turn: 0.5 MiB 53 -> 36 us, 12 MiB in 256-byte rows 234 -> 223 us.  The kernel tells the host
+// when it is done, and only where something has to wait for it on the device or a thread does, the scatter stream is made to wait
+// for its word and an event is recorded behind that (scatters_after_loads), 4 us of the call and a waiting queue
+// for as long as the transfer takes otherwise.  What the runtime does
 // for the first launch on a stream that has run nothing is now done inside the call: a program's
 // first 0.5 MiB takes 155-190 us instead of 150-160.
 // Not while the stream is being captured, not for a stream of another GPU, and not where the caller's
@@ -483,17 +514,24 @@ static lmc_status_t retrieve_in_steps(lmc_ctx *c, const lmc::LayerPtrs &ptrs, co
 // hipStreamPerThread is one name for many streams, one a thread: the library's stream it is.
 // A stream that is destroyed has finished its work (hipStreamDestroy blocks on this runtime), so a
 // stream that takes the handle of a destroyed one has nothing to be ordered behind.
-static bool launches_on_caller(const lmc_ctx *c, hipStream_t user) {
+static lmc_status_t launches_on_caller(lmc_ctx *c, hipStream_t user, bool *yes) {
+    *yes = false;
     if (!c->caller_waits || c->link_groups == 0 || user == hipStreamPerThread ||
         (c->cfg.flags & (LMC_FLAG_VALIDATE_SLOTS | LMC_FLAG_TIMING | LMC_FLAG_TRACE)) != 0)
-        return false;
+        return LMC_OK;
     for (const Op &o : c->ops)   // what reap() has left
-        if (!o.on_caller || o.caller != user) return false;
+        if (!o.on_caller || o.caller != user) return LMC_OK;
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    const hipError_t e = injected_failure(c) ? hipErrorUnknown : hipStreamIsCapturing(user, &capturing);
+    if (e == hipErrorStreamCaptureImplicit) {     // the null stream, while another is being captured
+        (void)hipGetLastError();
+        return LMC_OK;
+    }
+    HIPCHK(c, e);
     hipDevice_t dev = c->cfg.device;
-    const bool ok = !is_capturing(user) && (user == nullptr || hipStreamGetDevice(user, &dev) == hipSuccess) &&
-                    dev == c->cfg.device;
-    (void)hipGetLastError();
-    return ok;
+    if (user != nullptr) HIPCHK(c, hipStreamGetDevice(user, &dev));
+    *yes = capturing == hipStreamCaptureStatusNone && dev == c->cfg.device;
+    return LMC_OK;
 }
 
 // Does a retrieve of this size skip staging (lmc_ctx::direct_retrieve_below)?
@@ -527,10 +565,12 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     const lmc_kv_geom_t &geom = c->cfg.geom;
     const int64_t CT = geom.chunk_tokens;
     const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 || retrieves_directly(c, n_chunks, layers_per_step);
-    const bool on_caller = n_chunks > 0 && direct && layers_per_step == 0 && launches_on_caller(c, user);
+    bool on_caller = false;
+    if (n_chunks > 0 && direct && layers_per_step == 0 && (rc = launches_on_caller(c, user, &on_caller)) != LMC_OK) return rc;
     hipStream_t scatters = on_caller ? user : c->s_scatter;
     // the pages may still be in use, and the slot mapping still be on its way, by work
     // already on the caller's stream
+    if (n_chunks > 0 && !on_caller && (rc = scatters_after_loads(c)) != LMC_OK) return rc;
     if (n_chunks > 0 && !on_caller && (rc = order_after_caller(c, c->s_scatter, user)) != LMC_OK) return rc;
     rc = validate_slots(c, slot_mapping, n_chunks * CT, c->s_scatter);
     if (rc != LMC_OK) return rc;
@@ -613,22 +653,23 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
 
     auto enqueue = [&]() -> lmc_status_t {
         if (direct && !op.layerwise) {
-            lmc::Arrivals arrivals{nullptr, 0};
+            lmc::Arrivals arrivals{nullptr, 0, nullptr, 0};
             hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
             HIPCHK(c, hipStreamIsCapturing(c->s_scatter, &capturing));
             const bool tells = c->can_wait_for_words() && c->link_groups > 0 && capturing == hipStreamCaptureStatusNone;
-            if (tells) arrivals.words = c->word(lmc_ctx::kBulkWord);
+            if (tells) {
+                arrivals.words = c->word(lmc_ctx::kBulkWord);
+                arrivals.reached = c->word_target[lmc_ctx::kBulkWord];
+                if (on_caller) arrivals.host = c->stored_dev + lmc_ctx::kLoadedAt;
+            }
             rc = load_direct(lmc::bulk_view(c->kg), 0, nullptr, tells ? &arrivals : nullptr);
             c->word_target[lmc_ctx::kBulkWord] += arrivals.count;
             if (rc != LMC_OK) return rc;
             by_word = arrivals.count > 0;
-            // the operation's last event stays on a stream of the library's own: the caller may
+            // an event is a matter of the library's own streams: the caller may
             // destroy its stream before the event is asked for
-            if (on_caller) {
-                rc = by_word ? wait_for_word(c, c->s_scatter, lmc_ctx::kBulkWord, c->word_target[lmc_ctx::kBulkWord])
-                             : order_after(c, c->s_scatter, user);
-                if (rc != LMC_OK) return rc;
-            }
+            if (on_caller && by_word) op.loaded_target = c->word_target[lmc_ctx::kBulkWord];
+            else if (on_caller && (rc = order_after(c, c->s_scatter, user)) != LMC_OK) return rc;
         } else if (!op.layerwise) {
             const lmc::LaunchView view = lmc::bulk_view(c->kg);
             if ((rc = ring_reslot(c, ring, ring.buf_bytes, c->s_h2d, c->s_scatter, c->s_h2d2)) != LMC_OK) return rc;
@@ -680,7 +721,7 @@ static lmc_status_t do_retrieve(lmc_ctx *c, const uint64_t *ids, int64_t n_chunk
     };
     op.slots = pool_slots;
     const bool layerwise = op.layerwise;
-    if ((rc = enqueue()) == LMC_OK) rc = finish_op(c, std::move(op), c->s_scatter, true, ticket_out);
+    if ((rc = enqueue()) == LMC_OK) rc = finish_op(c, std::move(op), c->s_scatter, op.loaded_target == 0, ticket_out);
     if (rc != LMC_OK) {
         // Part of the call may be enqueued and still read the pool slots, which nothing
         // protects (the in-flight counts belong to a registered operation): it is waited

@@ -1,0 +1,207 @@
+"""Bulk retrieves on the caller's stream tell the host through a word of its memory that their last byte is
+in the pages, and have no event unless something has to wait for them.  Pages read as soon as the wait returns, for
+rows of every kind and odd numbers of groups; what is issued next from another stream, with value waits
+switched off meanwhile or into a graph, comes behind them; several threads wait for one; and an older ticket
+does not wait for a newer one."""
+import threading
+import time
+import zlib
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2510_09665_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "rows_of_256": dict(L=3, P=2, H=1, D=128, e=2, BS=16, NB=96, CT=64),
+    "rows_of_2048": dict(L=3, P=2, H=8, D=128, e=2, BS=16, NB=96, CT=128),
+    "wide_216": dict(L=4, P=2, H=3, D=72, e=1, BS=16, NB=96, CT=64),
+    "narrow": dict(L=2, P=1, H=1, D=5, e=1, BS=4, NB=90, CT=32),
+}
+
+
+def _case(shape, n, seed, sets=2):
+    """n chunks of random bytes for the pool, and `sets` ways to lay some of them into the same pages."""
+    from gpu_util import slots_to_device
+    g = W.KVGeometry(**SHAPES[shape])
+    rng = np.random.default_rng(zlib.crc32(shape.encode()) + seed)
+    want = rng.integers(0, 256, (sets * n, g.chunk_bytes), dtype=np.uint8)
+    tau = rng.permutation(g.n_slots)[:n * g.CT].astype(np.int64)
+    tau[rng.integers(0, n * g.CT, 2)] = -1
+    hosts = []
+    for k in range(sets):
+        hosts.append([W.sentinel_layer(g, l) for l in range(g.L)])
+        oracle.scatter(g, want[k * n:(k + 1) * n], tau, hosts[-1])
+    return g, want, np.arange(1, sets * n + 1, dtype=np.uint64), slots_to_device(tau), hosts
+
+
+def _pages(g):
+    import torch
+    return [torch.from_numpy(W.sentinel_layer(g, l)).cuda() for l in range(g.L)]
+
+
+def _products(stream, n=40):
+    import torch
+    with torch.cuda.stream(stream):
+        a = torch.ones(4096, 4096, device="cuda", dtype=torch.bfloat16)
+        for _ in range(n):
+            a = (a @ a).clamp_(-1, 1)
+    return a
+
+
+@pytest.mark.parametrize("shape", list(SHAPES))
+@pytest.mark.parametrize("groups", [64, 7, 1])
+def test_bytes_are_in_the_pages_when_the_wait_returns(shape, groups):
+    import torch
+    from gpu_util import assert_layers_equal
+    from paper_2510_09665_amd import lmc
+    n = 3
+    g, want, ids, d_tau, hosts = _case(shape, n, 1)
+    dev = _pages(g)
+    stream, reader = torch.cuda.Stream(), torch.cuda.Stream()
+    with lmc.Context(g, 2 * n * g.chunk_bytes, staging_chunks=2) as c:
+        c.put_host(ids, want)
+        c.tune("link_groups", groups)
+        torch.cuda.synchronize()
+        for k in range(8):
+            t = c.retrieve(ids[k % 2 * n:k % 2 * n + n], d_tau, dev, stream)
+            c.wait(t)
+            assert c.test(t)
+            with torch.cuda.stream(reader):
+                seen = [d.cpu().numpy() for d in dev]
+            assert_layers_equal(seen, hosts[k % 2], "pass %d" % k)
+        c.clear(ids)                                       # no count stays on the chunks
+
+
+@pytest.mark.parametrize("then", ["bulk", "layers", "staged", "no_value_waits", "graph"])
+def test_what_comes_next_from_another_stream_is_behind(then):
+    """The first retrieve has some milliseconds of products in front of it; the second fills the same pages."""
+    import torch
+    from gpu_util import assert_layers_equal
+    from paper_2510_09665_amd import lmc
+    n = 2
+    g, want, ids, d_tau, hosts = _case("rows_of_256", n, 2)
+    dev = _pages(g)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    with lmc.Context(g, 2 * n * g.chunk_bytes, staging_chunks=2) as c:
+        c.put_host(ids, want)
+        c.wait(c.retrieve(ids[:n], d_tau, dev, b))         # what a first launch costs is behind it
+        torch.cuda.synchronize()
+        keep = _products(a)
+        t = c.retrieve(ids[:n], d_tau, dev, a)
+        assert not c.test(t)
+        graph = None
+        if then == "layers":
+            u = c.retrieve_layerwise(ids[n:], d_tau, dev, 1, b)
+        elif then == "graph":
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=b, capture_error_mode="relaxed"):
+                u = c.retrieve(ids[n:], d_tau, dev, b)
+        else:
+            if then == "staged":
+                c.tune("direct_retrieve_below", 0)
+            if then == "no_value_waits":
+                c.tune("value_waits", 0)
+            u = c.retrieve(ids[n:], d_tau, dev, b)
+        if graph is not None:
+            c.wait(t)
+            torch.cuda.synchronize()
+            assert_layers_equal([d.cpu().numpy() for d in dev], hosts[0], "before the replay")
+            for _ in range(3):
+                for d in dev:
+                    d.fill_(0)
+                graph.replay()
+            torch.cuda.synchronize()
+            blank = [np.zeros(g.layer_bytes, dtype=np.uint8) for _ in range(g.L)]
+            oracle.scatter(g, want[n:], d_tau.cpu().numpy(), blank)
+            assert_layers_equal([d.cpu().numpy() for d in dev], blank, "after the replays")
+            del graph
+        else:
+            c.wait(u)
+            assert c.test(t) and c.test(u)
+            torch.cuda.synchronize()
+            assert_layers_equal([d.cpu().numpy() for d in dev], hosts[1])
+        del keep
+
+
+def test_an_older_ticket_does_not_wait_for_a_newer_one():
+    """The newer retrieve stands behind products of its own stream."""
+    import torch
+    from paper_2510_09665_amd import lmc
+    n = 2
+    g, want, ids, d_tau, hosts = _case("rows_of_256", n, 3)
+    dev = _pages(g)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    with lmc.Context(g, 2 * n * g.chunk_bytes, staging_chunks=2) as c:
+        c.put_host(ids, want)
+        for s in (a, b):
+            c.wait(c.retrieve(ids[:n], d_tau, dev, s))
+        del_me = _products(b, 2)
+        torch.cuda.synchronize()
+        keep = [_products(a, 20), _products(b, 400)]
+        old = c.retrieve(ids[:n], d_tau, dev, a)
+        new = c.retrieve(ids[n:], d_tau, dev, b)
+        c.wait(old)
+        early = not c.test(new)
+        c.wait(new)
+        torch.cuda.synchronize()
+        del keep, del_me
+        assert early
+
+
+def test_threads_wait_for_one_load_and_for_everything():
+    import torch
+    from gpu_util import assert_layers_equal
+    from paper_2510_09665_amd import lmc
+    n = 2
+    g, want, ids, d_tau, hosts = _case("rows_of_256", n, 4)
+    dev = _pages(g)
+    a = torch.cuda.Stream()
+    with lmc.Context(g, 2 * n * g.chunk_bytes, staging_chunks=2) as c:
+        c.put_host(ids, want)
+        torch.cuda.synchronize()
+        for k in range(6):
+            keep = _products(a, 10)
+            t = c.retrieve(ids[:n], d_tau, dev, a)
+            u = c.retrieve(ids[n:], d_tau, dev, a)
+            ends, errors = [], []
+
+            def wait(ticket):
+                try:
+                    c.wait(ticket)
+                    ends.append(c.test(ticket) if ticket else c.test(t) and c.test(u))
+                except Exception as e:
+                    errors.append(e)
+
+            threads = [threading.Thread(target=wait, args=(x,)) for x in (t, u, 0, t)]
+            for x in threads:
+                x.start()
+            for x in threads:
+                x.join()
+            del keep
+            assert not errors and ends == [True] * 4
+        torch.cuda.synchronize()
+        assert_layers_equal([d.cpu().numpy() for d in dev], hosts[1])
+
+
+def test_a_load_nobody_waits_for_is_found_done():
+    """No event, no wait: the ticket ends, and the chunks can go."""
+    import torch
+    from paper_2510_09665_amd import lmc
+    n = 2
+    g, want, ids, d_tau, _ = _case("rows_of_2048", n, 5)
+    dev = _pages(g)
+    a = torch.cuda.Stream()
+    with lmc.Context(g, 2 * n * g.chunk_bytes, staging_chunks=2) as c:
+        c.put_host(ids, want)
+        torch.cuda.synchronize()
+        for k in range(20):
+            t = c.retrieve(ids[:n], d_tau, dev, a)
+            end = time.monotonic() + 20
+            while not c.test(t):
+                assert time.monotonic() < end
+        c.clear(ids)
+        assert c.lookup(ids) == 0

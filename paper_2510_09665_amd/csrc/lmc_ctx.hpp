@@ -60,6 +60,8 @@ struct Op {
     // step i are in place when word i of the context has reached step_target[i].
     int32_t step_layers = 0;
     std::vector<uint64_t> step_target;
+    hipStream_t waiter = nullptr;         // the last stream that was made to wait for a step of it ...
+    int32_t waits_for = -1;               // ... and for which
 };
 
 // One timed step of a pipeline: a kernel launch (LMC_FLAG_TIMING, LMC_FLAG_TRACE) or the

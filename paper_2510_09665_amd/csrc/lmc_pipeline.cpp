@@ -1065,15 +1065,27 @@ lmc_status_t lmc_wait_layer(lmc_ctx_t *c, uint64_t ticket, int32_t layer, void *
     std::lock_guard<std::mutex> lock(c->mu);
     DeviceScope dev(c);
     if (ticket >= c->next_ticket) return LMC_ERR_INVAL;
-    const Op *op = find_op(c, ticket);
+    Op *op = find_op(c, ticket);
     if (op == nullptr) return LMC_OK;                       // finished long ago
     if (!op->layerwise) return LMC_ERR_INVAL;
     if (!op->step_target.empty()) {
         if (hipEventQuery(op->done) == hipSuccess) return LMC_OK;
         (void)hipGetLastError();   // "not ready" is an answer, not a failure
         const int32_t i = layer / op->step_layers;
-        if (may_wait_for_word(c, static_cast<hipStream_t>(stream)))
-            return wait_for_word(c, static_cast<hipStream_t>(stream), i, op->step_target[size_t(i)]);
+        hipStream_t user = static_cast<hipStream_t>(stream);
+        if (may_wait_for_word(c, user)) {
+            // The steps end in order, so a stream that has been made to wait for this one or a later one need
+            // not wait again: a wait takes the calling thread 3 us and the stream's queue as long, 32 of them more than
+            // 4 MiB take to come.  (A stream that takes the handle of a destroyed one has nothing to
+            // wait for: the destroyed one's wait was over, see launches_on_caller.)
+            if (user == op->waiter && i <= op->waits_for && user != hipStreamPerThread) return LMC_OK;
+            const lmc_status_t rc = wait_for_word(c, user, i, op->step_target[size_t(i)]);
+            if (rc == LMC_OK) {
+                op->waiter = user;
+                op->waits_for = i;
+            }
+            return rc;
+        }
         HIPCHK(c, hipStreamWaitEvent(static_cast<hipStream_t>(stream), op->done, 0));   // all layers
         return LMC_OK;
     }

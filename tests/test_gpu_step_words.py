@@ -210,3 +210,63 @@ def test_while_another_stream_is_captured():
         torch.cuda.synchronize()
         assert_layers_equal([d.cpu().numpy() for d in dev], host)
         assert x.cpu().tolist() == [3.0] * 64
+
+
+@pytest.mark.parametrize("how", ["in_turn", "last_first", "destroyed"])
+def test_layers_of_one_step_are_waited_for_once_by_each_stream(how):
+    """Two streams that wait for the same layers in turn, a stream that waits for the last layer before the
+    first, and a stream that is destroyed behind its wait, after which another may have its handle."""
+    import ctypes
+    import torch
+    from gpu_util import assert_layers_equal, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(L=6, P=2, H=8, D=128, e=2, BS=16, NB=256, CT=256)
+    rng = np.random.default_rng(51)
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    with lmc.Context(g, 5 * g.chunk_bytes, staging_chunks=2) as c:
+        want, ids = _pool(c, g, 4, False, rng)
+        tau = _request(g, 4, rng)
+        host = [W.sentinel_layer(g, l) for l in range(g.L)]
+        dev = [torch.from_numpy(h).cuda() for h in host]
+        d_tau = slots_to_device(tau)
+        oracle.scatter(g, want, tau, host)
+        for again in range(3):
+            for l, d in enumerate(dev):
+                d.copy_(torch.from_numpy(W.sentinel_layer(g, l)))
+            before = []
+            for s in (a, b):
+                with torch.cuda.stream(s):
+                    before.append([d.clone() for d in dev])     # the pages as they are now, in the caches
+            torch.cuda.synchronize()
+            t = c.retrieve_layerwise(ids, d_tau, dev, 3)        # two steps
+            seen = {}
+            if how == "destroyed":
+                raw = ctypes.c_void_p()
+                assert hip.hipStreamCreateWithFlags(ctypes.byref(raw), 1) == 0
+                c.wait_layer(t, 0, raw.value)
+                assert hip.hipStreamDestroy(raw) == 0
+                made = []
+                for _ in range(4):
+                    assert hip.hipStreamCreateWithFlags(ctypes.byref(raw), 1) == 0
+                    made.append(raw.value)
+                for k, h in enumerate(made):
+                    c.wait_layer(t, 1, h)
+                    with torch.cuda.stream(torch.cuda.ExternalStream(h)):
+                        seen[1, k] = dev[1].clone()
+                torch.cuda.synchronize()
+                for h in made:
+                    assert hip.hipStreamDestroy(ctypes.c_void_p(h)) == 0
+            else:
+                for l in (range(g.L) if how == "in_turn" else reversed(range(g.L))):
+                    for s in (a, b) if how == "in_turn" else (a,):
+                        c.wait_layer(t, l, s)
+                        with torch.cuda.stream(s):
+                            seen[l, s] = dev[l].clone()
+            torch.cuda.synchronize()
+            for (l, _), d in seen.items():
+                assert np.array_equal(d.cpu().numpy(), host[l]), (again, l)
+            c.wait(t)
+            assert_layers_equal([d.cpu().numpy() for d in dev], host)
+            del before

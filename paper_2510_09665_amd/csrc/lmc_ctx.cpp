@@ -231,13 +231,15 @@ lmc_status_t order_after(lmc_ctx *c, hipStream_t waiter, hipStream_t stream) {
 // there also waits for what the process's other blocking streams hold, and the runtime's
 // query of the null stream answers "not ready" while any of them is busy (checked by
 // tests/test_gpu_streams.py, with the producer of the KV on a blocking stream).
-lmc_status_t order_after_caller(lmc_ctx *c, hipStream_t waiter, hipStream_t user) {
+bool caller_is_idle(hipStream_t user) {
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(user, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone) {
-        if (hipStreamQuery(user) == hipSuccess) return LMC_OK;
-    }
+    const bool idle = hipStreamIsCapturing(user, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone &&
+                      hipStreamQuery(user) == hipSuccess;
     (void)hipGetLastError();   // "not ready" is an answer, not a failure
-    return order_after(c, waiter, user);
+    return idle;
+}
+lmc_status_t order_after_caller(lmc_ctx *c, hipStream_t waiter, hipStream_t user) {
+    return caller_is_idle(user) ? LMC_OK : order_after(c, waiter, user);
 }
 
 // Is an operation of the other direction still under way?  The second copy stream of a

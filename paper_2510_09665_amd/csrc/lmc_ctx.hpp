@@ -52,6 +52,10 @@ struct Op {
     int32_t next_layer = 0;               // first layer not yet submitted
     int32_t steps = 0;                    // pending store: lmc_store_layers calls served so far
     std::vector<hipStream_t> ends_on;     // pending store: the streams its steps so far end on
+    // pending store: not 0: its steps without staging on s_d2h2 are done when kStoreStepWord has reached this
+    uint64_t second_target = 0;
+    bool has_staged_steps = false;
+    bool began_idle = false;              // pending store: nothing was on the caller's stream when it began
     std::vector<int64_t> new_chunk;       // pending store: chunk numbers that are new
     const int64_t *slot_mapping = nullptr;  // pending store: the caller's slot mapping
     std::vector<hipEvent_t> layer_done;   // per layer: event after which the layer is in place
@@ -110,7 +114,7 @@ struct lmc_ctx {
     // process's slow first seconds from 44.5 to 54.5 GB/s.
     bool d2h_guard_on = true;
     uint64_t pieces_by_kernel_below = uint64_t(2) << 20;   // bytes per transfer; see copy_group
-    int32_t store_step_streams = 2;   // copy streams the steps of a layer-wise store take in turn
+    int32_t store_step_streams = 2;   // streams the steps of a layer-wise store take in turn, staged or not
     bool caller_waits = true;     // a bulk retrieve ends with the caller's stream waiting for it
     lmc::CopyEngineGuard d2h_guard;
     std::vector<CopyTiming> copy_timings;
@@ -152,6 +156,7 @@ struct lmc_ctx {
     // lmc_tune "direct_store_below" sets both lines.
     int64_t direct_store_below = int64_t(64) << 20, direct_store_steps_below = int64_t(256) << 20;
     static constexpr int64_t kDirectStoreStep = int64_t(2) << 20;
+    static constexpr int64_t kStoreStepsInTurn = int64_t(512) << 10;   // see lmc_store_layers
     // Retrieves: up to 256 MiB.  Bulk, 96, 128, 192, 256 MiB: 1857, 2444, 3616, 4793 us staged, 1757, 2340,
     // 3502, 4684 direct.  What else runs on the GPU loses a part of the compute units to the kernel, but a
     // staged retrieve makes two hardware queues besides the caller's stand still for as long as it takes,
@@ -196,10 +201,11 @@ struct lmc_ctx {
     // kStoreWord is for bulk stores without staging, whose kernels pass its value on to
     // *stored_host: a thread that waits for such a store sees it there 5 us before the event
     // behind the kernel completes.
+    // kStoreStepWord is for the steps of layer-wise stores that run on s_d2h2 (lmc_store_layers).
     // kFilledWord and kDoneWord are written by the streams themselves (hand_over) as groups of a bulk
     // retrieve reach the staging buffer, and as it ends.
     static constexpr int kBulkWord = LMC_MAX_LAYERS, kStoreWord = LMC_MAX_LAYERS + 1, kFilledWord = LMC_MAX_LAYERS + 2,
-                         kDoneWord = LMC_MAX_LAYERS + 3, kWords = LMC_MAX_LAYERS + 4;
+                         kDoneWord = LMC_MAX_LAYERS + 3, kStoreStepWord = LMC_MAX_LAYERS + 4, kWords = LMC_MAX_LAYERS + 5;
     // two words of host memory, kLoadedAt words apart, and their address on the GPU
     static constexpr int kLoadedAt = 8;
     uint64_t *stored_host = nullptr, *stored_dev = nullptr;
@@ -294,6 +300,7 @@ double seconds_now(const lmc_ctx *c);
 void recycle(lmc_ctx *c, hipEvent_t e);
 void reap(lmc_ctx *c);
 lmc_status_t order_after(lmc_ctx *c, hipStream_t waiter, hipStream_t stream);
+bool caller_is_idle(hipStream_t user);
 lmc_status_t order_after_caller(lmc_ctx *c, hipStream_t waiter, hipStream_t user);
 bool other_direction_busy(lmc_ctx *c, bool for_store);
 lmc_status_t validate_slots(lmc_ctx *c, const int64_t *slot_mapping, int64_t n_tokens,
@@ -311,7 +318,7 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
                           uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list = nullptr,
                           hipEvent_t stop = nullptr, lmc::Arrivals *arrivals = nullptr, uint32_t planes_per_step = 0,
-                          lmc::HostWord *told = nullptr);
+                          lmc::HostWord *told = nullptr, uint32_t groups = 0);
 lmc_status_t scatters_after_loads(lmc_ctx *c);
 // lmc_streams.cpp
 lmc_status_t shares_a_queue(lmc_ctx *c, hipStream_t busy, bool by_kernel, hipStream_t other, uint8_t *devbuf,

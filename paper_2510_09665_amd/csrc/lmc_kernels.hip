@@ -101,14 +101,15 @@ __device__ __forceinline__ void arrive(uint64_t word_at) {
     if ((threadIdx.x & 63u) == 0)
         (void)__hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)word_at, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-// The same for a whole workgroup, at the end of a kernel, and for the host too: the last one to arrive, which brings
-// the word to `target`, writes that to a word in host memory.  One count for each workgroup: by 192
+// The same for a whole workgroup, at the end of a kernel, and for the host too, if asked: the last one to arrive,
+// which brings the word to `target`, writes that to a word in host memory.  One count for each workgroup: by 192
 // wavefronts one address in memory is a microsecond longer at work.
 __device__ __forceinline__ void arrive_and_tell(const HostWord &told) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0 &&
-        __hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)told.word, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1 == told.target)
+        __hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)told.word, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1 == told.target &&
+        told.host != nullptr)
         __hip_atomic_store((LMC_GLOBAL uint64_t *)told.host, told.target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 

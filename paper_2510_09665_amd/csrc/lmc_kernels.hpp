@@ -106,7 +106,7 @@ struct Arrivals {
 };
 constexpr uint32_t kWordStride = 64;
 // Where a gather into the pool tells the host that its last store has reached the pool: the workgroups
-// count themselves off at `word`, and the one that brings it to `target` writes that to `host`.
+// count themselves off at `word`, and the one that brings it to `target` writes that to `host` (may be null).
 // Handed to a launch, target is what the word will have reached before it; it receives what it will
 // have reached behind it, or stays as it is where the launch cannot tell (its stores do not go
 // through the L2).

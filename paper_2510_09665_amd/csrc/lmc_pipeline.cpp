@@ -70,7 +70,7 @@ static lmc_status_t prepare_order_scratch(lmc_ctx *c, uint64_t n_tokens, hipStre
 lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
                           const lmc::LayerPtrs &ptrs, const int64_t *slots, uint32_t n_chunks,
                           uint8_t *staging, hipStream_t stream, const lmc::ChunkList *list, hipEvent_t stop,
-                          lmc::Arrivals *arrivals, uint32_t planes_per_step, lmc::HostWord *told) {
+                          lmc::Arrivals *arrivals, uint32_t planes_per_step, lmc::HostWord *told, uint32_t groups) {
     // LMC_FLAG_TIMING: the launch itself carries a start and a stop event, which receive
     // the kernel's own begin / end time stamps; the stream gets no extra marker.
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -83,7 +83,7 @@ lmc_status_t timed_launch(lmc_ctx *c, bool gather, const lmc::LaunchView &view,
     // a launch that reads or writes the pinned pool itself is paced by the host link
     if (c->pool_dev != nullptr && staging >= c->pool_dev &&
         staging < c->pool_dev + uint64_t(c->n_pool_slots) * uint64_t(c->chunk_bytes))
-        s.paced_groups = c->link_groups;
+        s.paced_groups = groups != 0 && c->link_groups != 0 ? groups : c->link_groups;
     // `stop` completes with the launch: as the launch's own stop event, which costs the GPU and
     // the calling thread 3 and 1 us less than an event recorded behind it, unless timing needs that
     // or the stream is being captured, where waits go by the events recorded on it
@@ -341,7 +341,7 @@ static lmc_status_t after_stores(lmc_ctx *c, const int64_t *pool_slots, int64_t 
 static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, uint64_t pool_off,
                                 const lmc::LayerPtrs &ptrs, const int64_t *slot_mapping, const int64_t *chunk,
                                 const int64_t *pool_slot, int64_t n, hipStream_t stream, hipEvent_t stop = nullptr,
-                                lmc::Arrivals *arrivals = nullptr, lmc::HostWord *told = nullptr) {
+                                lmc::Arrivals *arrivals = nullptr, lmc::HostWord *told = nullptr, uint32_t groups = 0) {
     const uint64_t cb = uint64_t(c->chunk_bytes);
     const int64_t CT = c->cfg.geom.chunk_tokens;
     view.chunk_stride = cb;  // chunks lie one pool slot apart
@@ -363,7 +363,7 @@ static lmc_status_t move_direct(lmc_ctx *c, bool gather, lmc::LaunchView view, u
         lmc_status_t rc = timed_launch(c, gather, view, ptrs, slot_mapping + (chunk ? chunk[i0] : i0) * CT, uint32_t(k),
                                        c->pool_dev + (listed ? 0 : uint64_t(pool_slot[i0]) * cb) + pool_off, stream,
                                        listed ? &list : nullptr, i0 + k == n ? stop : nullptr,
-                                       i0 + k == n ? arrivals : nullptr, 0, i0 + k == n ? told : nullptr);
+                                       i0 + k == n ? arrivals : nullptr, 0, i0 + k == n ? told : nullptr, groups);
         if (rc != LMC_OK) return rc;
         (gather ? c->stats.bytes_d2h : c->stats.bytes_h2d) += uint64_t(k) * view.by_n_lp.d * c->kg.plane_bytes;
         if ((rc = force_sync(c, stream)) != LMC_OK) return rc;
@@ -792,12 +792,12 @@ static lmc_status_t store_groups(lmc_ctx *c, const lmc::LaunchView &view, uint64
                                  const std::vector<int64_t> &new_slot, int64_t cap_chunks,
                                  bool edge_group, bool direct, bool layer_step = false, bool on_second_stream = false,
                                  std::vector<hipEvent_t> *group_events = nullptr, hipEvent_t stop = nullptr,
-                                 lmc::HostWord *told = nullptr) {
+                                 lmc::HostWord *told = nullptr, uint32_t groups = 0) {
     Ring &ring = c->store_ring;
     const int64_t CT = c->cfg.geom.chunk_tokens;
     if (direct)   // no staging, no copy: the gather kernel writes the pinned pool over the link
         return move_direct(c, true, view, pool_off, ptrs, slot_mapping, new_chunk.data(), new_slot.data(),
-                           int64_t(new_chunk.size()), c->s_gather, stop, nullptr, told);
+                           int64_t(new_chunk.size()), on_second_stream ? c->s_d2h2 : c->s_gather, stop, nullptr, told, groups);
     const size_t per = size_t(cap_chunks);
     const bool two_copy_streams = !other_direction_busy(c, true);
     hipStream_t copies = on_second_stream ? c->s_d2h2 : c->s_d2h, other = on_second_stream ? c->s_d2h : c->s_d2h2;
@@ -942,7 +942,8 @@ lmc_status_t lmc_store_begin(lmc_ctx_t *c, const int64_t *slot_mapping, const ui
     lmc_status_t rc;
     hipStream_t user = static_cast<hipStream_t>(stream_to_wait_on);
     const int64_t CT = c->cfg.geom.chunk_tokens;
-    if (n_chunks > 0 && (rc = order_after_caller(c, c->s_gather, user)) != LMC_OK) return rc;
+    const bool idle = n_chunks == 0 || caller_is_idle(user);
+    if (!idle && (rc = order_after(c, c->s_gather, user)) != LMC_OK) return rc;
     if ((rc = validate_slots(c, slot_mapping, n_chunks * CT, c->s_gather)) != LMC_OK) return rc;
     Op op;
     op.ticket = c->next_ticket++;
@@ -951,6 +952,7 @@ lmc_status_t lmc_store_begin(lmc_ctx_t *c, const int64_t *slot_mapping, const ui
     c->stats.chunks_stored += op.new_chunk.size();
     op.pending = !op.new_chunk.empty();   // nothing new: the ticket is complete at once
     op.slot_mapping = slot_mapping;
+    op.began_idle = idle;
     op.layer_done.assign(size_t(c->cfg.geom.num_layers), nullptr);
     if (ticket_out) *ticket_out = op.ticket;
     c->ops.push_back(std::move(op));
@@ -992,9 +994,29 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     // queue, see arrange_streams) the next step's copy is ready to start.  Not while a
     // retrieve is under way, whose kernels that stream would hold up.
     const bool on_second = !direct && (op->steps & 1) != 0 && c->store_step_streams == 2 && !other_direction_busy(c, true);
-    hipStream_t last = direct ? c->s_gather : on_second ? c->s_d2h2 : c->s_d2h;
+    // Where the producer has nothing more on its stream (nor had in front of the slot mapping), steps without staging take the gather stream and the second
+    // copy stream to the host in turn (which sits in the scatter stream's hardware queue, so that the library's kernels
+    // hold up no third one), each with half of the groups, so that one step's first slots and last stores do not leave the link idle: kernels of one stream
+    // follow each other 1.4 us apart, and the first store of one and the last of the other are some 3 more.  On one stream and on two, steps of
+    // 0.6, 0.9, 1, 1.3 MiB: 34 MiB 809 and 760 us, 22 490 and 461, 32 700 and 641, 105 2160 and 2020.  Not for steps under
+    // 0.5 MiB (1.1 MiB in four 52 and 77 us, 10.7 in 61 of 0.2 528 and 645), whose launches take the thread longer than the link,
+    // nor beside other operations, whose copies they might have to wait for.  Beside the producer's products, which put
+    // time between the steps, there is nothing to gain, and a second hardware queue would wait (64 MiB in steps of 2, 128 rows,
+    // over the four queues the producer's stream can be in, 5791 and 5905 us).  The last step is on the gather stream,
+    // behind the other's: what waits for the store waits for one stream.
+    const bool ends = first_layer + n_layers == geom.num_layers;
+    hipStream_t user = static_cast<hipStream_t>(stream_to_wait_on);
+    const bool idle = caller_is_idle(user);
+    const bool in_turn = idle && op->began_idle && direct && c->store_step_streams == 2 && c->ops.size() == 1 &&
+                         n_new * int64_t(layer_bytes) * n_layers >= lmc_ctx::kStoreStepsInTurn && may_wait_for_word(c, c->s_gather);
+    const bool beside = in_turn && !ends && (op->steps & 1) != 0;
+    hipStream_t last = direct ? (beside ? c->s_d2h2 : c->s_gather) : on_second ? c->s_d2h2 : c->s_d2h;
     // this layer's KV was produced by work already on the caller's stream
-    rc = order_after_caller(c, c->s_gather, static_cast<hipStream_t>(stream_to_wait_on));
+    rc = idle ? LMC_OK : order_after(c, c->s_gather, user);
+    if (rc == LMC_OK && direct && ends && op->second_target != 0 && !op->has_staged_steps && may_wait_for_word(c, c->s_gather)) {
+        rc = wait_for_word(c, c->s_gather, lmc_ctx::kStoreStepWord, op->second_target);
+        op->ends_on.erase(std::remove(op->ends_on.begin(), op->ends_on.end(), c->s_d2h2), op->ends_on.end());
+    }
     if (rc == LMC_OK && !direct)
         rc = ring_reslot(c, c->store_ring, (uint64_t(cap) * view.chunk_stride + 255) / 256 * 256, c->s_gather, c->s_d2h,
                          nullptr, c->s_d2h2);
@@ -1002,19 +1024,25 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     if (rc == LMC_OK) rc = get_event(c, false, &e);
     if (rc == LMC_OK) {
         op->owned_events.push_back(e);
-        // the last step of a store whose steps all ran on the gather stream ends the store
-        const bool tells = direct && first_layer + n_layers == geom.num_layers && tells_host(c) &&
+        // the last step of a store whose steps all ran on the gather stream, or are waited for there, ends the store
+        const bool tells = direct && ends && tells_host(c) &&
                            std::all_of(op->ends_on.begin(), op->ends_on.end(), [&](hipStream_t s) { return s == c->s_gather; });
-        uint64_t &reached = c->word_target[lmc_ctx::kStoreWord];
-        lmc::HostWord told{tells ? c->word(lmc_ctx::kStoreWord) : nullptr, c->stored_dev, reached};
+        uint64_t &reached = c->word_target[beside ? lmc_ctx::kStoreStepWord : lmc_ctx::kStoreWord];
+        lmc::HostWord told{nullptr, nullptr, reached};
+        if (beside) told.word = c->word(lmc_ctx::kStoreStepWord);
+        else if (tells) told = lmc::HostWord{c->word(lmc_ctx::kStoreWord), c->stored_dev, reached};
+        const uint32_t groups = in_turn ? std::max(1u, c->link_groups / 2) : 0u;
         rc = store_groups(c, view, uint64_t(first_layer) * layer_bytes, ptrs, op->slot_mapping, op->new_chunk,
-                          op->slots, cap, false, direct, true, on_second, nullptr, e, tells ? &told : nullptr);
-        if (told.target != reached) op->stored_target = reached = told.target;
+                          op->slots, cap, false, direct, true, on_second || beside, nullptr, e, beside || tells ? &told : nullptr, groups);
+        if (told.target != reached) (beside ? op->second_target : op->stored_target) = reached = told.target;
+        // a step that cannot count (lmc::HostWord) leaves the end to the events
+        else if (beside) op->has_staged_steps = true;
+        op->has_staged_steps = op->has_staged_steps || !direct;
     }
     if (rc == LMC_OK) {
         rc = [&]() -> lmc_status_t {
             if (!direct) HIPCHK(c, hipEventRecord(e, last));
-            if (first_layer + n_layers == geom.num_layers) {
+            if (ends) {
                 // the ticket is complete when the steps of every stream are
                 lmc_status_t r = LMC_OK;
                 for (hipStream_t s : op->ends_on)

@@ -169,3 +169,72 @@ def test_captured_into_a_graph(what, flag):
                 for i, w in zip(ids, want):
                     assert np.array_equal(c.get_host(i), w ^ (255 if replay % 2 == 0 else 0)), replay
         del graph
+
+
+@pytest.mark.parametrize("name,n,kw", [("llama3_8b", 1, dict(L=8, NB=64)),                     # steps of 1 MiB
+                                       ("llama3_8b", 2, dict(L=5, NB=96, layout="HND")),
+                                       ("llama3_8b", 3, dict(L=3, H=5, D=108, NB=96)),         # 1080-byte rows, in pieces
+                                       ("llama3_8b", 40, dict(L=4, H=1, D=33, e=1, CT=208, NB=1100))])   # rows that do not tell
+@pytest.mark.parametrize("how", ["idle", "busy_between", "another_between", "mixed", "odd_groups", "one_stream", "captured_between",
+                                 "late_mapping"])
+def test_store_steps_on_two_streams_in_turn(name, n, kw, how):
+    """Steps of 0.5 MiB and more from a stream that is idle: every byte is in the pool when the wait returns, and
+    a retrieve issued right behind sees all of them.  The slot mapping comes late on another stream, the stream becomes busy, another operation comes, a staged
+    step follows, or another stream is captured between two steps."""
+    import torch
+    from gpu_util import assert_layers_equal
+    from paper_2510_09665_amd import lmc
+    g, src, dst, want, d_slots, d_tau, ids = _setup(n, 61 + n, name=name, **kw)
+    stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+    x = torch.zeros(1 << 22, device="cuda")
+    with lmc.Context(g, (2 * n + 2) * g.chunk_bytes, staging_chunks=n) as c:
+        if how == "odd_groups":
+            c.tune("link_groups", 7)
+        if how == "one_stream":
+            c.tune("store_step_streams", 1)
+        for again in range(6):
+            for d in src.dev:
+                d.bitwise_xor_(255)
+            torch.cuda.synchronize()
+            if how == "late_mapping":
+                late = torch.full_like(d_slots, -1)
+                with torch.cuda.stream(other):
+                    for _ in range(100):
+                        x.add_(1)
+                    late.copy_(d_slots)
+                t = c.store_begin(late, ids, other)
+            else:
+                t = c.store_begin(d_slots, ids, stream)
+            graph = None
+            for l in range(g.L):
+                if l == 1 and how == "busy_between":
+                    with torch.cuda.stream(stream):
+                        for _ in range(20):
+                            x.add_(1)
+                if l == 2 and how == "another_between":
+                    c.store(src.dev, d_slots[:g.CT], np.array([1 << 40], dtype=np.uint64), other)
+                if how == "mixed" and l == 2:
+                    c.tune("direct_store_below", 0)
+                if how == "captured_between" and l == 1:
+                    graph = torch.cuda.CUDAGraph()
+                    with torch.cuda.graph(graph, stream=other, capture_error_mode="relaxed"):
+                        c.store_layers(t, l, 1, src.dev, stream)
+                        x.add_(1)
+                else:
+                    c.store_layers(t, l, 1, src.dev, stream)
+            if again % 2:
+                u = c.retrieve(ids, d_tau, dst.dev, other)
+                c.wait(u)
+                torch.cuda.synchronize()
+                assert_layers_equal([d.cpu().numpy() for d in dst.dev], dst.host, "pass %d" % again)
+            c.wait(t)
+            flip = 255 if again % 2 == 0 else 0
+            for i, w in zip(ids, want):
+                assert np.array_equal(c.get_host(i), w ^ flip), (again, i)
+            c.wait()
+            c.tune("direct_store_below", 64 << 20)
+            c.clear(ids)
+            c.clear(np.array([1 << 40], dtype=np.uint64))
+            del graph
+        if how in ("idle", "odd_groups", "one_stream") and "e" not in kw:
+            c.tune("expect_stores_told", 6)

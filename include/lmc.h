@@ -607,7 +607,8 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * lmc_retrieve_batch / lmc_retrieve_layerwise of at most that many bytes, goes the
  * LMC_FLAG_DIRECT way: one launch instead of kernel, event, copy, event; the
  * lmc_store_layers calls of a store with at most that many new bytes do; 0 = never.  As long as
- * the first is not set, lmc_store_layers calls that move at most 2 MiB go that way in stores of up to
+ * the first is not set, lmc_store_layers calls that move at most 2 MiB, or find the stream they are given idle
+ * and no other operation under way, go that way in stores of up to
  * 256 MiB; as long as the second is not, layer-wise retrieves in steps of at most 8 MiB up to
  * 512 MiB, and any retrieve up to 64 MiB only while a store is under way), "scatter_order" (default 0; 1 or 2:
  * scatter launches visit their rows in ascending slot order, built on the device, so that

@@ -152,7 +152,10 @@ struct lmc_ctx {
     // 10858, 14797 staged, 8678, 9060, 10866, 15002 direct; in steps of 16 8882, 8970, 10923, 14869 and 8690, 8984,
     // 10910, 14948; 160 MiB in steps of 2 15583, 15594, 19374, 28685 and 14302, 15279, 19751, 28909.  Larger
     // stores in larger steps would lose: 192 MiB in steps of 6 10085, 10105, 11891, 15773 and 9469, 10510, 12522,
-    // 16840, 320 MiB in steps of 4 16444, 16448, 20142, 29586 and 15092, 16886, 20496, 31202.
+    // 16840, 320 MiB in steps of 4 16444, 16448, 20142, 29586 and 15092, 16886, 20496, 31202.  But where the producer
+    // has nothing on its stream and no other operation is under way there is nothing of the producer's to slow down, and steps of any
+    // size go this way up to the second line: 65, 86, 168, 200, 224 MiB in steps of 9, 6, 11, 6, 7 1374, 1878, 3339, 4115,
+    // 4544 us staged and 1286, 1633, 3172, 3781, 4223 direct, and a first pass, with the runtime's copies still slow, 11-16 ms and 4.
     // lmc_tune "direct_store_below" sets both lines.
     int64_t direct_store_below = int64_t(64) << 20, direct_store_steps_below = int64_t(256) << 20;
     static constexpr int64_t kDirectStoreStep = int64_t(2) << 20;

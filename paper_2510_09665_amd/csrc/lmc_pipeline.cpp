@@ -985,16 +985,20 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     const uint64_t layer_bytes = uint64_t(geom.num_planes) * c->kg.plane_bytes;
     const int64_t cap = layer_group_chunks(c, c->store_ring, view, int64_t(op->new_chunk.size()));
     const int64_t n_new = int64_t(op->new_chunk.size());
+    const int64_t step_bytes = n_new * int64_t(layer_bytes) * n_layers;
+    hipStream_t user = static_cast<hipStream_t>(stream_to_wait_on);
+    const bool idle = caller_is_idle(user);
+    // the producer has nothing more on its stream (nor had in front of the slot mapping), and nothing else is under way
+    const bool undisturbed = idle && op->began_idle && c->ops.size() == 1;
     const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 || n_new * c->chunk_bytes <= c->direct_store_below ||
-                        (n_new * c->chunk_bytes <= c->direct_store_steps_below &&
-                         n_new * int64_t(layer_bytes) * n_layers <= lmc_ctx::kDirectStoreStep);
+                        (n_new * c->chunk_bytes <= c->direct_store_steps_below && (step_bytes <= lmc_ctx::kDirectStoreStep || undisturbed));
     // Steps take the two copy streams in turn (as the steps of a layer-wise retrieve do):
     // between two copies of one stream the runtime leaves the link idle for some 20 us,
     // 7 % of a step of one Llama-3-8B layer, while on the other stream (another hardware
     // queue, see arrange_streams) the next step's copy is ready to start.  Not while a
     // retrieve is under way, whose kernels that stream would hold up.
     const bool on_second = !direct && (op->steps & 1) != 0 && c->store_step_streams == 2 && !other_direction_busy(c, true);
-    // Where the producer has nothing more on its stream (nor had in front of the slot mapping), steps without staging take the gather stream and the second
+    // Then steps without staging take the gather stream and the second
     // copy stream to the host in turn (which sits in the scatter stream's hardware queue, so that the library's kernels
     // hold up no third one), each with half of the groups, so that one step's first slots and last stores do not leave the link idle: kernels of one stream
     // follow each other 1.4 us apart, and the first store of one and the last of the other are some 3 more.  On one stream and on two, steps of
@@ -1005,10 +1009,8 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     // over the four queues the producer's stream can be in, 5791 and 5905 us).  The last step is on the gather stream,
     // behind the other's: what waits for the store waits for one stream.
     const bool ends = first_layer + n_layers == geom.num_layers;
-    hipStream_t user = static_cast<hipStream_t>(stream_to_wait_on);
-    const bool idle = caller_is_idle(user);
-    const bool in_turn = idle && op->began_idle && direct && c->store_step_streams == 2 && c->ops.size() == 1 &&
-                         n_new * int64_t(layer_bytes) * n_layers >= lmc_ctx::kStoreStepsInTurn && may_wait_for_word(c, c->s_gather);
+    const bool in_turn = undisturbed && direct && c->store_step_streams == 2 && step_bytes >= lmc_ctx::kStoreStepsInTurn &&
+                         may_wait_for_word(c, c->s_gather);
     const bool beside = in_turn && !ends && (op->steps & 1) != 0;
     hipStream_t last = direct ? (beside ? c->s_d2h2 : c->s_gather) : on_second ? c->s_d2h2 : c->s_d2h;
     // this layer's KV was produced by work already on the caller's stream

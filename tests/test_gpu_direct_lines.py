@@ -1,7 +1,7 @@
 """Which calls skip staging by their size.  Retrieves: up to 256 MiB, up to 512 MiB layer by layer in
 steps of at most 8 MiB, up to 64 MiB beside a store that is under way.  Layer-wise stores: up to 64 MiB,
-up to 256 MiB steps of at most 2 MiB, which one store may mix with staged ones.  Where a line is set,
-up to that.  At each line, the last size on this side and the first on the other: the trace says
+up to 256 MiB steps of at most 2 MiB, which one store may mix with staged ones, and of any size from a
+stream that is idle.  Where a line is set, up to that.  At each line, the last size on this side and the first on the other: the trace says
 whether copies between staging and the pool were made, and the bytes are the same either way."""
 import numpy as np
 import pytest
@@ -72,29 +72,37 @@ def test_lines(kv, chunks, step, store, line, direct):
         assert (v[:, blocks[1][chunks * per:]] == 0x5A).all()
 
 
-@pytest.mark.parametrize("chunks,steps,line,staged", [
-    (8, (64,), None, 0), (9, (64,), None, 1),                              # 64 MiB
-    (9, (1,) * 64, None, 0), (16, (1,) * 64, None, 0), (17, (1,) * 64, None, 64),   # steps of 2 MiB
-    (9, (1, 2, 1, 60), None, 2), (16, (2, 1, 61), None, 2),                # mixed
-    (33, (1,) * 64, None, 64),                                             # 256 MiB
-    (2, (64,), 16, 0), (3, (1,) * 64, 16, 64), (1, (32, 32), 0, 2),
+@pytest.mark.parametrize("chunks,steps,busy,line,staged", [
+    (8, (64,), True, None, 0), (9, (64,), True, None, 1),                  # 64 MiB
+    (9, (1,) * 64, True, None, 0), (16, (1,) * 64, True, None, 0), (17, (1,) * 64, True, None, 64),   # steps of 2 MiB
+    (9, (1, 2, 1, 60), True, None, 2), (16, (2, 1, 61), True, None, 2),    # mixed
+    (9, (64,), False, None, 0), (17, (1, 31, 32), False, None, 0), (32, (8,) * 8, False, None, 0),
+    (33, (1,) * 64, True, None, 64), (33, (32, 32), False, None, 2),       # 256 MiB
+    (2, (64,), False, 16, 0), (3, (1,) * 64, False, 16, 64), (1, (32, 32), False, 0, 2),
 ])
-def test_lines_of_layerwise_stores(kv, chunks, steps, line, staged):
+def test_lines_of_layerwise_stores(kv, chunks, steps, busy, line, staged):
     import torch
     from paper_2510_09665_amd import lmc
     pages, blocks, slots = kv
     n, per = chunks * G.CT, G.CT // G.BS
     layers = [p.view(torch.uint8) for p in pages.unbind(0)]
+    stream = torch.cuda.Stream()
+    work = torch.ones(4096, 4096, device="cuda", dtype=torch.bfloat16)
     torch.cuda.synchronize()
     with lmc.Context(G, chunks * G.chunk_bytes, staging_chunks=chunks) as c:
         ids = np.arange(1, chunks + 1, dtype=np.uint64)
         if line is not None:
             c.tune("direct_store_below", line * MIB)
         c.tune("trace", 1)
-        t, l = c.store_begin(slots[0][:n], ids), 0
+        if busy:
+            with torch.cuda.stream(stream):
+                for _ in range(400):
+                    work = (work @ work).clamp_(-1, 1)
+        t, l = c.store_begin(slots[0][:n], ids, stream), 0
         for k in steps:
-            c.store_layers(t, l, k, layers)
+            c.store_layers(t, l, k, layers, stream)
             l += k
+        assert not busy or not stream.query()
         assert l == G.L
         c.wait(t)
         assert sum(r["stage"] == lmc.LMC_STAGE_D2H for r in c.trace_read()[0]) == staged

@@ -59,6 +59,12 @@ struct Op {
     std::vector<int64_t> new_chunk;       // pending store: chunk numbers that are new
     const int64_t *slot_mapping = nullptr;  // pending store: the caller's slot mapping
     std::vector<hipEvent_t> layer_done;   // per layer: event after which the layer is in place
+    // ... or, for steps of a store that count themselves off, the word and the value it has then (0: no such step)
+    struct Count {
+        int word = 0;
+        uint64_t target = 0;
+    };
+    std::vector<Count> layer_count;
     std::vector<hipEvent_t> owned_events; // the distinct events behind layer_done
     // A layer-wise retrieve that runs as one launch (retrieve_in_steps) has words instead: the layers of
     // step i are in place when word i of the context has reached step_target[i].

@@ -107,10 +107,13 @@ __device__ __forceinline__ void arrive(uint64_t word_at) {
 __device__ __forceinline__ void arrive_and_tell(const HostWord &told) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0 &&
-        __hip_atomic_fetch_add((LMC_GLOBAL uint64_t *)told.word, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1 == told.target &&
-        told.host != nullptr)
+    if (threadIdx.x != 0) return;
+    LMC_GLOBAL uint64_t *word = (LMC_GLOBAL uint64_t *)told.word;
+    if (told.host == nullptr) {
+        (void)__hip_atomic_fetch_add(word, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else if (__hip_atomic_fetch_add(word, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1 == told.target) {
         __hip_atomic_store((LMC_GLOBAL uint64_t *)told.host, told.target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // Keeps a wave-uniform value in scalar registers from this point on.

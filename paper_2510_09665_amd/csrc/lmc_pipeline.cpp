@@ -954,6 +954,7 @@ lmc_status_t lmc_store_begin(lmc_ctx_t *c, const int64_t *slot_mapping, const ui
     op.slot_mapping = slot_mapping;
     op.began_idle = idle;
     op.layer_done.assign(size_t(c->cfg.geom.num_layers), nullptr);
+    op.layer_count.assign(size_t(c->cfg.geom.num_layers), Op::Count());
     if (ticket_out) *ticket_out = op.ticket;
     c->ops.push_back(std::move(op));
     return fits ? LMC_OK : LMC_ERR_NOMEM;
@@ -1022,24 +1023,41 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     if (rc == LMC_OK && !direct)
         rc = ring_reslot(c, c->store_ring, (uint64_t(cap) * view.chunk_stride + 255) / 256 * 256, c->s_gather, c->s_d2h,
                          nullptr, c->s_d2h2);
+    // A step without staging counts itself off at its stream's word, whose steps end in order: an event as the launch's
+    // stop event takes the thread 2 us more, and whoever waits for it 10 us more.
     hipEvent_t e = nullptr;
-    if (rc == LMC_OK) rc = get_event(c, false, &e);
+    auto own_event = [&]() -> lmc_status_t {
+        const lmc_status_t r = get_event(c, false, &e);
+        if (r == LMC_OK) op->owned_events.push_back(e);
+        return r;
+    };
+    const bool counts = direct && (beside || (c->cfg.flags & (LMC_FLAG_TIMING | LMC_FLAG_TRACE)) == 0) && may_wait_for_word(c, c->s_gather);
+    if (rc == LMC_OK && !counts) rc = own_event();
+    Op::Count count;
     if (rc == LMC_OK) {
-        op->owned_events.push_back(e);
         // the last step of a store whose steps all ran on the gather stream, or are waited for there, ends the store
         const bool tells = direct && ends && tells_host(c) &&
                            std::all_of(op->ends_on.begin(), op->ends_on.end(), [&](hipStream_t s) { return s == c->s_gather; });
-        uint64_t &reached = c->word_target[beside ? lmc_ctx::kStoreStepWord : lmc_ctx::kStoreWord];
-        lmc::HostWord told{nullptr, nullptr, reached};
-        if (beside) told.word = c->word(lmc_ctx::kStoreStepWord);
-        else if (tells) told = lmc::HostWord{c->word(lmc_ctx::kStoreWord), c->stored_dev, reached};
+        const int word = beside ? lmc_ctx::kStoreStepWord : lmc_ctx::kStoreWord;
+        uint64_t &reached = c->word_target[word];
+        lmc::HostWord told{counts || tells ? c->word(word) : nullptr, tells ? c->stored_dev : nullptr, reached};
         const uint32_t groups = in_turn ? std::max(1u, c->link_groups / 2) : 0u;
         rc = store_groups(c, view, uint64_t(first_layer) * layer_bytes, ptrs, op->slot_mapping, op->new_chunk,
-                          op->slots, cap, false, direct, true, on_second || beside, nullptr, e, beside || tells ? &told : nullptr, groups);
-        if (told.target != reached) (beside ? op->second_target : op->stored_target) = reached = told.target;
-        // a step that cannot count (lmc::HostWord) leaves the end to the events
-        else if (beside) op->has_staged_steps = true;
+                          op->slots, cap, false, direct, true, on_second || beside, nullptr, e, told.word != nullptr ? &told : nullptr, groups);
+        if (told.target != reached) {
+            reached = told.target;
+            if (counts) count = Op::Count{word, reached};
+            if (beside) op->second_target = reached;
+            if (tells) op->stored_target = reached;
+        } else if (beside) {
+            op->has_staged_steps = true;     // rows that cannot count (lmc::HostWord): the end is left to the events
+        }
         op->has_staged_steps = op->has_staged_steps || !direct;
+        if (rc == LMC_OK && counts && count.target == 0 && (rc = own_event()) == LMC_OK)
+            rc = [&]() -> lmc_status_t {
+                HIPCHK(c, hipEventRecord(e, last));
+                return LMC_OK;
+            }();
     }
     if (rc == LMC_OK) {
         rc = [&]() -> lmc_status_t {
@@ -1069,7 +1087,10 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
         for (hipEvent_t x : gone.owned_events) recycle(c, x);
         return rc;
     }
-    for (int32_t l = first_layer; l < first_layer + n_layers; l++) op->layer_done[size_t(l)] = e;
+    for (int32_t l = first_layer; l < first_layer + n_layers; l++) {
+        op->layer_done[size_t(l)] = e;
+        op->layer_count[size_t(l)] = count;
+    }
     op->next_layer = first_layer + n_layers;
     op->steps++;
     if (std::find(op->ends_on.begin(), op->ends_on.end(), last) == op->ends_on.end()) op->ends_on.push_back(last);
@@ -1118,6 +1139,11 @@ lmc_status_t lmc_wait_layer(lmc_ctx_t *c, uint64_t ticket, int32_t layer, void *
         }
         HIPCHK(c, hipStreamWaitEvent(static_cast<hipStream_t>(stream), op->done, 0));   // all layers
         return LMC_OK;
+    }
+    if (!op->layer_count.empty() && op->layer_count[size_t(layer)].target != 0) {
+        const Op::Count &n = op->layer_count[size_t(layer)];
+        if (may_wait_for_word(c, static_cast<hipStream_t>(stream))) return wait_for_word(c, static_cast<hipStream_t>(stream), n.word, n.target);
+        return order_after(c, static_cast<hipStream_t>(stream), n.word == lmc_ctx::kStoreWord ? c->s_gather : c->s_d2h2);
     }
     if (op->layer_done.empty() || (op->layer_done[size_t(layer)] == nullptr && !op->pending))
         return LMC_OK;                                      // nothing was enqueued for it

@@ -238,3 +238,38 @@ def test_store_steps_on_two_streams_in_turn(name, n, kw, how):
             del graph
         if how in ("idle", "odd_groups", "one_stream") and "e" not in kw:
             c.tune("expect_stores_told", 6)
+
+
+@pytest.mark.parametrize("kw", [dict(L=8, NB=64), dict(L=6, H=1, NB=64), dict(L=5, H=1, D=33, e=1, CT=208, NB=64)],
+                         ids=["steps_of_1_mib", "small_steps", "rows_that_do_not_count"])
+@pytest.mark.parametrize("how", ["words", "no_value_waits_any_more", "timed", "after_all"])
+def test_pages_may_be_written_again_behind_the_wait_for_a_stored_layer(kw, how):
+    """A stream that waits for a layer of a store writes the layer's pages: the pool has what was in them before."""
+    import torch
+    from paper_2510_09665_amd import lmc
+    g, src, dst, want, d_slots, d_tau, ids = _setup(1, 83, **kw)
+    stream, writer = torch.cuda.Stream(), torch.cuda.Stream()
+    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=1, flags=lmc.LMC_FLAG_TIMING if how == "timed" else 0) as c:
+        for again in range(4):
+            live = [d.clone() for d in src.dev]
+            torch.cuda.synchronize()
+            t = c.store_begin(d_slots, ids, stream)
+            for l in range(g.L):
+                c.store_layers(t, l, 1, live, stream)
+                if how == "no_value_waits_any_more":
+                    c.tune("value_waits", 0)
+                if how != "after_all":
+                    c.wait_layer(t, l, writer)
+                    with torch.cuda.stream(writer):
+                        live[l].fill_(0xEE)
+                c.tune("value_waits", 1)
+            if how == "after_all":
+                for l in reversed(range(g.L)):
+                    c.wait_layer(t, l, writer)
+                    with torch.cuda.stream(writer):
+                        live[l].fill_(0xEE)
+            c.wait(t)
+            for i, w in zip(ids, want):
+                assert np.array_equal(c.get_host(i), w), again
+            torch.cuda.synchronize()
+            c.clear(ids)

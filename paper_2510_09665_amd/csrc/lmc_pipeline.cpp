@@ -1130,12 +1130,21 @@ lmc_status_t lmc_wait_layer(lmc_ctx_t *c, uint64_t ticket, int32_t layer, void *
             // 4 MiB take to come.  (A stream that takes the handle of a destroyed one has nothing to
             // wait for: the destroyed one's wait was over, see launches_on_caller.)
             if (user == op->waiter && i <= op->waits_for && user != hipStreamPerThread) return LMC_OK;
-            const lmc_status_t rc = wait_for_word(c, user, i, op->step_target[size_t(i)]);
-            if (rc == LMC_OK) {
-                op->waiter = user;
-                op->waits_for = i;
+            lmc_status_t rc = wait_for_word(c, user, i, op->step_target[size_t(i)]);
+            if (rc != LMC_OK) return rc;
+            op->waiter = user;
+            op->waits_for = i;
+            if (size_t(i) + 1 == op->step_target.size()) {
+                // Behind the last wait an event: asked whether a stream has work whose last entry is a wait for a
+                // value, the runtime takes 16 us and says yes however long ago that was over, and the next
+                // retrieve waits for it by another event, 14 us more.
+                hipEvent_t e = nullptr;
+                if ((rc = get_event(c, false, &e)) != LMC_OK) return rc;
+                const hipError_t x = injected_failure(c) ? hipErrorUnknown : hipEventRecord(e, user);
+                c->free_sync_events.push_back(e);
+                HIPCHK(c, x);
             }
-            return rc;
+            return LMC_OK;
         }
         HIPCHK(c, hipStreamWaitEvent(static_cast<hipStream_t>(stream), op->done, 0));   // all layers
         return LMC_OK;

@@ -158,22 +158,25 @@ struct lmc_ctx {
     // 10858, 14797 staged, 8678, 9060, 10866, 15002 direct; in steps of 16 8882, 8970, 10923, 14869 and 8690, 8984,
     // 10910, 14948; 160 MiB in steps of 2 15583, 15594, 19374, 28685 and 14302, 15279, 19751, 28909.  Larger
     // stores in larger steps would lose: 192 MiB in steps of 6 10085, 10105, 11891, 15773 and 9469, 10510, 12522,
-    // 16840, 320 MiB in steps of 4 16444, 16448, 20142, 29586 and 15092, 16886, 20496, 31202.  But where the producer
-    // has nothing on its stream and no other operation is under way there is nothing of the producer's to slow down, and steps of any
-    // size go this way up to the second line: 65, 86, 168, 200, 224 MiB in steps of 9, 6, 11, 6, 7 1374, 1878, 3339, 4115,
-    // 4544 us staged and 1286, 1633, 3172, 3781, 4223 direct, and a first pass, with the runtime's copies still slow, 11-16 ms and 4.
+    // 16840, 320 MiB in steps of 4 16444, 16448, 20142, 29586 and 15092, 16886, 20496, 31202. But where the
+    // producer has nothing on its stream and no other operation is under way there is nothing of the producer's to
+    // slow down, and steps of any size go this way up to the second line: 65, 86, 168, 200, 224 MiB in steps of 9,
+    // 6, 11, 6, 7 1374, 1878, 3339, 4115, 4544 us staged and 1286, 1633, 3172, 3781, 4223 direct, and a first
+    // pass, with the runtime's copies still slow, 11-16 ms and 4.
     // lmc_tune "direct_store_below" sets both lines.
     int64_t direct_store_below = int64_t(64) << 20, direct_store_steps_below = int64_t(256) << 20;
     static constexpr int64_t kDirectStoreStep = int64_t(2) << 20;
     static constexpr int64_t kStoreStepsInTurn = int64_t(512) << 10;   // see lmc_store_layers
-    // Retrieves: up to 256 MiB.  Bulk, 96, 128, 192, 256 MiB: 1857, 2444, 3616, 4793 us staged, 1757, 2340,
-    // 3502, 4684 direct.  What else runs on the GPU loses a part of the compute units to the kernel, but a
-    // staged retrieve makes two hardware queues besides the caller's stand still for as long as it takes,
-    // the copy stream's and the scatter stream's, a direct one only the latter.  128 MiB beside products of 128, 512,
-    // 1536, 4096 rows by 4096 x 4096 of another stream, all of which take 3313, 3238, 3447, 3457 us alone: the
-    // stream in a queue that nothing holds up 3588, 3267, 3259, 4253 (staged) against 3601, 3825, 3924, 4119;
-    // in the copy stream's 5727, 5486, 5676, 5806 against 3581, 3861, 3957, 4170; in the scatter stream's about
-    // 5700 either way; over the four queues 4663, 4381, 4475, 5046 against 4113, 4265, 4368, 4555.
+    // Retrieves: up to 256 MiB. Bulk, 96, 128, 192, 256 MiB: 1857, 2444, 3616, 4793 us staged, 1757, 2340, 3502,
+    // 4684 direct. What else runs on the GPU loses a part of the compute units to the kernel, but a staged
+    // retrieve makes two hardware queues besides the caller's stand still for as long as it takes, the copy
+    // stream's and the scatter stream's, a direct one on the caller's stream none. 128 MiB beside products of 128,
+    // 512, 1536, 4096 rows by 4096 x 4096 of another stream, all of which take 3283, 2979, 2872, 3040 us alone:
+    // the stream in a queue that nothing holds up 3682, 3360, 3123, 4168 (staged) against 3625, 3845, 3794, 4044;
+    // in the copy stream's or the scatter stream's about 5740, 5460, 5340, 5520 against 3630, 3830, 3800, 4050;
+    // over the four queues 4693, 4387, 4226, 4844 against 3626, 3833, 3795, 4046; 256 MiB 9221, 8677, 8697, 10003
+    // against 7147, 7632, 7588, 8254. Beyond, 100 us are 2 % and less, and a stream that has been placed
+    // (lmc_probe_stream) keeps its compute units.
     // Layer by layer a stage costs 10 us between two copies and 5-7 more for a rectangle besides, so
     // steps of at most 8 MiB go this way up to twice as much.  The consumer's products between the
     // layers, 128 MiB in steps of 4 MiB: 9274, 9100, 11231, 14595 staged, 8343, 8996, 10856, 14459 direct with

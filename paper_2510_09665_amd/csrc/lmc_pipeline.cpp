@@ -493,12 +493,11 @@ static lmc_status_t retrieve_in_steps(lmc_ctx *c, const lmc::LayerPtrs &ptrs, co
 // event has to cross from that stream to the library's and back: those two hand-overs cost the
 // calling thread 26 us (a query and a wait between streams are 12-14 us each on this runtime)
 // and leave the link idle in between when one such retrieve follows another.  Call after call, three
-// contexts in turn: 0.5 MiB 53 -> 36 us, 12 MiB in 256-byte rows 234 -> 223 us.  The kernel tells the host
-// when it is done, and only where something has to wait for it on the device or a thread does, the scatter stream is made to wait
-// for its word and an event is recorded behind that (scatters_after_loads), 4 us of the call and a waiting queue
-// for as long as the transfer takes otherwise.  What the runtime does
-// for the first launch on a stream that has run nothing is now done inside the call: a program's
-// first 0.5 MiB takes 155-190 us instead of 150-160.
+// contexts in turn: 0.5 MiB 53 -> 36 us, 12 MiB in 256-byte rows 234 -> 223 us. The kernel tells the host
+// when it is done; only where something has to wait for it on the device, or a thread does, is the scatter
+// stream made to wait for its word and an event recorded behind that (scatters_after_loads), which else
+// takes 4 us of the call and a hardware queue for as long as the transfer lasts (0.5 MiB 15.9 -> 9.5 us).
+// What the runtime does for the first launch on a stream that has run nothing is done inside the call.
 // Not while the stream is being captured, not for a stream of another GPU, and not where the caller's
 // stream is not to wait ("caller_waits" 0), where the library itself waits before it launches
 // (LMC_FLAG_VALIDATE_SLOTS) or where a launch leaves an event behind on its stream (timing,
@@ -991,24 +990,26 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     const bool idle = caller_is_idle(user);
     // the producer has nothing more on its stream (nor had in front of the slot mapping), and nothing else is under way
     const bool undisturbed = idle && op->began_idle && c->ops.size() == 1;
-    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 || n_new * c->chunk_bytes <= c->direct_store_below ||
-                        (n_new * c->chunk_bytes <= c->direct_store_steps_below && (step_bytes <= lmc_ctx::kDirectStoreStep || undisturbed));
+    const int64_t bytes = n_new * c->chunk_bytes;
+    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 || bytes <= c->direct_store_below ||
+                        (bytes <= c->direct_store_steps_below && (step_bytes <= lmc_ctx::kDirectStoreStep || undisturbed));
     // Steps take the two copy streams in turn (as the steps of a layer-wise retrieve do):
     // between two copies of one stream the runtime leaves the link idle for some 20 us,
     // 7 % of a step of one Llama-3-8B layer, while on the other stream (another hardware
     // queue, see arrange_streams) the next step's copy is ready to start.  Not while a
     // retrieve is under way, whose kernels that stream would hold up.
     const bool on_second = !direct && (op->steps & 1) != 0 && c->store_step_streams == 2 && !other_direction_busy(c, true);
-    // Then steps without staging take the gather stream and the second
-    // copy stream to the host in turn (which sits in the scatter stream's hardware queue, so that the library's kernels
-    // hold up no third one), each with half of the groups, so that one step's first slots and last stores do not leave the link idle: kernels of one stream
-    // follow each other 1.4 us apart, and the first store of one and the last of the other are some 3 more.  On one stream and on two, steps of
-    // 0.6, 0.9, 1, 1.3 MiB: 34 MiB 809 and 760 us, 22 490 and 461, 32 700 and 641, 105 2160 and 2020.  Not for steps under
-    // 0.5 MiB (1.1 MiB in four 52 and 77 us, 10.7 in 61 of 0.2 528 and 645), whose launches take the thread longer than the link,
-    // nor beside other operations, whose copies they might have to wait for.  Beside the producer's products, which put
-    // time between the steps, there is nothing to gain, and a second hardware queue would wait (64 MiB in steps of 2, 128 rows,
-    // over the four queues the producer's stream can be in, 5791 and 5905 us).  The last step is on the gather stream,
-    // behind the other's: what waits for the store waits for one stream.
+    // In an undisturbed store the steps without staging take the gather stream and the second copy stream to the
+    // host in turn (which sits in the scatter stream's hardware queue, so that the library's kernels hold up no
+    // third one), each with half of the groups, so that one step's first slots and last stores do not leave the
+    // link idle: kernels of one stream follow each other 1.4 us apart, and the first store of one and the last of
+    // the other are some 3 more. On one stream and on two, steps of 0.6, 0.9, 1, 1.3 MiB: 34 MiB 809 and 760 us,
+    // 22 490 and 461, 32 700 and 641, 105 2160 and 2020. Not for steps under 0.5 MiB (1.1 MiB in four 52 and 77
+    // us, 10.7 in 61 of 0.2 528 and 645), whose launches take the thread longer than the link, nor beside other
+    // operations, whose copies they might have to wait for. Behind a producer at work, which puts time between the
+    // steps, there is nothing to gain, and a second hardware queue would wait (64 MiB in steps of 2, products of
+    // 128 rows, over the four queues the producer's stream can be in, 5791 and 5905 us). The last step is on the
+    // gather stream, behind the other's: what waits for the store waits for one stream.
     const bool ends = first_layer + n_layers == geom.num_layers;
     const bool in_turn = undisturbed && direct && c->store_step_streams == 2 && step_bytes >= lmc_ctx::kStoreStepsInTurn &&
                          may_wait_for_word(c, c->s_gather);
@@ -1023,15 +1024,16 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     if (rc == LMC_OK && !direct)
         rc = ring_reslot(c, c->store_ring, (uint64_t(cap) * view.chunk_stride + 255) / 256 * 256, c->s_gather, c->s_d2h,
                          nullptr, c->s_d2h2);
-    // A step without staging counts itself off at its stream's word, whose steps end in order: an event as the launch's
-    // stop event takes the thread 2 us more, and whoever waits for it 10 us more.
+    // A step without staging counts itself off at its stream's word, whose steps end in order: an event as the
+    // launch's stop event takes the thread 2 us more, and whoever waits for it 10 us more.
     hipEvent_t e = nullptr;
     auto own_event = [&]() -> lmc_status_t {
         const lmc_status_t r = get_event(c, false, &e);
         if (r == LMC_OK) op->owned_events.push_back(e);
         return r;
     };
-    const bool counts = direct && (beside || (c->cfg.flags & (LMC_FLAG_TIMING | LMC_FLAG_TRACE)) == 0) && may_wait_for_word(c, c->s_gather);
+    const bool timed = (c->cfg.flags & (LMC_FLAG_TIMING | LMC_FLAG_TRACE)) != 0;
+    const bool counts = direct && (beside || !timed) && may_wait_for_word(c, c->s_gather);
     if (rc == LMC_OK && !counts) rc = own_event();
     Op::Count count;
     if (rc == LMC_OK) {
@@ -1043,7 +1045,8 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
         lmc::HostWord told{counts || tells ? c->word(word) : nullptr, tells ? c->stored_dev : nullptr, reached};
         const uint32_t groups = in_turn ? std::max(1u, c->link_groups / 2) : 0u;
         rc = store_groups(c, view, uint64_t(first_layer) * layer_bytes, ptrs, op->slot_mapping, op->new_chunk,
-                          op->slots, cap, false, direct, true, on_second || beside, nullptr, e, told.word != nullptr ? &told : nullptr, groups);
+                          op->slots, cap, false, direct, true, on_second || beside, nullptr, e,
+                          told.word != nullptr ? &told : nullptr, groups);
         if (told.target != reached) {
             reached = told.target;
             if (counts) count = Op::Count{word, reached};
@@ -1125,10 +1128,10 @@ lmc_status_t lmc_wait_layer(lmc_ctx_t *c, uint64_t ticket, int32_t layer, void *
         const int32_t i = layer / op->step_layers;
         hipStream_t user = static_cast<hipStream_t>(stream);
         if (may_wait_for_word(c, user)) {
-            // The steps end in order, so a stream that has been made to wait for this one or a later one need
-            // not wait again: a wait takes the calling thread 3 us and the stream's queue as long, 32 of them more than
-            // 4 MiB take to come.  (A stream that takes the handle of a destroyed one has nothing to
-            // wait for: the destroyed one's wait was over, see launches_on_caller.)
+            // The steps end in order, so a stream that has been made to wait for this one or a later one need not
+            // wait again: a wait takes the calling thread 3 us and the stream's queue as long, 32 of them more
+            // than 4 MiB take to come. (A stream that takes the handle of a destroyed one has nothing to wait for:
+            // the destroyed one's wait was over, see launches_on_caller.)
             if (user == op->waiter && i <= op->waits_for && user != hipStreamPerThread) return LMC_OK;
             lmc_status_t rc = wait_for_word(c, user, i, op->step_target[size_t(i)]);
             if (rc != LMC_OK) return rc;
@@ -1137,7 +1140,8 @@ lmc_status_t lmc_wait_layer(lmc_ctx_t *c, uint64_t ticket, int32_t layer, void *
             if (size_t(i) + 1 == op->step_target.size()) {
                 // Behind the last wait an event: asked whether a stream has work whose last entry is a wait for a
                 // value, the runtime takes 16 us and says yes however long ago that was over, and the next
-                // retrieve waits for it by another event, 14 us more.
+                // retrieve then waits for it by another event, 14 us more. 0.5 MiB layer by layer, three contexts
+                // in turn: 45 -> 21 us.
                 hipEvent_t e = nullptr;
                 if ((rc = get_event(c, false, &e)) != LMC_OK) return rc;
                 const hipError_t x = injected_failure(c) ? hipErrorUnknown : hipEventRecord(e, user);
@@ -1151,8 +1155,9 @@ lmc_status_t lmc_wait_layer(lmc_ctx_t *c, uint64_t ticket, int32_t layer, void *
     }
     if (!op->layer_count.empty() && op->layer_count[size_t(layer)].target != 0) {
         const Op::Count &n = op->layer_count[size_t(layer)];
-        if (may_wait_for_word(c, static_cast<hipStream_t>(stream))) return wait_for_word(c, static_cast<hipStream_t>(stream), n.word, n.target);
-        return order_after(c, static_cast<hipStream_t>(stream), n.word == lmc_ctx::kStoreWord ? c->s_gather : c->s_d2h2);
+        hipStream_t user = static_cast<hipStream_t>(stream);
+        if (may_wait_for_word(c, user)) return wait_for_word(c, user, n.word, n.target);
+        return order_after(c, user, n.word == lmc_ctx::kStoreWord ? c->s_gather : c->s_d2h2);
     }
     if (op->layer_done.empty() || (op->layer_done[size_t(layer)] == nullptr && !op->pending))
         return LMC_OK;                                      // nothing was enqueued for it

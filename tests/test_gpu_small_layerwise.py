@@ -179,8 +179,9 @@ def test_captured_into_a_graph(what, flag):
                                  "late_mapping"])
 def test_store_steps_on_two_streams_in_turn(name, n, kw, how):
     """Steps of 0.5 MiB and more from a stream that is idle: every byte is in the pool when the wait returns, and
-    a retrieve issued right behind sees all of them.  The slot mapping comes late on another stream, the stream becomes busy, another operation comes, a staged
-    step follows, or another stream is captured between two steps."""
+    a retrieve issued right behind sees all of them.  The slot mapping comes late on another stream, the
+    stream becomes busy, another operation comes, a staged step follows, or another stream is captured
+    between two steps."""
     import torch
     from gpu_util import assert_layers_equal
     from paper_2510_09665_amd import lmc

@@ -409,10 +409,9 @@ lmc_status_t scatters_after_loads(lmc_ctx *c) {
     for (const Op &o : c->ops)
         if (lacks_event(o)) last = &o;      // tickets are in order, and so are the targets; all are on one stream
     if (last == nullptr) return LMC_OK;
-    if (is_capturing(c->s_scatter)) {       // what is outside a capture cannot be waited for inside
-        while (!c->is_loaded(last->loaded_target)) __builtin_ia32_pause();
-        return LMC_OK;
-    }
+    // What is outside a capture cannot be waited for inside.  No call gets here: a load tells only while the
+    // scatter stream is not being captured, and the stream joins a capture behind this function.
+    if (is_capturing(c->s_scatter)) return LMC_ERR_BUSY;
     // "value_waits" may have been switched off since; a stream with work is not destroyed (launches_on_caller)
     lmc_status_t rc = may_wait_for_word(c, c->s_scatter) ? wait_for_word(c, c->s_scatter, lmc_ctx::kBulkWord, last->loaded_target)
                                                          : order_after(c, c->s_scatter, last->caller);

@@ -345,23 +345,25 @@ static bool waits_block() {
 // once, or a little longer, and leaves the rest to the event.  The thread stays on its core meanwhile, as
 // it does in hipEventSynchronize to the end of any wait (a store behind 50 ms of other work: 50 ms of
 // the core either way), unless the process has asked for waits that block: then it looks for 50 us (the
-// runtime itself for 0.7 ms) and sleeps.
+// runtime itself for 0.7 ms) and sleeps.  A load that tells has no event: whatever stream one were
+// recorded on, it might lie behind newer work.  The thread goes on looking, where waits block every 50 us.
 static hipError_t await(const lmc_ctx *c, const Awaited &a) {
-    if (a.stored_target != 0 || a.loaded_target != 0) {
-        using std::chrono::microseconds;
-        const auto begin = std::chrono::steady_clock::now();
-        bool asked = false;
-        for (auto now = begin; now < begin + microseconds(1500); now = std::chrono::steady_clock::now()) {
-            for (int i = 0; i < 64; i++) {
-                if (c->is_stored(a.stored_target) || c->is_loaded(a.loaded_target)) return hipSuccess;
-                __builtin_ia32_pause();
-            }
-            if (asked || now < begin + microseconds(50)) continue;   // the shortest stores end before they ask
-            asked = true;
-            if (waits_block()) break;
+    if (a.stored_target == 0 && a.loaded_target == 0) return hipEventSynchronize(a.event);
+    using std::chrono::microseconds;
+    const auto begin = std::chrono::steady_clock::now();
+    bool asked = false, blocks = false;
+    for (;;) {
+        for (int i = 0; i < 64; i++) {
+            if (c->is_stored(a.stored_target) || c->is_loaded(a.loaded_target)) return hipSuccess;
+            __builtin_ia32_pause();
         }
+        const auto now = std::chrono::steady_clock::now();
+        if (now < begin + microseconds(50)) continue;   // the shortest transfers end before they ask
+        if (!asked) blocks = waits_block();
+        asked = true;
+        if (a.event != nullptr && (blocks || now >= begin + microseconds(1500))) return hipEventSynchronize(a.event);
+        if (blocks) std::this_thread::sleep_for(microseconds(50));
     }
-    return hipEventSynchronize(a.event);
 }
 
 // Sleeps until everything in `all` has completed, with the context's mutex released so
@@ -627,12 +629,13 @@ lmc_status_t lmc_wait(lmc_ctx_t *c, uint64_t ticket) {
     if (!c->has_device) return LMC_OK;
     DeviceScope dev(c);
     // Operations end on different streams that are not ordered among each other (a staged
-    // store on the D2H stream, a store without staging on the gather stream, every
-    // retrieve on the scatter stream), so the newest operation alone says nothing about
-    // the older ones: the newest event of every such stream is waited for.
+    // store on the D2H stream, a store without staging on the gather stream, a retrieve on
+    // the scatter stream or on a caller's), so the newest operation alone says nothing about
+    // the older ones: the newest of every such stream is waited for.  Retrieves count as one
+    // stream: those on a caller's are in its order, and the scatter stream waits for them.
     std::vector<hipStream_t> streams;
     std::vector<Awaited> last;
-    for (Op &o : c->ops) {
+    for (const Op &o : c->ops) {
         if (o.ticket > ticket) continue;
         if (o.pending) {
             // a layer-wise store still short of layers cannot be waited for; when it is
@@ -640,12 +643,7 @@ lmc_status_t lmc_wait(lmc_ctx_t *c, uint64_t ticket) {
             if (everything || o.ticket == ticket) return LMC_ERR_BUSY;
             continue;
         }
-        if (c->is_loaded(o.loaded_target)) continue;
-        if (o.loaded_target != 0 && o.done == nullptr) {
-            const lmc_status_t rc = scatters_after_loads(c);
-            if (rc != LMC_OK) return rc;
-        }
-        if (o.done == nullptr) continue;
+        if (o.done == nullptr && o.loaded_target == 0) continue;
         // a layer-wise store ends when its last layer is submitted, perhaps behind a newer
         // ticket on the same stream: it is waited for by itself
         const size_t i = o.layerwise ? streams.size()
@@ -886,6 +884,11 @@ lmc_status_t lmc_tune(lmc_ctx_t *c, const char *key, int64_t value) {
     } else if (k == "caller_waits" && value <= 1) {
         c->caller_waits = value != 0;
     } else if (k == "value_waits" && value <= 1) {
+        if (value == 0 && c->can_wait_for_words()) {     // what was to wait for a word later does so now
+            DeviceScope dev(c);
+            const lmc_status_t rc = scatters_after_loads(c);
+            if (rc != LMC_OK) return rc;
+        }
         c->value_waits = value != 0;
     } else if (k == "copy_kernel" && value <= 3) {
         c->copy_kernel = uint32_t(value);

@@ -14,6 +14,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/lmc.h"
@@ -41,7 +42,7 @@ struct Op {
     hipEvent_t done = nullptr;       // null: nothing enqueued (yet) for this ticket
     hipStream_t final_stream = nullptr;  // the library stream `done` was recorded on
     // Not 0: finished when the word of host memory has reached this.  A load that tells (its kernels run on the
-    // caller's own stream) has no event until somebody has to wait for it (scatters_after_loads).
+    // caller's own stream) has no event.
     uint64_t stored_target = 0, loaded_target = 0;
     bool on_caller = false;              // its kernels run on the caller's own stream ...
     hipStream_t caller = nullptr;        // ... this one
@@ -224,8 +225,9 @@ struct lmc_ctx {
     bool is_stored(uint64_t target) const { return target != 0 && __atomic_load_n(stored_host, __ATOMIC_ACQUIRE) >= target; }
     // A bulk load that runs on the caller's stream tells the host likewise, at kBulkWord and the second word: nothing
     // of the library's then waits for it, on no stream, unless something else is to use the scatter stream meanwhile
-    // or a thread waits for the load.
+    // (scatters_behind: the value that stream has been made to wait for).
     bool is_loaded(uint64_t target) const { return target != 0 && __atomic_load_n(stored_host + kLoadedAt, __ATOMIC_ACQUIRE) >= target; }
+    uint64_t scatters_behind = 0;
     uint64_t *words = nullptr;
     uint64_t word_target[kWords] = {};
     // May a stream be made to wait for a word (lmc_tune "value_waits")?  The runtime waits for a value,

@@ -401,32 +401,19 @@ static lmc_status_t wait_for_word(lmc_ctx *c, hipStream_t stream, int word, uint
     return LMC_OK;
 }
 
-// Orders the scatter stream behind the bulk loads that run on a caller's stream and have told nobody yet, and
-// gives them their events, which lie in front of whatever the scatter stream is given next.
+// Orders the scatter stream behind the bulk loads that run on a caller's stream and have not told yet.  They are all
+// on one stream (launches_on_caller), so the newest's value is enough.
 lmc_status_t scatters_after_loads(lmc_ctx *c) {
-    auto lacks_event = [c](const Op &o) { return o.loaded_target != 0 && o.done == nullptr && !c->is_loaded(o.loaded_target); };
-    const Op *last = nullptr;
+    uint64_t newest = 0;
     for (const Op &o : c->ops)
-        if (lacks_event(o)) last = &o;      // tickets are in order, and so are the targets; all are on one stream
-    if (last == nullptr) return LMC_OK;
+        if (!c->is_loaded(o.loaded_target)) newest = std::max(newest, o.loaded_target);
+    if (newest <= c->scatters_behind) return LMC_OK;
     // What is outside a capture cannot be waited for inside.  No call gets here: a load tells only while the
-    // scatter stream is not being captured, and the stream joins a capture behind this function.
-    if (is_capturing(c->s_scatter)) return LMC_ERR_BUSY;
-    // "value_waits" may have been switched off since; a stream with work is not destroyed (launches_on_caller)
-    lmc_status_t rc = may_wait_for_word(c, c->s_scatter) ? wait_for_word(c, c->s_scatter, lmc_ctx::kBulkWord, last->loaded_target)
-                                                         : order_after(c, c->s_scatter, last->caller);
-    for (Op &o : c->ops) {
-        if (rc != LMC_OK) return rc;
-        if (!lacks_event(o)) continue;
-        hipEvent_t e = nullptr;
-        if ((rc = get_event(c, false, &e)) != LMC_OK) return rc;
-        const hipError_t x = injected_failure(c) ? hipErrorUnknown : hipEventRecord(e, c->s_scatter);
-        if (x != hipSuccess) {
-            c->free_sync_events.push_back(e);
-            HIPCHK(c, x);
-        }
-        o.done = e;
-    }
+    // scatter stream is not being captured, and the stream joins a capture behind this function; "value_waits"
+    // is switched off behind it too.
+    if (!may_wait_for_word(c, c->s_scatter)) return LMC_ERR_BUSY;
+    const lmc_status_t rc = wait_for_word(c, c->s_scatter, lmc_ctx::kBulkWord, newest);
+    if (rc == LMC_OK) c->scatters_behind = newest;
     return rc;
 }
 
@@ -493,8 +480,8 @@ static lmc_status_t retrieve_in_steps(lmc_ctx *c, const lmc::LayerPtrs &ptrs, co
 // calling thread 26 us (a query and a wait between streams are 12-14 us each on this runtime)
 // and leave the link idle in between when one such retrieve follows another.  Call after call, three
 // contexts in turn: 0.5 MiB 53 -> 36 us, 12 MiB in 256-byte rows 234 -> 223 us. The kernel tells the host
-// when it is done; only where something has to wait for it on the device, or a thread does, is the scatter
-// stream made to wait for its word and an event recorded behind that (scatters_after_loads), which else
+// when it is done; only where something of the library's has to wait for it on the device is the scatter
+// stream made to wait for its word (scatters_after_loads), which else
 // takes 4 us of the call and a hardware queue for as long as the transfer lasts (0.5 MiB 15.9 -> 9.5 us).
 // What the runtime does for the first launch on a stream that has run nothing is done inside the call.
 // Not while the stream is being captured, not for a stream of another GPU, and not where the caller's

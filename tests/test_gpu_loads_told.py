@@ -1,8 +1,8 @@
 """Bulk retrieves on the caller's stream tell the host through a word of its memory that their last byte is
-in the pages, and have no event unless something has to wait for them.  Pages read as soon as the wait returns, for
+in the pages, and have no event.  Pages read as soon as the wait returns, for
 rows of every kind and odd numbers of groups; what is issued next from another stream, with value waits
-switched off meanwhile or into a graph, comes behind them; several threads wait for one; and an older ticket
-does not wait for a newer one."""
+switched off meanwhile or into a graph, comes behind them; several threads wait for one; an older ticket
+does not wait for a newer one, be it of the same stream; and a process that asked for waits that block sleeps."""
 import threading
 import time
 import zlib
@@ -150,6 +150,103 @@ def test_an_older_ticket_does_not_wait_for_a_newer_one():
         torch.cuda.synchronize()
         del keep, del_me
         assert early
+
+
+@pytest.mark.parametrize("how", ["wait", "threads", "no_value_waits", "two_older", "another_stream"])
+def test_an_older_ticket_does_not_wait_for_a_newer_one_of_its_stream(how):
+    """Some ten milliseconds of work, a retrieve, several times as much work, another retrieve, all on one stream:
+    the wait for the first lasts long enough to have stopped looking at anything but its end."""
+    import torch
+    from gpu_util import assert_layers_equal
+    from paper_2510_09665_amd import lmc
+    n = 2
+    g, want, ids, d_tau, hosts = _case("rows_of_256", n, 6)
+    dev, elsewhere = _pages(g), _pages(g)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    with lmc.Context(g, 2 * n * g.chunk_bytes, staging_chunks=2) as c:
+        c.put_host(ids, want)
+        c.wait(c.retrieve(ids[:n], d_tau, dev, a))
+        torch.cuda.synchronize()
+        for again in range(2):
+            with torch.cuda.stream(a):
+                torch.cuda._sleep(1 << 25)
+            old = c.retrieve(ids[:n], d_tau, dev, a)
+            if how == "two_older":
+                old = c.retrieve(ids[:n], d_tau, dev, a)
+            with torch.cuda.stream(a):
+                for _ in range(4):
+                    torch.cuda._sleep(1 << 25)
+            new = c.retrieve(ids[n:], d_tau, dev, a)
+            third = c.retrieve(ids[:n], d_tau, elsewhere, b) if how == "another_stream" else None
+            if how == "no_value_waits":
+                c.tune("value_waits", 0)
+            assert not c.test(old)
+            if how == "threads":
+                done = []
+                threads = [threading.Thread(target=lambda: (c.wait(old), done.append(c.test(old) and not c.test(new))))
+                           for _ in range(3)]
+                for x in threads:
+                    x.start()
+                for x in threads:
+                    x.join()
+                early = done == [True] * 3
+            else:
+                c.wait(old)
+                early = c.test(old) and not c.test(new)
+            c.tune("value_waits", 1)
+            c.wait(third or new)
+            assert c.test(new)
+            torch.cuda.synchronize()
+            assert early, again
+            assert_layers_equal([d.cpu().numpy() for d in dev], hosts[1])
+        c.clear(ids)
+
+
+BLOCKING = """
+import ctypes, sys, time
+sys.path[:0] = [%r, %r]
+import torch
+from conftest import _hip_runtime
+from paper_2510_09665_amd import lmc
+from test_gpu_loads_told import _case, _pages
+torch.zeros(1, device="cuda")
+assert _hip_runtime().hipSetDeviceFlags(ctypes.c_uint(4)) == 0          # hipDeviceScheduleBlockingSync
+n = 2
+g, want, ids, d_tau, _ = _case("rows_of_256", n, 7)
+dev, s = _pages(g), torch.cuda.Stream()
+with lmc.Context(g, 2 * n * g.chunk_bytes, staging_chunks=1) as c:
+    c.put_host(ids, want)
+    spent, early = [], 0
+    for k in range(6):
+        torch.cuda.synchronize()
+        begin = time.perf_counter()
+        with torch.cuda.stream(s):
+            torch.cuda._sleep(1 << 25)
+            old = c.retrieve(ids[:n], d_tau, dev, s)
+            torch.cuda._sleep(1 << 25)
+            new = c.retrieve(ids[n:], d_tau, dev, s)
+        cpu = time.thread_time()
+        c.wait(old)
+        spent.append(time.thread_time() - cpu)
+        early += c.test(old) and not c.test(new)
+        took = time.perf_counter() - begin
+        c.wait(new)
+print(sorted(spent)[2], took, early)
+"""
+
+
+def test_a_process_that_asked_for_blocking_waits_does_not_spin():
+    """A load behind some ten milliseconds of other work, in front of as much and another load."""
+    import os
+    import subprocess
+    import sys
+    here = os.path.dirname(os.path.abspath(__file__))
+    res = subprocess.run([sys.executable, "-c", BLOCKING % (os.path.dirname(here), here)], capture_output=True, text=True,
+                         timeout=110)
+    assert res.returncode == 0, res.stderr[-2000:]
+    cpu, took, early = map(float, res.stdout.split()[-3:])
+    assert took > 5e-3 and early == 6, res.stdout
+    assert cpu < 0.25 * took, res.stdout          # 1.00 where it looks all the time; 15 us of every 100 where it sleeps
 
 
 def test_threads_wait_for_one_load_and_for_everything():

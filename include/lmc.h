@@ -642,7 +642,8 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * error paths: the n-th HIP call the library checks from now on is not made and counts as
  * failed, once; 0 = off.  Nothing on the device goes wrong), "expect_stores_told" (likewise for
  * tests: LMC_OK if that many stores without staging have told the host of their end by a word in its
- * memory, and not by an event, since the context was made, else LMC_ERR_INVAL; sets nothing).
+ * memory, and not by an event, since the context was made, else LMC_ERR_INVAL; sets nothing),
+ * "expect_groups_staged" (likewise: that many groups of stores have gone through staging).
  * Unknown key or out-of-range value: LMC_ERR_INVAL. */
 lmc_status_t lmc_tune(lmc_ctx_t *ctx, const char *key, int64_t value);
 

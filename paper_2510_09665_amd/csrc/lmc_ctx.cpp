@@ -915,6 +915,8 @@ lmc_status_t lmc_tune(lmc_ctx_t *c, const char *key, int64_t value) {
         c->fail_hip_after = uint32_t(value);
     } else if (k == "expect_stores_told") {
         return uint64_t(value) == c->stores_told ? LMC_OK : LMC_ERR_INVAL;
+    } else if (k == "expect_groups_staged") {
+        return uint64_t(value) == c->groups_staged ? LMC_OK : LMC_ERR_INVAL;
     } else if (k == "nt_load" && value <= 1) {
         c->shape.nt_load = value != 0;
     } else if (k == "nt_store" && value <= 1) {

@@ -259,8 +259,9 @@ struct lmc_ctx {
     // Test hook (lmc_tune "fail_hip_after"): the n-th checked HIP call from now is not made
     // and counts as failed.  Forces the error paths without any fault on the device.
     uint32_t fail_hip_after = 0;
-    // and another ("expect_stores_told"): stores that the host was told the end of by the word
-    uint64_t stores_told = 0;
+    // and two others ("expect_stores_told", "expect_groups_staged"): stores that the host was told the end of by
+    // the word, and groups of stores that went through a staging buffer
+    uint64_t stores_told = 0, groups_staged = 0;
     lmc_stats_t stats{};
     int32_t last_hip_error = 0;
 };

@@ -824,6 +824,7 @@ static lmc_status_t store_groups(lmc_ctx *c, const lmc::LaunchView &view, uint64
             HIPCHK(c, lmc::launch_fill(buf, 0xA5, uint64_t(k) * view.chunk_stride, copies));
         HIPCHK(c, hipEventRecord(ring.drained[b], copies));
         ring.used[b] = 1;
+        c->groups_staged++;
         if (group_events != nullptr) {
             // "these chunks are in the pool": an event of the group's own (drained[b] is recorded
             // again whenever the buffer comes round), kept by the store until it is reaped

@@ -26,23 +26,30 @@ def _setup(n, seed, name="llama3_8b", **kw):
     return g, src, dst, want, slots_to_device(slots), slots_to_device(tau), np.arange(1, 1 + n, dtype=np.uint64)
 
 
-@pytest.mark.parametrize("steps", [(1,) * 8, (1, 2, 1, 3, 1), (3, 1, 4), (2, 2, 2, 1, 1), (8,)])
-@pytest.mark.parametrize("timing", [False, True])
-def test_store_steps_of_any_size(steps, timing):
+@pytest.mark.parametrize("steps,staged", [((1,) * 8, ()), ((1,) * 8, (0, 2, 4, 6)), ((1,) * 8, (1, 3, 5, 7)), ((1, 2, 1, 3, 1), (1, 3)),
+                                          ((3, 1, 4), (0, 2)), ((2, 2, 2, 1, 1), (0, 1, 2)), ((2, 2, 2, 1, 1), (2,)),
+                                          ((7, 1), (0,)), ((1, 1, 1, 1, 3, 1), (4,)), ((1, 7), (1,)), ((8,), (0,))])
+@pytest.mark.parametrize("how", ["behind_a_producer", "idle", "timed"])
+def test_store_steps_of_any_size(steps, staged, how):
+    """Steps of one store with staging (`staged`: which) and without, behind each other in every order, in turn on
+    two streams where the caller's is idle: a store whose last step goes without staging has ended when the
+    copies of the others have, and only one that has none of them says so by the word."""
     import torch
     from paper_2510_09665_amd import lmc
     g, src, dst, want, d_slots, d_tau, ids = _setup(2, sum(i * s for i, s in enumerate(steps)))
     stream = torch.cuda.Stream()
-    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=2, flags=lmc.LMC_FLAG_TIMING if timing else 0) as c:
-        for again in range(2):
-            live = [torch.zeros_like(d) for d in src.dev]        # filled layer by layer on the caller's stream
+    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=2, flags=lmc.LMC_FLAG_TIMING if how == "timed" else 0) as c:
+        for again in range(4):
+            live = [torch.zeros_like(d) if how == "behind_a_producer" else d for d in src.dev]
             torch.cuda.synchronize()
             t = c.store_begin(d_slots, ids, stream)
             l = 0
-            for k in steps:
-                with torch.cuda.stream(stream):
-                    for i in range(l, l + k):
-                        live[i].copy_(src.dev[i])
+            for i, k in enumerate(steps):
+                if how == "behind_a_producer":               # filled layer by layer on the caller's stream
+                    with torch.cuda.stream(stream):
+                        for x in range(l, l + k):
+                            live[x].copy_(src.dev[x])
+                c.tune("direct_store_below", 0 if i in staged else 64 << 20)
                 c.store_layers(t, l, k, live, stream)
                 l += k
             assert l == g.L
@@ -51,6 +58,10 @@ def test_store_steps_of_any_size(steps, timing):
             for i, w in zip(ids, want):
                 assert np.array_equal(c.get_host(i), w)
             assert c.get_stats()["bytes_d2h"] == (again + 1) * 2 * g.chunk_bytes
+            c.tune("expect_groups_staged", (again + 1) * len(staged))
+            c.tune("expect_stores_told", again + 1 if not staged and how != "timed" else 0)
+            c.clear(ids)
+            c.put_host(ids, want ^ 255)                       # the slots hold other bytes before the next pass
             c.clear(ids)
 
 

@@ -56,6 +56,7 @@ struct Op {
     // pending store: not 0: its steps without staging on s_d2h2 are done when kStoreStepWord has reached this
     uint64_t second_target = 0;
     bool has_staged_steps = false;
+    hipStream_t producer = nullptr;       // pending store: the stream its last step was handed in with
     bool began_idle = false;              // pending store: nothing was on the caller's stream when it began
     std::vector<int64_t> new_chunk;       // pending store: chunk numbers that are new
     const int64_t *slot_mapping = nullptr;  // pending store: the caller's slot mapping
@@ -71,8 +72,23 @@ struct Op {
     // step i are in place when word i of the context has reached step_target[i].
     int32_t step_layers = 0;
     std::vector<uint64_t> step_target;
-    hipStream_t waiter = nullptr;         // the last stream that was made to wait for a step of it ...
-    int32_t waits_for = -1;               // ... and for which
+    // The last stream that was made to wait for a step of it, and how far: for the steps of a load (waited[0]: how
+    // many), for the values of kStoreWord and kStoreStepWord.  Steps end in order, so a stream that waits for one
+    // need not wait for it or an earlier one again: a wait takes the calling thread 3 us and the stream's queue as
+    // long, 32 of them more than 4 MiB take to come.  (A stream that takes the handle of a destroyed one has nothing
+    // to wait for: the destroyed one's wait was over, see launches_on_caller.)
+    hipStream_t waiter = nullptr;
+    uint64_t waited[2] = {0, 0};
+    bool waits_last = false;              // the newest wait has no event behind it (event_behind_wait)
+    bool has_waiting(hipStream_t s, int which, uint64_t upto) const {
+        return s == waiter && upto <= waited[which] && s != hipStreamPerThread;
+    }
+    void made_wait(hipStream_t s, int which, uint64_t upto) {
+        if (s != waiter) waited[0] = waited[1] = 0;
+        waiter = s;
+        waited[which] = upto;
+        waits_last = true;
+    }
 };
 
 // One timed step of a pipeline: a kernel launch (LMC_FLAG_TIMING, LMC_FLAG_TRACE) or the

@@ -285,3 +285,43 @@ def test_pages_may_be_written_again_behind_the_wait_for_a_stored_layer(kw, how):
                 assert np.array_equal(c.get_host(i), w), again
             torch.cuda.synchronize()
             c.clear(ids)
+
+
+@pytest.mark.parametrize("step", [1, 4])
+def test_waits_for_a_stored_layer_are_skipped_where_they_are_over(step):
+    """A stream that already waits for a step, and a store that has ended: nothing is enqueued, and the next call on
+    the stream finds it idle.  Waits in every order, by two streams in turn, while layers are still handed in."""
+    import time
+    import torch
+    from paper_2510_09665_amd import lmc
+    g, src, dst, want, d_slots, d_tau, ids = _setup(1, 97 + step, L=16, NB=64)
+    stream, writer, third = (torch.cuda.Stream() for _ in range(3))
+    with lmc.Context(g, 3 * g.chunk_bytes, staging_chunks=1) as c:
+        for again in range(4):
+            live = [d.clone() for d in src.dev]
+            torch.cuda.synchronize()
+            t = c.store_begin(d_slots, ids, stream)
+            for l in range(0, g.L, step):
+                c.store_layers(t, l, step, live, stream)
+                if again % 2:
+                    for k in range(l + step - 1, -1, -1):      # the newest first, by two streams in turn
+                        for s in (writer, third):
+                            c.wait_layer(t, k, s)
+                    with torch.cuda.stream(writer if l // step % 2 else third):
+                        for k in range(l, l + step):
+                            live[k].fill_(0xEE)
+            if again == 2:
+                time.sleep(0.01)                              # in the pool long ago, and nobody has looked
+                assert writer.query()
+                for l in range(g.L):
+                    c.wait_layer(t, l, writer)
+                assert writer.query()                          # nothing stands on the stream
+            for l in range(g.L):
+                c.wait_layer(t, l, writer)
+                with torch.cuda.stream(writer):
+                    live[l].fill_(0xEE)
+            c.wait(t)
+            for i, w in zip(ids, want):
+                assert np.array_equal(c.get_host(i), w), again
+            torch.cuda.synchronize()
+            c.clear(ids)

@@ -1005,8 +1005,8 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     const bool on_second = !direct && (op->steps & 1) != 0 && c->store_step_streams == 2 && !other_direction_busy(c, true);
     // In an undisturbed store the steps without staging take the gather stream and the second copy stream to the
     // host in turn (which sits in the scatter stream's hardware queue, so that the library's kernels hold up no
-    // third one), each with half of the groups, so that one step's first slots and last stores do not leave the
-    // link idle: kernels of one stream follow each other 1.4 us apart, and the first store of one and the last of
+    // third one), side by side with half of the groups each, so that one step's first slots and last stores do not
+    // leave the link idle: kernels of one stream follow each other 1.4 us apart, and the first store of one and the last of
     // the other are some 3 more. On one stream and on two, steps of 0.6, 0.9, 1, 1.3 MiB: 34 MiB 809 and 760 us,
     // 22 490 and 461, 32 700 and 641, 105 2160 and 2020. Not for steps under 0.5 MiB (1.1 MiB in four 52 and 77
     // us, 10.7 in 61 of 0.2 528 and 645), whose launches take the thread longer than the link, nor beside other
@@ -1014,6 +1014,10 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     // steps, there is nothing to gain, and a second hardware queue would wait (64 MiB in steps of 2, products of
     // 128 rows, over the four queues the producer's stream can be in, 5791 and 5905 us). The last step is on the
     // gather stream, behind the other's: what waits for the store waits for one stream.
+    // All groups for a step that has the link to itself: the last one, and one that the last one follows if that is
+    // as large. 16, 32, 64, 192 MiB in one call by half of them 310, 609, 1217, 3665 us, by all 306, 600, 1189,
+    // 3550; in two 316, 612, 1219, 3664 and 309, 603, 1192, 3554; in four 315, 610, 1208, 3611 and 314, 606, 1195,
+    // 3559. (Half also for one that only finds another still running on the second stream: four calls 3586.)
     const bool ends = first_layer + n_layers == geom.num_layers;
     const bool in_turn = undisturbed && direct && c->store_step_streams == 2 && step_bytes >= lmc_ctx::kStoreStepsInTurn &&
                          may_wait_for_word(c, c->s_gather);
@@ -1048,7 +1052,8 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
         const int word = beside ? lmc_ctx::kStoreStepWord : lmc_ctx::kStoreWord;
         uint64_t &reached = c->word_target[word];
         lmc::HostWord told{counts || tells ? c->word(word) : nullptr, tells ? c->stored_dev : nullptr, reached};
-        const uint32_t groups = in_turn ? std::max(1u, c->link_groups / 2) : 0u;
+        const bool shares = beside || (in_turn && int64_t(first_layer) + 2 * int64_t(n_layers) < geom.num_layers);
+        const uint32_t groups = shares ? std::max(1u, c->link_groups / 2) : 0u;
         rc = store_groups(c, view, uint64_t(first_layer) * layer_bytes, ptrs, op->slot_mapping, op->new_chunk,
                           op->slots, cap, false, direct, true, on_second || beside, nullptr, e,
                           told.word != nullptr ? &told : nullptr, groups);

@@ -28,7 +28,7 @@ def _setup(n, seed, name="llama3_8b", **kw):
 
 @pytest.mark.parametrize("steps,staged", [((1,) * 8, ()), ((1,) * 8, (0, 2, 4, 6)), ((1,) * 8, (1, 3, 5, 7)), ((1, 2, 1, 3, 1), (1, 3)),
                                           ((3, 1, 4), (0, 2)), ((2, 2, 2, 1, 1), (0, 1, 2)), ((2, 2, 2, 1, 1), (2,)),
-                                          ((7, 1), (0,)), ((1, 1, 1, 1, 3, 1), (4,)), ((1, 7), (1,)), ((8,), (0,))])
+                                          ((8,), ()), ((4, 4), ()), ((3, 3, 2), ()), ((7, 1), (0,)), ((1, 1, 1, 1, 3, 1), (4,)), ((1, 7), (1,)), ((8,), (0,))])
 @pytest.mark.parametrize("how", ["behind_a_producer", "idle", "timed"])
 def test_store_steps_of_any_size(steps, staged, how):
     """Steps of one store with staging (`staged`: which) and without, behind each other in every order, in turn on
@@ -325,3 +325,31 @@ def test_waits_for_a_stored_layer_are_skipped_where_they_are_over(step):
                 assert np.array_equal(c.get_host(i), w), again
             torch.cuda.synchronize()
             c.clear(ids)
+
+
+def test_a_step_without_a_partner_has_all_groups():
+    """With so few groups that they, and not the link, set the pace, a store in one or two calls takes as long where
+    steps go on two streams in turn as where they go on one."""
+    import time
+    import torch
+    from paper_2510_09665_amd import lmc
+    g, src, dst, want, d_slots, d_tau, ids = _setup(1, 3, L=16, NB=64)
+    stream = torch.cuda.Stream()
+    with lmc.Context(g, 2 * g.chunk_bytes, staging_chunks=1) as c:
+        c.tune("link_groups", 8)
+        for calls in (1, 2):
+            took = {}
+            for streams in (1, 2, 1, 2):
+                c.tune("store_step_streams", streams)
+                for _ in range(4):
+                    c.clear(ids)
+                    torch.cuda.synchronize()
+                    begin = time.perf_counter()
+                    t = c.store_begin(d_slots, ids, stream)
+                    for i in range(calls):
+                        c.store_layers(t, i * g.L // calls, g.L // calls, src.dev, stream)
+                    c.wait(t)
+                    took.setdefault(streams, []).append(time.perf_counter() - begin)
+            assert np.array_equal(c.get_host(ids[0]), want[0])
+            # half of the groups took 1.9 times as long
+            assert min(took[2]) < 1.3 * min(took[1]), (calls, took)

@@ -89,9 +89,10 @@ enum {
                                       gather kernel writes, and the scatter kernel reads, the
                                       pinned pool over the host link (some tens of workgroups,
                                       resident for the length of the transfer).  Same results.
-                                      Without the flag only stores of at most 64 MiB and
-                                      retrieves of at most 256 MiB go this way (lmc_tune
-                                      "direct_store_below" / "..._retrieve_below"). */
+                                      Without the flag only transfers up to some size go this
+                                      way: 64 MiB, and under conditions bulk retrieves and
+                                      layer-wise stores up to 256, layer-wise retrieves up to 512
+                                      (lmc_tune "direct_store_below" / "..._retrieve_below"). */
 #define LMC_FLAG_EVICT_LRU 32u     /* a new chunk that finds the pool full takes the slot of
                                       the least recently used chunk that is not pinned, has
                                       no transfer in flight and is not used by the same
@@ -573,6 +574,9 @@ lmc_status_t lmc_measure_link_duplex_kernel(lmc_ctx_t *ctx, uint64_t nbytes, int
  * retrieves if bits 0, 1 and 5 are clear, with stores if bits 2, 3 and 4 are).
  * 0 = no sharing: pick such a stream
  * for compute, or raise GPU_MAX_HW_QUEUES so that every stream has a queue of its own.
+ * Once a call has found a stream that overlaps with retrieves (or stores), the context takes it
+ * that the caller's other work is on such streams, and leaves more of them (of the layer-wise ones) to the copy
+ * engines, which that work does not notice: see lmc_tune "direct_store_below".
  * Blocks for some milliseconds; waits for the device first.  LMC_ERR_NOMEM, LMC_ERR_HIP. */
 lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
 
@@ -602,15 +606,16 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *ctx, void *stream, uint32_t *mask_out);
  * "edge_chunks" (size
  * of the group at the exposed end of a pipeline, 0 = none), "timing" (0/1: switches
  * LMC_FLAG_TIMING), "trace" (0/1: switches LMC_FLAG_TRACE; 1 also empties the trace and
- * restarts its clock), "direct_store_below" / "direct_retrieve_below" (bytes, default 64 and
- * 256 MiB: an lmc_store with at most that many new bytes, or an lmc_retrieve /
+ * restarts its clock), "direct_store_below" / "direct_retrieve_below" (bytes: an lmc_store, or the
+ * lmc_store_layers calls of a store, with at most that many new bytes, or an lmc_retrieve /
  * lmc_retrieve_batch / lmc_retrieve_layerwise of at most that many bytes, goes the
- * LMC_FLAG_DIRECT way: one launch instead of kernel, event, copy, event; the
- * lmc_store_layers calls of a store with at most that many new bytes do; 0 = never.  As long as
- * the first is not set, lmc_store_layers calls that move at most 2 MiB, or find the stream they are given idle
- * and no other operation under way, go that way in stores of up to
- * 256 MiB; as long as the second is not, layer-wise retrieves in steps of at most 8 MiB up to
- * 512 MiB, and any retrieve up to 64 MiB only while a store is under way), "scatter_order" (default 0; 1 or 2:
+ * LMC_FLAG_DIRECT way: one launch instead of kernel, event, copy, event; 0 = never.  As long as the first is not set
+ * that holds for stores of at most 64 MiB, layer-wise ones only until lmc_probe_stream has found a stream that
+ * overlaps with stores, and up to 256 MiB for lmc_store_layers calls that move at most 2 MiB, or find the
+ * stream they are given idle and no other operation under way.  As long as the second is not set it holds for
+ * retrieves of at most 64 MiB; up to 256 MiB, and layer by layer in steps of at most 8 MiB up to 512, where no
+ * store is under way, until lmc_probe_stream has found a stream that overlaps with retrieves: from
+ * then on layer by layer in steps of at most 3 MiB up to 512 where no store is under way), "scatter_order" (default 0; 1 or 2:
  * scatter launches visit their rows in ascending slot order, built on the device, so that
  * the writes sweep every plane once; 1 = only launches with at least "ordered_min_pages"
  * pages that cover at least one block in "ordered_min_density_inv" of a plane, 2 = every

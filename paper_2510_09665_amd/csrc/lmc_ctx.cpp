@@ -869,9 +869,9 @@ lmc_status_t lmc_tune(lmc_ctx_t *c, const char *key, int64_t value) {
     } else if (k == "edge_chunks") {
         c->edge_chunks = value;
     } else if (k == "direct_store_below") {
-        c->direct_store_below = c->direct_store_steps_below = value;
+        c->direct_store_below = c->direct_store_steps_below = c->direct_placed_store_below = value;
     } else if (k == "direct_retrieve_below") {
-        c->direct_retrieve_below = c->direct_steps_below = c->direct_beside_store_below = value;
+        c->direct_retrieve_below = c->direct_steps_below = c->direct_small_retrieve_below = value;
     } else if (k == "xcd_run") {
         if (value > (1 << 20)) return LMC_ERR_INVAL;
         c->shape.xcd_run = uint32_t(value);
@@ -910,6 +910,7 @@ lmc_status_t lmc_tune(lmc_ctx_t *c, const char *key, int64_t value) {
         if (!c->ops.empty() || !c->held_events.empty()) return LMC_ERR_BUSY;
         DeviceScope dev(c);
         arrange_streams(c);
+        c->loads_placed = c->stores_placed = false;
     } else if (k == "fail_hip_after") {
         if (value > 0xFFFFFFFFll) return LMC_ERR_INVAL;
         c->fail_hip_after = uint32_t(value);

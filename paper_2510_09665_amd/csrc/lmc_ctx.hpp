@@ -158,55 +158,46 @@ struct lmc_ctx {
     std::vector<void *> order_retired; // outgrown scratch, freed with the context
     uint64_t use_calls = 0;         // number of the latest call that used chunks (recency of use)
     std::vector<uint64_t> evicted;  // LMC_FLAG_EVICT_LRU: ids evicted and not yet drained
-    // Bulk calls that move at most this many bytes skip staging and the copy engine (the
-    // kernel itself crosses the link).  Small transfers are bound by launch latencies, which
-    // one launch instead of kernel, event, copy, event halves; beyond the line the staged pipeline
-    // keeps the compute units free.  0 = never.
-    // Stores: up to 64 MiB the single launch is 2-7 % faster and over within a millisecond or so.  At 96
-    // and 128 MiB it is 3-4 % faster, and products of 512 to 4096 rows beside it, averaged over the four
-    // hardware queues they can be in, take 9-15 % longer than beside a staged one.
-    // A layer-wise store's steps go this way up to the same line, and steps of at most 2 MiB up to 256 MiB:
-    // a stage costs a step 10 us of the one copy engine that serves copies to the host, besides the calls.
-    // Alone, 32 MiB in steps of 4, 8, 16 MiB: 690, 766, 825 us staged, 660, 618, 612 direct; 64 MiB in steps of
-    // 4, 16, 32: 1434, 1320, 1253 and 1275, 1209, 1204; 80, 160 MiB in steps of 1, 2: 2300-3100, 3800 and 1744,
-    // 3222 (and while the runtime's copies to the host are slow, see copy_kernel, 5977 us for the 64 MiB in steps
-    // of 4 and 16132 for the 160 MiB).  With the producer's products of 128, 512, 1536, 4096 rows before
-    // every step, averaged over the four hardware queues its stream can be in: 64 MiB in steps of 4 MiB 9039, 9036,
-    // 10858, 14797 staged, 8678, 9060, 10866, 15002 direct; in steps of 16 8882, 8970, 10923, 14869 and 8690, 8984,
-    // 10910, 14948; 160 MiB in steps of 2 15583, 15594, 19374, 28685 and 14302, 15279, 19751, 28909.  Larger
-    // stores in larger steps would lose: 192 MiB in steps of 6 10085, 10105, 11891, 15773 and 9469, 10510, 12522,
-    // 16840, 320 MiB in steps of 4 16444, 16448, 20142, 29586 and 15092, 16886, 20496, 31202. But where the
-    // producer has nothing on its stream and no other operation is under way there is nothing of the producer's to
-    // slow down, and steps of any size go this way up to the second line: 65, 86, 168, 200, 224 MiB in steps of 9,
-    // 6, 11, 6, 7 1374, 1878, 3339, 4115, 4544 us staged and 1286, 1633, 3172, 3781, 4223 direct, and a first
-    // pass, with the runtime's copies still slow, 11-16 ms and 4.
-    // lmc_tune "direct_store_below" sets both lines.
-    int64_t direct_store_below = int64_t(64) << 20, direct_store_steps_below = int64_t(256) << 20;
+    // Calls that move at most this many bytes skip staging and the copy engine: the kernel itself crosses the link.
+    // That saves a small transfer launches and hand-overs and a long one 100 us, and takes 24 compute units for as
+    // long as it lasts; staging makes two hardware queues (a load) or one (a store) besides the caller's stand still, and whatever
+    // stream of the process happens to be in them.  So the lines depend on whether the caller has placed its streams
+    // (lmc_probe_stream).  Figures: us for a transfer and products of 128, 512, 1536, 4096 rows by 4096 x 4096 beside
+    // it, staged and direct.  lmc_tune "direct_store_below" / "direct_retrieve_below" set all lines of a direction; 0 = never.
+    //
+    // Stores, bulk: up to 64 MiB.  Alone 2-7 % faster; 96 and 128 MiB 3-4 %, but products over the four queues
+    // they can be in 9-15 % slower.
+    int64_t direct_store_below = int64_t(64) << 20;
+    // Layer-wise stores: up to the same line (64 MiB in steps of 4, over the four queues: 9039, 9036, 10858, 14797
+    // and 8678, 9060, 10866, 15002); if a stream has been found that stores do not hold up, steps of at most 2 MiB
+    // (64 MiB there, in steps of 4: 2650, 1936, 2116, 3711 and 2313, 1711, 2252, 4384; of 2: 6075, 3204, 3233,
+    // 3848 and 3139, 2312, 2565, 4143).
+    int64_t direct_placed_store_below = 0;
+    // Such steps up to 256 MiB (160 MiB in steps of 2 over the four queues: 15583, 15594, 19374, 28685 and 14302,
+    // 15279, 19751, 28909; 192 MiB in steps of 6 would lose: 10085, 10105, 11891, 15773 and 9469, 10510, 12522, 16840),
+    // and steps of any size where the producer has nothing on its stream and no other operation is under way, so
+    // that there is nothing to slow down (86, 168, 224 MiB in steps of 6, 11, 7: 1878, 3339, 4544 and 1633, 3172, 4223).
+    int64_t direct_store_steps_below = int64_t(256) << 20;
     static constexpr int64_t kDirectStoreStep = int64_t(2) << 20;
     static constexpr int64_t kStoreStepsInTurn = int64_t(512) << 10;   // see lmc_store_layers
-    // Retrieves: up to 256 MiB. Bulk, 96, 128, 192, 256 MiB: 1857, 2444, 3616, 4793 us staged, 1757, 2340, 3502,
-    // 4684 direct. What else runs on the GPU loses a part of the compute units to the kernel, but a staged
-    // retrieve makes two hardware queues besides the caller's stand still for as long as it takes, the copy
-    // stream's and the scatter stream's, a direct one on the caller's stream none. 128 MiB beside products of 128,
-    // 512, 1536, 4096 rows by 4096 x 4096 of another stream, all of which take 3283, 2979, 2872, 3040 us alone:
-    // the stream in a queue that nothing holds up 3682, 3360, 3123, 4168 (staged) against 3625, 3845, 3794, 4044;
-    // in the copy stream's or the scatter stream's about 5740, 5460, 5340, 5520 against 3630, 3830, 3800, 4050;
-    // over the four queues 4693, 4387, 4226, 4844 against 3626, 3833, 3795, 4046; 256 MiB 9221, 8677, 8697, 10003
-    // against 7147, 7632, 7588, 8254. Beyond, 100 us are 2 % and less, and a stream that has been placed
-    // (lmc_probe_stream) keeps its compute units.
-    // Layer by layer a stage costs 10 us between two copies and 5-7 more for a rectangle besides, so
-    // steps of at most 8 MiB go this way up to twice as much.  The consumer's products between the
-    // layers, 128 MiB in steps of 4 MiB: 9274, 9100, 11231, 14595 staged, 8343, 8996, 10856, 14459 direct with
-    // its stream in the free queue, about 10700, 10900, 13300, 16800 against 8400, 9000, 11000, 14700 in the two copy
-    // streams' queues; 256 MiB in steps of 16: 8997, 8939, 10719, 14104 against 9039, 10054, 11962, 16048 and about
-    // 12800, 13200, 15800, 19300 against 8900, 10100, 12100, 15900; 480 MiB in steps of 6: 15542, 15638, 20038, 28485
-    // against 13938, 16004, 20283, 29657 and 22000, 23600, 28000, 36900 against 13900, 16000, 20400, 29600.
-    // Beside a store that is under way the line is at 64 MiB: a kernel that reads the link while copies write
-    // it gets half of its rate (128 MiB behind a store of 768 MiB 5.3 ms, staged 3.4; 64 MiB 4.2 and 2.0).
-    // lmc_tune "direct_retrieve_below" sets all three.
-    int64_t direct_retrieve_below = int64_t(256) << 20, direct_steps_below = int64_t(512) << 20,
-            direct_beside_store_below = int64_t(64) << 20;
-    static constexpr int64_t kDirectRetrieveStep = int64_t(8) << 20;
+    // Retrieves: up to 256 MiB (128 MiB over the four queues 4693, 4387, 4226, 4844 and 3626, 3833, 3795, 4046; the
+    // load itself 2452 and 2341).
+    int64_t direct_retrieve_below = int64_t(256) << 20;
+    // Up to 64 MiB if a stream has been found that loads do not hold up: there, products beside 128 MiB take 3682,
+    // 3360, 3123, 4168 and 3625, 3845, 3794, 4044, as much as 22 % more for a load that is 2-5 % faster.  And beside
+    // a store that is under way: a kernel that reads the link while copies write it gets half of its rate (128 MiB
+    // behind a store of 768 MiB 3.4 ms and 5.3, 64 MiB 2.0 and 4.2).
+    int64_t direct_small_retrieve_below = int64_t(64) << 20;
+    // Layer by layer a stage costs 10 us between two copies and 5-7 more for a rectangle besides, so small steps go
+    // this way up to 512 MiB: of 8 MiB, or, where a stream has been found, of 3 (there, the consumer's products
+    // between the layers, 96 MiB in steps of 3: 2931, 3054, 2484, 4234 and 2421, 2794, 2425, 4274; 128 in steps of
+    // 4: 3907, 4052, 4168, 4387 and 3479, 3989, 4249, 4571; of 8: 3625, 3658, 3808, 3913 and 3463, 4003, 4235, 4454; in the
+    // queues that a staged load holds up 4120-5700, 5730-6380 and 5560-6190 staged, and direct as above).
+    int64_t direct_steps_below = int64_t(512) << 20;
+    static constexpr int64_t kDirectRetrieveStep = int64_t(8) << 20, kPlacedRetrieveStep = int64_t(3) << 20;
+    // Has lmc_probe_stream found a stream that staged loads, or stores, do not hold up?  Then the caller is taken to
+    // have its other work there.  Not remembered: which.  Until the library's own streams are placed anew.
+    bool loads_placed = false, stores_placed = false;
     int64_t chunk_bytes = 0;
     int64_t n_pool_slots = 0;
     uint8_t *pool = nullptr;

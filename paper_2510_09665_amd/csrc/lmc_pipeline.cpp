@@ -536,13 +536,14 @@ static lmc_status_t launches_on_caller(lmc_ctx *c, hipStream_t user, bool *yes) 
     return LMC_OK;
 }
 
-// Does a retrieve of this size skip staging (lmc_ctx::direct_retrieve_below)?
+// Does a retrieve of this size skip staging (lmc_ctx::direct_retrieve_below and what follows it)?
 static bool retrieves_directly(lmc_ctx *c, int64_t n_chunks, int32_t layers_per_step) {
     const int64_t bytes = n_chunks * c->chunk_bytes;
     const int64_t step = bytes / c->cfg.geom.num_layers * layers_per_step;
-    const bool small_steps = layers_per_step > 0 && step <= lmc_ctx::kDirectRetrieveStep;
-    if (bytes > (small_steps ? std::max(c->direct_steps_below, c->direct_retrieve_below) : c->direct_retrieve_below)) return false;
-    return bytes <= c->direct_beside_store_below || !other_direction_busy(c, false);
+    const bool small_steps = layers_per_step > 0 && step <= (c->loads_placed ? lmc_ctx::kPlacedRetrieveStep : lmc_ctx::kDirectRetrieveStep);
+    const int64_t line = c->loads_placed ? c->direct_small_retrieve_below : c->direct_retrieve_below;
+    if (bytes > (small_steps ? std::max(c->direct_steps_below, line) : line)) return false;
+    return bytes <= c->direct_small_retrieve_below || !other_direction_busy(c, false);
 }
 
 // Retrieve, bulk (layers_per_step == 0) or layer by layer (paper section 5.2).
@@ -995,7 +996,8 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *c, uint64_t ticket, int32_t first_layer
     // the producer has nothing more on its stream (nor had in front of the slot mapping), and nothing else is under way
     const bool undisturbed = idle && op->began_idle && c->ops.size() == 1;
     const int64_t bytes = n_new * c->chunk_bytes;
-    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 || bytes <= c->direct_store_below ||
+    const bool direct = (c->cfg.flags & LMC_FLAG_DIRECT) != 0 ||
+                        bytes <= (c->stores_placed ? c->direct_placed_store_below : c->direct_store_below) ||
                         (bytes <= c->direct_store_steps_below && (step_bytes <= lmc_ctx::kDirectStoreStep || undisturbed));
     // Steps take the two copy streams in turn (as the steps of a layer-wise retrieve do):
     // between two copies of one stream the runtime leaves the link idle for some 20 us,

@@ -195,6 +195,10 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *c, void *stream, uint32_t *mask_out) {
     (void)hipFree(devbuf);
     (void)hipGetLastError();
     *mask_out = mask;
+    if (rc == LMC_OK) {
+        c->loads_placed |= (mask & 0x23u) == 0;
+        c->stores_placed |= (mask & 0x1cu) == 0;
+    }
     return rc;
 }
 

@@ -4,6 +4,10 @@
 
 namespace lmci {
 
+// An event from the free list may have been recorded last on a stream of the caller's that is gone by now
+// (order_after, event_behind_wait, lmc_probe_stream).  The runtime looks that stream up when the event is queried or
+// waited for, not when it is recorded or destroyed (tests/test_gpu_step_words.py has such events in use): whoever
+// takes one records it before anything else.
 lmc_status_t get_event(lmc_ctx *c, bool timing, hipEvent_t *out) {
     std::vector<hipEvent_t> &pool = timing ? c->free_time_events : c->free_sync_events;
     if (!pool.empty()) {

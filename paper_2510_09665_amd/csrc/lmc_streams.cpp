@@ -135,9 +135,9 @@ void arrange_streams(lmc_ctx *c) {
     } else {
         for (size_t i = 0; i < 6; i++) keep[i] = 1;
     }
-    // The streams not chosen live on, unused, until the context goes: events that were
-    // recorded on them are in circulation (the three of the test above, and after a
-    // repeated arrangement every event of the rings), and the runtime looks up the stream an
+    // The streams not chosen live on, unused, until the context goes: after a repeated
+    // arrangement the events of the rings were last recorded on them and are waited for
+    // again before they are recorded anew, and the runtime looks up the stream an
     // event was last recorded on when the event is queried or waited for.  With the stream
     // destroyed, hipEventQuery now and then answered "operation not permitted when stream is
     // capturing" from whatever lay in the freed stream's place.
@@ -184,14 +184,8 @@ lmc_status_t lmc_probe_stream(lmc_ctx_t *c, void *stream, uint32_t *mask_out) {
         if (rc == LMC_OK && shares) mask |= 1u << i;
     }
     (void)hipDeviceSynchronize();
-    for (hipEvent_t ev : {a0, a1})
+    for (hipEvent_t ev : {a0, a1, k1})
         if (ev) c->free_time_events.push_back(ev);
-    // k1 was recorded on the caller's stream, which the caller may destroy while the event
-    // is still in circulation here (see arrange_streams): it is not kept
-    if (k1) {
-        c->all_events.erase(std::remove(c->all_events.begin(), c->all_events.end(), k1), c->all_events.end());
-        (void)hipEventDestroy(k1);
-    }
     (void)hipFree(devbuf);
     (void)hipGetLastError();
     *mask_out = mask;

@@ -270,3 +270,55 @@ def test_layers_of_one_step_are_waited_for_once_by_each_stream(how):
             c.wait(t)
             assert_layers_equal([d.cpu().numpy() for d in dev], host)
             del before
+
+
+def test_events_recorded_on_streams_that_are_gone_go_on_in_use():
+    """A busy stream that stores, a stream that waits for layers and is destroyed, and one that is probed: the events
+    recorded on them come back as those of other calls, and go with the context."""
+    import ctypes
+    import torch
+    from conftest import _hip_runtime
+    from gpu_util import assert_layers_equal, slots_to_device
+    from paper_2510_09665_amd import lmc
+    g = W.KVGeometry(L=6, P=2, H=8, D=128, e=2, BS=16, NB=256, CT=256)
+    rng = np.random.default_rng(67)
+    hip = _hip_runtime()
+    for _ in range(2):
+        with lmc.Context(g, 9 * g.chunk_bytes, staging_chunks=2) as c:
+            want, ids = _pool(c, g, 4, False, rng)
+            new = np.arange(100, 104, dtype=np.uint64)
+            tau = _request(g, 4, rng)
+            host = [W.sentinel_layer(g, l) for l in range(g.L)]
+            dev = [torch.from_numpy(h).cuda() for h in host]
+            d_tau = slots_to_device(tau)
+            oracle.scatter(g, want, tau, host)
+            kept = oracle.gather(g, host, tau)
+            for k in range(12):
+                for l, d in enumerate(dev):
+                    d.copy_(torch.from_numpy(W.sentinel_layer(g, l)))
+                torch.cuda.synchronize()
+                c.tune("direct_retrieve_below", 0 if k % 3 == 2 else 64 << 20)
+                c.tune("direct_store_below", 0 if k % 3 == 1 else 64 << 20)
+                made = []
+                for _ in range(3):
+                    raw = ctypes.c_void_p()
+                    assert hip.hipStreamCreateWithFlags(ctypes.byref(raw), 1) == 0
+                    made.append(raw)
+                t = c.retrieve_layerwise(ids, d_tau, dev, 1 + k % 4)
+                for raw in made:
+                    for l in range(g.L):
+                        c.wait_layer(t, l, raw.value)
+                if k == 5:
+                    c.probe_stream(made[0].value)
+                with torch.cuda.stream(torch.cuda.ExternalStream(made[1].value)):
+                    torch.cuda._sleep(1 << 18)
+                u = c.store(dev, d_tau, new, made[1].value)
+                for raw in made:
+                    assert hip.hipStreamDestroy(raw) == 0
+                c.wait(u)
+                assert c.test(t)
+                for i, w in zip(new, kept):
+                    assert np.array_equal(c.get_host(i), w), k
+                c.clear(new)
+                torch.cuda.synchronize()
+                assert_layers_equal([d.cpu().numpy() for d in dev], host, "pass %d" % k)

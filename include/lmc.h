@@ -41,11 +41,16 @@
  *   - A chunk id is a 64-bit value, normally from lmc_hash_chunks.  Equal ids mean
  *     the same chunk.
  *   - One context may be used from several threads; calls are serialised inside.
- *   - Kernels that read or write the pinned pool themselves (small calls, LMC_FLAG_DIRECT, pieces
- *     of scattered chunks) start on compute units of which other kernels hold at most 32 KiB of LDS.
- *     A kernel that stays on the GPU and holds more on every compute unit keeps them waiting until
- *     it ends: if it is itself to wait for a store, a retrieve or a layer of one, call
- *     lmc_tune("link_lds_kib", 0) first, and they ask for none.
+ *   - Kernels that read or write the pinned pool themselves start on compute units of which other
+ *     kernels hold at most 32 KiB of LDS.  A kernel that stays on the GPU and holds more on every compute
+ *     unit keeps them waiting until it ends: if it is itself to wait for a store, a retrieve or a layer of
+ *     one, call lmc_tune("link_lds_kib", 0) first, and they ask for none.  Which calls have such
+ *     kernels: all under LMC_FLAG_DIRECT, pieces of scattered chunks at any size, and by their size stores
+ *     of up to 64 MiB, layer-wise stores and retrieves of up to 256 and layer-wise retrieves of
+ *     up to 512 (the conditions: lmc_tune "direct_store_below"; with both lines at 0 none by size).
+ *     They keep 24 compute units (32 and more for pieces and for stores of rows that are no multiples of 16
+ *     bytes) for as long as the transfer lasts; a product that fills every compute unit once then takes
+ *     1.4 to 1.7 times as long, one that leaves some free as long as alone.
  */
 #ifndef LMC_H
 #define LMC_H
@@ -242,7 +247,7 @@ lmc_status_t lmc_store(lmc_ctx_t *ctx, void *const *kv_layers, const int64_t *sl
 
 /* Retrieve (sections 4 and 5.1).  All n_chunks ids must be present, else LMC_ERR_MISS
  * and no page byte is written.  Each chunk is copied from its pool slot into a staging
- * buffer (or, for a small call or under LMC_FLAG_DIRECT, read where it is) and scattered
+ * buffer (or, up to some size and under LMC_FLAG_DIRECT, read where it is) and scattered
  * into the pages named by slot_mapping (DEVICE
  * int64[n_chunks*chunk_tokens]); bytes of the pages that no slot names are not
  * touched.  stream_to_signal: a hipStream_t (NULL names the null stream).  The scatter
@@ -280,7 +285,7 @@ lmc_status_t lmc_retrieve_batch(lmc_ctx_t *ctx, int64_t n_req, const int64_t *re
  * slots) and scattered, then the next layers follow, so that layer l's pages are
  * complete long before the last layer's.  The consumer orders itself per layer with
  * lmc_wait_layer; unlike lmc_retrieve, no stream is made to wait for the whole call.
- * Without staging (a small call, or LMC_FLAG_DIRECT) one launch moves all the layers, step by
+ * Without staging (up to some size, see LMC_FLAG_DIRECT) one launch moves all the layers, step by
  * step, unless the stream is being captured, "link_groups" or "value_waits" is 0, more than 256 chunks lie in
  * scattered slots or one of LMC_FLAG_TIMING, _TRACE and _FORCE_SYNC is set: then each step is
  * a launch.
@@ -314,10 +319,12 @@ lmc_status_t lmc_store_layers(lmc_ctx_t *ctx, uint64_t ticket, int32_t first_lay
 /* Make `stream` (hipStream_t, NULL = null stream) wait, on the device, until layer
  * `layer` of a layer-wise ticket is in place: loaded into its pages (retrieve) or
  * arrived in the pool (store).  The host does not block.  A finished ticket needs no
- * wait and returns LMC_OK.  Where one launch moves all the layers (lmc_retrieve_layerwise) the
- * stream waits for a value in device memory, which the runtime does by a kernel of one wavefront
- * that runs on the stream until the layer is there (lmc_tune "value_waits"); a stream of another GPU, or any
- * stream with "value_waits" 0, then waits for all the layers.  LMC_ERR_INVAL for a ticket that is not layer-wise or a
+ * wait and returns LMC_OK.  Where one launch moves all the layers (lmc_retrieve_layerwise), and for
+ * steps of a store that go without staging, the stream waits for a value in device memory, which the
+ * runtime does by a kernel of one wavefront that runs on the stream until the layer is there (lmc_tune
+ * "value_waits"); a stream of another GPU, or any stream with "value_waits" 0, then waits for all
+ * the layers, or for all steps of a store handed in so far.
+ * LMC_ERR_INVAL for a ticket that is not layer-wise or a
  * layer out of range; LMC_ERR_BUSY for a store layer that has not been submitted. */
 lmc_status_t lmc_wait_layer(lmc_ctx_t *ctx, uint64_t ticket, int32_t layer, void *stream);
 
